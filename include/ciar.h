@@ -270,8 +270,8 @@ int ciar_finish_rows(const void* draft_logits, const void* radius, const void* t
  *                             the averaged centre distribution.
  * Any output may be NULL; at least one must be given.  1 <= heads <= 8.  workspace: at least
  * ciar_multihead_workspace_bytes(N, heads, params) bytes, rules as above.  Every head's rows are
- * streamed once (Voting) or twice (Ensemble: the second sweep forms the token-wise averages once
- * every head's partition sum and caps are known).
+ * streamed once; Ensemble sweeps a position's rows a second time where a cap is active or the averaged widths hardly
+ * differ, and every row twice for V <= 64 and V > 16384.
  */
 enum { CIAR_VOTING = 0, CIAR_ENSEMBLE = 1 };
 

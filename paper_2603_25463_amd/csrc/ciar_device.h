@@ -36,6 +36,33 @@ __device__ __forceinline__ float exp2_ref(float x, float n)
 // every 2^(x log2e - n) is <= 1 (up to rounding).  -inf (nothing but masked tokens) maps to -inf.
 __device__ __forceinline__ float ref_of(float m) { return ceilf(m * 1.44269504f); }
 
+// Maximum of three logits.  (None is a signalling NaN: plain v_max3_f32, without the quieting of each operand that fmaxf
+// adds for values the compiler knows nothing about.)
+__device__ __forceinline__ float max3(float a, float b, float c)
+{
+    float m;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));
+    return m;
+}
+template <int N>
+__device__ __forceinline__ float max_of(const float (&v)[N])
+{
+    static_assert(N >= 4 && N % 2 == 0, "pairs");
+    float m = max3(v[0], v[0], v[1]);
+#pragma unroll
+    for (int i = 2; i < N; i += 2) m = max3(m, v[i], v[i + 1]);
+    return m;
+}
+
+// 1 / x for an ordinary positive x, to the last bit or so (hardware estimate and two Newton steps: a third of the
+// instructions of the division, which also covers operands at the ends of the range)
+__device__ __forceinline__ double recip(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(r, fma(-x, r, 1.0), r);
+    return fma(r, fma(-x, r, 1.0), r);
+}
+
 // 2^k as a double for an integer-valued float difference k <= 0 (clamped: below 2^-1000 it is 0 anyway)
 __device__ __forceinline__ double pow2_of(float k) { return ldexp(1.0, (int)fmaxf(k, -1000.f)); }
 
@@ -283,6 +310,14 @@ __device__ __forceinline__ int wave_max_i(int v)
     return __builtin_amdgcn_readlane(v, 63);
 }
 
+// Workgroup barrier for data exchanged through LDS only: waits for this wave's LDS operations and joins the barrier.
+// __syncthreads() also waits for every outstanding load into LDS (its fence covers them), and with it for the rows that
+// a kernel has in flight there while it works on the current one.
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // ---- per-token InterFuse arithmetic, shared by the streaming kernel and the dense export ------------
 
 // Constants of one row for a scalar radius.  Units: e_i as held by the lane, S = sum e_i in the same units.
@@ -292,10 +327,9 @@ struct FuseRow {
     float b, omb;        // b and 1-b:  dl = 1 - (1-b) x = b + (1-b)(1-x), free of cancellation as x -> 1
 };
 
-__device__ __forceinline__ FuseRow fuse_row(double S, double a, double b)
+__device__ __forceinline__ FuseRow fuse_row_inv(double invS, double a, double b)
 {
     FuseRow r;
-    const double invS = 1.0 / S;
     r.cu = (float)((a - 1.0) * invS);
     r.nih = (float)(-invS);
     r.nil = (float)(-invS - (double)r.nih);
@@ -303,6 +337,7 @@ __device__ __forceinline__ FuseRow fuse_row(double S, double a, double b)
     r.omb = (float)(1.0 - b);
     return r;
 }
+__device__ __forceinline__ FuseRow fuse_row(double S, double a, double b) { return fuse_row_inv(1.0 / S, a, b); }
 
 // One token of the scalar-radius interval pass:  g = e / (du dl), so that gl = g du and gw = g om (om = 1 - x)
 // with p^l = (b/S) gl and w = p^u - p^l = ((a-b)/S) gw.

@@ -38,7 +38,6 @@ __global__ __launch_bounds__(256) void ensemble_kernel(const RowArgs A, const in
     const bool rad = A.radius != nullptr;
     const bool need_argmax = A.ids == nullptr && (A.p_lo || A.p_mid || A.p_hi);
     bool flat_h = true;                                            // this lane's head: a flat row (see below)
-
     if (tid < H) {
         const RowStats st = A.stats[(int64_t)tid * A.N + row];
         flat_h = (double)exp2_ref(st.mc, st.n == -INFINITY ? 0.f : st.n) * (double)V <= 2.0 * st.S;
@@ -730,6 +729,471 @@ void ensemble_fused_kernel(const RowArgs A, const int64_t head_stride)
     }
 }
 
+// Ensemble in one sweep: every row of a position -- H centre rows and, with a radius tensor, H raw-radius rows -- is read
+// from memory once.  A workgroup takes one position at a time and its heads one after another:
+//   1. the head's centre row: per-wave maximum, e_i = 2^(c_i log2e - n_w), S_w;  -- barrier: (max, n_w, S_w) --
+//   2. with S known, the head's widths, added to D_i = sum_h w_{h,i} token by token (fp64 registers), and where its caps
+//      may be active the sums of p^l and of the widths.
+// No row has to be kept for a later head: of a position only the D_i stay, so any number of heads fits the registers, and
+// the next two rows are on their way into LDS all the time.  What binds is instructions: a row costs a wave ~350 of them
+// whatever its length (reductions, the exchange, row constants), so a lane takes 32 tokens (e 32, D 64 registers) and two
+// waves per SIMD share the registers; with 16 tokens per lane and four waves per SIMD the same call took 150-169 us
+// (2048 x 16384 x 3 heads fp32 with radius; two sweeps over every row: 318 us).  Omega = sum D_i / H and Sigma^2 = sum D_i^2 / (H^2 V) - (Omega / V)^2 hold as they stand when no head has an active
+// cap.  The positions where one has are swept a second time, with the caps known, when the workgroup is through with
+// its positions.  Those whose D_i agree to better than a hundredth of their mean (fp64 sums about 0 lose nothing elsewhere),
+// rows flat in every head and widths that all crowd against 1 are swept a second time in fp64.
+// The positions' scalars are parked in LDS and turned into outputs after the workgroup's last one, a lane per position: the
+// logits of the reported tokens are then fetched for all of them at once instead of in a chain per position.
+constexpr int kNonTemporal = 2;                                    // cache policy of global_load_lds: every row is used once
+constexpr int kSweepTokens = 32;                                   // tokens of a row per lane
+template <int THREADS> constexpr int sweep_rows() { return THREADS >= 256 ? 32 : THREADS / 8; }   // most positions of a workgroup
+
+// ARGMAX = no drafted ids: the reported token is the arg-max of the averaged centre distribution.
+template <typename T, int THREADS, bool RAD, bool UNIT, bool ARGMAX>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2)))
+void ensemble_sweep_kernel(const RowArgs A, const int H, const int64_t head_stride, const int wide,
+                           const int flat_in_fp64)
+{
+    using E = Elt<T>;
+    constexpr int EPV = E::kPerVec, NVEC = kSweepTokens / EPV, NW = THREADS / 64, ROWS = sweep_rows<THREADS>();
+    extern __shared__ u32x4 sm_next[];                             // [2][NVEC][THREADS]: the two rows in flight
+    // exchange slots: written before an item's barrier, read behind it; items (a head of a position) alternate between two
+    __shared__ float sm_ref[2][NW];
+    __shared__ double sm_S[2][NW];
+    __shared__ double sm_red[NW][48];                              // per wave: the slots of wave_sum3
+    // a position's sums per wave, read by wave 0 behind the next position's first barrier; positions alternate
+    __shared__ double sm_cap[2][kMaxHeads][2][NW];
+    __shared__ double sm_sum[2][2][NW];
+    __shared__ float sm_min[2][NW], sm_pm[2][NW];
+    __shared__ int sm_pi[2][NW];
+    // parked positions
+    __shared__ double pk_S[ROWS][kMaxHeads], pk_al[ROWS][kMaxHeads], pk_au[ROWS][kMaxHeads];
+    __shared__ double pk_sum[ROWS][2];
+    __shared__ float pk_n[ROWS][kMaxHeads], pk_mc[ROWS][kMaxHeads];
+    __shared__ int pk_id[ARGMAX ? ROWS : 1];
+    __shared__ int pk_state[ROWS];                           // see kDone ...
+    constexpr int kDone = 0, kCaps = 1, kFp64 = 2;                 // finished / an active cap / for ensemble_marked_kernel
+
+    // (the lane's index is asked for anew wherever it is used, through an empty asm: no LDS address formed from it is
+    // held in registers, or spilled, through the loop -- and a reload would wait for the rows in flight)
+    auto my_tid = []() {
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int V = A.V;
+    const int last_vec = (V + EPV - 1) / EPV - 1;
+    const bool partial = V < THREADS * kSweepTokens;               // the row does not fill the tile
+    RadiusMode rm = {false, 0.f, 0.f, 0.f};
+    if constexpr (RAD) {
+        rm = radius_mode(A);
+        rm.kappa = uniform_f(rm.kappa); rm.rmax = uniform_f(rm.rmax); rm.am1_max = uniform_f(rm.am1_max);
+    }
+    const uint32_t n_rows = (uint32_t)A.N, step = gridDim.x;
+
+    using lds_ptr = __attribute__((address_space(3))) void*;
+    using glb_ptr = const __attribute__((address_space(1))) void*;
+    auto row_base = [&](const void* rows, uint32_t row, int h) {
+        const uint64_t b = (uint64_t)(static_cast<const T*>(rows) + (int64_t)h * head_stride + (int64_t)row * A.stride);
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+        const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+        return (gbytes)(((uint64_t)hi << 32) | lo);
+    };
+    // A row goes in flight, straight into LDS (lane l of a wave lands 16 l bytes behind the address the wave names; no
+    // register is held while it is on its way).  A lane reads back only what its own wave has requested, so the
+    // hand-over is the wave's own count of outstanding loads and no barrier.  whole = false: there is no such row; a few
+    // bytes are fetched all the same, so that the count is the same.
+    auto fetch = [&](int slot, const void* rows, uint32_t row, int h, bool whole, int tid) {
+        const gbytes base = row_base(rows, row, h);
+        if (partial || !whole) {
+            const int t = whole ? tid : 0, end = whole ? last_vec : 0;
+#pragma unroll
+            for (int j = 0; j < NVEC; ++j)
+                __builtin_amdgcn_global_load_lds((glb_ptr)(base + (uint32_t)min(j * THREADS + t, end) * 16u),
+                                                 (lds_ptr)(sm_next + (slot * NVEC + j) * THREADS + wave * 64), 16, 0, kNonTemporal);
+        } else {
+            const uint32_t off = (uint32_t)tid * 16u;
+#pragma unroll
+            for (int j = 0; j < NVEC; ++j)
+                __builtin_amdgcn_global_load_lds((glb_ptr)(base + (uint64_t)j * (THREADS * 16u) + off),
+                                                 (lds_ptr)(sm_next + (slot * NVEC + j) * THREADS + wave * 64), 16, 0, kNonTemporal);
+        }
+    };
+    // the older of the two rows in flight has landed; it moves to registers and its slot is free again
+    auto take = [&](int slot, u32x4 (&buf)[NVEC], int tid) {
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NVEC) : "memory");
+#pragma unroll
+        for (int j = 0; j < NVEC; ++j) buf[j] = sm_next[(slot * NVEC + j) * THREADS + tid];
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    };
+    // (the second sweep of a position: a row into registers)
+    auto request = [&](u32x4 (&buf)[NVEC], const void* rows, uint32_t row, int h, int tid) {
+        const gbytes base = row_base(rows, row, h);
+#pragma unroll
+        for (int j = 0; j < NVEC; ++j)
+            buf[j] = __builtin_nontemporal_load((gvec)(base + (uint32_t)min(j * THREADS + tid, last_vec) * 16u));
+    };
+    auto unpack_row = [&](u32x4 (&buf)[NVEC], float (&v)[kSweepTokens], bool centre, int tid) {
+        if (partial) {
+#pragma unroll
+            for (int j = 0; j < NVEC; ++j) {
+                if (centre) E::mask_tail(buf[j], (j * THREADS + tid) * EPV, V);
+                else E::zero_tail(buf[j], (j * THREADS + tid) * EPV, V);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < NVEC; ++j) E::unpack(buf[j], &v[j * EPV]);
+    };
+    auto sum_of_position = [&](const double (&D)[kSweepTokens], int p) {
+        const int lane = my_tid() & 63;
+        double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+        for (int i = 0; i < kSweepTokens; ++i) { s1 += D[i]; s2 = fma(D[i], D[i], s2); }
+        s1 = wave_sum(s1); s2 = wave_sum(s2);
+        if (lane == 0) { sm_sum[p][0][wave] = s1; sm_sum[p][1][wave] = s2; }
+    };
+    // wave 0: the sums of a position over the waves -> whether they are to be done again in fp64
+    auto total_of_position = [&](int at, int p) {
+        const int lane = my_tid() & 63;
+        const int src = lane < NW ? lane : 0;
+        const double s1 = row16_sum(lane < NW ? sm_sum[p][0][src] : 0.0), s2 = row16_sum(lane < NW ? sm_sum[p][1][src] : 0.0);
+        // sum D_i and sum (D_i - mean)^2
+        const double spread = s2 - s1 * s1 / (double)V;
+        if (lane == 0) { pk_sum[at][0] = s1; pk_sum[at][1] = spread; }
+        return !(spread >= 1e-4 * (s2 - spread));
+    };
+    // wave 0 parks a position: lane h settles head h's caps
+    auto park = [&](int at, int p, bool all_flat, unsigned summed) {
+        const int lane = my_tid() & 63;
+        double al = 1.0, au = 1.0;
+        if (lane < H) {
+            if (A.normalize && (summed >> lane & 1u)) {
+                double g0 = 0.0, g1 = 0.0;
+                for (int w = 0; w < NW; ++w) { g0 += sm_cap[p][lane][0][w]; g1 += sm_cap[p][lane][1][w]; }
+                al = fmin(1.0, A.cap_lo / fmin(1.0, g0));
+                au = fmax(1.0, A.cap_hi / fmax(1.0, g0 + g1));
+            }
+            pk_al[at][lane] = al; pk_au[at][lane] = au;
+        }
+        const bool caps = __builtin_amdgcn_ballot_w64(al != 1.0 || au != 1.0) != 0;
+        bool fp64 = total_of_position(at, p) || (all_flat && flat_in_fp64);
+        if (wide) {
+            // every mean width close to 1/2 or above it: the complements have to be looked at
+            const int src = lane < NW ? lane : 0;
+            const float least = -row16_max(lane < NW ? -sm_min[p][src] : -INFINITY);
+            fp64 = fp64 || least > 0.45f * (float)H;
+        }
+        if constexpr (ARGMAX) {
+            const float pm = lane < NW ? sm_pm[p][lane] : -INFINITY, top = row16_max(pm);
+            const int best = wave_min_i(lane < NW && pm == top ? sm_pi[p][lane < NW ? lane : 0] : INT_MAX);
+            if (lane == 0) pk_id[at] = best == INT_MAX ? 0 : best;
+        }
+        if (lane == 0) pk_state[at] = caps && !(all_flat && flat_in_fp64) ? kCaps : fp64 ? kFp64 : kDone;
+    };
+
+    uint32_t row = blockIdx.x;
+    if (row >= n_rows) return;
+    // With a radius tensor the two rows in flight are a head's centre row (slot 0) and its radius row (slot 1), each
+    // requested when the one before it has moved to registers; without one, the centre rows of the next two heads.
+    fetch(0, A.draft, row, 0, true, my_tid());
+    if constexpr (RAD) fetch(1, A.radius, row, 0, true, my_tid());
+    else fetch(1, A.draft, H > 1 ? row : row + step < n_rows ? row + step : row, H > 1 ? 1 : 0, true, my_tid());
+    int done = 0, item = 0;
+    bool flat_before = false;
+    unsigned summed_before = 0;                                    // heads of the last position whose cap sums were taken
+    for (;; ++done) {
+        double D[kSweepTokens];
+#pragma unroll
+        for (int i = 0; i < kSweepTokens; ++i) D[i] = 0.0;
+        float pm[ARGMAX ? kSweepTokens : 1];                       // the heads' probabilities added up
+#pragma unroll
+        for (int i = 0; i < (ARGMAX ? kSweepTokens : 1); ++i) pm[i] = 0.f;
+        bool all_flat = true;
+        unsigned summed = 0;
+        const bool more_rows = row + step < n_rows && done + 1 < ROWS;
+        for (int h = 0; h < H; ++h, ++item) {
+            const int p = item & 1;
+            const int tid = my_tid(), lane = tid & 63;
+            // the item AHEAD items on (the same one where there is none)
+            constexpr int AHEAD = RAD ? 1 : 2;
+            uint32_t next_row = row;
+            int next_h = h + AHEAD, next_done = done;
+            while (next_h >= H) { next_h -= H; next_row += step; ++next_done; }
+            const bool has_next = next_row < n_rows && next_done < ROWS;
+            if (!has_next) { next_row = row; next_h = h; }
+            // ---- 1: the centre row ---------------------------------------------------------------------------------
+            float e[kSweepTokens];
+            {
+                u32x4 cbuf[NVEC];
+                take(RAD ? 0 : p, cbuf, tid);
+                fetch(RAD ? 0 : p, A.draft, next_row, next_h, has_next, tid);
+                unpack_row(cbuf, e, true, tid);
+            }
+            const float mw = wave_max(max_of(e)), nw = ref_of(mw), nref = nw == -INFINITY ? 0.f : nw;
+            double sacc[2] = {0.0, 0.0};
+#pragma unroll
+            for (int i = 0; i < kSweepTokens; ++i) {
+                e[i] = exp2_ref(e[i], nref);
+                sacc[i & 1] += (double)e[i];
+            }
+            // S_w over the wave, together with the cap sums of the head before (in their slots since its end)
+            double g0, g1, Sw = sacc[0] + sacc[1];
+            wave_sum3_put(Sw, sm_red[wave], 2, lane);
+            wave_sum3_get(sm_red[wave], lane, g0, g1, Sw);
+            if (lane == 0) {
+                sm_ref[p][wave] = mw; sm_S[p][wave] = Sw;
+                if (item > 0) {
+                    const int hb = h > 0 ? h - 1 : H - 1, pb = h > 0 ? done & 1 : (done - 1) & 1;
+                    sm_cap[pb][hb][0][wave] = g0; sm_cap[pb][hb][1][wave] = g1;
+                }
+            }
+            lds_barrier();
+            if (wave == 0 && h == 0 && done > 0) park(done - 1, (done - 1) & 1, flat_before, summed_before);
+            // the waves' results combined, across the first lanes of every wave
+            const int src = lane < NW ? lane : 0;
+            // (the row's reference is the largest of the waves': the reference of the largest logit)
+            const float m_l = sm_ref[p][src], n_l = ref_of(m_l), mc = row16_max(m_l), n = ref_of(mc);
+            const double S = row16_sum(lane < NW && n_l != -INFINITY ? sm_S[p][src] * pow2_of(n_l - n) : 0.0);
+            // (the radius constants through an empty asm, formed anew for every row, and what is the same in every lane of
+            // the wave moved to scalar registers: nothing of it is held in vector registers, or spilled, through the loop)
+            double ra = A.a, rb = A.b;
+            asm volatile("" : "+s"(ra), "+s"(rb));
+            if (tid == 0) { pk_S[done][h] = S; pk_n[done][h] = n; pk_mc[done][h] = mc; }
+            const double emax = (double)exp2_ref(mc, n == -INFINITY ? 0.f : n);
+            all_flat = all_flat && emax * (double)V <= 2.0 * S;
+            const double Su = nw == -INFINITY ? 1.0 : ldexp(S, (int)fminf(n - nw, 1000.f));   // S in this wave's units
+            const double inv = uniform_d(recip(Su));
+            // ---- 2: the head's widths ------------------------------------------------------------------------------
+            const FuseRow fr = uniform_fr(fuse_row_inv(inv, ra, rb));
+            const double cw = RAD ? inv : uniform_d((ra - rb) * inv);
+            if constexpr (ARGMAX) {
+                const float invf = (float)inv;
+#pragma unroll
+                for (int i = 0; i < kSweepTokens; ++i) pm[i] = fmaf(e[i], invf, pm[i]);
+            }
+            g0 = 0.0; g1 = 0.0;
+            if constexpr (RAD) {
+                float rv[kSweepTokens];
+                {
+                    u32x4 rbuf[NVEC];
+                    take(1, rbuf, tid);
+                    fetch(1, A.radius, next_row, next_h, has_next, tid);
+                    unpack_row(rbuf, rv, false, tid);
+                }
+#pragma unroll
+                for (int j = 0; j < NVEC; ++j) {
+                    if (j * THREADS * EPV < V) {                   // uniform: the chunk holds tokens
+#pragma unroll
+                        for (int k = 0; k < EPV; ++k) {
+                            float gl, gw;                          // (a slot past the row's end holds e = 0: both are 0)
+                            fuse_token_rad<UNIT>(e[j * EPV + k], rv[j * EPV + k], fr, rm.kappa, rm.rmax, rm.am1_max, gl, gw);
+                            const double w = (double)gw;
+                            g0 += (double)gl; g1 += w;
+                            D[j * EPV + k] = fma(cw, w, D[j * EPV + k]);
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                g0 *= inv; g1 *= inv;
+                summed |= 1u << h;
+            } else {
+                // (the host's bound on the largest probability, as in the streaming kernel)
+                const bool capless = !A.normalize || emax <= A.capless_xmax * S;          // uniform over the workgroup
+                const float is = -fr.nih, is2 = is * is;
+                const bool poly = capless && A.wpoly_x >= 0.f && (double)exp2_ref(mw, nref) <= (double)A.wpoly_x * Su;
+                if (poly) {                                        // uniform over the wave: see RowArgs::wpoly
+                    const float d0 = uniform_f(A.wpoly[0] * is), d1 = uniform_f(A.wpoly[1] * is2);
+                    const float d2 = uniform_f(A.wpoly[2] * (is2 * is)), d3 = uniform_f(A.wpoly[3] * (is2 * is2));
+#pragma unroll
+                    for (int i = 0; i < kSweepTokens; ++i) {
+                        const float G = fmaf(fmaf(fmaf(fmaf(d3, e[i], d2), e[i], d1), e[i], d0), e[i], 1.0f);
+                        D[i] = fma(cw, (double)(e[i] * G), D[i]);
+                        if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < kSweepTokens; ++i) {
+                        float gl, gw;
+                        fuse_token(e[i], fr, gl, gw);
+                        const double w = (double)gw;
+                        g0 += (double)gl; g1 += w;
+                        D[i] = fma(cw, w, D[i]);
+                        if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+                    }
+                    g0 *= rb * inv; g1 *= cw;
+                }
+                if (!capless) summed |= 1u << h;
+            }
+            wave_sum3_put(g0, sm_red[wave], 0, lane);
+            wave_sum3_put(g1, sm_red[wave], 1, lane);
+        }
+        sum_of_position(D, done & 1);
+        if constexpr (ARGMAX) {
+            const int tid = my_tid();
+            float best = -INFINITY;
+            int at = INT_MAX;
+#pragma unroll
+            for (int i = 0; i < kSweepTokens; ++i) {               // (ascending tokens: the first of equal values stays)
+                const int tok = (i / EPV * THREADS + tid) * EPV + i % EPV;
+                if (tok < V && pm[i] > best) { best = pm[i]; at = tok; }
+            }
+            const float top = wave_max(best);
+            at = wave_min_i(best == top ? at : INT_MAX);
+            if ((tid & 63) == 0) { sm_pm[done & 1][wave] = top; sm_pi[done & 1][wave] = at; }
+        }
+        if (wide) {
+            const int tid = my_tid();
+            float least = INFINITY;
+#pragma unroll
+            for (int i = 0; i < kSweepTokens; ++i)
+                if ((i / EPV * THREADS + tid) * EPV + i % EPV < V) least = fminf(least, (float)D[i]);
+            least = -wave_max(-least);
+            if ((tid & 63) == 0) sm_min[done & 1][wave] = least;
+        }
+        flat_before = all_flat;
+        summed_before = summed;
+        if (!more_rows) break;
+        row += step;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                // (the requests without a row have landed)
+    {
+        double g0, g1, g2;
+        const int lane = my_tid() & 63;
+        wave_sum3_get(sm_red[wave], lane, g0, g1, g2);
+        if (lane == 0) { sm_cap[done & 1][H - 1][0][wave] = g0; sm_cap[done & 1][H - 1][1][wave] = g1; }
+    }
+    __syncthreads();
+    if (wave == 0) park(done, done & 1, flat_before, summed_before);
+    __syncthreads();
+    // ---- the positions with an active cap once more: delta_i = alpha_u w_i + (alpha_u - alpha_l) p^l_i -----------------
+    for (int at = 0; at <= done; ++at) {
+        if (pk_state[at] != kCaps) continue;                       // uniform
+        const uint32_t r = blockIdx.x + (uint32_t)at * step;
+        const int tid = my_tid();
+        double D[kSweepTokens];
+#pragma unroll
+        for (int i = 0; i < kSweepTokens; ++i) D[i] = 0.0;
+        for (int h = 0; h < H; ++h) {
+            u32x4 cbuf[NVEC], rbuf[NVEC];
+            request(cbuf, A.draft, r, h, tid);
+            if constexpr (RAD) request(rbuf, A.radius, r, h, tid);
+            const double S = pk_S[at][h], al = pk_al[at][h], au = pk_au[at][h], inv = 1.0 / S;
+            const float n = pk_n[at][h];
+            const FuseRow fr = fuse_row(S, A.a, A.b);
+            const double cw = au * (RAD ? inv : (A.a - A.b) * inv), cl = (au - al) * (RAD ? inv : A.b * inv);
+            float e[kSweepTokens], rv[kSweepTokens];
+            unpack_row(cbuf, e, true, tid);
+            if constexpr (RAD) unpack_row(rbuf, rv, false, tid);
+#pragma unroll
+            for (int i = 0; i < kSweepTokens; ++i) {
+                const float ek = exp2_ref(e[i], n == -INFINITY ? 0.f : n);
+                float gl, gw;
+                if constexpr (RAD) fuse_token_rad<UNIT>(ek, rv[i], fr, rm.kappa, rm.rmax, rm.am1_max, gl, gw);
+                else fuse_token(ek, fr, gl, gw);
+                D[i] = fma(cw, (double)gw, fma(cl, (double)gl, D[i]));
+                if ((i & 1) == 1) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        sum_of_position(D, 0);
+        __syncthreads();
+        if (wave == 0) {
+            const bool fp64 = total_of_position(at, 0);
+            if (my_tid() == 0) pk_state[at] = fp64 ? kFp64 : kDone;
+        }
+        __syncthreads();
+    }
+    // ---- and those that want fp64, from the logits; the sums about D and C of the position's first token, so that a spread
+    // far below the mean is not the difference of two large moments.  C_i = sum_h (1 - width_{h,i}): where every mean width is
+    // above 1/2 and no cap is active (wide calls), Omega and Sigma are taken from the C_i, which resolve a spread that the
+    // widths, all rounding to 1, no longer show.
+    for (int at = 0; at <= done; ++at) {
+        if (pk_state[at] != kFp64) continue;                       // uniform
+        const int64_t r = (int64_t)blockIdx.x + (int64_t)at * step;
+        const int tid = my_tid();
+        auto token = [&](int i, double& d, double& c) {
+            d = 0.0; c = 0.0;
+            for (int h = 0; h < H; ++h) {
+                const int64_t off = (int64_t)h * head_stride + r * A.stride;
+                const double S = pk_S[at][h];
+                const double ed = exp((double)load_logit(static_cast<const T*>(A.draft) + off, i) - (double)pk_n[at][h] * kLn2);
+                const double x = ed / S, omx = fmax(0.0, S - ed) / S;
+                double a = A.a, b = A.b;
+                if constexpr (RAD) {
+                    const double rr = radius_of((double)load_logit(static_cast<const T*>(A.radius) + off, i), A.kappa, A.rmax);
+                    a = exp(rr); b = exp(-rr);
+                }
+                const double du = 1.0 + (a - 1.0) * x, dl = b + (1.0 - b) * omx;
+                d += pk_au[at][h] * a * x / du - pk_al[at][h] * b * x / dl;
+                c += (1.0 - 2.0 * (1.0 - b) * x * omx) / (du * dl);
+            }
+        };
+        double KD, KC;
+        token(0, KD, KC);
+        double q[4] = {0.0, 0.0, 0.0, 0.0}, most = 0.0;
+        for (int i = tid; i < V; i += THREADS) {
+            double d, c;
+            token(i, d, c);
+            most = fmax(most, c);
+            d -= KD; c -= KC;
+            q[0] += d; q[1] = fma(d, d, q[1]); q[2] += c; q[3] = fma(c, c, q[3]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            q[i] = wave_sum(q[i]);
+            if ((tid & 63) == 0) sm_red[wave][i] = q[i];
+        }
+        most = wave_max(most);
+        if ((tid & 63) == 0) sm_red[wave][4] = most;
+        __syncthreads();
+        if (tid == 0) {
+            double t[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+            for (int w = 0; w < NW; ++w) {
+                for (int i = 0; i < 4; ++i) t[i] += sm_red[w][i];
+                t[4] = fmax(t[4], sm_red[w][4]);
+            }
+            bool plain = wide && t[4] < kComplementBelow * (double)H;
+            for (int h = 0; h < H; ++h) plain = plain && pk_al[at][h] == 1.0 && pk_au[at][h] == 1.0;
+            const double Vd = (double)V;
+            pk_sum[at][0] = plain ? (double)H * Vd - (t[2] + Vd * KC) : t[0] + Vd * KD;
+            pk_sum[at][1] = plain ? t[3] - t[2] * t[2] / Vd : t[1] - t[0] * t[0] / Vd;
+        }
+        __syncthreads();
+    }
+    // ---- a lane per position --------------------------------------------------------------------------------------
+    const int t = my_tid();
+    if (t > done) return;
+    const int64_t r = (int64_t)blockIdx.x + (int64_t)t * step;
+    const double Hd = (double)H, Vd = (double)V;
+    const double omega = pk_sum[t][0] / Hd, sigma = sqrt(fmax(0.0, pk_sum[t][1]) / (Hd * Hd * Vd)), score = omega * sigma;
+    if (A.omega) A.omega[r] = (float)omega;
+    if (A.sigma) A.sigma[r] = (float)sigma;
+    if (A.score) A.score[r] = (float)score;
+    if (A.flags) A.flags[r] = (uint8_t)(score > A.tau);
+    if (A.p_lo || A.p_mid || A.p_hi) {
+        int xid = ARGMAX ? pk_id[ARGMAX ? t : 0] : A.ids[r];
+        xid = xid < 0 ? 0 : (xid >= V ? V - 1 : xid);
+        double lo = 0.0, mid = 0.0, hi = 0.0;
+        for (int h = 0; h < H; ++h) {
+            const T* crow = static_cast<const T*>(A.draft) + (int64_t)h * head_stride + r * A.stride;
+            const double Sh = pk_S[t][h], ex = (double)exp2_ref(load_logit(crow, xid), pk_n[t][h]);
+            const double x = ex / Sh, omx = fmax(0.0, Sh - ex) / Sh;
+            double a = A.a, b = A.b;
+            if constexpr (RAD) {
+                const T* rrow = static_cast<const T*>(A.radius) + (int64_t)h * head_stride + r * A.stride;
+                const double rr = radius_of((double)load_logit(rrow, xid), A.kappa, A.rmax);
+                a = exp(rr); b = exp(-rr);
+            }
+            mid += x;
+            lo += pk_al[t][h] * b * x / (b + (1.0 - b) * omx);
+            hi += pk_au[t][h] * a * x / (1.0 + (a - 1.0) * x);
+        }
+        if (A.p_lo) A.p_lo[r] = (float)(lo / Hd);
+        if (A.p_mid) A.p_mid[r] = (float)(mid / Hd);
+        if (A.p_hi) A.p_hi[r] = (float)(hi / Hd);
+    }
+}
+
 // Voting: flags[row] = strict majority of head_flags[h][row].
 __global__ __launch_bounds__(256) void vote_kernel(const uint8_t* __restrict__ head_flags, int H, int64_t N,
                                                    uint8_t* __restrict__ flags)
@@ -759,13 +1223,77 @@ hipError_t launch_ensemble(int dtype, const RowArgs& args, int heads, int64_t he
     return hipGetLastError();
 }
 
-bool ensemble_fused_fits(int dtype, const RowArgs& args, int heads)
+// 32 tokens of a row per lane of at most 512: V <= 16384.  (The fp64 token path of tiny vocabularies is ensemble_kernel's.)
+bool ensemble_sweep_fits(const RowArgs& args) { return args.V > kTinyVocab && args.V <= 512 * kSweepTokens; }
+
+namespace {
+template <typename T, int THREADS, bool RAD, bool UNIT, bool ARGMAX>
+hipError_t launch_sweep_cfg(const RowArgs& a, int heads, int64_t head_stride, hipStream_t stream)
 {
-    if (args.radius || wide_radius(args) || needs_flat_pass(args) || heads < 1 || heads > kFusedHeads || args.V <= 64) return false;
-    const int epv = dtype == 0 ? 4 : 8;
-    const int nvec = (args.V + epv - 1) / epv;
-    const int per_lane = (nvec + kFusedThreads - 1) / kFusedThreads * epv;   // elements of one head's row per lane
-    return per_lane <= 32;
+    constexpr unsigned lds = 2u * kSweepTokens * sizeof(T) * THREADS;              // two rows: 8 to 128 KiB
+    {
+        // with the static arrays above the default limit: raised once per device and instance
+        static std::mutex guard;
+        static bool raised[64] = {};
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
+        std::lock_guard<std::mutex> lock(guard);
+        if (!raised[dev]) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ensemble_sweep_kernel<T, THREADS, RAD, UNIT, ARGMAX>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+            raised[dev] = true;
+        }
+    }
+    const int64_t resident = (int64_t)(512 / THREADS) * compute_units();
+    int64_t g = a.N < resident ? a.N : resident;
+    const int64_t need = (a.N + sweep_rows<THREADS>() - 1) / sweep_rows<THREADS>();
+    if (g < need) g = need;
+    const int wide = wide_radius(a) ? 1 : 0, flat64 = a.radius || needs_flat_pass(a) ? 1 : 0;
+    hipLaunchKernelGGL((ensemble_sweep_kernel<T, THREADS, RAD, UNIT, ARGMAX>), dim3((unsigned)g), dim3(THREADS), lds, stream, a, heads,
+                       head_stride, wide, flat64);
+    return hipGetLastError();
+}
+template <typename T, int THREADS, bool ARGMAX>
+hipError_t launch_sweep_radius(const RowArgs& a, int heads, int64_t head_stride, hipStream_t stream)
+{
+    if (!a.radius) return launch_sweep_cfg<T, THREADS, false, false, ARGMAX>(a, heads, head_stride, stream);
+    if (a.kappa == 1.0) return launch_sweep_cfg<T, THREADS, true, true, ARGMAX>(a, heads, head_stride, stream);
+    return launch_sweep_cfg<T, THREADS, true, false, ARGMAX>(a, heads, head_stride, stream);
+}
+template <typename T, int THREADS>
+hipError_t launch_sweep_tile(const RowArgs& a, int heads, int64_t head_stride, hipStream_t stream)
+{
+    const bool argmax = a.ids == nullptr && (a.p_lo || a.p_mid || a.p_hi);
+    return argmax ? launch_sweep_radius<T, THREADS, true>(a, heads, head_stride, stream)
+                  : launch_sweep_radius<T, THREADS, false>(a, heads, head_stride, stream);
+}
+template <typename T>
+hipError_t launch_sweep_typed(const RowArgs& a, int heads, int64_t head_stride, hipStream_t stream)
+{
+    if (a.V <= 64 * kSweepTokens) return launch_sweep_tile<T, 64>(a, heads, head_stride, stream);
+    if (a.V <= 128 * kSweepTokens) return launch_sweep_tile<T, 128>(a, heads, head_stride, stream);
+    if (a.V <= 256 * kSweepTokens) return launch_sweep_tile<T, 256>(a, heads, head_stride, stream);
+    return launch_sweep_tile<T, 512>(a, heads, head_stride, stream);
+}
+}  // namespace
+
+hipError_t launch_ensemble_sweep(int dtype, const RowArgs& args, int heads, int64_t head_stride, hipStream_t stream)
+{
+    if (args.N <= 0) return hipSuccess;
+    if (!ensemble_sweep_fits(args)) return hipErrorInvalidValue;
+    return dtype == 0 ? launch_sweep_typed<float>(args, heads, head_stride, stream)
+                      : launch_sweep_typed<bf16_t>(args, heads, head_stride, stream);
+}
+
+// Where its four waves per SIMD beat ensemble_sweep_kernel's two: a lane's share of a row filled with 17 to 32 tokens
+// (2048 positions x 16384 tokens, bf16: 58.8 against 68.2 us with two heads, 83.9 against 96.9 with three; fp32: 73.4 / 78.5,
+// 98.1 / 100.2; with 8192 tokens x 4096 positions the other way round: bf16 80.2 against 72.6, 117 against 103; fp32 87.8 / 75.5,
+// 127 / 107).
+bool ensemble_fused_fits(const RowArgs& args, int heads)
+{
+    return !args.radius && !wide_radius(args) && !needs_flat_pass(args) && heads >= 1 && heads <= kFusedHeads &&
+           args.V > 16 * kFusedThreads && args.V <= 32 * kFusedThreads;
 }
 
 namespace {
@@ -811,17 +1339,9 @@ hipError_t launch_ensemble_fused_cfg(const RowArgs& a, int heads, int64_t head_s
 hipError_t launch_ensemble_fused(int dtype, const RowArgs& args, int heads, int64_t head_stride, hipStream_t stream)
 {
     if (args.N <= 0) return hipSuccess;
-    if (!ensemble_fused_fits(dtype, args, heads)) return hipErrorInvalidValue;
-    const int epv = dtype == 0 ? 4 : 8;
-    const int nvec = (args.V + epv - 1) / epv;
-    const int per_lane = (nvec + kFusedThreads - 1) / kFusedThreads;
-    if (dtype == 0) {
-        if (per_lane <= 2) return launch_ensemble_fused_cfg<float, 2>(args, heads, head_stride, stream);
-        if (per_lane <= 4) return launch_ensemble_fused_cfg<float, 4>(args, heads, head_stride, stream);
-        return launch_ensemble_fused_cfg<float, 8>(args, heads, head_stride, stream);
-    }
-    if (per_lane <= 2) return launch_ensemble_fused_cfg<bf16_t, 2>(args, heads, head_stride, stream);
-    return launch_ensemble_fused_cfg<bf16_t, 4>(args, heads, head_stride, stream);
+    if (!ensemble_fused_fits(args, heads)) return hipErrorInvalidValue;
+    return dtype == 0 ? launch_ensemble_fused_cfg<float, 8>(args, heads, head_stride, stream)
+                      : launch_ensemble_fused_cfg<bf16_t, 4>(args, heads, head_stride, stream);
 }
 
 hipError_t launch_vote(const uint8_t* head_flags, int heads, int64_t N, uint8_t* flags, hipStream_t stream)

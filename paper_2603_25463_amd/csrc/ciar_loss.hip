@@ -65,14 +65,6 @@ constexpr uint32_t kRuledOutBits = 0xf1800000u;                    // (its upper
 //   CE(p_cloud, softmax(o)) = (reference + ln S_o) - (sum_i et_i o_i) / Z,
 //   KL(p_cloud || p_mid)    = ln S_mid - ln Z + (sum_i et_i ((t_i - max t) - (c_i - max c))) / Z.
 // terms[k * N + row], k = 0..6: L1(mid), L1(up), L1(lo), CE(mid), CE(up), CE(lo), KL.
-// Workgroup barrier for data exchanged through LDS only: waits for this wave's LDS operations and joins the barrier.
-// __syncthreads() would also wait for every outstanding global load (its fence covers all memory), and with it for
-// the next row that dro_row_stream_kernel has in flight while it works on the current one.
-__device__ __forceinline__ void lds_barrier()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // One row's totals (see dro_finish_row) from the three rows as loaded (lane t holds 16-byte vectors j * 1024 + t;
 // vectors past the end of the row hold copies of its last vector and are masked here), left in fin[kDroTotals] (LDS)
 // by lane 0.  Called by every lane of a 1024-lane workgroup; sm_d: 7 doubles per wave of LDS scratch.  Ends with every

@@ -531,6 +531,55 @@ def test_ensemble_one_sweep_special_rows(ciar, oracle, H, V, stride, N, dtype):
             parity.check_flags(ge["flags"], oe, float(np.float32(tau)))
 
 
+SWEEP_EDGES = [  # H, V, stride, N, dtype: both sides of every tile's end, several positions per workgroup, H from 1 to 8
+    (4, 65, 68, 2600, torch.float32), (2, 2048, 2048, 2100, torch.float32), (5, 2049, 2052, 1100, torch.float32),
+    (3, 4096, 4096, 1100, torch.bfloat16), (4, 4097, 4104, 530, torch.bfloat16), (2, 8192, 8192, 600, torch.float32),
+    (8, 8193, 8196, 40, torch.float32), (2, 16384, 16384, 300, torch.bfloat16), (4, 16384, 16384, 70, torch.float32),
+]
+
+
+@pytest.mark.parametrize("H,V,stride,N,dtype", SWEEP_EDGES)
+@pytest.mark.parametrize("kw", [dict(confidence=0.9), dict(tensor=True, radius_scale=1.0),
+                                dict(tensor=True, radius_scale=0.7, radius_max=3.0)])
+def test_ensemble_sweep_edges(ciar, oracle, H, V, stride, N, dtype, kw):
+    """The one-sweep Ensemble kernel at the edges of its tiles, on ordinary rows among those it treats apart: active caps
+    (nearly one-hot rows, radii next to nothing) and, for the fp64 kernel behind it, rows flat in every head and widths
+    that agree to within a hundredth; with and without drafted ids."""
+    kw = dict(kw)
+    tensor = kw.pop("tensor", False)
+    heads = _head_stack(H, V, stride, N, torch.float32, seed=8000 + V + H)
+    rows = torch.arange(N, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(12)
+    tok = torch.randint(0, V, (N,), generator=g, device="cuda")
+    heads[:, rows[1::6], tok[1::6]] += 28.0                  # every head nearly one-hot
+    heads[0, rows[2::6], tok[2::6]] += 28.0                  # one head nearly one-hot
+    heads[:, rows[3::12]] *= 0.003                           # flat in every head
+    heads[:, rows[4::12], : V // 4] = float("-inf")          # masked tokens
+    if stride > V:
+        heads[:, :, V:] = 1e30
+    heads = heads.to(dtype).contiguous()
+    raw = None
+    if tensor:
+        raw = torch.stack([_raw_radius(N, stride, V, torch.float32, seed=5500 + V + h) for h in range(H)])
+        raw[:, rows[5::12], :V] = -6.0                       # radii of 0.0025: the caps are active whatever the row
+        raw = raw.to(dtype).contiguous()
+    ids = torch.randint(0, V, (N,), generator=g, device="cuda").to(torch.int32)
+    ids[1::6] = tok[1::6].to(torch.int32)
+    hh, rh = heads.cpu(), None if raw is None else raw.cpu()
+    say(f"[ensemble sweep] H={H} V={V} stride={stride} N={N} {dtype} {kw} {'tensor' if tensor else 'scalar'}")
+    o0 = oracle.quantify_multihead(hh, ids.cpu().numpy(), _oparams(oracle, ciar.Params(**kw)), oracle.ENSEMBLE, vocab=V,
+                                   radius_heads=rh)
+    tau = float(np.float32(np.median(o0["score"])))
+    P = ciar.Params(tau=tau, **kw)
+    for with_ids in (True, False):
+        ge = ciar.quantify_multihead(heads, ids if with_ids else None, P, ciar.ENSEMBLE, vocab=V, radius_heads=raw)
+        torch.cuda.synchronize()
+        oe = oracle.quantify_multihead(hh, ids.cpu().numpy() if with_ids else None, _oparams(oracle, P), oracle.ENSEMBLE,
+                                       vocab=V, radius_heads=rh)
+        parity.check_floats(ge, oe)
+        parity.check_flags(ge["flags"], oe, float(np.float32(tau)))
+
+
 # ---- Inter-DRO loss, forward (Sec. 3.2.3) -------------------------------------------------------------------
 
 def _check_dro(g, o, N):
