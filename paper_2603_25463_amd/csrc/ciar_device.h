@@ -44,6 +44,12 @@ __device__ __forceinline__ float max3(float a, float b, float c)
     asm("v_max3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));
     return m;
 }
+__device__ __forceinline__ float max2(float a, float b)
+{
+    float m;
+    asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"(a), "v"(b));
+    return m;
+}
 template <int N>
 __device__ __forceinline__ float max_of(const float (&v)[N])
 {
@@ -163,9 +169,19 @@ __device__ __forceinline__ int dpp_or(int fill, int v)
     return __builtin_amdgcn_update_dpp(fill, v, CTRL, ROW_MASK, 0xf, false);
 }
 
+// the same with 0 for lanes without a source, all rows written (no register has to be cleared for the result first)
+template <int CTRL>
+__device__ __forceinline__ int dpp_zero(int v)
+{
+    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
+}
+constexpr bool dpp_in_row(int ctrl) { return ctrl != 0x142 && ctrl != 0x143; }   // (not a broadcast from row to row)
+
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ double dpp_add(double v)
 {
+    if constexpr (ROW_MASK == 0xf && dpp_in_row(CTRL))
+        return v + __hiloint2double(dpp_zero<CTRL>(__double2hiint(v)), dpp_zero<CTRL>(__double2loint(v)));
     const int lo = dpp_or<CTRL, ROW_MASK>(0, __double2loint(v));
     const int hi = dpp_or<CTRL, ROW_MASK>(0, __double2hiint(v));
     return v + __hiloint2double(hi, lo);           // lanes without a source add +0.0
@@ -242,7 +258,7 @@ template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ float dpp_max(float v)
 {
     // lanes without a source get their own value back: max(v, v) = v
-    return fmaxf(v, __int_as_float(dpp_or<CTRL, ROW_MASK>(__float_as_int(v), __float_as_int(v))));
+    return max2(v, __int_as_float(dpp_or<CTRL, ROW_MASK>(__float_as_int(v), __float_as_int(v))));
 }
 
 __device__ __forceinline__ float wave_max(float v)

@@ -672,10 +672,7 @@ void stream_kernel(const RowArgs A)
         }
 #pragma unroll
         for (int j = 0; j < NVEC; ++j) E::unpack(buf[j], &e[j * EPV]);
-        float mcl = e[0];
-#pragma unroll
-        for (int i = 1; i < EPT; ++i) mcl = fmaxf(mcl, e[i]);
-        const float mcw = wave_max(mcl);
+        const float mcw = wave_max(max_of(e));
         const float nw = ref_of(mcw);
         double Sw;
         {
@@ -717,16 +714,15 @@ void stream_kernel(const RowArgs A)
         // (by_lanes: across the first lanes of the wave, which must all be active; else in a loop)
         auto combine_S = [&](auto by_lanes, float& mc, float& n, double& S) {
             if constexpr (decltype(by_lanes)::value) {
+                // (the row's reference is the largest of the waves': the reference of the largest logit)
                 const float mc_l = sm_ref[src * 2], n_l = sm_ref[src * 2 + 1];
-                mc = row16_max(mc_l); n = row16_max(n_l);
+                mc = row16_max(mc_l); n = ref_of(mc);
                 S = row16_sum(lane < NW && n_l != -INFINITY ? sm_S[src] * pow2_of(n_l - n) : 0.0);
             } else {
-                mc = sm_ref[0]; n = sm_ref[1];
+                mc = sm_ref[0];
 #pragma unroll
-                for (int w = 1; w < NW; ++w) {
-                    mc = fmaxf(mc, sm_ref[w * 2]);
-                    n = fmaxf(n, sm_ref[w * 2 + 1]);
-                }
+                for (int w = 1; w < NW; ++w) mc = max2(mc, sm_ref[w * 2]);
+                n = ref_of(mc);
                 S = 0.0;
 #pragma unroll
                 for (int w = 0; w < NW; ++w) {
@@ -773,7 +769,7 @@ void stream_kernel(const RowArgs A)
             double ra = A.a, rb = A.b;
             float wpx = A.wpoly_x;
             if constexpr (sizeof(T) == 2) asm volatile("" : "+s"(ra), "+s"(rb), "+s"(wpx));   // (fp32 instances: no gain, measured)
-            const FuseRow fr = fuse_row(Su, ra, rb);
+            const FuseRow fr = fuse_row_inv(recip(Su), ra, rb);
             double q5[NQ];
             auto shift_of = [&](float eref, const FuseRow& r) {
                 Shift k;
