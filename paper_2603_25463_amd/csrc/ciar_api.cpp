@@ -320,6 +320,13 @@ int run_stream(const Call& c, ciar::Mode mode)
     if (int rc = fill(c, mode, &a)) return rc;
     if (c.N == 0) return CIAR_OK;
     discard_stale_hip_error();
+    if (mode == ciar::Mode::Quantify && ciar::radius_quantify_fits(a)) {
+        // a radius tensor and no verifier row: a kernel of its own, arg-max tokens and flat rows included
+        a.precise_flat = ciar::needs_flat_pass(a) ? 1 : 0;
+        const hipError_t e = ciar::launch_radius_quantify(c.params->dtype, a, 1, nullptr, c.stream, c.ev_start, c.ev_stop);
+        if (e != hipSuccess) return hip_fail(e, "radius kernel launch");
+        return CIAR_OK;
+    }
     if (needs_argmax(a)) {
         const hipError_t e = ciar::launch_argmax(c.params->dtype, a, a.reject_list, c.stream);
         if (e != hipSuccess) return hip_fail(e, "arg-max kernel launch");
@@ -676,6 +683,14 @@ int ciar_quantify_multihead(const void* draft_heads, const void* radius_heads, i
             a.ids_period = heads > 1 ? N : 0;
             a.p_lo = p_lo; a.p_mid = p_mid; a.p_hi = p_hi;
             a.omega = omega; a.sigma = sigma; a.score = score;
+            if (ciar::radius_quantify_fits(a)) {
+                // with a radius tensor one kernel takes all heads of a position, and the vote
+                a.flags = head_flags;
+                a.precise_flat = ciar::needs_flat_pass(a) ? 1 : 0;
+                const hipError_t e = ciar::launch_radius_quantify(params->dtype, a, heads, flags, stream);
+                if (e != hipSuccess) return hip_fail(e, "radius kernel launch");
+                return CIAR_OK;
+            }
             a.flags = head_flags ? head_flags : ws_flags;
             if (needs_argmax(a)) {
                 const hipError_t e = ciar::launch_argmax(params->dtype, a, a.reject_list, stream);
@@ -693,7 +708,9 @@ int ciar_quantify_multihead(const void* draft_heads, const void* radius_heads, i
             }
         } else {
             // Ensemble: only every head's RowStats
-            const hipError_t e = ciar::launch_stream(ciar::Mode::Quantify, params->dtype, a, false, stream);
+            const hipError_t e = ciar::radius_quantify_fits(a)
+                                     ? ciar::launch_radius_quantify(params->dtype, a, heads, nullptr, stream)
+                                     : ciar::launch_stream(ciar::Mode::Quantify, params->dtype, a, false, stream);
             if (e != hipSuccess) return hip_fail(e, "streaming kernel launch");
         }
     }

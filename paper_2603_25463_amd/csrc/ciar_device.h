@@ -20,6 +20,8 @@ constexpr double kLn2 = 0.69314718055994530942;
 
 __device__ __forceinline__ float bits_f(uint32_t u) { return __uint_as_float(u); }
 
+constexpr int kNonTemporal = 2;        // cache policy of global_load_lds for rows that are used once
+
 // 16 bytes as loaded: a native vector type, so it can be read through an address-space pointer.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 using gbytes = const __attribute__((address_space(1))) char*;
@@ -578,8 +580,9 @@ __device__ __forceinline__ int accept_quick(float cx, float tx, float u, float n
 // steps): score, flag, the reported token's interval, the accept test in the log domain.  xid = the reported
 // token (-1: the arg-max token, whose logit is st.mc), cx / tx / rawx = its centre logit, verifier logit and raw
 // radius, u = the row's uniform for the accept test.  Returns whether the drafted token is rejected.
+// raw_top: tensor radius, rows with a token above 1/2: that token's raw radius.
 __device__ __forceinline__ bool finish_row(const RowArgs& A, int64_t row, const RowStats& st, float cx, float tx,
-                                           float rawx, float u, bool do_q, bool do_v)
+                                           float rawx, float u, bool do_q, bool do_v, float raw_top = 0.f)
 {
     const double S = st.S;
     const float n = st.n;
@@ -592,23 +595,36 @@ __device__ __forceinline__ bool finish_row(const RowArgs& A, int64_t row, const 
         // 0.01 (a seeded random case: 2.04e-7 off).  At most one token of a row is above 1/2: the row's largest, whose
         // wave has the row's reference, so its e and the fp32 values that the scalar-radius pass has added to the sums
         // can be formed again here, by the same instructions, and exchanged for the fp64 values.  (Plain sums only:
-        // such a row is not flat.  Tensor-radius, wide-radius and tiny-vocabulary rows come from other passes.)
+        // such a row is not flat.  Wide scalar radii and tiny vocabularies come from other passes.)
+        // With a radius tensor likewise, from the fp32 radius: its error moves the bounds by p (1 - p) times as much.
         // (the call's constants through an empty asm: what is derived from them here is otherwise formed at the top of
         // the calling kernel and kept -- in the streaming kernel: spilled -- through its row loop)
         double fa = A.a, fb = A.b;
         int fv = A.V;
         asm volatile("" : "+s"(fa), "+s"(fb), "+s"(fv));
-        if (st.mode == kSumsFull && A.normalize && !A.radius && fv > kTinyVocab && fa < 3.0 * (double)fv &&
+        if (st.mode == kSumsFull && A.normalize && fv > kTinyVocab && (A.radius || fa < 3.0 * (double)fv) &&
             st.kl == 0.0 && st.kw == 0.0) {
             const float etop = exp2_ref(st.mc, n == -INFINITY ? 0.f : n);
             if ((double)etop > 0.5 * S) {
                 const double ed = (double)etop, invS = 1.0 / S;
                 const double x = ed * invS, om = fmax(0.0, S - ed) * invS;      // 1 - x from the sum of the other tokens
-                const double du = 1.0 + (fa - 1.0) * x, dl = fb + (1.0 - fb) * om;
-                const double gl = ed / dl, gw = gl * om / du;
-                float g, duf, omf;
-                fuse_parts<true>(etop, fuse_row(S, fa, fb), g, duf, omf);
-                const double glf = (double)(g * duf), gwf = (double)(g * omf);
+                double gl, gw, glf, gwf;
+                if (A.radius) {
+                    const RadiusMode rm = radius_mode(A);
+                    float plf, wf;
+                    fuse_token_rad(etop, raw_top, fuse_row_inv(recip(S), fa, fb), rm, plf, wf);
+                    glf = (double)plf; gwf = (double)wf;
+                    const double am1 = (double)(rm.unit ? radius_am1<true>(raw_top, rm.kappa, rm.rmax, rm.am1_max)
+                                                        : radius_am1<false>(raw_top, rm.kappa, rm.rmax, rm.am1_max));
+                    gl = ed / (1.0 + am1 * om);
+                    gw = am1 * (am1 + 2.0) * om * gl / (1.0 + am1 * x);
+                } else {
+                    const double du = 1.0 + (fa - 1.0) * x, dl = fb + (1.0 - fb) * om;
+                    gl = ed / dl; gw = gl * om / du;
+                    float g, duf, omf;
+                    fuse_parts<true>(etop, fuse_row_inv(recip(S), fa, fb), g, duf, omf);
+                    glf = (double)(g * duf); gwf = (double)(g * omf);
+                }
                 q[0] += gl - glf;
                 q[1] += gw - gwf;
                 q[2] += gl * gl - glf * glf;

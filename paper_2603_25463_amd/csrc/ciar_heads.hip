@@ -744,7 +744,6 @@ void ensemble_fused_kernel(const RowArgs A, const int64_t head_stride)
 // rows flat in every head and widths that all crowd against 1 are swept a second time in fp64.
 // The positions' scalars are parked in LDS and turned into outputs after the workgroup's last one, a lane per position: the
 // logits of the reported tokens are then fetched for all of them at once instead of in a chain per position.
-constexpr int kNonTemporal = 2;                                    // cache policy of global_load_lds: every row is used once
 constexpr int kSweepTokens = 32;                                   // tokens of a row per lane
 template <int THREADS> constexpr int sweep_rows() { return THREADS >= 256 ? 32 : THREADS / 8; }   // most positions of a workgroup
 

@@ -159,6 +159,13 @@ hipError_t launch_windows(const uint8_t* accept, const int32_t* row_id, int64_t 
 hipError_t launch_dro(int dtype, const RowArgs& args, float* terms, double lambda_v, double lambda_p,
                       double lambda_beta, double alpha, float* weights, float* losses, hipStream_t stream);
 
+// The quantifier of calls with a radius tensor and more than 64 tokens, all outputs written (ids may be null: the arg-max
+// token; args.precise_flat as for the streaming kernel; args.stats is written).  args.N rows = heads x positions; votes (may be
+// null): per position the strict majority of the heads' flags.
+bool radius_quantify_fits(const RowArgs& args);
+hipError_t launch_radius_quantify(int dtype, const RowArgs& args, int heads, uint8_t* votes, hipStream_t stream,
+                                  hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+
 // Several heads.  Head h of args.draft / args.radius starts h * head_stride elements after head 0;
 // args.stats holds [heads][N] RowStats left by one streaming pass per head.
 int max_heads();

@@ -1,0 +1,434 @@
+// gfx950 quantifier for calls with a radius tensor and no verifier row (Sec. 3.2.3: r = Softplus of the Interval Head's radius
+// half): ciar_quantify in tensor mode, every head of Voting, the consumer of ciar_interhead_quantify.
+//
+// Two rows per position, the second of which (the raw radius) is wanted only once the partition sum of the first is known.
+// Per row, in a workgroup that walks over its rows:
+//   1. centre row: per-wave maximum, e_i = 2^(c_i log2e - n_w) in registers, S_w;  -- barrier: (max, S_w) --
+//   2. radius row, vector by vector: p^l_i and p^u_i - p^l_i from e_i, S and the token's own a_i - 1; five sums.
+// Both rows come through the same slots of LDS (global_load_lds: no register is held while a row is on its way): when the centre
+// row has moved to registers its slots are requested full of the radius row, which arrives during step 1, and every slot
+// that step 2 has read is requested full of the next centre row, which arrives during the rest of step 2.  A lane reads back
+// only slots that its own wave has requested, so the hand-over is the wave's own count of outstanding loads.  128 bytes of a
+// row per lane (32 fp32 or 64 bf16 tokens) at four waves per SIMD: what a row costs a wave whatever its length (reductions,
+// exchange, constants: ~300 instructions) is spread over as many tokens as the registers hold.
+// What the streaming kernel did for such calls before: the radius row requested into registers behind the barrier (its trip to
+// memory exposed, two thirds of the time of a row), bf16 rows with 76-250 B of scratch per lane, a second launch for flat
+// rows and a third for the vote.
+//
+// A row's scalars are parked in LDS; after the workgroup's last row a lane per row turns them into the outputs.  Rows whose
+// widths agree to better than a hundredth of their mean, flat rows of calls whose widths are not small (needs_flat_pass) and
+// rows whose widths crowd against 1 (wide_radius) are swept again in fp64 before that is written.
+#include "ciar_device.h"
+
+#include <hip/hip_ext.h>
+#include <mutex>
+
+namespace ciar {
+namespace {
+
+constexpr int kRadVecs = 8;                                        // 16-byte vectors of a row per lane
+template <int THREADS> constexpr int radius_rows() { return THREADS >= 512 ? 128 : THREADS / 4; }   // most rows of a workgroup
+
+struct RadiusRow { double S, q[5]; float n, mc, raw_top; };        // see RowStats, finish_row
+
+// The five sums of a row in fp64 from the logits, about the first token's values, by the whole workgroup; red: 6 doubles per wave.
+template <typename T, int THREADS>
+__device__ void radius_row_fp64(const RowArgs& A, int64_t row, double (*red)[48], RowStats& st)
+{
+    constexpr int NW = THREADS / 64;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = tid >> 6;
+    const T* crow = static_cast<const T*>(A.draft) + row_offset(A, row);
+    const T* rrow = static_cast<const T*>(A.radius) + row_offset(A, row);
+    const double mc = (double)st.mc;
+    auto total = [&](double v) {
+        v = wave_sum(v);
+        __syncthreads();                                           // the slots may still be read from the last use
+        if (lane == 0) red[wave][0] = v;
+        __syncthreads();
+        return row16_sum(lane < NW ? red[lane < NW ? lane : 0][0] : 0.0);
+    };
+    double s = 0.0;
+    for (int i = tid; i < A.V; i += THREADS) s += exp((double)load_logit(crow, i) - mc);   // masked token: exp(-inf) = 0
+    const double invS = 1.0 / total(s);
+    auto token = [&](int i, double& pl, double& w) {
+        const double x = exp((double)load_logit(crow, i) - mc) * invS;
+        const double r = radius_of((double)load_logit(rrow, i), A.kappa, A.rmax);
+        const double a = exp(r), b = exp(-r), om = 1.0 - x, dl = b + (1.0 - b) * om, du = 1.0 + (a - 1.0) * x;
+        pl = b * x / dl;
+        w = (a - b) * x * om / (du * dl);
+    };
+    double kl, kw;
+    token(0, kl, kw);                                              // every lane forms the same shift
+    double q[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int i = tid; i < A.V; i += THREADS) {
+        double pl, w;
+        token(i, pl, w);
+        pl -= kl; w -= kw;
+        q[0] += pl; q[1] += w;
+        q[2] = fma(pl, pl, q[2]); q[3] = fma(w, w, q[3]); q[4] = fma(pl, w, q[4]);
+    }
+#pragma unroll
+    for (int i = 0; i < 5; ++i) st.q[i] = total(q[i]);
+    st.kl = kl; st.kw = kw;
+    st.mode = kSumsDirect;
+}
+
+// A.N rows: [H, P] if A.head_rows is set (H heads of P positions), else P = A.N positions of one head.
+// ARGMAX = no drafted ids: every row reports its arg-max token.  votes: [P] flags by strict majority, or null.
+template <typename T, int THREADS, bool UNIT, bool ARGMAX>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)))
+void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __restrict__ votes)
+{
+    using E = Elt<T>;
+    constexpr int EPV = E::kPerVec, NVEC = kRadVecs, EPT = NVEC * EPV, NW = THREADS / 64, ROWS = radius_rows<THREADS>();
+    constexpr int CHUNK = THREADS * EPV;                           // tokens of one vector of every lane
+    extern __shared__ u32x4 sm_next[];                             // [NVEC][THREADS]: the row in flight
+    // exchange slots of a row: written before its barrier, read behind it; rows alternate between two sets
+    __shared__ float sm_ref[2][NW];
+    __shared__ double sm_S[2][NW], sm_tot[2][NW][5];
+    __shared__ double sm_red[NW][48];                              // per wave: [five sums of the row before, S_w][eight groups of lanes]
+    __shared__ int sm_pi[2][ARGMAX ? NW : 1];
+    // parked rows
+    __shared__ RadiusRow pk[ROWS];
+    __shared__ int pk_id[ARGMAX ? ROWS : 1];
+    __shared__ uint8_t pk_fp64[ROWS], pk_flag[ROWS];
+
+    // (the lane's index is asked for anew wherever it is used, through an empty asm: no LDS address formed from it is held in
+    // registers, or spilled, through the loop -- and a reload would wait for the row in flight)
+    auto my_tid = []() {
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+    auto uniform = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int V = A.V;
+    const int nch = (V + CHUNK - 1) / CHUNK;                       // vectors of a lane that hold tokens at all
+    const int last_vec = (V + EPV - 1) / EPV - 1;
+    const uint32_t P = (uint32_t)(A.head_rows ? A.head_rows : A.N), step = gridDim.x;
+    const float kappa = uniform((float)A.kappa), rmax = uniform((float)A.rmax), am1_max = uniform((float)expm1(A.rmax));
+    // this workgroup's rows: H of each of its positions blockIdx.x, blockIdx.x + step, ...
+    const uint32_t mine = blockIdx.x < P ? (P - blockIdx.x + step - 1u) / step : 0u;
+    const int count = (int)mine * H;                               // <= ROWS: the launcher sizes the grid accordingly
+    if (count == 0) return;
+
+    using lds_ptr = __attribute__((address_space(3))) void*;
+    using glb_ptr = const __attribute__((address_space(1))) void*;
+    auto row_base = [&](const void* rows, uint32_t pos, int h) {
+        const uint64_t b = (uint64_t)(static_cast<const T*>(rows) + (int64_t)h * A.head_stride + (int64_t)pos * A.stride);
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+        const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+        return (gbytes)(((uint64_t)hi << 32) | lo);
+    };
+    // vector j of a row goes in flight (lane l of a wave lands 16 l bytes behind the address the wave names); lanes past the end
+    // of the row fetch its last vector
+    auto fetch = [&](gbytes base, int j, int tid) {
+        if (j < nch) {                                             // uniform
+            const uint32_t v = (j + 1) * THREADS - 1 <= last_vec ? (uint32_t)(j * THREADS + tid) : (uint32_t)min(j * THREADS + tid, last_vec);
+            __builtin_amdgcn_global_load_lds((glb_ptr)(base + v * 16u), (lds_ptr)(sm_next + j * THREADS + wave * 64), 16, 0, kNonTemporal);
+        }
+    };
+    // wave 0: a row's sums over the waves, parked
+    auto park = [&](int at, int p) {
+        const int lane = my_tid() & 63, grp = lane >> 3, part = lane & 7;
+        double v = 0.0;
+        if (grp < 5) {
+            if (part < NW) v = sm_tot[p][part][grp];
+            if (NW > 8) v += sm_tot[p][part + (NW > 8 ? 8 : 0)][grp];
+        }
+        v = dpp_add<0xB1, 0xf>(v);                                 // lane ^ 1, lane ^ 2, the other quad of the eight
+        v = dpp_add<0x4E, 0xf>(v);
+        v = dpp_add<0x141, 0xf>(v);
+        if (grp < 5 && part == 0) pk[at].q[grp] = v;
+    };
+    // the six quantities of a wave reduced together: every lane's value -> groups of eight lanes (three DPP steps) -> LDS
+    auto put = [&](double v, int which, int lane) {
+        v = dpp_add<0xB1, 0xf>(v);
+        v = dpp_add<0x4E, 0xf>(v);
+        v = dpp_add<0x141, 0xf>(v);
+        if ((lane & 7) == 0) sm_red[wave][which * 8 + (lane >> 3)] = v;
+    };
+    auto get = [&](int lane) {                                     // lanes 8 q ... 8 q + 7: quantity q over the wave
+        double v = sm_red[wave][lane < 48 ? lane : 0];
+        v = dpp_add<0xB1, 0xf>(v);
+        v = dpp_add<0x4E, 0xf>(v);
+        return dpp_add<0x141, 0xf>(v);
+    };
+
+    uint32_t pos = blockIdx.x;
+    int h = 0;
+    {
+        const gbytes base = row_base(A.draft, pos, h);
+        const int tid = my_tid();
+#pragma unroll
+        for (int j = 0; j < NVEC; ++j) fetch(base, j, tid);
+    }
+    if constexpr (THREADS < 1024) {
+        if (count > 1) __builtin_amdgcn_s_setprio(3);
+    }
+    for (int done = 0;; ++done) {
+        const int p = done & 1;
+        const int tid = my_tid(), lane = tid & 63;
+        const bool has_next = done + 1 < count;                    // uniform
+        // ---- 1: the centre row ------------------------------------------------------------------------------------------
+        float e[EPT];
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        {
+            u32x4 buf[NVEC];
+#pragma unroll
+            for (int j = 0; j < NVEC; ++j) buf[j] = sm_next[j * THREADS + tid];
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            const gbytes base = row_base(A.radius, pos, h);
+#pragma unroll
+            for (int j = 0; j < NVEC; ++j) fetch(base, j, tid);
+#pragma unroll
+            for (int j = 0; j < NVEC; ++j) {
+                if ((j + 1) * CHUNK > V) E::mask_tail(buf[j], (j * THREADS + tid) * EPV, V);      // uniform
+                E::unpack(buf[j], &e[j * EPV]);
+            }
+        }
+        const float mw = wave_max(max_of(e)), nw = ref_of(mw), nref = nw == -INFINITY ? 0.f : nw;
+        if constexpr (ARGMAX) {
+            int at = INT_MAX;
+#pragma unroll
+            for (int i = EPT - 1; i >= 0; --i)
+                if (e[i] == mw) at = (i / EPV * THREADS + tid) * EPV + i % EPV;
+            at = wave_min_i(at);
+            if (lane == 0) sm_pi[p][wave] = at;
+        }
+        double Sl = 0.0;
+#pragma unroll
+        for (int j = 0; j < NVEC; ++j) {
+            if (j < nch) {
+#pragma unroll
+                for (int k = 0; k < EPV; ++k) {
+                    e[j * EPV + k] = exp2_ref(e[j * EPV + k], nref);
+                    Sl += (double)e[j * EPV + k];
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        put(Sl, 5, lane);
+        {
+            const double v = get(lane);
+            const int grp = lane >> 3;
+            if ((lane & 7) == 0) {
+                if (grp < 5) { if (done > 0) sm_tot[p ^ 1][wave][grp] = v; }
+                else if (grp == 5) sm_S[p][wave] = v;
+            }
+            if (lane == 0) sm_ref[p][wave] = mw;
+        }
+        lds_barrier();
+        if (wave == 0 && done > 0) park(done - 1, p ^ 1);
+        const int src = lane < NW ? lane : 0;
+        const float m_l = sm_ref[p][src], n_l = ref_of(m_l), mc = row16_max(m_l), n = ref_of(mc);
+        const double S = row16_sum(lane < NW && n_l != -INFINITY ? sm_S[p][src] * pow2_of(n_l - n) : 0.0);
+        if constexpr (ARGMAX) {
+            if (wave == 0) {                                       // the lowest index of the waves that hold the maximum
+                const int best = wave_min_i(lane < NW && m_l == mc ? sm_pi[p][src] : INT_MAX);
+                if (lane == 0) pk_id[done] = best == INT_MAX ? 0 : best;
+            }
+        }
+        if (tid == 0) { pk[done].S = S; pk[done].n = n; pk[done].mc = mc; }
+        const double fw = nw == -INFINITY ? 0.0 : pow2_of(nw - n);                         // this wave's e_i are 1 / fw too large
+        const double Su = nw == -INFINITY ? 1.0 : ldexp(S, (int)fminf(n - nw, 1000.f));   // S in this wave's units
+        const bool top = (double)exp2_ref(mc, n == -INFINITY ? 0.f : n) > 0.5 * S;         // uniform over the workgroup
+        FuseRow fr;
+        {
+            const double inv = recip(Su);
+            const float nih = (float)-inv;
+            fr = {0.f, uniform(nih), uniform((float)(-inv - (double)nih)), 0.f, 0.f};
+        }
+        // ---- 2: the radius row; its slots take the next centre row as they are read ---------------------------------------
+        uint32_t npos = pos;
+        int nh = h;
+        if (has_next) {
+            if (++nh == H) { nh = 0; npos += step; }
+        }
+        const gbytes next = row_base(A.draft, npos, nh);
+        double q[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+        const float half = 0.5f * (float)Su;
+        float raw_top = INFINITY;                                  // raw radius of a token above 1/2, for finish_row
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int g = 0; g < NVEC; g += 4) {
+            u32x4 rb[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) rb[u] = sm_next[(g + u) * THREADS + tid];
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (has_next) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) fetch(next, g + u, tid);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int j = g + u;
+                if (j < nch) {                                     // uniform: the vectors hold tokens
+                    if ((j + 1) * CHUNK > V) E::zero_tail(rb[u], (j * THREADS + tid) * EPV, V);
+                    float rv[EPV];
+                    E::unpack(rb[u], rv);
+#pragma unroll
+                    for (int k = 0; k < EPV; ++k) {
+                        float pl, w;                               // (a slot past the row's end holds e = 0: both are 0)
+                        fuse_token_rad<UNIT>(e[j * EPV + k], rv[k], fr, kappa, rmax, am1_max, pl, w);
+                        const double dl = (double)pl, dw = (double)w;
+                        q[0] += dl; q[1] += dw;
+                        q[2] = fma(dl, dl, q[2]); q[3] = fma(dw, dw, q[3]); q[4] = fma(dl, dw, q[4]);
+                    }
+                    if (top) {                                     // uniform: some probability above 1/2 (at most one)
+#pragma unroll
+                        for (int k = 0; k < EPV; ++k) raw_top = e[j * EPV + k] >= half ? rv[k] : raw_top;
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (raw_top != INFINITY) pk[done].raw_top = raw_top;       // (at most one lane of the workgroup)
+        {
+            const double f2 = fw * fw;                             // to row units
+            put(q[0] * fw, 0, lane); put(q[1] * fw, 1, lane);
+            put(q[2] * f2, 2, lane); put(q[3] * f2, 3, lane); put(q[4] * f2, 4, lane);
+        }
+        if (!has_next) break;
+        pos = npos; h = nh;
+        // wave priority by progress: whoever of the workgroups of a compute unit is behind is served first
+        if constexpr (THREADS < 1024) {
+            if (done + 1 < (count + 3) >> 2) __builtin_amdgcn_s_setprio(3);
+            else if (done + 1 < (count + 1) >> 1) __builtin_amdgcn_s_setprio(2);
+            else if (done + 1 < (3 * count + 3) >> 2) __builtin_amdgcn_s_setprio(1);
+            else __builtin_amdgcn_s_setprio(0);
+        }
+    }
+    {
+        const int lane = my_tid() & 63;
+        const double v = get(lane);
+        if ((lane & 7) == 0 && lane < 40) sm_tot[(count - 1) & 1][wave][lane >> 3] = v;
+    }
+    __syncthreads();
+    if (wave == 0) park(count - 1, (count - 1) & 1);
+    __syncthreads();
+    // ---- a lane per row ---------------------------------------------------------------------------------------------------
+    auto stats_of = [&](int at) {
+        RowStats st;
+        st.S = pk[at].S; st.Z = 0.0; st.n = pk[at].n; st.nt = 0.f; st.mc = pk[at].mc;
+#pragma unroll
+        for (int i = 0; i < 5; ++i) st.q[i] = pk[at].q[i];
+        st.kl = 0.0; st.kw = 0.0; st.mode = kSumsFull;
+        return st;
+    };
+    auto row_of = [&](int at) { return (int64_t)(at % H) * P + blockIdx.x + (int64_t)(at / H) * step; };
+    auto finish = [&](int at, const RowStats& st) {
+        const int64_t r = row_of(at);
+        const int64_t off = (int64_t)(at % H) * A.head_stride + (r - (int64_t)(at % H) * P) * A.stride;
+        int xid = ARGMAX ? pk_id[ARGMAX ? at : 0] : A.ids ? A.ids[ids_index(A, r)] : 0;
+        xid = xid < 0 ? 0 : (xid >= V ? V - 1 : xid);
+        const float cx = load_logit(static_cast<const T*>(A.draft) + off, xid);
+        const float rawx = load_logit(static_cast<const T*>(A.radius) + off, xid);
+        finish_row(A, r, st, cx, 0.f, rawx, 0.f, true, false, pk[at].raw_top);
+        A.stats[r] = st;
+    };
+    {
+        const int t = my_tid();
+        if (t < count) {
+            const RowStats st = stats_of(t);
+            const RowScore rs = finish_score(st.q, st.S, st.mode, A, 0.0, 0.0);
+            const double Vd = (double)V, mean = rs.omega / Vd;
+            const double etop = (double)exp2_ref(st.mc, st.n == -INFINITY ? 0.f : st.n);
+            const bool fp64 = !(rs.sigma * rs.sigma >= 1e-4 * mean * mean) || (A.precise_flat && etop * Vd <= 2.0 * st.S) ||
+                              (wide && mean > 0.45);
+            pk_fp64[t] = (uint8_t)fp64;
+            pk_flag[t] = (uint8_t)(rs.score > A.tau);
+            if (!fp64) finish(t, st);
+        }
+    }
+    __syncthreads();
+    for (int at = 0; at < count; ++at) {
+        if (!pk_fp64[at]) continue;                                // uniform
+        RowStats st = stats_of(at);
+        radius_row_fp64<T, THREADS>(A, row_of(at), sm_red, st);
+        if (my_tid() == 0) {
+            pk_flag[at] = (uint8_t)(finish_score(st.q, st.S, st.mode, A, st.kl, st.kw).score > A.tau);
+            finish(at, st);
+        }
+    }
+    if (votes) {
+        __syncthreads();
+        const int t = my_tid();
+        if (t < (int)mine) {
+            int yes = 0;
+            for (int i = 0; i < H; ++i) yes += pk_flag[t * H + i];
+            votes[blockIdx.x + (int64_t)t * step] = (uint8_t)(2 * yes > H);
+        }
+    }
+}
+
+template <typename T, int THREADS, bool UNIT, bool ARGMAX>
+hipError_t launch_radius_cfg(const RowArgs& a, int heads, uint8_t* votes, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop)
+{
+    constexpr unsigned lds = kRadVecs * 16u * THREADS;             // 8 to 128 KiB
+    if (lds > 32u * 1024u) {
+        // with the static arrays above the default limit: raised once per device and instance
+        static std::mutex guard;
+        static bool raised[64] = {};
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
+        std::lock_guard<std::mutex> lock(guard);
+        if (!raised[dev]) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&radius_kernel<T, THREADS, UNIT, ARGMAX>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+            raised[dev] = true;
+        }
+    }
+    const int64_t P = a.N / heads, resident = (int64_t)(1024 / THREADS) * compute_units();
+    const int64_t per_wg = radius_rows<THREADS>() / heads;         // positions (>= 2: heads <= 8)
+    int64_t g = P < resident ? P : resident;
+    const int64_t need = (P + per_wg - 1) / per_wg;
+    if (g < need) g = need;
+    const dim3 grid((unsigned)g), block(THREADS);
+    const int wide = wide_radius(a) ? 1 : 0;
+    if (ev_start && ev_stop)
+        hipExtLaunchKernelGGL((radius_kernel<T, THREADS, UNIT, ARGMAX>), grid, block, lds, stream, ev_start, ev_stop, 0, a, heads,
+                              wide, votes);
+    else
+        hipLaunchKernelGGL((radius_kernel<T, THREADS, UNIT, ARGMAX>), grid, block, lds, stream, a, heads, wide, votes);
+    return hipGetLastError();
+}
+template <typename T, int THREADS>
+hipError_t launch_radius_tile(const RowArgs& a, int heads, uint8_t* votes, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop)
+{
+    const bool argmax = a.ids == nullptr && (a.p_lo || a.p_mid || a.p_hi);
+    if (a.kappa == 1.0) return argmax ? launch_radius_cfg<T, THREADS, true, true>(a, heads, votes, stream, ev_start, ev_stop)
+                                      : launch_radius_cfg<T, THREADS, true, false>(a, heads, votes, stream, ev_start, ev_stop);
+    return argmax ? launch_radius_cfg<T, THREADS, false, true>(a, heads, votes, stream, ev_start, ev_stop)
+                  : launch_radius_cfg<T, THREADS, false, false>(a, heads, votes, stream, ev_start, ev_stop);
+}
+template <typename T>
+hipError_t launch_radius_typed(const RowArgs& a, int heads, uint8_t* votes, hipStream_t stream, hipEvent_t ev_start,
+                               hipEvent_t ev_stop)
+{
+    const int vecs = (a.V + Elt<T>::kPerVec - 1) / Elt<T>::kPerVec;
+    if (vecs <= 64 * kRadVecs) return launch_radius_tile<T, 64>(a, heads, votes, stream, ev_start, ev_stop);
+    if (vecs <= 128 * kRadVecs) return launch_radius_tile<T, 128>(a, heads, votes, stream, ev_start, ev_stop);
+    if (vecs <= 256 * kRadVecs) return launch_radius_tile<T, 256>(a, heads, votes, stream, ev_start, ev_stop);
+    if (vecs <= 512 * kRadVecs) return launch_radius_tile<T, 512>(a, heads, votes, stream, ev_start, ev_stop);
+    if (vecs <= 1024 * kRadVecs) return launch_radius_tile<T, 1024>(a, heads, votes, stream, ev_start, ev_stop);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+bool radius_quantify_fits(const RowArgs& args) { return args.radius != nullptr && args.V > kTinyVocab; }
+
+hipError_t launch_radius_quantify(int dtype, const RowArgs& args, int heads, uint8_t* votes, hipStream_t stream,
+                                  hipEvent_t ev_start, hipEvent_t ev_stop)
+{
+    if (args.N <= 0) return hipSuccess;
+    if (!radius_quantify_fits(args) || heads < 1) return hipErrorInvalidValue;
+    return dtype == 0 ? launch_radius_typed<float>(args, heads, votes, stream, ev_start, ev_stop)
+                      : launch_radius_typed<bf16_t>(args, heads, votes, stream, ev_start, ev_stop);
+}
+
+}  // namespace ciar

@@ -252,8 +252,9 @@ __device__ __forceinline__ void fuse_sums_tiny(const float (&e)[EPV], const u32x
 // UNIT = the radius scale is 1 (see radius_am1).
 template <typename T, int THREADS, int NVEC, bool WIDE, bool UNIT>
 __device__ __forceinline__ void fuse_sums_rad(const float (&e)[NVEC * Elt<T>::kPerVec], const u32x4 (&rad)[NVEC],
-                                              const FuseRow& fr, const RadiusMode& rm, const Shift& sh, int V,
-                                              int tid, double (&q5)[WIDE ? 8 : 5])
+                                              const FuseRow& fr, const RadiusMode& rm, const Shift& sh, bool top,
+                                              float half, float& raw_top, int V, int tid,
+                                              double (&q5)[WIDE ? 8 : 5])
 {
     const float kappa = rm.kappa, rmax = rm.rmax, am1_max = rm.am1_max;
     constexpr int EPV = Elt<T>::kPerVec;
@@ -286,6 +287,10 @@ __device__ __forceinline__ void fuse_sums_rad(const float (&e)[NVEC * Elt<T>::kP
             a2[k & 1] = fma(dl, dl, a2[k & 1]);
             a3[k & 1] = fma(dw, dw, a3[k & 1]);
             a4[k & 1] = fma(dl, dw, a4[k & 1]);
+        }
+        if (top) {                                                 // uniform: some probability above 1/2 (at most one)
+#pragma unroll
+            for (int k = 0; k < EPV; ++k) raw_top = e[j * EPV + k] >= half ? raw[k] : raw_top;
         }
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -367,6 +372,7 @@ void stream_kernel(const RowArgs A)
     // the reported token's centre logit, raw radius and verifier logit, the row's two uniforms.
     __shared__ RowStats sm_rows[kMaxRowsPerWg];
     __shared__ float    sm_fx[kMaxRowsPerWg][4];    // cx, rawx, tx, u_accept
+    __shared__ float    sm_rtop[RAD ? kMaxRowsPerWg : 1];     // tensor radius: raw radius of the row's token above 1/2, if any
     __shared__ float    sm_ur[DO_V ? kMaxRowsPerWg : 1];
     __shared__ int      sm_draw[DO_V ? kMaxRowsPerWg : 1];   // -1: the drafted token was accepted; else the row's draw
     __shared__ uint8_t  sm_close[DO_V ? kMaxRowsPerWg : 1];  // the fp32 accept test could not decide the row
@@ -533,7 +539,7 @@ void stream_kernel(const RowArgs A)
                 A.stats[r] = st;
                 if constexpr (DO_Q) {
                     const float cx = A.ids ? sm_fx[i][0] : st.mc;  // no ids: the arg-max token is reported
-                    finish_row(A, r, st, cx, 0.f, sm_fx[i][1], 0.f, true, false);
+                    finish_row(A, r, st, cx, 0.f, sm_fx[i][1], 0.f, true, false, sm_rtop[RAD ? i : 0]);
                 }
             }
         };
@@ -833,8 +839,11 @@ void stream_kernel(const RowArgs A)
 #pragma unroll
                     for (int j = 0; j < NVEC; ++j) E::zero_tail(buf[j], (j * THREADS + tid) * EPV, V);
                 }
-                if (rm.unit) fuse_sums_rad<T, THREADS, NVEC, WIDE, true>(e, buf, fr, rm, sh, V, tid, q5);
-                else         fuse_sums_rad<T, THREADS, NVEC, WIDE, false>(e, buf, fr, rm, sh, V, tid, q5);
+                const float half = 0.5f * (float)Su;
+                float raw_top = INFINITY;                          // raw radius of a token above 1/2, for finish_row
+                if (rm.unit) fuse_sums_rad<T, THREADS, NVEC, WIDE, true>(e, buf, fr, rm, sh, split, half, raw_top, V, tid, q5);
+                else         fuse_sums_rad<T, THREADS, NVEC, WIDE, false>(e, buf, fr, rm, sh, split, half, raw_top, V, tid, q5);
+                if (raw_top != INFINITY) sm_rtop[done] = raw_top;  // (at most one lane of the workgroup)
 #pragma unroll
                 for (int i = 0; i < 5; ++i) q5[i] = wave_sum(q5[i]);
             } else if constexpr (WIDE) {
@@ -1339,17 +1348,23 @@ template <typename T, int THREADS, int NVEC>
 hipError_t launch_stream_cfg(Mode mode, const RowArgs& a, StreamLaunch& s)
 {
     const bool rad = a.radius != nullptr;
+    if (mode == Mode::Quantify && rad) {
+        // (more than 64 tokens: radius_kernel's)
+        if constexpr (NVEC == 1) {
+            if (!radius_quantify_fits(a))
+                return wide_radius(a) ? launch_stream_kernel<T, THREADS, 1, true, false, true, true>(a, s)
+                                      : launch_stream_kernel<T, THREADS, 1, true, false, true>(a, s);
+        }
+        return hipErrorInvalidValue;
+    }
     if (mode != Mode::Verify && wide_radius(a)) {
         // radii at which the widths crowd against 1: the variants that also accumulate their complements
-        if (mode == Mode::Quantify)
-            return rad ? launch_stream_kernel<T, THREADS, NVEC, true, false, true, true>(a, s)
-                       : launch_stream_kernel<T, THREADS, NVEC, true, false, false, true>(a, s);
+        if (mode == Mode::Quantify) return launch_stream_kernel<T, THREADS, NVEC, true, false, false, true>(a, s);
         return rad ? launch_stream_kernel<T, THREADS, NVEC, true, true, true, true>(a, s)
                    : launch_stream_kernel<T, THREADS, NVEC, true, true, false, true>(a, s);
     }
     switch (mode) {
-    case Mode::Quantify: return rad ? launch_stream_kernel<T, THREADS, NVEC, true, false, true>(a, s)
-                                    : launch_stream_kernel<T, THREADS, NVEC, true, false, false>(a, s);
+    case Mode::Quantify: return launch_stream_kernel<T, THREADS, NVEC, true, false, false>(a, s);
     case Mode::Verify:   return launch_stream_kernel<T, THREADS, NVEC, false, true, false>(a, s);
     case Mode::Fused:    return rad ? launch_stream_kernel<T, THREADS, NVEC, true, true, true>(a, s)
                                     : launch_stream_kernel<T, THREADS, NVEC, true, true, false>(a, s);

@@ -82,6 +82,15 @@ hipError_t launch_dro(int, const RowArgs& a, float* terms, double, double, doubl
     touch(terms, 7 * (size_t)a.N); touch(weights, (size_t)a.N); touch(losses, 5);
     return hipSuccess;
 }
+bool radius_quantify_fits(const RowArgs& a) { return a.radius && a.V > 64; }
+hipError_t launch_radius_quantify(int, const RowArgs& a, int heads, uint8_t* votes, hipStream_t, hipEvent_t, hipEvent_t)
+{
+    ++stubs::launches; stubs::last_args = a;
+    const size_t N = (size_t)a.N;
+    touch(a.p_lo, N); touch(a.p_mid, N); touch(a.p_hi, N); touch(a.omega, N); touch(a.sigma, N); touch(a.score, N);
+    touch(a.flags, N); touch(a.stats, N); touch(votes, N / (size_t)heads);
+    return hipSuccess;
+}
 hipError_t launch_ensemble(int, const RowArgs& a, int heads, int64_t, hipStream_t)
 {
     ++stubs::launches; stubs::last_args = a;
