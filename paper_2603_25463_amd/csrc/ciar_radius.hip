@@ -124,11 +124,11 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
     };
     // vector j of a row goes in flight (lane l of a wave lands 16 l bytes behind the address the wave names); lanes past the end
     // of the row fetch its last vector
+    const uint32_t last_off = (uint32_t)last_vec * 16u;
     auto fetch = [&](gbytes base, int j, int tid) {
-        if (j < nch) {                                             // uniform
-            const uint32_t v = (j + 1) * THREADS - 1 <= last_vec ? (uint32_t)(j * THREADS + tid) : (uint32_t)min(j * THREADS + tid, last_vec);
-            __builtin_amdgcn_global_load_lds((glb_ptr)(base + v * 16u), (lds_ptr)(sm_next + j * THREADS + wave * 64), 16, 0, kNonTemporal);
-        }
+        if (j < nch)                                               // uniform
+            __builtin_amdgcn_global_load_lds((glb_ptr)(base + min((uint32_t)(j * THREADS + tid) * 16u, last_off)),
+                                             (lds_ptr)(sm_next + j * THREADS + wave * 64), 16, 0, kNonTemporal);
     };
     // wave 0: a row's sums over the waves, parked
     auto park = [&](int at, int p) {
