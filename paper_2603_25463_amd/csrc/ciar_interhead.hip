@@ -17,7 +17,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // Workgroup tile (64 MB) x (64 NB) x 64 with four waves in a 2 x 2 grid, each wave (32 MB) x (32 NB) = MB x NB MFMA
 // blocks of 32 x 32.  MB = NB = 4 (256 x 256, a wave 128 x 128) is the shape for real vocabularies: a wave then
 // reads 8 operand vectors from LDS for 16 matrix instructions, half the LDS traffic per instruction of the
-// 128 x 128 tile (MB = NB = 2), which serves vocabularies that are not a multiple of 256 and very small batches.
+// 128 x 128 tile (MB = NB = 2), which serves 33 to 128 rows.
+// Measured (2048 rows, V = 16384): D = 1280 202 -> 192 us, D = 4096 510 -> 463 us when the requests moved between the matrix
+// instructions of the fourth slice and the epilogue lost its barriers.
 //
 // Operand tiles go from memory straight into LDS (global_load_lds_dwordx4: no staging registers, and a request
 // has a whole tile's multiplication to arrive in).  One such instruction writes the 64 lanes'
@@ -30,8 +32,12 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int BK = kHeadTileDepth;
 constexpr int ROWB = BK * 2;            // bytes of a tile row in LDS
 static_assert(BK == 64, "a tile row is eight 16-byte chunks");
+using gbytes = const __attribute__((address_space(1))) char*;
 using gptr = const __attribute__((address_space(1))) void*;
 using lptr = __attribute__((address_space(3))) void*;
+
+// Joins the workgroup's barrier when this wave's LDS operations are done (requests under way are not waited for).
+__device__ __forceinline__ void lds_join() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // Lane layout of v_mfma_f32_32x32x16_bf16: lane l supplies row (A) / column (B) l % 32 with the eight consecutive k
 // 8 (l / 32) .. + 7; accumulator register v of lane l is the element (8 (v / 4) + 4 (l / 32) + v % 4, l % 32).
@@ -43,7 +49,8 @@ __global__ __launch_bounds__(256) void interhead_gemm_kernel(const HeadArgs A)
     constexpr int BUF = (BM + BN) * ROWB;                          // bytes of one buffer: the A tile, then the B tile
     extern __shared__ __attribute__((aligned(1024))) char lds[];   // two buffers
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // (the wave's index in a scalar register, and with it the LDS addresses of its requests)
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     // Workgroups are handed to the eight XCDs in turn (workgroup b runs on XCD b % 8), and every XCD has an L2 of its
     // own.  So the tiles are dealt by XCD: XCD x takes the column tiles x, x + 8, ..., and its consecutive
@@ -74,17 +81,26 @@ __global__ __launch_bounds__(256) void interhead_gemm_kernel(const HeadArgs A)
     }
 #pragma unroll
     for (int u = 0; u < CB; ++u) ob[u] = (uint32_t)(8 * (wave + 4 * u) + rl) * (uint32_t)A.D * 2u + (uint32_t)chunk * 16u;
-    const char* const baseA = reinterpret_cast<const char*>(A.hidden + m0 * A.D);
-    const char* const baseB = reinterpret_cast<const char*>(A.weight + (int64_t)n0 * A.D);
+    const gbytes baseA = (gbytes)(A.hidden + m0 * A.D), baseB = (gbytes)(A.weight + (int64_t)n0 * A.D);
+    // (the bases through an empty asm: a request is then one load from a scalar base and a 32-bit lane offset, not a 64-bit
+    // address per lane and request)
+    uint64_t kA, kB;
+    int dst;
+    auto request_from = [&](int k0, int buf) {
+        kA = (uint64_t)baseA + (uint32_t)k0 * 2u;
+        kB = (uint64_t)baseB + (uint32_t)k0 * 2u;
+        dst = buf * BUF + wave * 8 * ROWB;
+        asm volatile("" : "+s"(kA), "+s"(kB));
+    };
+    auto request_one = [&](int u) {
+        if (u < CA) __builtin_amdgcn_global_load_lds((gptr)((gbytes)kA + oa[u < CA ? u : 0]), (lptr)(lds + dst + u * 32 * ROWB), 16, 0, 0);
+        else __builtin_amdgcn_global_load_lds((gptr)((gbytes)kB + ob[u < CA ? 0 : u - CA]),
+                                              (lptr)(lds + dst + BM * ROWB + (u - CA) * 32 * ROWB), 16, 0, 0);
+    };
     auto request = [&](int k0, int buf) {
-        char* const dA = lds + buf * BUF + wave * 8 * ROWB;
-        char* const dB = dA + BM * ROWB;
+        request_from(k0, buf);
 #pragma unroll
-        for (int u = 0; u < CA; ++u)
-            __builtin_amdgcn_global_load_lds((gptr)(baseA + k0 * 2 + oa[u]), (lptr)(dA + u * 32 * ROWB), 16, 0, 0);
-#pragma unroll
-        for (int u = 0; u < CB; ++u)
-            __builtin_amdgcn_global_load_lds((gptr)(baseB + k0 * 2 + ob[u]), (lptr)(dB + u * 32 * ROWB), 16, 0, 0);
+        for (int u = 0; u < CA + CB; ++u) request_one(u);
     };
 
     f32x16 acc[MB][NB];
@@ -134,6 +150,26 @@ __global__ __launch_bounds__(256) void interhead_gemm_kernel(const HeadArgs A)
         }
         __builtin_amdgcn_sched_group_barrier(0x008, MB * NB - (MB + NB), 0);
     };
+    // The fourth slice, written out: behind each matrix instruction one LDS read (the next tile's first operands) while there are
+    // any, and a request or two.  (One behind another the requests hold the matrix pipe up for ~400 cycles a tile.)
+    auto last_slice = [&](const char* nxt) {
+        constexpr int PER = (CA + CB + MB * NB - 1) / (MB * NB), READS = (MB + NB + MB * NB - 1) / (MB * NB);
+        const int pos = sw * 16;
+#pragma unroll
+        for (int g = 0; g < MB * NB; ++g) {
+            const int i = g / NB, j = g % NB;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1][i], b[1][j], acc[i][j], 0, 0, 0);
+#pragma unroll
+            for (int q = g * READS; q < (g + 1) * READS; ++q) {
+                if (q < MB) a[0][q < MB ? q : 0] = *reinterpret_cast<const bf16x8*>(nxt + offA + q * 32 * ROWB + pos);
+                else if (q < MB + NB) b[0][q < MB ? 0 : (q - MB < NB ? q - MB : 0)] = *reinterpret_cast<const bf16x8*>(nxt + offB + (q - MB) * 32 * ROWB + pos);
+            }
+#pragma unroll
+            for (int u = g * PER; u < (g + 1) * PER; ++u)
+                if (u < CA + CB) request_one(u);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
     request(0, 0);
     request(BK < klast ? BK : klast, 1);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -157,16 +193,25 @@ __global__ __launch_bounds__(256) void interhead_gemm_kernel(const HeadArgs A)
         // so the wait is written out: only then may the other waves read what this wave has requested.
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();                                           // the next tile has arrived in every wave's part,
-        request(k0 + 2 * BK < klast ? k0 + 2 * BK : klast, buf);   // and this tile's buffer is free for the one after
-        operands(nxt, 0, 0);
-        multiply(1);
-        pattern();
+        // and this tile's buffer is free for the one after
+        if constexpr (MB == 4) {
+            request_from(k0 + 2 * BK < klast ? k0 + 2 * BK : klast, buf);
+            last_slice(nxt);
+        } else {
+            request(k0 + 2 * BK < klast ? k0 + 2 * BK : klast, buf);
+            operands(nxt, 0, 0);
+            multiply(1);
+            pattern();
+        }
     }
 
     // Epilogue: bias, then the tile's half of the head (a tile never straddles V: V is a multiple of BN).  The
     // accumulators hold columns across lanes and rows across registers; stored as they are, an instruction would
     // write 128-byte pieces of two rows.  Each wave instead passes its block through LDS, 32 rows at a time (the
-    // operand buffers are free by now), and writes whole row segments of 32 NB floats: 16 bytes per lane.
+    // operand buffers are free by now), and writes whole row segments of 32 NB floats: 16 bytes per lane.  The staging
+    // area is the wave's own, so nothing but the wave's own LDS operations is awaited, and all reads of 32 rows are under
+    // way together (one wave per SIMD: read, wait and store in turn, with a barrier on either side, stood still for a
+    // third of a launch of 20 k tiles).
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                // the last (repeated) requests have landed
     __syncthreads();                                               // every wave has read its last operands
     constexpr int WCOLS = 32 * NB, SP = WCOLS + 4;                 // staging pitch in floats: rows 4 apart differ in bank
@@ -176,8 +221,11 @@ __global__ __launch_bounds__(256) void interhead_gemm_kernel(const HeadArgs A)
     float bj[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) bj[j] = A.bias ? A.bias[n0 + wn * WCOLS + j * 32 + lrow] : 0.f;
-    constexpr int LPR = WCOLS / 4, RPI = 64 / LPR;                 // lanes per row segment, rows per store instruction
+    constexpr int LPR = WCOLS / 4, RPI = 64 / LPR, ST = 32 / RPI;  // lanes per row segment, rows per store instruction, stores
     const int srow = lane / LPR, scol = (lane % LPR) * 4;
+    const bool whole = m0 + BM <= A.N;                             // uniform: no row of the tile past the end of the batch
+    const int64_t row0 = m0 + wm * 32 * MB + srow;
+    float* const orow = out + row0 * A.stride + cwave + scol;
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
 #pragma unroll
@@ -185,15 +233,15 @@ __global__ __launch_bounds__(256) void interhead_gemm_kernel(const HeadArgs A)
 #pragma unroll
             for (int v = 0; v < 16; ++v)
                 stage[(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * SP + j * 32 + lrow] = acc[i][j][v] + bj[j];
-        __syncthreads();
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        f32x4 val[ST];
 #pragma unroll
-        for (int t = 0; t < 32 / RPI; ++t) {
-            const int r = t * RPI + srow;
-            const int64_t row = m0 + wm * 32 * MB + i * 32 + r;
-            const f32x4 val = *reinterpret_cast<const f32x4*>(&stage[r * SP + scol]);
-            if (row < A.N) *reinterpret_cast<f32x4*>(&out[row * A.stride + cwave + scol]) = val;
-        }
-        __syncthreads();
+        for (int t = 0; t < ST; ++t) val[t] = *reinterpret_cast<const f32x4*>(&stage[(t * RPI + srow) * SP + scol]);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int t = 0; t < ST; ++t)
+            if (whole || row0 + i * 32 + t * RPI < A.N)
+                *reinterpret_cast<f32x4*>(&orow[(int64_t)(i * 32 + t * RPI) * A.stride]) = val[t];
     }
 }
 
@@ -230,14 +278,343 @@ hipError_t launch_tile(const HeadArgs& a, hipStream_t stream, hipEvent_t ev_star
     return hipGetLastError();
 }
 
+// ---- many rows -------------------------------------------------------------------------------------------------------
+
+// 256 x 128 workgroup tiles, 32 deep, four waves in a 2 x 2 grid of 128 x 64 (4 x 2 matrix blocks, 128 accumulator registers): two
+// workgroups share a compute unit, so that one multiplies while the other waits at a barrier, starts a tile or writes one
+// out.  For batches whose 256 x 256 tiles would leave compute units without work, and vocabularies that are not a multiple of
+// 256; a large batch does better with the larger tile, which brings a third less into LDS per matrix instruction.
+// Three stages of 24 KiB: a slice is requested two slices ahead and awaited by count (the one behind it may still be under
+// way).  A tile row is four 16-byte chunks, chunk q of row r at position q ^ ((r / 4) % 4): four rows fill the 64 banks, and
+// any 16 consecutive rows at the same k cover every bank once.
+constexpr int BK2 = 32, ROWB2 = BK2 * 2;
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void interhead_pair_kernel(const HeadArgs A)
+{
+    constexpr int MB = 4, NB = 2, BM = 64 * MB, BN = 64 * NB, STAGES = 3;
+    constexpr int CA = BM / 64, CB = BN / 64, LOADS = CA + CB;     // load instructions per wave and slice (16 rows each)
+    constexpr int STAGE = (BM + BN) * ROWB2;
+    extern __shared__ __attribute__((aligned(1024))) char lds[];   // [STAGES][hidden tile, weight tile]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    // the tiles are dealt by XCD, see interhead_gemm_kernel
+    int rt, ct;
+    if (A.col_tiles % 8 == 0) {
+        const int x = (int)(blockIdx.x & 7), local = (int)(blockIdx.x >> 3);
+        rt = local % A.row_tiles;
+        ct = (local / A.row_tiles) * 8 + x;
+    } else {
+        rt = (int)(blockIdx.x % A.row_tiles);
+        ct = (int)(blockIdx.x / A.row_tiles);
+    }
+    const int64_t m0 = (int64_t)rt * BM;
+    const int n0 = ct * BN;
+
+    // Requests: instruction u of wave w covers the tile rows 16 (w + 4 u) .. + 15; lane l asks for row + l / 4 and, of that row,
+    // the chunk that belongs at position l % 4.
+    uint32_t oa[CA], ob[CB];
+    const int rl = lane >> 2, chunk = (lane & 3) ^ ((rl >> 2) & 3);
+    const int64_t last = A.N - 1 - m0;                             // >= 0: the tile starts inside the batch
+#pragma unroll
+    for (int u = 0; u < CA; ++u) {
+        const int row = 16 * (wave + 4 * u) + rl;
+        oa[u] = (uint32_t)(row <= last ? row : (int)last) * (uint32_t)A.D * 2u + (uint32_t)chunk * 16u;
+    }
+#pragma unroll
+    for (int u = 0; u < CB; ++u) ob[u] = (uint32_t)(16 * (wave + 4 * u) + rl) * (uint32_t)A.D * 2u + (uint32_t)chunk * 16u;
+    const gbytes baseA = (gbytes)(A.hidden + m0 * A.D), baseB = (gbytes)(A.weight + (int64_t)n0 * A.D);
+    const int klast = A.D - BK2;                                   // (past the last slice the requests repeat it)
+    uint64_t kA, kB;
+    int dst;
+    auto request_from = [&](int k0, int stage) {
+        k0 = k0 < klast ? k0 : klast;
+        kA = (uint64_t)baseA + (uint32_t)k0 * 2u;
+        kB = (uint64_t)baseB + (uint32_t)k0 * 2u;
+        dst = stage * STAGE + wave * 16 * ROWB2;
+        asm volatile("" : "+s"(kA), "+s"(kB));
+    };
+    auto request_one = [&](int u) {
+        if (u < CA) __builtin_amdgcn_global_load_lds((gptr)((gbytes)kA + oa[u < CA ? u : 0]), (lptr)(lds + dst + u * 64 * ROWB2), 16, 0, 0);
+        else __builtin_amdgcn_global_load_lds((gptr)((gbytes)kB + ob[u < CA ? 0 : u - CA]),
+                                              (lptr)(lds + dst + BM * ROWB2 + (u - CA) * 64 * ROWB2), 16, 0, 0);
+    };
+
+    f32x16 acc[MB][NB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+    // Operand reads: lane l reads row l % 32 of each 32-row block; its chunk in step sl (k 16 sl .. + 15) is 2 sl + l / 32.
+    const int lrow = lane & 31, sw = (lane >> 5) ^ ((lrow >> 2) & 3);
+    const int offA = (wm * 32 * MB + lrow) * ROWB2, offB = BM * ROWB2 + (wn * 32 * NB + lrow) * ROWB2;
+    bf16x8 a[2][MB], b[2][NB];
+    auto operand = [&](int stage, int sl, int set, int q) {        // operand q of a step: the MB of A, then the NB of B
+        const char* const tile = lds + stage * STAGE + ((2 * sl) ^ sw) * 16;
+        if (q < MB) a[set][q < MB ? q : 0] = *reinterpret_cast<const bf16x8*>(tile + offA + q * 32 * ROWB2);
+        else b[set][q < MB ? 0 : q - MB] = *reinterpret_cast<const bf16x8*>(tile + offB + (q - MB) * 32 * ROWB2);
+    };
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        request_from(t * BK2, t);
+#pragma unroll
+        for (int u = 0; u < LOADS; ++u) request_one(u);
+    }
+    request_from(2 * BK2, 2);
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) request_one(u);
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * LOADS) : "memory");
+    lds_join();
+#pragma unroll
+    for (int q = 0; q < MB + NB; ++q) operand(0, 0, 0, q);
+    int stage = 0;
+    for (int k0 = 0; k0 < A.D; k0 += BK2) {
+        const int next = stage + 1 == STAGES ? 0 : stage + 1;
+        __builtin_amdgcn_sched_barrier(0);
+        // first step: the second step's operands are read meanwhile
+#pragma unroll
+        for (int g = 0; g < MB * NB; ++g) {
+            acc[g / NB][g % NB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][g / NB], b[0][g % NB], acc[g / NB][g % NB], 0, 0, 0);
+            if (g < MB + NB) operand(stage, 1, 1, g);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // Every wave holds its last operands of this slice: its stage is free for the slice three on.  The next slice has landed
+        // when all but the LOADS requests behind it have.
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(LOADS) : "memory");
+        lds_join();
+        request_from(k0 + STAGES * BK2, stage);
+#pragma unroll
+        for (int g = 0; g < MB * NB; ++g) {
+            acc[g / NB][g % NB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1][g / NB], b[1][g % NB], acc[g / NB][g % NB], 0, 0, 0);
+            if (g < MB + NB) operand(next, 0, 0, g);
+            if (g < LOADS) request_one(g);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        stage = next;
+    }
+
+    // Epilogue: as in interhead_gemm_kernel, 32 rows at a time through the wave's own part of LDS.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                // the last (repeated) requests have landed
+    lds_join();                                                    // every wave has read its last operands
+    constexpr int WCOLS = 32 * NB, SP = WCOLS + 4;
+    float* const staged = reinterpret_cast<float*>(lds) + wave * 32 * SP;
+    float* out = n0 < A.V ? A.centre : A.radius;                   // (V is a multiple of 128: a tile never straddles it)
+    const int cwave = (n0 < A.V ? n0 : n0 - A.V) + wn * WCOLS;
+    float bj[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) bj[j] = A.bias ? A.bias[n0 + wn * WCOLS + j * 32 + lrow] : 0.f;
+    constexpr int LPR = WCOLS / 4, RPI = 64 / LPR, ST = 32 / RPI;
+    const int srow = lane / LPR, scol = (lane % LPR) * 4;
+    const bool whole = m0 + BM <= A.N;                             // uniform
+    const int64_t row0 = m0 + wm * 32 * MB + srow;
+    float* const orow = out + row0 * A.stride + cwave + scol;
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                staged[(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * SP + j * 32 + lrow] = acc[i][j][v] + bj[j];
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        f32x4 val[ST];
+#pragma unroll
+        for (int t = 0; t < ST; ++t) val[t] = *reinterpret_cast<const f32x4*>(&staged[(t * RPI + srow) * SP + scol]);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int t = 0; t < ST; ++t)
+            if (whole || row0 + i * 32 + t * RPI < A.N)
+                *reinterpret_cast<f32x4*>(&orow[(int64_t)(i * 32 + t * RPI) * A.stride]) = val[t];
+    }
+}
+
+hipError_t launch_pair(const HeadArgs& a, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop)
+{
+    constexpr size_t lds_bytes = (size_t)3 * (256 + 128) * ROWB2;  // 72 KB: two workgroups per compute unit
+    {
+        static std::mutex mu;
+        static bool raised[64] = {};
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
+        std::lock_guard<std::mutex> lock(mu);
+        if (!raised[dev]) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&interhead_pair_kernel),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+            if (e != hipSuccess) return e;
+            raised[dev] = true;
+        }
+    }
+    HeadArgs args = a;
+    args.row_tiles = (int32_t)((a.N + 255) / 256);
+    args.col_tiles = 2 * a.V / 128;
+    const unsigned grid = (unsigned)args.row_tiles * (unsigned)args.col_tiles;
+    if (ev_start && ev_stop)
+        hipExtLaunchKernelGGL(interhead_pair_kernel, dim3(grid), dim3(256), lds_bytes, stream, ev_start, ev_stop, 0, args);
+    else
+        hipLaunchKernelGGL(interhead_pair_kernel, dim3(grid), dim3(256), lds_bytes, stream, args);
+    return hipGetLastError();
+}
+
+// ---- few rows --------------------------------------------------------------------------------------------------------
+
+// The same maps for at most 32 rows (a drafted window or two): bound by reading the weights once.  A wave multiplies 32 output
+// columns by all rows, on its own: its 32 weight rows stream through a ring of stages in LDS that only this wave writes and
+// reads (a stage is a 64-deep slice: 4 KiB of weights and the same slice of the hidden states, 1 KiB per eight rows), so that
+// nothing but its own count of outstanding loads has to be awaited -- no barrier, and STAGES - 1 slices per wave, 96 to 120 KiB
+// per compute unit, on their way all the time (the 128 x 128 tile waited for one 32 KiB tile after another: 18.3 us for
+// 8 x 1280 x 2 * 16384, 84 MB of weights).  KS waves of a workgroup share the columns and divide the depth when the vocabulary alone
+// would leave compute units without work; their blocks are added up in LDS in a fixed order.
+// The weights are the A operand: a lane then holds four consecutive output columns of one row per register group, a 16-byte
+// store.
+template <int HB> constexpr int few_stages() { return HB == 1 ? 7 : HB == 2 ? 6 : 4; }   // HB = eight-row groups of hidden states
+
+template <int HB, int KS>
+__global__ __launch_bounds__(256) void interhead_few_kernel(const HeadArgs A)
+{
+    constexpr int STAGES = few_stages<HB>(), STAGE = 4096 + HB * 1024, LOADS = 4 + HB;
+    extern __shared__ __attribute__((aligned(1024))) char lds[];   // [4 waves][STAGES][STAGE]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int part = wave % KS, n0 = ((int)blockIdx.x * (4 / KS) + wave / KS) * 32;       // slice of the depth; first output column
+    char* const ring = lds + wave * STAGES * STAGE;
+
+    // requests: as in interhead_gemm_kernel, an instruction fills eight tile rows of 64 bf16, chunk q of row r at position
+    // q ^ ((r / 2) % 8)
+    const int rl = lane >> 3;
+    const uint32_t pitch = (uint32_t)A.D * 2u;
+    uint32_t ow[4], oh[HB];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) ow[u] = (uint32_t)(8 * u + rl) * pitch + (uint32_t)((lane & 7) ^ ((4 * (u & 1)) | (rl >> 1))) * 16u;
+#pragma unroll
+    for (int u = 0; u < HB; ++u) {
+        const int row = 8 * u + rl, last = (int)A.N - 1;           // (rows past the end of the batch repeat the last row)
+        oh[u] = (uint32_t)(row < last ? row : last) * pitch + (uint32_t)((lane & 7) ^ ((4 * (u & 1)) | (rl >> 1))) * 16u;
+    }
+    const char* const baseW = reinterpret_cast<const char*>(A.weight + (int64_t)n0 * A.D);
+    const char* const baseH = reinterpret_cast<const char*>(A.hidden);
+    const int tiles = A.D / BK, per = (tiles + KS - 1) / KS;       // 64-deep slices, and of this wave
+    const int first = part * per, count = max(0, min(tiles, first + per) - first);
+    // (past its last slice a wave requests that one again: the number of outstanding loads stays what the waits assume)
+    auto request = [&](int t, int stage) {
+        const int k0 = (first + min(t, max(count - 1, 0))) * BK * 2;
+        const int at = min(k0, (tiles - 1) * BK * 2);
+        char* const d = ring + stage * STAGE;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            __builtin_amdgcn_global_load_lds((gptr)(baseW + at + ow[u]), (lptr)(d + u * 1024), 16, 0, 0);
+#pragma unroll
+        for (int u = 0; u < HB; ++u)
+            __builtin_amdgcn_global_load_lds((gptr)(baseH + at + oh[u]), (lptr)(d + 4096 + u * 1024), 16, 0, 0);
+    };
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    const int lrow = lane & 31, sw = (lane >> 5) ^ ((lrow >> 1) & 7);
+    const int hrow = lrow < 8 * HB ? lrow : 8 * HB - 1;            // (columns past the batch: any row, never stored)
+    const int hsw = (lane >> 5) ^ ((hrow >> 1) & 7);
+#pragma unroll
+    for (int t = 0; t < STAGES - 1; ++t) request(t, t);
+    int stage = 0;
+    for (int t = 0; t < count; ++t) {
+        // the oldest slice has landed; the one that was read last is free for the request
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"((STAGES - 2) * LOADS) : "memory");
+        const char* const d = ring + stage * STAGE;
+        bf16x8 w[4], x[4];
+#pragma unroll
+        for (int sl = 0; sl < 4; ++sl) {
+            w[sl] = *reinterpret_cast<const bf16x8*>(d + lrow * ROWB + ((2 * sl) ^ sw) * 16);
+            x[sl] = *reinterpret_cast<const bf16x8*>(d + 4096 + hrow * ROWB + ((2 * sl) ^ hsw) * 16);
+        }
+        request(t + STAGES - 1, stage == 0 ? STAGES - 1 : stage - 1);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int sl = 0; sl < 4; ++sl) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[sl], x[sl], acc, 0, 0, 0);
+        stage = stage + 1 == STAGES ? 0 : stage + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                // the repeated requests have landed
+    if constexpr (KS > 1) {
+        // the other waves' blocks, [register][lane], added by the first of the KS waves in order
+        float* const block = reinterpret_cast<float*>(ring);
+        if (part > 0) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) block[v * 64 + lane] = acc[v];
+        }
+        __syncthreads();
+        if (part > 0) return;
+#pragma unroll
+        for (int o = 1; o < KS; ++o) {
+            const float* const other = reinterpret_cast<const float*>(ring + o * STAGES * STAGE);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] += other[v * 64 + lane];
+        }
+    }
+    if (lrow >= A.N) return;
+    float* const out = n0 < A.V ? A.centre : A.radius;             // (V is a multiple of 128: a block never straddles it)
+    const int col = (n0 < A.V ? n0 : n0 - A.V) + 4 * (lane >> 5);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        f32x4 val = {acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+        if (A.bias) {
+            const float* const b = A.bias + n0 + 4 * (lane >> 5) + 8 * g;
+            val += f32x4{b[0], b[1], b[2], b[3]};
+        }
+        *reinterpret_cast<f32x4*>(&out[(int64_t)lrow * A.stride + col + 8 * g]) = val;
+    }
+}
+
+template <int HB, int KS>
+hipError_t launch_few(const HeadArgs& a, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop)
+{
+    constexpr size_t lds_bytes = (size_t)4 * few_stages<HB>() * (4096 + HB * 1024);       // 128 to 144 KB of the 160 KB
+    {
+        static std::mutex mu;
+        static bool raised[64] = {};
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
+        std::lock_guard<std::mutex> lock(mu);
+        if (!raised[dev]) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&interhead_few_kernel<HB, KS>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+            if (e != hipSuccess) return e;
+            raised[dev] = true;
+        }
+    }
+    const unsigned grid = (unsigned)(2 * a.V / 32 / (4 / KS));
+    if (ev_start && ev_stop)
+        hipExtLaunchKernelGGL((interhead_few_kernel<HB, KS>), dim3(grid), dim3(256), lds_bytes, stream, ev_start, ev_stop, 0, a);
+    else
+        hipLaunchKernelGGL((interhead_few_kernel<HB, KS>), dim3(grid), dim3(256), lds_bytes, stream, a);
+    return hipGetLastError();
+}
+template <int HB>
+hipError_t launch_few_split(const HeadArgs& a, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop)
+{
+    // 2 V / 32 column blocks, four waves per compute unit wanted: the depth is divided where there are fewer
+    if (a.V >= 12288) return launch_few<HB, 1>(a, stream, ev_start, ev_stop);
+    if (a.V >= 6144) return launch_few<HB, 2>(a, stream, ev_start, ev_stop);
+    return launch_few<HB, 4>(a, stream, ev_start, ev_stop);
+}
+
 }  // namespace
 
 hipError_t launch_interhead(const HeadArgs& args, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     if (args.N <= 0) return hipSuccess;
     static_assert(kHeadTileCols == 128, "the small tile is the one the C ABI's shape check is written for");
-    if (args.V % 256 == 0 && args.N > 128) return launch_tile<4, 4>(args, stream, ev_start, ev_stop);
-    return launch_tile<2, 2>(args, stream, ev_start, ev_stop);
+    if (args.N <= 8) return launch_few_split<1>(args, stream, ev_start, ev_stop);
+    if (args.N <= 16) return launch_few_split<2>(args, stream, ev_start, ev_stop);
+    if (args.N <= 32) return launch_few_split<4>(args, stream, ev_start, ev_stop);
+    if (args.N <= 128) return launch_tile<2, 2>(args, stream, ev_start, ev_stop);
+    // 256 x 256 tiles read the least per matrix instruction; where they are fewer than the compute units, two 256 x 128 workgroups
+    // per compute unit do better (785 x 2240 x 2 * 2560: 51 -> 34.5 us, 256 x 1280 x 2 * 16384: 49 -> 41.6 us; with one tile per
+    // compute unit, 512 x 1280 x 2 * 16384, 66 against 59 us, with four 236 against 200 us)
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        cus = 256;
+    const int64_t tiles = (args.N + 255) / 256 * (2 * (int64_t)args.V / 256);
+    if (args.V % 256 == 0 && tiles >= cus) return launch_tile<4, 4>(args, stream, ev_start, ev_stop);
+    return launch_pair(args, stream, ev_start, ev_stop);
 }
 
 }  // namespace ciar

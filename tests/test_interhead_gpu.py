@@ -182,3 +182,23 @@ def test_interhead_rejects_unsupported_shapes(ciar):
     out = ciar.interhead_quantify(h[:0], torch.zeros((256, 64), dtype=torch.bfloat16, device="cuda"), None, None,
                                   ciar.Params())
     assert out["score"].numel() == 0
+
+
+@pytest.mark.parametrize("N", [1, 8, 9, 16, 17, 31, 32, 33])
+@pytest.mark.parametrize("D,V", [(64, 128), (320, 6016), (192, 6144), (704, 12288)])
+def test_interhead_few_rows(ciar, oracle, N, D, V):
+    """The kernel for at most 32 rows, whose waves divide the depth where the vocabulary is small: slices that do not divide
+    evenly, waves without a slice, every group of rows; integer operands, so any wrong element shows exactly."""
+    g = torch.Generator().manual_seed(100 * N + D + V)
+    h = torch.randint(-4, 5, (N, D), generator=g).bfloat16()
+    w = torch.randint(-4, 5, (2 * V, D), generator=g).bfloat16()
+    b = torch.randint(-8, 9, (2 * V,), generator=g).float()
+    say(f"[interhead few rows] N={N} D={D} V={V}")
+    for bias in (b, None):
+        out = tuple(torch.full((N, V + 4), 7.5, device="cuda") for _ in range(2))
+        c, r = ciar.interhead_logits(h.cuda(), w.cuda(), None if bias is None else bias.cuda(), ciar.Params(), row_stride=V + 4,
+                                     out=out)
+        torch.cuda.synchronize()
+        ref = h.double() @ w.double().T + (0.0 if bias is None else bias.double())
+        assert torch.equal(c[:, :V].double().cpu(), ref[:, :V]) and torch.equal(r[:, :V].double().cpu(), ref[:, V:])
+        assert bool((c[:, V:] == 7.5).all()) and bool((r[:, V:] == 7.5).all())
