@@ -30,6 +30,9 @@ class CiarParams(ctypes.Structure):
                 ("normalize", ctypes.c_int32), ("reserved", ctypes.c_int32)]
 
 
+_PARAMS_SIZE = ctypes.sizeof(CiarParams)
+
+
 class CiarError(RuntimeError):
     def __init__(self, status: int, message: str):
         super().__init__(f"{STATUS.get(status, status)}: {message}")
@@ -121,36 +124,30 @@ class Params:
     window: int = 8
 
     def to_c(self, logits: torch.Tensor, vocab: int | None = None) -> CiarParams:
-        p = CiarParams()
-        lib().ciar_params_default(ctypes.byref(p))
         if logits.dtype == torch.float32:
-            p.dtype = CIAR_F32
+            dtype = CIAR_F32
         elif logits.dtype == torch.bfloat16:
-            p.dtype = CIAR_BF16
+            dtype = CIAR_BF16
         else:
             raise TypeError(f"logits must be float32 or bfloat16, got {logits.dtype}")
         if logits.dim() != 2 or logits.stride(1) != 1:
             raise ValueError("logits must be a 2-D tensor with unit stride along the vocabulary")
-        p.vocab = int(logits.shape[1] if vocab is None else vocab)
-        p.row_stride = int(logits.stride(0)) if logits.shape[0] > 1 else max(int(logits.stride(0)), p.vocab)
-        p.window = int(self.window)
-        p.confidence = float(self.confidence)
-        p.radius_scale = float(self.radius_scale)
-        p.radius_max = float(self.radius_max)
-        p.tau = float(self.tau)
-        p.lower_cap = float(self.lower_cap)
-        p.upper_cap = float(self.upper_cap)
-        p.normalize = int(bool(self.normalize))
-        return p
+        rows, columns = logits.shape
+        stride = logits.stride(0)
+        vocab = int(columns if vocab is None else vocab)
+        # (every field is given: one constructor call instead of the library's defaults and a dozen assignments)
+        return CiarParams(_PARAMS_SIZE, vocab, dtype, int(self.window), stride if rows > 1 else max(stride, vocab),
+                          float(self.confidence), float(self.radius_scale), float(self.radius_max), float(self.tau),
+                          float(self.lower_cap), float(self.upper_cap), 1 if self.normalize else 0, 0)
 
 
+# (plain integers: the declared argument types turn them into pointers)
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def _check(rc: int):
@@ -172,6 +169,19 @@ def _like_draft(t, draft, name: str):
     """``target`` / ``radius`` tensors share the layout of the draft logits."""
     if t is not None and (t.dtype != draft.dtype or t.shape != draft.shape or t.stride() != draft.stride()):
         raise ValueError(f"{name} must match draft in dtype, shape and strides")
+
+
+_FLOATS = ("p_lo", "p_mid", "p_hi", "omega", "sigma", "score")
+
+
+def _interval_outputs(N: int, dev, o: dict) -> dict:
+    """Adds the quantifier's outputs that ``o`` does not bring (what it brings is not allocated again)."""
+    for k in _FLOATS:
+        if k not in o:
+            o[k] = torch.empty(N, dtype=torch.float32, device=dev)
+    if "flags" not in o:
+        o["flags"] = torch.empty(N, dtype=torch.uint8, device=dev)
+    return o
 
 
 def width_polynomial(cparams: CiarParams):
@@ -204,10 +214,7 @@ def quantify(draft: torch.Tensor, ids: torch.Tensor | None, params: Params, voca
     N, dev = draft.shape[0], draft.device
     cp = params.to_c(draft, vocab)
     workspace, wsb = _workspace(N, cp, dev, workspace)
-    o = dict(out) if out else {}
-    for k in ("p_lo", "p_mid", "p_hi", "omega", "sigma", "score"):
-        o.setdefault(k, torch.empty(N, dtype=torch.float32, device=dev))
-    o.setdefault("flags", torch.empty(N, dtype=torch.uint8, device=dev))
+    o = _interval_outputs(N, dev, dict(out) if out else {})
     _check(lib().ciar_quantify(_ptr(draft), _ptr(radius), _ptr(ids), N, ctypes.byref(cp),
                                _ptr(o["p_lo"]), _ptr(o["p_mid"]), _ptr(o["p_hi"]), _ptr(o["omega"]),
                                _ptr(o["sigma"]), _ptr(o["score"]), _ptr(o["flags"]), _ptr(workspace), wsb,
@@ -218,10 +225,10 @@ def quantify(draft: torch.Tensor, ids: torch.Tensor | None, params: Params, voca
 def _verify_outputs(N: int, K: int, dev, out: dict | None) -> dict:
     W = (N + K - 1) // K
     o = dict(out) if out else {}
-    o.setdefault("accept", torch.empty(N, dtype=torch.uint8, device=dev))
-    o.setdefault("row_id", torch.empty(N, dtype=torch.int32, device=dev))
-    o.setdefault("accept_len", torch.empty(W, dtype=torch.int32, device=dev))
-    o.setdefault("resampled_id", torch.empty(W, dtype=torch.int32, device=dev))
+    for k, n, dtype in (("accept", N, torch.uint8), ("row_id", N, torch.int32), ("accept_len", W, torch.int32),
+                        ("resampled_id", W, torch.int32)):
+        if k not in o:
+            o[k] = torch.empty(n, dtype=dtype, device=dev)
     return o
 
 
@@ -249,10 +256,7 @@ def quantify_verify(draft, target, ids, u_accept, u_resample, params: Params, vo
     cp = params.to_c(draft, vocab)
     _like_draft(target, draft, "target")
     _like_draft(radius, draft, "radius")
-    o = _verify_outputs(N, cp.window, dev, out)
-    for k in ("p_lo", "p_mid", "p_hi", "omega", "sigma", "score"):
-        o.setdefault(k, torch.empty(N, dtype=torch.float32, device=dev))
-    o.setdefault("flags", torch.empty(N, dtype=torch.uint8, device=dev))
+    o = _interval_outputs(N, dev, _verify_outputs(N, cp.window, dev, out))
     workspace, wsb = _workspace(N, cp, dev, workspace)
     _check(lib().ciar_quantify_verify(
         _ptr(draft), _ptr(radius), _ptr(target), _ptr(ids), _ptr(u_accept), _ptr(u_resample), N, ctypes.byref(cp),
@@ -291,9 +295,7 @@ def _staged(entry, draft, target, ids, u_accept, u_resample, params: Params, wor
     if target is not None:
         o = _verify_outputs(N, cp.window, dev, o)
     if with_intervals:
-        for k in ("p_lo", "p_mid", "p_hi", "omega", "sigma", "score"):
-            o.setdefault(k, torch.empty(N, dtype=torch.float32, device=dev))
-        o.setdefault("flags", torch.empty(N, dtype=torch.uint8, device=dev))
+        _interval_outputs(N, dev, o)
     g = lambda k: _ptr(o.get(k))
     _check(entry(
         _ptr(draft), _ptr(radius), _ptr(target), _ptr(ids), _ptr(u_accept), _ptr(u_resample), N, ctypes.byref(cp),
@@ -339,8 +341,9 @@ def window_epilogue(accept: torch.Tensor, row_id: torch.Tensor, params: Params, 
     cp.window = K
     W = (N + K - 1) // K
     o = dict(out) if out else {}
-    o.setdefault("accept_len", torch.empty(W, dtype=torch.int32, device=accept.device))
-    o.setdefault("resampled_id", torch.empty(W, dtype=torch.int32, device=accept.device))
+    for k in ("accept_len", "resampled_id"):
+        if k not in o:
+            o[k] = torch.empty(W, dtype=torch.int32, device=accept.device)
     _check(lib().ciar_window_epilogue(_ptr(accept), _ptr(row_id), N, ctypes.byref(cp), _ptr(o["accept_len"]),
                                       _ptr(o["resampled_id"]), _stream(stream)))
     return o
@@ -481,14 +484,10 @@ def interhead_quantify(hidden: torch.Tensor, weight: torch.Tensor, bias: torch.T
     N, D, V, cp = _head_params(hidden, weight, bias, params, row_stride)
     _need_cuda(ids)
     dev = hidden.device
-    need = interhead_workspace_bytes(N, cp)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
+        workspace = torch.empty(max(interhead_workspace_bytes(N, cp), 16), dtype=torch.uint8, device=dev)
     _need_cuda(workspace)
-    o = dict(out) if out else {}
-    for k in ("p_lo", "p_mid", "p_hi", "omega", "sigma", "score"):
-        o.setdefault(k, torch.empty(N, dtype=torch.float32, device=dev))
-    o.setdefault("flags", torch.empty(N, dtype=torch.uint8, device=dev))
+    o = _interval_outputs(N, dev, dict(out) if out else {})
     _check(lib().ciar_interhead_quantify(_ptr(hidden), _ptr(weight), _ptr(bias), D, _ptr(ids), N, ctypes.byref(cp),
                                          _ptr(o["p_lo"]), _ptr(o["p_mid"]), _ptr(o["p_hi"]), _ptr(o["omega"]),
                                          _ptr(o["sigma"]), _ptr(o["score"]), _ptr(o["flags"]), _ptr(workspace),
