@@ -202,3 +202,24 @@ def test_interhead_few_rows(ciar, oracle, N, D, V):
         ref = h.double() @ w.double().T + (0.0 if bias is None else bias.double())
         assert torch.equal(c[:, :V].double().cpu(), ref[:, :V]) and torch.equal(r[:, :V].double().cpu(), ref[:, V:])
         assert bool((c[:, V:] == 7.5).all()) and bool((r[:, V:] == 7.5).all())
+
+
+@pytest.mark.parametrize("N,V", [(129, 128), (129, 256), (255, 384), (256, 640), (257, 1152), (511, 256), (770, 896)])
+@pytest.mark.parametrize("D", [64, 128, 320])
+def test_interhead_two_workgroups_per_unit(ciar, oracle, N, V, D):
+    """The kernel for batches that leave compute units without a 256 x 256 tile, or vocabularies that are no multiple of 256:
+    ragged last rows, tiles that straddle the centre and the radius half's end, fewer depth slices than stages; integer
+    operands, so any wrong element shows exactly."""
+    g = torch.Generator().manual_seed(100 * N + D + V)
+    h = torch.randint(-4, 5, (N, D), generator=g).bfloat16()
+    w = torch.randint(-4, 5, (2 * V, D), generator=g).bfloat16()
+    b = torch.randint(-8, 9, (2 * V,), generator=g).float()
+    say(f"[interhead pair] N={N} D={D} V={V}")
+    for bias in (b, None):
+        out = tuple(torch.full((N, V + 4), 7.5, device="cuda") for _ in range(2))
+        c, r = ciar.interhead_logits(h.cuda(), w.cuda(), None if bias is None else bias.cuda(), ciar.Params(), row_stride=V + 4,
+                                     out=out)
+        torch.cuda.synchronize()
+        ref = h.double() @ w.double().T + (0.0 if bias is None else bias.double())
+        assert torch.equal(c[:, :V].double().cpu(), ref[:, :V]) and torch.equal(r[:, :V].double().cpu(), ref[:, V:])
+        assert bool((c[:, V:] == 7.5).all()) and bool((r[:, V:] == 7.5).all())

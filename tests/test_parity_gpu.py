@@ -580,6 +580,64 @@ def test_ensemble_sweep_edges(ciar, oracle, H, V, stride, N, dtype, kw):
         parity.check_flags(ge["flags"], oe, float(np.float32(tau)))
 
 
+RADIUS_EDGES = [  # H, V, stride, N, dtype: both sides of every tile's end, several rows per workgroup, H from 1 to 8
+    (1, 65, 68, 9001, torch.float32), (3, 2048, 2048, 3001, torch.float32), (1, 2049, 2052, 4100, torch.float32),
+    (8, 4096, 4096, 130, torch.float32), (2, 4097, 4100, 700, torch.float32), (1, 8193, 8196, 1031, torch.float32),
+    (1, 16385, 16388, 517, torch.float32), (2, 32768, 32768, 70, torch.float32),
+    (5, 72, 72, 2000, torch.bfloat16), (1, 4097, 4104, 2100, torch.bfloat16), (3, 8192, 8192, 700, torch.bfloat16),
+    (1, 16385, 16392, 1031, torch.bfloat16), (2, 32769, 32776, 270, torch.bfloat16), (1, 65535, 65536, 260, torch.bfloat16),
+]
+
+
+@pytest.mark.parametrize("H,V,stride,N,dtype", RADIUS_EDGES)
+@pytest.mark.parametrize("kw", [dict(radius_scale=1.0), dict(radius_scale=0.7, radius_max=9.0)])
+def test_radius_kernel_edges(ciar, oracle, H, V, stride, N, dtype, kw):
+    """The quantifier with a radius tensor, one head and several that vote, at the edges of its tiles, on ordinary rows among
+    those it treats apart: nearly one-hot rows (caps, the token above one half), flat rows (fp64), masked tokens, wide radii and
+    radii next to nothing; with and without drafted ids.  Tolerances: those of the oracle comparison (tests/parity.py)."""
+    heads = _head_stack(H, V, stride, N, torch.float32, seed=8500 + V + H)
+    rows = torch.arange(N, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(13)
+    tok = torch.randint(0, V, (N,), generator=g, device="cuda")
+    heads[:, rows[1::6], tok[1::6]] += 28.0
+    heads[0, rows[2::6], tok[2::6]] += 12.0
+    heads[:, rows[3::12]] *= 0.003
+    heads[:, rows[4::12], : V // 4] = float("-inf")
+    if stride > V:
+        heads[:, :, V:] = 1e30
+    heads = heads.to(dtype).contiguous()
+    raw = torch.stack([_raw_radius(N, stride, V, torch.float32, seed=5600 + V + h) for h in range(H)])
+    raw[:, rows[5::12], :V] = -6.0
+    raw[:, rows[8::24], :V] += 6.0                           # wide radii (those of 0.7 reach the clamp)
+    raw = raw.to(dtype).contiguous()
+    ids = torch.randint(0, V, (N,), generator=g, device="cuda").to(torch.int32)
+    ids[1::6] = tok[1::6].to(torch.int32)
+    hh, rh, idh = heads.cpu(), raw.cpu(), ids.cpu().numpy()
+    say(f"[radius edges] H={H} V={V} stride={stride} N={N} {dtype} {kw}")
+    tau = None
+    for with_ids in (True, False):
+        gi, oi = (ids, idh) if with_ids else (None, None)
+        OP = _oparams(oracle, ciar.Params(tau=tau or 0.3, **kw))
+        ov = oracle.quantify_multihead(hh, oi, OP, oracle.VOTING, vocab=V, radius_heads=rh)
+        if tau is None:
+            tau = float(np.float32(np.median(ov["score"])))
+            ov["head_flags"] = (ov["score"] > tau).astype(np.uint8)
+        P = ciar.Params(tau=tau, **kw)
+        gv = ciar.quantify_multihead(heads, gi, P, ciar.VOTING, vocab=V, radius_heads=raw)
+        gq = ciar.quantify(heads[0], gi, P, vocab=V, radius=raw[0])
+        torch.cuda.synchronize()
+        for h in range(H):
+            oh = {k: ov[k][h] for k in parity.FLOAT_KEYS}
+            oh["flags"] = ov["head_flags"][h]
+            parity.check_floats({k: gv[k][h] for k in parity.FLOAT_KEYS}, oh)
+            parity.check_flags(gv["head_flags"][h], oh, tau)
+            if h == 0:
+                parity.check_floats(gq, oh)
+                parity.check_flags(gq["flags"], oh, tau)
+        votes = gv["head_flags"].sum(0, dtype=torch.int32)
+        assert torch.equal(gv["flags"], (2 * votes > H).to(torch.uint8))
+
+
 # ---- Inter-DRO loss, forward (Sec. 3.2.3) -------------------------------------------------------------------
 
 def _check_dro(g, o, N):
