@@ -58,29 +58,29 @@ __device__ __forceinline__ float exp_rel(float x, float m)
 constexpr float kRuledOut = -1267650600228229401496703205376.0f;
 constexpr uint32_t kRuledOutBits = 0xf1800000u;                    // (its upper half is the bf16 number)
 
-// Per-row terms of the loss.  One 1024-lane workgroup per row holds the centre, raw-radius and cloud rows as
+// Per-row terms of the loss.  One workgroup per row holds the centre, raw-radius and cloud rows as
 // loaded (12 registers per vector) and makes three passes over them: the maxima of the centre and the cloud logits
 // and a reference radius, the four partition sums together with the p_cloud-weighted sums of the exponents for the
 // cross-entropies, and the three L1 distances, which need all four normalisers.  With e = exp(o - reference):
 //   CE(p_cloud, softmax(o)) = (reference + ln S_o) - (sum_i et_i o_i) / Z,
 //   KL(p_cloud || p_mid)    = ln S_mid - ln Z + (sum_i et_i ((t_i - max t) - (c_i - max c))) / Z.
 // terms[k * N + row], k = 0..6: L1(mid), L1(up), L1(lo), CE(mid), CE(up), CE(lo), KL.
-// One row's totals (see dro_finish_row) from the three rows as loaded (lane t holds 16-byte vectors j * 1024 + t;
+// One row's totals (see dro_finish_row) from the three rows as loaded (lane t holds 16-byte vectors j * THREADS + t;
 // vectors past the end of the row hold copies of its last vector and are masked here), left in fin[kDroTotals] (LDS)
-// by lane 0.  Called by every lane of a 1024-lane workgroup; sm_d: 7 doubles per wave of LDS scratch.  Ends with every
+// by lane 0.  Called by every lane of the workgroup; sm_d: 7 doubles per wave of LDS scratch.  Ends with every
 // lane past the last read of sm_d except wave 0's.
 // The radius parameters as the row arithmetic takes them: floats, formed by the host, so that they arrive in scalar
 // registers with the kernel arguments.  (Converted from RowArgs' doubles inside a kernel they are loop invariants that
 // the optimiser holds in vector registers, or spills, through the whole row loop.)
 struct DroRadius { float kappa, rmax, scalar; };                   // scalar = min(kappa, rmax), the radius without a tensor
 
-template <typename T, int NVEC>
+template <typename T, int NVEC, int THREADS>
 __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadius R, double* fin,
                                                 u32x4 (&cw)[NVEC], u32x4 (&tw)[NVEC], u32x4 (&rw)[NVEC], double* sm_d,
                                                 const int tid)
 {
     using E = Elt<T>;
-    constexpr int EPV = E::kPerVec, THREADS = 1024, NW = 16;
+    constexpr int EPV = E::kPerVec, NW = THREADS / 64;
     const int lane = tid & 63, wave = tid >> 6;
     const int V = A.V;
     const bool rad = A.radius != nullptr;                          // uniform
@@ -201,12 +201,12 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     // LDS for the reductions over the workgroup (see pass 2 for the scheme: quad sums by DPP, then transposed through
     // LDS so that one short reduction serves all quantities at once)
     __shared__ __attribute__((aligned(16))) double sm_w[NW][8][16];   // per wave: [quantity][quad]
-    __shared__ __attribute__((aligned(16))) double sm_x[8][16];       // [quantity][wave]
+    __shared__ __attribute__((aligned(16))) double sm_x[8][NW];       // [quantity][wave]
     float rref;
     {
         // the four maxima over the workgroup: quads by DPP, the 16 quad maxima of each quantity through LDS into one
         // DPP row each (lanes 16 q ... 16 q + 15 take quantity q), one row reduction for all four; the same again
-        // over the sixteen waves.  (Four wave-wide DPP maxima, twice, cost ~240 instructions.)
+        // over the waves.  (Four wave-wide DPP maxima, twice, cost ~240 instructions.)
         float m4[4] = {mc, mt, key, 0.f};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -214,7 +214,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
             m4[i] = dpp_max<0x4E, 0xf>(m4[i]);
         }
         float* fw = reinterpret_cast<float*>(&sm_w[wave][0][0]);   // [4][16] floats of this wave
-        __shared__ float sm_m[4 * 16];                             // [quantity][wave], this step's own (no barrier behind it)
+        __shared__ float sm_m[4 * NW];                             // [quantity][wave], this step's own (no barrier behind it)
         float* fx = sm_m;
         if ((lane & 3) == 0) {
 #pragma unroll
@@ -228,9 +228,13 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
             return v;
         };
         float v = row_max(fw[lane]);                               // (= fw[(lane >> 4) * 16 + (lane & 15)])
-        if ((lane & 15) == 15) fx[(lane >> 4) * 16 + wave] = v;
-        lds_barrier();
-        v = row_max(fx[lane]);
+        if constexpr (NW > 1) {
+            if ((lane & 15) == 15) fx[(lane >> 4) * NW + wave] = v;
+            lds_barrier();
+            v = row_max(fx[(lane >> 4) * NW + (lane & (NW - 1))]);     // (fewer than sixteen waves: their values repeated)
+        } else {
+            lds_barrier();                                         // (one wave: only what it has read stays ahead of its writes)
+        }
         mc = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 15));
         mt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 31));
         rref = (float)(__builtin_amdgcn_readlane(__float_as_int(v), 47) & 0xFFF) * (1.0f / 128.0f);
@@ -337,7 +341,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     // Instead: two DPP steps leave every quad's sum in its lanes; the quad leaders put them into LDS, quantity by
     // quantity; lane l then takes two of the 16 quad sums of quantity l / 8 (one 16-byte read) and three butterfly
     // steps over its group of eight lanes finish the wave's sums of all quantities at once.  Across the waves the same
-    // two last steps run on the sixteen wave sums.
+    // two last steps run on the wave sums.
     const int grp = lane >> 3, part = lane & 7;
     auto group8_total = [](double a) {
         a = dpp_add<0xB1, 0xf>(a);                                 // lane ^ 1  (quad_perm 1,0,3,2)
@@ -354,17 +358,26 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
 #pragma unroll
         for (int i = 0; i < 8; ++i) sm_w[wave][i][lane >> 2] = acc[i];
     }
+    double wave_total;
     {
         // (the wave reads what its own lanes have written: LDS operations of a wave complete in order)
         const double* pr = &sm_w[wave][grp][2 * part];
         const double a = group8_total(pr[0] + pr[1]);
-        if (part == 0) sm_x[grp][wave] = a;
+        wave_total = a;
+        if (NW > 1 && part == 0) sm_x[grp][wave] = a;
     }
     lds_barrier();
     double tot[8];
     {
-        const double* pr = &sm_x[grp][2 * part];
-        const double a = group8_total(pr[0] + pr[1]);
+        double a = wave_total;
+        if constexpr (NW == 16) {
+            const double* pr = &sm_x[grp][2 * part];
+            a = group8_total(pr[0] + pr[1]);
+        } else if constexpr (NW > 1) {
+            const double* pr = &sm_x[grp][(2 * part) & (NW - 1)];
+            const double p2 = pr[0] + pr[1];
+            a = group8_total(2 * part < NW ? p2 : 0.0);
+        }
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             tot[i] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(a), 8 * i),
@@ -496,28 +509,30 @@ __global__ __launch_bounds__(1024) void dro_row_kernel(const RowArgs A, const Dr
         if (rad) rw[j] = __builtin_nontemporal_load((gvec)(rb + off));
     }
     __shared__ double sm_fin[kDroTotals];
-    dro_row_compute<T, NVEC>(A, R, sm_fin, cw, tw, rw, sm_d, tid);
+    dro_row_compute<T, NVEC, THREADS>(A, R, sm_fin, cw, tw, rw, sm_d, tid);
     if (tid == 0) dro_finish_row(A, terms, row, sm_fin);           // (the lane that has written the totals)
 }
 
-constexpr int kDroRowsPerWg = 64;                                  // most rows a workgroup of dro_row_stream_kernel takes
+// Most rows that a workgroup of dro_row_stream_kernel takes: what fits in its share of a compute unit's LDS next to the rows
+// in flight.
+template <int THREADS> constexpr int dro_rows() { return THREADS >= 512 ? 64 : THREADS / 8; }
 
-// The same with the next row on its way while a row is worked on.  One 1024-lane workgroup per compute unit walks
+// The same with the next row on its way while a row is worked on.  1024 / THREADS workgroups per compute unit walk
 // over rows blockIdx.x, blockIdx.x + gridDim.x, ...; the three rows of a position and the working set leave no
-// registers to fetch ahead into, and a second workgroup does not fit a compute unit, so the centre and cloud rows of
+// registers to fetch ahead into, and no further workgroup fits a compute unit, so the centre and cloud rows of
 // the NEXT position are loaded straight into LDS (global_load_lds_dwordx4: the data of lane l of a wave lands 16 l
 // bytes behind the LDS address the wave names; no register is held while the load is in flight) and the raw-radius
 // row into the NVEC registers that the current radius row has left.  Every lane reads back only the slots that its own
 // wave's loads have written, so the hand-over needs the wave's own vmcnt(0) and no barrier.
-// Dynamic LDS: 2 x NVEC x 16 KiB (NVEC <= 4).
-template <typename T, int NVEC>
-__global__ __launch_bounds__(1024) void dro_row_stream_kernel(const RowArgs A, const DroRadius R,
+// Dynamic LDS: 2 x NVEC x 16 x THREADS bytes (NVEC <= 4).
+template <typename T, int NVEC, int THREADS>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) void dro_row_stream_kernel(const RowArgs A, const DroRadius R,
                                                               float* __restrict__ terms)
 {
-    constexpr int THREADS = 1024, NW = 16;
+    constexpr int NW = THREADS / 64, ROWS = dro_rows<THREADS>();
     extern __shared__ u32x4 sm_rows[];                             // [2][NVEC][THREADS]: next centre row, next cloud row
     __shared__ double sm_d[NW * 7];
-    __shared__ double sm_fin[kDroRowsPerWg][kDroTotals];           // the totals of this workgroup's rows
+    __shared__ double sm_fin[ROWS][kDroTotals];           // the totals of this workgroup's rows
     const int tid = threadIdx.x;
     const int wave_s = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int last_vec = (A.V + Elt<T>::kPerVec - 1) / Elt<T>::kPerVec - 1;
@@ -551,7 +566,7 @@ __global__ __launch_bounds__(1024) void dro_row_stream_kernel(const RowArgs A, c
     // a 64-bit comparison of two scalars is a vector instruction that wants one of them in vector registers, for good)
     const uint32_t n_rows = (uint32_t)A.N;
     uint32_t row = blockIdx.x;
-    int done = 0;                                                  // rows of this workgroup finished so far (<= kDroRowsPerWg)
+    int done = 0;                                                  // rows of this workgroup finished so far (<= ROWS)
     if (row < n_rows) {
         request_rows(row, tid);
         if (rad) request_radius(row, rnext, tid);
@@ -577,7 +592,7 @@ __global__ __launch_bounds__(1024) void dro_row_stream_kernel(const RowArgs A, c
             request_rows(next, t);
             if (rad) request_radius(next, rnext, t);
         }
-        dro_row_compute<T, NVEC>(A, R, sm_fin[done], cw, tw, rw, sm_d, t);
+        dro_row_compute<T, NVEC, THREADS>(A, R, sm_fin[done], cw, tw, rw, sm_d, t);
         // (no barrier here: what wave 0 still reads of sm_d is written again only in the next row's pass 3, two
         // barriers on)
         ++done;
@@ -694,10 +709,10 @@ __global__ __launch_bounds__(T) void dro_batch_kernel(const float* __restrict__ 
 }  // namespace
 
 namespace {
-template <typename T, int NVEC>
+template <typename T, int NVEC, int THREADS>
 hipError_t launch_dro_stream_cfg(const RowArgs& a, float* terms, hipStream_t stream)
 {
-    constexpr unsigned lds = 2u * NVEC * 1024u * 16u;
+    constexpr unsigned lds = 2u * NVEC * THREADS * 16u;
     if (lds > 48u * 1024u) {
         // above the default limit on dynamic LDS: raised once per device and instance
         static std::mutex guard;
@@ -706,29 +721,39 @@ hipError_t launch_dro_stream_cfg(const RowArgs& a, float* terms, hipStream_t str
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
         std::lock_guard<std::mutex> lock(guard);
         if (!raised[dev]) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dro_row_stream_kernel<T, NVEC>),
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dro_row_stream_kernel<T, NVEC, THREADS>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
             raised[dev] = true;
         }
     }
-    // one workgroup per compute unit; more of them (taking their turn) when that would give a workgroup more than
-    // kDroRowsPerWg rows
-    int64_t g = compute_units();
-    const int64_t need = (a.N + kDroRowsPerWg - 1) / kDroRowsPerWg;
-    if (g < need) g = need;
+    // as many workgroups as are resident at a time, or that several times over (taking their turn) where a workgroup would
+    // otherwise get more rows than it has room for: whole rounds, so that the last one leaves no unit idle (20000 rows of
+    // 16384 tokens fp32, radius tensor: 1355 us with the fewest workgroups that hold them, 313, 882 us with 512)
+    const int64_t resident = (int64_t)(1024 / THREADS) * compute_units();
+    int64_t g = resident * ((a.N + resident * dro_rows<THREADS>() - 1) / (resident * dro_rows<THREADS>()));
     if (g > a.N) g = a.N;
-    const dim3 grid((unsigned)g), block(1024);
+    const dim3 grid((unsigned)g), block(THREADS);
     const DroRadius R = {(float)a.kappa, (float)a.rmax, (float)fmin(a.kappa, a.rmax)};
-    hipLaunchKernelGGL((dro_row_stream_kernel<T, NVEC>), grid, block, lds, stream, a, R, terms);
+    hipLaunchKernelGGL((dro_row_stream_kernel<T, NVEC, THREADS>), grid, block, lds, stream, a, R, terms);
     return hipGetLastError();
 }
+// 16 tokens per lane -- the most whose exponentials pass 3 finds in registers -- and as many lanes as the row then takes:
+// a workgroup's reductions, barriers and fp64 tails cost the same for a row of 1024 tokens as for one of 16384, so on small
+// vocabularies the rows of a compute unit run next to each other in workgroups of their own.  600 MB of rows and a radius
+// tensor, with 1024 lanes to every row -> with these: V = 1024 726 -> 183 us (bf16: 2667 -> 340), 4096 204 -> 148 (bf16:
+// 861 -> 271), 8192 168 -> 154 (bf16: 298 -> 243); 257 to 1000 rows, where the calls wait for latency, 18 to 26 us -> 17 to 20.
+// bf16 rows of 16385 to 32768 tokens take 32 tokens per lane.
 template <typename T>
-hipError_t launch_dro_stream(int nvec, const RowArgs& a, float* terms, hipStream_t stream)
+hipError_t launch_dro_stream(int vecs, const RowArgs& a, float* terms, hipStream_t stream)
 {
-    if (nvec == 1) return launch_dro_stream_cfg<T, 1>(a, terms, stream);
-    if (nvec == 2) return launch_dro_stream_cfg<T, 2>(a, terms, stream);
-    return launch_dro_stream_cfg<T, 4>(a, terms, stream);
+    constexpr int NV = 16 / Elt<T>::kPerVec;
+    if (vecs <= 64 * NV) return launch_dro_stream_cfg<T, NV, 64>(a, terms, stream);
+    if (vecs <= 128 * NV) return launch_dro_stream_cfg<T, NV, 128>(a, terms, stream);
+    if (vecs <= 256 * NV) return launch_dro_stream_cfg<T, NV, 256>(a, terms, stream);
+    if (vecs <= 512 * NV) return launch_dro_stream_cfg<T, NV, 512>(a, terms, stream);
+    if (vecs <= 1024 * NV) return launch_dro_stream_cfg<T, NV, 1024>(a, terms, stream);
+    return launch_dro_stream_cfg<T, 4, 1024>(a, terms, stream);
 }
 }  // namespace
 
@@ -751,9 +776,8 @@ hipError_t launch_dro(int dtype, const RowArgs& args, float* terms, double lambd
         else hipLaunchKernelGGL(dro_row_tiny_kernel<bf16_t>, tgrid, tblock, 0, stream, args, terms);
     } else if (vecs <= 4096 && args.N > (int64_t)compute_units()) {
         // more rows than compute units: persistent workgroups that fetch the next row through LDS
-        const int nv = vecs <= 1024 ? 1 : vecs <= 2048 ? 2 : 4;
-        const hipError_t e = dtype == 0 ? launch_dro_stream<float>(nv, args, terms, stream)
-                                        : launch_dro_stream<bf16_t>(nv, args, terms, stream);
+        const hipError_t e = dtype == 0 ? launch_dro_stream<float>(vecs, args, terms, stream)
+                                        : launch_dro_stream<bf16_t>(vecs, args, terms, stream);
         if (e != hipSuccess) return e;
     } else if (vecs <= 1024) CIAR_DRO_LAUNCH(1);
     else if (vecs <= 2048) CIAR_DRO_LAUNCH(2);

@@ -718,6 +718,25 @@ def test_interdro_loss_many_rows(ciar, oracle, V, stride, N, dtype, tensor_radiu
     _check_dro(g, o, N)
 
 
+# The persistent row kernel at both ends of each workgroup size (one to sixteen waves to a row), and with more rows than the
+# workgroups of each have room for.
+DRO_TILE_EDGES = [
+    (65, 68, 33000, torch.float32), (1024, 1024, 4200, torch.float32), (1025, 1028, 2100, torch.float32),
+    (2048, 2048, 270, torch.float32), (2049, 2052, 1100, torch.float32), (4096, 4096, 258, torch.float32),
+    (4097, 4100, 520, torch.float32), (8193, 8196, 300, torch.float32), (66, 72, 40000, torch.bfloat16),
+    (1024, 1024, 300, torch.bfloat16), (1025, 1032, 33000, torch.bfloat16), (2049, 2056, 1100, torch.bfloat16),
+    (4097, 4104, 530, torch.bfloat16), (8192, 8192, 600, torch.bfloat16), (16385, 16392, 260, torch.bfloat16),
+]
+
+
+@pytest.mark.parametrize("V,stride,N,dtype", DRO_TILE_EDGES)
+@pytest.mark.parametrize("tensor_radius", [True, False])
+def test_interdro_loss_tile_edges(ciar, oracle, V, stride, N, dtype, tensor_radius):
+    test_interdro_loss_many_rows(ciar, oracle, V, stride, N, dtype, tensor_radius)
+    if N < 5000:
+        test_interdro_tokens_the_device_rules_out(ciar, oracle, stride, N, dtype)      # (its rows are not padded)
+
+
 @pytest.mark.parametrize("V,N,dtype", [(1000, 40, torch.float32), (4100, 300, torch.float32), (16384, 270, torch.float32),
                                        (16384, 300, torch.bfloat16), (40000, 7, torch.bfloat16)])
 def test_interdro_tokens_the_device_rules_out(ciar, oracle, V, N, dtype):
