@@ -1244,10 +1244,7 @@ hipError_t launch_sweep_cfg(const RowArgs& a, int heads, int64_t head_stride, hi
             raised[dev] = true;
         }
     }
-    const int64_t resident = (int64_t)(512 / THREADS) * compute_units();
-    int64_t g = a.N < resident ? a.N : resident;
-    const int64_t need = (a.N + sweep_rows<THREADS>() - 1) / sweep_rows<THREADS>();
-    if (g < need) g = need;
+    const int64_t g = whole_rounds(a.N, sweep_rows<THREADS>(), (int64_t)(512 / THREADS) * compute_units());
     const int wide = wide_radius(a) ? 1 : 0, flat64 = a.radius || needs_flat_pass(a) ? 1 : 0;
     hipLaunchKernelGGL((ensemble_sweep_kernel<T, THREADS, RAD, UNIT, ARGMAX>), dim3((unsigned)g), dim3(THREADS), lds, stream, a, heads,
                        head_stride, wide, flat64);

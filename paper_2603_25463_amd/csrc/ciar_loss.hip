@@ -727,12 +727,7 @@ hipError_t launch_dro_stream_cfg(const RowArgs& a, float* terms, hipStream_t str
             raised[dev] = true;
         }
     }
-    // as many workgroups as are resident at a time, or that several times over (taking their turn) where a workgroup would
-    // otherwise get more rows than it has room for: whole rounds, so that the last one leaves no unit idle (20000 rows of
-    // 16384 tokens fp32, radius tensor: 1355 us with the fewest workgroups that hold them, 313, 882 us with 512)
-    const int64_t resident = (int64_t)(1024 / THREADS) * compute_units();
-    int64_t g = resident * ((a.N + resident * dro_rows<THREADS>() - 1) / (resident * dro_rows<THREADS>()));
-    if (g > a.N) g = a.N;
+    const int64_t g = whole_rounds(a.N, dro_rows<THREADS>(), (int64_t)(1024 / THREADS) * compute_units());
     const dim3 grid((unsigned)g), block(THREADS);
     const DroRadius R = {(float)a.kappa, (float)a.rmax, (float)fmin(a.kappa, a.rmax)};
     hipLaunchKernelGGL((dro_row_stream_kernel<T, NVEC, THREADS>), grid, block, lds, stream, a, R, terms);

@@ -382,11 +382,8 @@ hipError_t launch_radius_cfg(const RowArgs& a, int heads, uint8_t* votes, hipStr
             raised[dev] = true;
         }
     }
-    const int64_t P = a.N / heads, resident = (int64_t)(1024 / THREADS) * compute_units();
     const int64_t per_wg = radius_rows<THREADS>() / heads;         // positions (>= 2: heads <= 8)
-    int64_t g = P < resident ? P : resident;
-    const int64_t need = (P + per_wg - 1) / per_wg;
-    if (g < need) g = need;
+    const int64_t g = whole_rounds(a.N / heads, per_wg, (int64_t)(1024 / THREADS) * compute_units());
     const dim3 grid((unsigned)g), block(THREADS);
     const int wide = wide_radius(a) ? 1 : 0;
     if (ev_start && ev_stop)

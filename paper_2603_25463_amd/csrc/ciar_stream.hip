@@ -1300,12 +1300,8 @@ hipError_t launch_stream_kernel(const RowArgs& a, StreamLaunch& L)
     constexpr int per_cu = target_waves<T, THREADS, NVEC, RAD, DO_V>() * 256 / THREADS;
     const int64_t resident = (int64_t)per_cu * compute_units();
     const int64_t N = a.N;
-    // (at most kMaxRowsPerWg rows per workgroup: beyond that many rows per resident workgroup the grid grows instead)
-    auto grid_for = [&](int64_t pieces, int64_t per_wg) {
-        const int64_t g = pieces < resident ? pieces : resident, need = (pieces + per_wg - 1) / per_wg;
-        return g > need ? g : need;
-    };
-    const int64_t grid1 = grid_for(N, kMaxRowsPerWg), max1 = (N + grid1 - 1) / grid1;
+    // (at most kMaxRowsPerWg rows per workgroup)
+    const int64_t grid1 = whole_rounds(N, kMaxRowsPerWg, resident), max1 = (N + grid1 - 1) / grid1;
     StreamPlan& p = L.plan;
     p.unit = 1;
     p.grid = (unsigned)grid1;
@@ -1315,7 +1311,7 @@ hipError_t launch_stream_kernel(const RowArgs& a, StreamLaunch& L)
         // Whole windows per workgroup, so that the kernel writes the window outputs as well, unless that would leave
         // the busiest workgroup with noticeably more rows than a row-by-row split (few windows on many compute units)
         const int64_t K = a.window, units = (N + K - 1) / K;
-        const int64_t gridk = grid_for(units, kMaxRowsPerWg / K), maxk = (units + gridk - 1) / gridk * K;
+        const int64_t gridk = whole_rounds(units, kMaxRowsPerWg / K, resident), maxk = (units + gridk - 1) / gridk * K;
         if (maxk <= max1 + max1 / 8) {
             p.unit = (int)K;
             p.grid = (unsigned)gridk;
