@@ -581,6 +581,7 @@ __device__ __forceinline__ int accept_quick(float cx, float tx, float u, float n
 // token (-1: the arg-max token, whose logit is st.mc), cx / tx / rawx = its centre logit, verifier logit and raw
 // radius, u = the row's uniform for the accept test.  Returns whether the drafted token is rejected.
 // raw_top: tensor radius, rows with a token above 1/2: that token's raw radius.
+template <bool RAD_TOP = false>
 __device__ __forceinline__ bool finish_row(const RowArgs& A, int64_t row, const RowStats& st, float cx, float tx,
                                            float rawx, float u, bool do_q, bool do_v, float raw_top = 0.f)
 {
@@ -596,20 +597,22 @@ __device__ __forceinline__ bool finish_row(const RowArgs& A, int64_t row, const 
         // wave has the row's reference, so its e and the fp32 values that the scalar-radius pass has added to the sums
         // can be formed again here, by the same instructions, and exchanged for the fp64 values.  (Plain sums only:
         // such a row is not flat.  Wide scalar radii and tiny vocabularies come from other passes.)
-        // With a radius tensor likewise, from the fp32 radius: its error moves the bounds by p (1 - p) times as much.
+        // With a radius tensor likewise (RAD_TOP: raw_top is that token's raw radius), from the fp32 radius: its error moves
+        // the bounds by p (1 - p) times as much.  (A template parameter: one window in a tight loop waits for the kernel's
+        // instructions to arrive as well.)
         // (the call's constants through an empty asm: what is derived from them here is otherwise formed at the top of
         // the calling kernel and kept -- in the streaming kernel: spilled -- through its row loop)
         double fa = A.a, fb = A.b;
         int fv = A.V;
         asm volatile("" : "+s"(fa), "+s"(fb), "+s"(fv));
-        if (st.mode == kSumsFull && A.normalize && fv > kTinyVocab && (A.radius || fa < 3.0 * (double)fv) &&
+        if (st.mode == kSumsFull && A.normalize && fv > kTinyVocab && (RAD_TOP || (!A.radius && fa < 3.0 * (double)fv)) &&
             st.kl == 0.0 && st.kw == 0.0) {
             const float etop = exp2_ref(st.mc, n == -INFINITY ? 0.f : n);
             if ((double)etop > 0.5 * S) {
                 const double ed = (double)etop, invS = 1.0 / S;
                 const double x = ed * invS, om = fmax(0.0, S - ed) * invS;      // 1 - x from the sum of the other tokens
                 double gl, gw, glf, gwf;
-                if (A.radius) {
+                if constexpr (RAD_TOP) {
                     const RadiusMode rm = radius_mode(A);
                     float plf, wf;
                     fuse_token_rad(etop, raw_top, fuse_row_inv(recip(S), fa, fb), rm, plf, wf);

@@ -326,7 +326,7 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
         xid = xid < 0 ? 0 : (xid >= V ? V - 1 : xid);
         const float cx = load_logit(static_cast<const T*>(A.draft) + off, xid);
         const float rawx = load_logit(static_cast<const T*>(A.radius) + off, xid);
-        finish_row(A, r, st, cx, 0.f, rawx, 0.f, true, false, pk[at].raw_top);
+        finish_row<true>(A, r, st, cx, 0.f, rawx, 0.f, true, false, pk[at].raw_top);
         A.stats[r] = st;
     };
     {

@@ -539,7 +539,7 @@ void stream_kernel(const RowArgs A)
                 A.stats[r] = st;
                 if constexpr (DO_Q) {
                     const float cx = A.ids ? sm_fx[i][0] : st.mc;  // no ids: the arg-max token is reported
-                    finish_row(A, r, st, cx, 0.f, sm_fx[i][1], 0.f, true, false, sm_rtop[RAD ? i : 0]);
+                    finish_row<RAD>(A, r, st, cx, 0.f, sm_fx[i][1], 0.f, true, false, RAD ? sm_rtop[i] : 0.f);
                 }
             }
         };
