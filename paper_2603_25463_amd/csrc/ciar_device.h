@@ -580,10 +580,12 @@ __device__ __forceinline__ int accept_quick(float cx, float tx, float u, float n
 // steps): score, flag, the reported token's interval, the accept test in the log domain.  xid = the reported
 // token (-1: the arg-max token, whose logit is st.mc), cx / tx / rawx = its centre logit, verifier logit and raw
 // radius, u = the row's uniform for the accept test.  Returns whether the drafted token is rejected.
-// raw_top: tensor radius, rows with a token above 1/2: that token's raw radius.
+// raw_top: tensor radius, rows with a token above 1/2: that token's raw radius.  flag: where the row's flag goes besides
+// A.flags, if anywhere.
 template <bool RAD_TOP = false>
 __device__ __forceinline__ bool finish_row(const RowArgs& A, int64_t row, const RowStats& st, float cx, float tx,
-                                           float rawx, float u, bool do_q, bool do_v, float raw_top = 0.f)
+                                           float rawx, float u, bool do_q, bool do_v, float raw_top = 0.f,
+                                           uint8_t* flag = nullptr)
 {
     const double S = st.S;
     const float n = st.n;
@@ -640,6 +642,7 @@ __device__ __forceinline__ bool finish_row(const RowArgs& A, int64_t row, const 
         if (A.sigma) A.sigma[row] = (float)rs.sigma;
         if (A.score) A.score[row] = (float)rs.score;
         if (A.flags) A.flags[row] = (uint8_t)(rs.score > A.tau);
+        if (flag) *flag = (uint8_t)(rs.score > A.tau);
         if (A.p_lo || A.p_mid || A.p_hi) {
             // e_x exactly as the streaming kernel summed it into S (the arg-max token, the only one whose
             // probability can approach 1, sits in a wave whose reference is n), so that S - e_x is the

@@ -326,7 +326,7 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
         xid = xid < 0 ? 0 : (xid >= V ? V - 1 : xid);
         const float cx = load_logit(static_cast<const T*>(A.draft) + off, xid);
         const float rawx = load_logit(static_cast<const T*>(A.radius) + off, xid);
-        finish_row<true>(A, r, st, cx, 0.f, rawx, 0.f, true, false, pk[at].raw_top);
+        finish_row<true>(A, r, st, cx, 0.f, rawx, 0.f, true, false, pk[at].raw_top, &pk_flag[at]);   // (the vote counts the flags as written)
         A.stats[r] = st;
     };
     {
@@ -339,7 +339,6 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
             const bool fp64 = !(rs.sigma * rs.sigma >= 1e-4 * mean * mean) || (A.precise_flat && etop * Vd <= 2.0 * st.S) ||
                               (wide && mean > 0.45);
             pk_fp64[t] = (uint8_t)fp64;
-            pk_flag[t] = (uint8_t)(rs.score > A.tau);
             if (!fp64) finish(t, st);
         }
     }
@@ -348,10 +347,7 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
         if (!pk_fp64[at]) continue;                                // uniform
         RowStats st = stats_of(at);
         radius_row_fp64<T, THREADS>(A, row_of(at), sm_red, st);
-        if (my_tid() == 0) {
-            pk_flag[at] = (uint8_t)(finish_score(st.q, st.S, st.mode, A, st.kl, st.kw).score > A.tau);
-            finish(at, st);
-        }
+        if (my_tid() == 0) finish(at, st);
     }
     if (votes) {
         __syncthreads();

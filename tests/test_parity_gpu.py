@@ -638,6 +638,30 @@ def test_radius_kernel_edges(ciar, oracle, H, V, stride, N, dtype, kw):
         assert torch.equal(gv["flags"], (2 * votes > H).to(torch.uint8))
 
 
+@pytest.mark.parametrize("V,dtype", [(1024, torch.float32), (16384, torch.bfloat16)])
+def test_radius_vote_is_the_majority_of_the_flags(ciar, V, dtype):
+    """Voting with radius tensors on nearly one-hot rows, whose score is corrected for the token above one half after the
+    sweep: the vote is the strict majority of the flags that the same call writes, with tau at the rows' scores and within a
+    few fp32 steps of them (the correction moves a score by several)."""
+    N, H = 512, 3
+    heads = _head_stack(H, V, V, N, torch.float32, seed=9100 + V)
+    tok = torch.randint(0, V, (N,), generator=torch.Generator(device="cuda").manual_seed(14), device="cuda")
+    heads[:, torch.arange(N, device="cuda"), tok] += 14.0
+    heads = heads.to(dtype).contiguous()
+    raw = torch.stack([_raw_radius(N, V, V, torch.float32, seed=5700 + V + h) for h in range(H)]).to(dtype).contiguous()
+    score = ciar.quantify_multihead(heads, None, ciar.Params(radius_scale=1.0), ciar.VOTING, radius_heads=raw)["score"].cpu().numpy()
+    say(f"[vote] V={V} {dtype}")
+    flags = set()
+    for s in score[0, ::8]:
+        for k in (-6, -2, 0, 2, 6):
+            tau = float((np.array(s).view(np.int32) + np.int32(k)).view(np.float32))
+            g = ciar.quantify_multihead(heads, None, ciar.Params(radius_scale=1.0, tau=tau), ciar.VOTING, radius_heads=raw)
+            votes = g["head_flags"].sum(0, dtype=torch.int32)
+            assert torch.equal(g["flags"], (2 * votes > H).to(torch.uint8)), tau
+            flags |= set(g["flags"].unique().tolist())
+    assert flags == {0, 1}
+
+
 # ---- Inter-DRO loss, forward (Sec. 3.2.3) -------------------------------------------------------------------
 
 def _check_dro(g, o, N):
