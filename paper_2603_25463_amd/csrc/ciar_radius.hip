@@ -249,8 +249,12 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
         }
         const gbytes next = row_base(A.draft, npos, nh);
         double q[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-        const float half = 0.5f * (float)Su;
-        float raw_top = INFINITY;                                  // raw radius of a token above 1/2, for finish_row
+        // A row with a token above 1/2: its raw radius is parked for finish_row by the lane that has it, in the wave with the row's
+        // largest token.  (No other token has its e: two of them would be all of S.)
+        const bool search = top && mw == mc;                       // uniform over the wave
+        const float etop = uniform(exp2_ref(mw, nref));
+        float raw_top = 0.f;
+        bool found = false;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
         for (int g = 0; g < NVEC; g += 4) {
@@ -277,15 +281,19 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
                         q[0] += dl; q[1] += dw;
                         q[2] = fma(dl, dl, q[2]); q[3] = fma(dw, dw, q[3]); q[4] = fma(dl, dw, q[4]);
                     }
-                    if (top) {                                     // uniform: some probability above 1/2 (at most one)
+                    if (search) {
 #pragma unroll
-                        for (int k = 0; k < EPV; ++k) raw_top = e[j * EPV + k] >= half ? rv[k] : raw_top;
+                        for (int k = 0; k < EPV; ++k) {
+                            const bool is = e[j * EPV + k] == etop;
+                            raw_top = is ? rv[k] : raw_top;
+                            found = found || is;
+                        }
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        if (raw_top != INFINITY) pk[done].raw_top = raw_top;       // (at most one lane of the workgroup)
+        if (found) pk[done].raw_top = raw_top;                     // (one lane of the workgroup)
         {
             const double f2 = fw * fw;                             // to row units
             put(q[0] * fw, 0, lane); put(q[1] * fw, 1, lane);

@@ -250,11 +250,13 @@ __device__ __forceinline__ void fuse_sums_tiny(const float (&e)[EPV], const u32x
 // padding already zeroed); the sums are of p^l_i S and (p^u_i - p^l_i) S themselves, about the shift sh.
 // WIDE: also the complement sums of fuse_sums_wide.
 // UNIT = the radius scale is 1 (see radius_am1).
+// The raw radius of a row's token above 1/2, picked up on the way: looked for in the wave that holds the row's largest
+// token, by that token's e.  (No other token has it: two of them would be all of S.)
+struct TopToken { bool search, found; float e, raw; };             // search: uniform over the wave; found: this lane's
 template <typename T, int THREADS, int NVEC, bool WIDE, bool UNIT>
 __device__ __forceinline__ void fuse_sums_rad(const float (&e)[NVEC * Elt<T>::kPerVec], const u32x4 (&rad)[NVEC],
-                                              const FuseRow& fr, const RadiusMode& rm, const Shift& sh, bool top,
-                                              float half, float& raw_top, int V, int tid,
-                                              double (&q5)[WIDE ? 8 : 5])
+                                              const FuseRow& fr, const RadiusMode& rm, const Shift& sh, int V,
+                                              int tid, double (&q5)[WIDE ? 8 : 5], TopToken& top)
 {
     const float kappa = rm.kappa, rmax = rm.rmax, am1_max = rm.am1_max;
     constexpr int EPV = Elt<T>::kPerVec;
@@ -288,9 +290,13 @@ __device__ __forceinline__ void fuse_sums_rad(const float (&e)[NVEC * Elt<T>::kP
             a3[k & 1] = fma(dw, dw, a3[k & 1]);
             a4[k & 1] = fma(dl, dw, a4[k & 1]);
         }
-        if (top) {                                                 // uniform: some probability above 1/2 (at most one)
+        if (top.search) {
 #pragma unroll
-            for (int k = 0; k < EPV; ++k) raw_top = e[j * EPV + k] >= half ? raw[k] : raw_top;
+            for (int k = 0; k < EPV; ++k) {
+                const bool is = e[j * EPV + k] == top.e;
+                top.raw = is ? raw[k] : top.raw;
+                top.found = top.found || is;
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -839,11 +845,11 @@ void stream_kernel(const RowArgs A)
 #pragma unroll
                     for (int j = 0; j < NVEC; ++j) E::zero_tail(buf[j], (j * THREADS + tid) * EPV, V);
                 }
-                const float half = 0.5f * (float)Su;
-                float raw_top = INFINITY;                          // raw radius of a token above 1/2, for finish_row
-                if (rm.unit) fuse_sums_rad<T, THREADS, NVEC, WIDE, true>(e, buf, fr, rm, sh, split, half, raw_top, V, tid, q5);
-                else         fuse_sums_rad<T, THREADS, NVEC, WIDE, false>(e, buf, fr, rm, sh, split, half, raw_top, V, tid, q5);
-                if (raw_top != INFINITY) sm_rtop[done] = raw_top;  // (at most one lane of the workgroup)
+                TopToken top = {split && mcw == mc, false, 0.f, 0.f};
+                top.e = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(exp2_ref(mcw, nw))));
+                if (rm.unit) fuse_sums_rad<T, THREADS, NVEC, WIDE, true>(e, buf, fr, rm, sh, V, tid, q5, top);
+                else         fuse_sums_rad<T, THREADS, NVEC, WIDE, false>(e, buf, fr, rm, sh, V, tid, q5, top);
+                if (top.found) sm_rtop[done] = top.raw;            // (one lane of the workgroup), for finish_row
 #pragma unroll
                 for (int i = 0; i < 5; ++i) q5[i] = wave_sum(q5[i]);
             } else if constexpr (WIDE) {

@@ -638,6 +638,36 @@ def test_radius_kernel_edges(ciar, oracle, H, V, stride, N, dtype, kw):
         assert torch.equal(gv["flags"], (2 * votes > H).to(torch.uint8))
 
 
+@pytest.mark.parametrize("V", [512, 1024, 4096, 16384, 32768])
+@pytest.mark.parametrize("kw", [dict(radius_scale=1.0), dict(radius_scale=0.7, radius_max=2.0)])
+def test_top_token_of_a_near_tie(ciar, V, kw):
+    """Rows of two live tokens whose exponentials differ by a few units in the last place, with radii far apart: the token
+    above one half is told by what it is, not by where it lies, so the outputs are the same bits whichever of the two comes
+    first in the row, in the next lane or in the same one.  (Every sum of such a row has two terms: its order is no matter.)"""
+    N = 1536
+    g = torch.Generator(device="cuda").manual_seed(15)
+    c0 = (torch.rand(N, generator=g, device="cuda") * 8.0 - 4.0).to(torch.float32)
+    c1 = (c0.view(torch.int32) - torch.sign(c0).to(torch.int32) * (1 + torch.arange(N, device="cuda", dtype=torch.int32) % 6)).view(torch.float32)
+    assert bool((c1 < c0).all())
+    r = torch.randn(2, N, generator=g, device="cuda") * 2.0
+    u = torch.rand(2, N, generator=g, device="cuda")
+    rows = torch.arange(N, device="cuda")
+    say(f"[near tie] V={V} {kw}")
+    P = ciar.Params(**kw)
+    for i, j in ((8, 9), (8, 12), (8, 500)):
+        got = []
+        for a, b in ((i, j), (j, i)):
+            c = torch.full((N, V), float("-inf"), device="cuda")
+            raw = torch.zeros(N, V, device="cuda")
+            c[rows, a], c[rows, b], raw[rows, a], raw[rows, b] = c0, c1, r[0], r[1]
+            ids = torch.full((N,), a, dtype=torch.int32, device="cuda")
+            q = ciar.quantify(c, ids, P, radius=raw)
+            f = ciar.quantify_verify(c, c, ids, u[0], u[1], P, radius=raw)
+            got.append([x[k] for x in (q, f) for k in parity.FLOAT_KEYS])
+        for x, y in zip(*got):
+            assert torch.equal(x, y), (i, j)
+
+
 @pytest.mark.parametrize("V,dtype", [(1024, torch.float32), (16384, torch.bfloat16)])
 def test_radius_vote_is_the_majority_of_the_flags(ciar, V, dtype):
     """Voting with radius tensors on nearly one-hot rows, whose score is corrected for the token above one half after the
