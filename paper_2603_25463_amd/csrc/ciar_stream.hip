@@ -726,15 +726,19 @@ void stream_kernel(const RowArgs A)
         // (by_lanes: across the first lanes of the wave, which must all be active; else in a loop)
         auto combine_S = [&](auto by_lanes, float& mc, float& n, double& S) {
             if constexpr (decltype(by_lanes)::value) {
-                // (the row's reference is the largest of the waves': the reference of the largest logit)
+                // (n is the largest of the waves' references.  It is ref_of(mc) as well, but formed from mc it comes later and in a
+                // vector register: one 1024-token row verified 5.45 -> 5.63 us, 36621 of them 109 -> 116, 65104 bf16 rows
+                // quantified and verified with a radius tensor 529 -> 620)
                 const float mc_l = sm_ref[src * 2], n_l = sm_ref[src * 2 + 1];
-                mc = row16_max(mc_l); n = ref_of(mc);
+                mc = row16_max(mc_l); n = row16_max(n_l);
                 S = row16_sum(lane < NW && n_l != -INFINITY ? sm_S[src] * pow2_of(n_l - n) : 0.0);
             } else {
-                mc = sm_ref[0];
+                mc = sm_ref[0]; n = sm_ref[1];
 #pragma unroll
-                for (int w = 1; w < NW; ++w) mc = max2(mc, sm_ref[w * 2]);
-                n = ref_of(mc);
+                for (int w = 1; w < NW; ++w) {
+                    mc = fmaxf(mc, sm_ref[w * 2]);
+                    n = fmaxf(n, sm_ref[w * 2 + 1]);
+                }
                 S = 0.0;
 #pragma unroll
                 for (int w = 0; w < NW; ++w) {
