@@ -190,6 +190,7 @@ ciar::RowArgs base_args(const ciar_params* p, const Resolved& r, int64_t N)
     const WidthPolyFit& wf = width_poly(r.a, r.b);
     for (int j = 0; j < 4; ++j) a.wpoly[j] = wf.c[j];
     a.wpoly_x = wf.x;
+    a.am1_max = (float)std::expm1(a.rmax);
     return a;
 }
 

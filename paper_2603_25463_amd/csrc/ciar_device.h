@@ -20,6 +20,9 @@ constexpr double kLn2 = 0.69314718055994530942;
 
 __device__ __forceinline__ float bits_f(uint32_t u) { return __uint_as_float(u); }
 
+// A value that is the same in every lane of the wave, moved to a scalar register.
+__device__ __forceinline__ float uniform_f(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
+
 constexpr int kNonTemporal = 2;        // cache policy of global_load_lds for rows that are used once
 
 // 16 bytes as loaded: a native vector type, so it can be read through an address-space pointer.
@@ -468,7 +471,7 @@ __device__ __forceinline__ void fuse_token_rad_wide(float e, float raw, const Fu
 struct RadiusMode { bool unit; float kappa, rmax, am1_max; };
 __device__ __forceinline__ RadiusMode radius_mode(const RowArgs& A)
 {
-    return {A.kappa == 1.0, (float)A.kappa, (float)A.rmax, (float)expm1(A.rmax)};
+    return {A.kappa == 1.0, (float)A.kappa, (float)A.rmax, A.am1_max};
 }
 __device__ __forceinline__ void fuse_token_rad(float e, float raw, const FuseRow& r, const RadiusMode& m, float& pl,
                                                float& w)

@@ -346,7 +346,6 @@ __global__ __launch_bounds__(256) void ensemble_kernel(const RowArgs A, const in
 }
 
 // Values that are the same in every lane of a wave, moved to scalar registers.
-__device__ __forceinline__ float uniform_f(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
 __device__ __forceinline__ double uniform_d(double v)
 {
     const long long b = __double_as_longlong(v);

@@ -79,6 +79,7 @@ struct RowArgs {
     // for x = e_i / S <= wpoly_x (negative: no such polynomial for this call)
     float    wpoly[4];
     float    wpoly_x;
+    float    am1_max;           // e^rmax - 1: the largest a_i - 1 of a tensor-radius call
 };
 
 enum class Mode { Quantify, Verify, Fused };

@@ -108,7 +108,7 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
     const int nch = (V + CHUNK - 1) / CHUNK;                       // vectors of a lane that hold tokens at all
     const int last_vec = (V + EPV - 1) / EPV - 1;
     const uint32_t P = (uint32_t)(A.head_rows ? A.head_rows : A.N), step = gridDim.x;
-    const float kappa = uniform((float)A.kappa), rmax = uniform((float)A.rmax), am1_max = uniform((float)expm1(A.rmax));
+    const float kappa = uniform((float)A.kappa), rmax = uniform((float)A.rmax), am1_max = A.am1_max;
     // this workgroup's rows: H of each of its positions blockIdx.x, blockIdx.x + step, ...
     const uint32_t mine = blockIdx.x < P ? (P - blockIdx.x + step - 1u) / step : 0u;
     const int count = (int)mine * H;                               // <= ROWS: the launcher sizes the grid accordingly

@@ -358,6 +358,11 @@ void stream_kernel(const RowArgs A)
     // wait for memory, measured 1 % slower with it and keep one reduction per sum.)
     constexpr bool BATCH3 = DO_Q && DO_V && !RAD && !WIDE && sizeof(T) == 2;
     constexpr int NQ = WIDE ? 8 : 5;                // interval sums a wave hands over
+    // A row with a token above 1/2 and a radius tensor: finish_row wants that token's raw radius.  It is picked up in the
+    // interval pass -- except in the instances of 1024 lanes with bf16 rows, which spill: there only the token's index is
+    // parked, ahead of the pass, and the finishing lane fetches its radius (picked up in the pass: 1017 rows of 65536 tokens
+    // 157 us against 148, 1666 of 40000 288 against 268; the other instances lose up to 9 % by the index).
+    constexpr bool TOP_INDEX = RAD && sizeof(T) == 2 && THREADS == 1024;
     constexpr int NT = NVEC * NW;                   // pieces of a row in token order: (vector j, wave w) -> j NW + w
 
     // Exchange slots.  Two barriers per row order every write against every read: the centre-row
@@ -378,7 +383,8 @@ void stream_kernel(const RowArgs A)
     // the reported token's centre logit, raw radius and verifier logit, the row's two uniforms.
     __shared__ RowStats sm_rows[kMaxRowsPerWg];
     __shared__ float    sm_fx[kMaxRowsPerWg][4];    // cx, rawx, tx, u_accept
-    __shared__ float    sm_rtop[RAD ? kMaxRowsPerWg : 1];     // tensor radius: raw radius of the row's token above 1/2, if any
+    __shared__ float    sm_rtop[RAD && !TOP_INDEX ? kMaxRowsPerWg : 1];   // raw radius of the row's token above 1/2, if any
+    __shared__ int      sm_top[TOP_INDEX ? kMaxRowsPerWg : 1];            // or its index
     __shared__ float    sm_ur[DO_V ? kMaxRowsPerWg : 1];
     __shared__ int      sm_draw[DO_V ? kMaxRowsPerWg : 1];   // -1: the drafted token was accepted; else the row's draw
     __shared__ uint8_t  sm_close[DO_V ? kMaxRowsPerWg : 1];  // the fp32 accept test could not decide the row
@@ -394,7 +400,11 @@ void stream_kernel(const RowArgs A)
     const int wave = sizeof(T) == 2 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
     const int V = A.V;
     RadiusMode rm = {false, 0.f, 0.f, 0.f};
-    if constexpr (RAD) rm = radius_mode(A);
+    if constexpr (RAD) {
+        rm = radius_mode(A);
+        // (in scalar registers; the fp32 instances of eight and sixteen waves spill with it)
+        if constexpr (sizeof(T) == 2 || THREADS == 256) { rm.kappa = uniform_f(rm.kappa); rm.rmax = uniform_f(rm.rmax); rm.am1_max = uniform_f(rm.am1_max); }
+    }
     const bool partial = V != NVEC * CHUNK;                        // uniform: the row does not fill the tile
     const int last_vec = (V + EPV - 1) / EPV - 1;
     const int nrows = (int)A.N;
@@ -545,7 +555,10 @@ void stream_kernel(const RowArgs A)
                 A.stats[r] = st;
                 if constexpr (DO_Q) {
                     const float cx = A.ids ? sm_fx[i][0] : st.mc;  // no ids: the arg-max token is reported
-                    finish_row<RAD>(A, r, st, cx, 0.f, sm_fx[i][1], 0.f, true, false, RAD ? sm_rtop[i] : 0.f);
+                    float raw_top = RAD && !TOP_INDEX ? sm_rtop[RAD && !TOP_INDEX ? i : 0] : 0.f;
+                    if (TOP_INDEX && (double)exp2_ref(st.mc, st.n == -INFINITY ? 0.f : st.n) > 0.5 * st.S)
+                        raw_top = load_logit(static_cast<const T*>(A.radius) + row_offset(A, r), sm_top[TOP_INDEX ? i : 0]);
+                    finish_row<RAD>(A, r, st, cx, 0.f, sm_fx[i][1], 0.f, true, false, raw_top);
                 }
             }
         };
@@ -785,7 +798,8 @@ void stream_kernel(const RowArgs A)
             double ra = A.a, rb = A.b;
             float wpx = A.wpoly_x;
             if constexpr (sizeof(T) == 2) asm volatile("" : "+s"(ra), "+s"(rb), "+s"(wpx));   // (fp32 instances: no gain, measured)
-            const FuseRow fr = fuse_row_inv(recip(Su), ra, rb);
+            // (by division in the bf16 instances of 1024 lanes, which spill: 1017 rows of 65536 tokens 168 -> 158 us)
+            const FuseRow fr = TOP_INDEX ? fuse_row(Su, ra, rb) : fuse_row_inv(recip(Su), ra, rb);
             double q5[NQ];
             auto shift_of = [&](float eref, const FuseRow& r) {
                 Shift k;
@@ -845,15 +859,22 @@ void stream_kernel(const RowArgs A)
                 // the raw radius row comes into the registers the centre row came in
                 __builtin_amdgcn_sched_barrier(0);
                 load_row(buf, A.radius, row);
+                if (TOP_INDEX && split && mcw == mc) {
+                    // (uniform over the wave: it holds the row's largest token; as for TopToken)
+                    const float etop = exp2_ref(mcw, nw);
+                    int at = -1;
+#pragma unroll
+                    for (int i = 0; i < EPT; ++i) at = e[i] == etop ? i : at;
+                    if (at >= 0) sm_top[TOP_INDEX ? done : 0] = (at / EPV * THREADS + tid) * EPV + at % EPV;
+                }
                 if (partial) {
 #pragma unroll
                     for (int j = 0; j < NVEC; ++j) E::zero_tail(buf[j], (j * THREADS + tid) * EPV, V);
                 }
-                TopToken top = {split && mcw == mc, false, 0.f, 0.f};
-                top.e = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(exp2_ref(mcw, nw))));
+                TopToken top = {!TOP_INDEX && split && mcw == mc, false, uniform_f(exp2_ref(mcw, nw)), 0.f};
                 if (rm.unit) fuse_sums_rad<T, THREADS, NVEC, WIDE, true>(e, buf, fr, rm, sh, V, tid, q5, top);
                 else         fuse_sums_rad<T, THREADS, NVEC, WIDE, false>(e, buf, fr, rm, sh, V, tid, q5, top);
-                if (top.found) sm_rtop[done] = top.raw;            // (one lane of the workgroup), for finish_row
+                if (top.found) sm_rtop[TOP_INDEX ? 0 : done] = top.raw;            // (one lane of the workgroup), for finish_row
 #pragma unroll
                 for (int i = 0; i < 5; ++i) q5[i] = wave_sum(q5[i]);
             } else if constexpr (WIDE) {

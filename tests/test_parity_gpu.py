@@ -638,27 +638,32 @@ def test_radius_kernel_edges(ciar, oracle, H, V, stride, N, dtype, kw):
         assert torch.equal(gv["flags"], (2 * votes > H).to(torch.uint8))
 
 
-@pytest.mark.parametrize("V", [512, 1024, 4096, 16384, 32768])
+@pytest.mark.parametrize("V,dtype", [(512, torch.float32), (1024, torch.float32), (4096, torch.float32), (16384, torch.float32),
+                                     (32768, torch.float32), (1024, torch.bfloat16), (32768, torch.bfloat16),
+                                     (40000, torch.bfloat16), (65536, torch.bfloat16)])
 @pytest.mark.parametrize("kw", [dict(radius_scale=1.0), dict(radius_scale=0.7, radius_max=2.0)])
-def test_top_token_of_a_near_tie(ciar, V, kw):
-    """Rows of two live tokens whose exponentials differ by a few units in the last place, with radii far apart: the token
+def test_top_token_of_a_near_tie(ciar, V, dtype, kw):
+    """Rows of two live tokens whose logits (and with fp32 their exponentials) differ by a few units in the last place, with radii far apart: the token
     above one half is told by what it is, not by where it lies, so the outputs are the same bits whichever of the two comes
     first in the row, in the next lane or in the same one.  (Every sum of such a row has two terms: its order is no matter.)"""
-    N = 1536
+    N = 1536 if V <= 32768 else 300
     g = torch.Generator(device="cuda").manual_seed(15)
     c0 = (torch.rand(N, generator=g, device="cuda") * 8.0 - 4.0).to(torch.float32)
     c1 = (c0.view(torch.int32) - torch.sign(c0).to(torch.int32) * (1 + torch.arange(N, device="cuda", dtype=torch.int32) % 6)).view(torch.float32)
+    if dtype == torch.bfloat16:
+        c0 = c0.to(dtype)
+        c1 = (c0.view(torch.int16) - torch.sign(c0).to(torch.int16)).view(dtype)
     assert bool((c1 < c0).all())
-    r = torch.randn(2, N, generator=g, device="cuda") * 2.0
+    r = (torch.randn(2, N, generator=g, device="cuda") * 2.0).to(dtype)
     u = torch.rand(2, N, generator=g, device="cuda")
     rows = torch.arange(N, device="cuda")
-    say(f"[near tie] V={V} {kw}")
+    say(f"[near tie] V={V} {dtype} {kw}")
     P = ciar.Params(**kw)
-    for i, j in ((8, 9), (8, 12), (8, 500)):
+    for i, j in ((8, 9), (8, 12), (8, V - 3)):
         got = []
         for a, b in ((i, j), (j, i)):
-            c = torch.full((N, V), float("-inf"), device="cuda")
-            raw = torch.zeros(N, V, device="cuda")
+            c = torch.full((N, V), float("-inf"), device="cuda", dtype=dtype)
+            raw = torch.zeros(N, V, device="cuda", dtype=dtype)
             c[rows, a], c[rows, b], raw[rows, a], raw[rows, b] = c0, c1, r[0], r[1]
             ids = torch.full((N,), a, dtype=torch.int32, device="cuda")
             q = ciar.quantify(c, ids, P, radius=raw)
