@@ -685,8 +685,8 @@ int ciar_quantify_multihead(const void* draft_heads, const void* radius_heads, i
             a.p_lo = p_lo; a.p_mid = p_mid; a.p_hi = p_hi;
             a.omega = omega; a.sigma = sigma; a.score = score;
             if (ciar::radius_quantify_fits(a)) {
-                // with a radius tensor one kernel takes all heads of a position, and the vote
-                a.flags = head_flags;
+                // with a radius tensor one kernel takes all heads, and the vote
+                a.flags = head_flags ? head_flags : ws_flags;
                 a.precise_flat = ciar::needs_flat_pass(a) ? 1 : 0;
                 const hipError_t e = ciar::launch_radius_quantify(params->dtype, a, heads, flags, stream);
                 if (e != hipSuccess) return hip_fail(e, "radius kernel launch");

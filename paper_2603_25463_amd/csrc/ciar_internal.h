@@ -162,7 +162,7 @@ hipError_t launch_dro(int dtype, const RowArgs& args, float* terms, double lambd
 
 // The quantifier of calls with a radius tensor and more than 64 tokens, all outputs written (ids may be null: the arg-max
 // token; args.precise_flat as for the streaming kernel; args.stats is written).  args.N rows = heads x positions; votes (may be
-// null): per position the strict majority of the heads' flags.
+// null): per position the strict majority of the heads' flags, which args.flags then takes.
 bool radius_quantify_fits(const RowArgs& args);
 hipError_t launch_radius_quantify(int dtype, const RowArgs& args, int heads, uint8_t* votes, hipStream_t stream,
                                   hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);

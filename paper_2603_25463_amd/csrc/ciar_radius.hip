@@ -75,7 +75,8 @@ __device__ void radius_row_fp64(const RowArgs& A, int64_t row, double (*red)[48]
     st.mode = kSumsDirect;
 }
 
-// A.N rows: [H, P] if A.head_rows is set (H heads of P positions), else P = A.N positions of one head.
+// A.N rows: H > 1: [H, P], H heads of P = A.head_rows positions, the H rows of a position one after another in one workgroup,
+// which can then vote; H = 1: P = A.N rows dealt singly, of one head or of several (see row_offset).
 // ARGMAX = no drafted ids: every row reports its arg-max token.  votes: [P] flags by strict majority, or null.
 template <typename T, int THREADS, bool UNIT, bool ARGMAX>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)))
@@ -107,7 +108,7 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
     const int V = A.V;
     const int nch = (V + CHUNK - 1) / CHUNK;                       // vectors of a lane that hold tokens at all
     const int last_vec = (V + EPV - 1) / EPV - 1;
-    const uint32_t P = (uint32_t)(A.head_rows ? A.head_rows : A.N), step = gridDim.x;
+    const uint32_t P = (uint32_t)(H > 1 ? A.head_rows : A.N), step = gridDim.x;
     const float kappa = uniform((float)A.kappa), rmax = uniform((float)A.rmax), am1_max = A.am1_max;
     // this workgroup's rows: H of each of its positions blockIdx.x, blockIdx.x + step, ...
     const uint32_t mine = blockIdx.x < P ? (P - blockIdx.x + step - 1u) / step : 0u;
@@ -116,8 +117,11 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
 
     using lds_ptr = __attribute__((address_space(3))) void*;
     using glb_ptr = const __attribute__((address_space(1))) void*;
+    auto offset_of = [&](uint32_t pos, int h) {
+        return H > 1 ? (int64_t)h * A.head_stride + (int64_t)pos * A.stride : row_offset(A, pos);
+    };
     auto row_base = [&](const void* rows, uint32_t pos, int h) {
-        const uint64_t b = (uint64_t)(static_cast<const T*>(rows) + (int64_t)h * A.head_stride + (int64_t)pos * A.stride);
+        const uint64_t b = (uint64_t)(static_cast<const T*>(rows) + offset_of(pos, h));
         const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
         const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
         return (gbytes)(((uint64_t)hi << 32) | lo);
@@ -329,7 +333,7 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
     auto row_of = [&](int at) { return (int64_t)(at % H) * P + blockIdx.x + (int64_t)(at / H) * step; };
     auto finish = [&](int at, const RowStats& st) {
         const int64_t r = row_of(at);
-        const int64_t off = (int64_t)(at % H) * A.head_stride + (r - (int64_t)(at % H) * P) * A.stride;
+        const int64_t off = row_offset(A, r);
         int xid = ARGMAX ? pk_id[ARGMAX ? at : 0] : A.ids ? A.ids[ids_index(A, r)] : 0;
         xid = xid < 0 ? 0 : (xid >= V ? V - 1 : xid);
         const float cx = load_logit(static_cast<const T*>(A.draft) + off, xid);
@@ -371,6 +375,21 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
 template <typename T, int THREADS, bool UNIT, bool ARGMAX>
 hipError_t launch_radius_cfg(const RowArgs& a, int heads, uint8_t* votes, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
+    constexpr int kPerUnit = 1024 / THREADS;                       // workgroups a compute unit holds
+    const int64_t resident = (int64_t)kPerUnit * compute_units(), positions = a.N / heads;
+    // Several heads: the rows of a position in one workgroup, which takes the vote, or -- where the chip then goes through
+    // fewer rows in turn -- every row for itself and the vote in a launch of its own.  (fp32, by position / by row: 8 positions
+    // of 8 heads 1024 tokens 31.8 / 10.8 us, 16384 tokens 49.2 / 13.5, 32768 tokens 79.8 / 19.4; 300 of 5 heads 1024 tokens
+    // 23.6 / 14.9, 16384 tokens 54.3 / 43.4; 600 of 3 heads 32768 tokens 102 / 97.)  Small workgroups slow each other down when
+    // all places are taken: half the rows in turn are wanted (2048 of 3 heads, 1024 tokens, two thirds: 22.1 / 23.9); of the large
+    // ones a tenth less is enough (2100 of 2 heads, 32768 tokens bf16, 17 instead of 18: 162 / 167).
+    const int64_t turns = (positions + resident - 1) / resident * heads, turns_by_row = (a.N + resident - 1) / resident;
+    const bool by_row = heads > 1 && (THREADS < 512 ? 2 * turns_by_row <= turns : 10 * turns_by_row <= 9 * turns);
+    if (by_row && !votes) heads = 1;
+    if (by_row && votes) {
+        const hipError_t e = launch_radius_cfg<T, THREADS, UNIT, ARGMAX>(a, 1, nullptr, stream, ev_start, ev_stop);
+        return e != hipSuccess ? e : launch_vote(a.flags, heads, positions, votes, stream);
+    }
     constexpr unsigned lds = kRadVecs * 16u * THREADS;             // 8 to 128 KiB
     if (lds > 32u * 1024u) {
         // with the static arrays above the default limit: raised once per device and instance
@@ -387,7 +406,7 @@ hipError_t launch_radius_cfg(const RowArgs& a, int heads, uint8_t* votes, hipStr
         }
     }
     const int64_t per_wg = radius_rows<THREADS>() / heads;         // positions (>= 2: heads <= 8)
-    const int64_t g = whole_rounds(a.N / heads, per_wg, (int64_t)(1024 / THREADS) * compute_units());
+    const int64_t g = whole_rounds(a.N / heads, per_wg, resident);
     const dim3 grid((unsigned)g), block(THREADS);
     const int wide = wide_radius(a) ? 1 : 0;
     if (ev_start && ev_stop)
@@ -427,7 +446,7 @@ hipError_t launch_radius_quantify(int dtype, const RowArgs& args, int heads, uin
                                   hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     if (args.N <= 0) return hipSuccess;
-    if (!radius_quantify_fits(args) || heads < 1) return hipErrorInvalidValue;
+    if (!radius_quantify_fits(args) || heads < 1 || (votes && !args.flags)) return hipErrorInvalidValue;
     return dtype == 0 ? launch_radius_typed<float>(args, heads, votes, stream, ev_start, ev_stop)
                       : launch_radius_typed<bf16_t>(args, heads, votes, stream, ev_start, ev_stop);
 }

@@ -673,6 +673,39 @@ def test_top_token_of_a_near_tie(ciar, V, dtype, kw):
             assert torch.equal(x, y), (i, j)
 
 
+VOTE_DEALS = [  # H, V, N, dtype: a workgroup per row and the vote behind it (first of a pair) or per position (second)
+    (2, 1024, 300, torch.float32), (2, 1024, 2100, torch.float32), (3, 16384, 8, torch.float32), (3, 16384, 2048, torch.float32),
+    (8, 4100, 8, torch.bfloat16), (8, 4100, 2048, torch.bfloat16), (2, 33000, 270, torch.bfloat16), (2, 33000, 256, torch.bfloat16),
+]
+
+
+@pytest.mark.parametrize("H,V,N,dtype", VOTE_DEALS)
+def test_radius_vote_however_the_rows_are_dealt(ciar, H, V, N, dtype):
+    """Voting with radius tensors, the rows dealt singly or by position: every head's outputs are the bits of a call for that
+    head alone, and the vote is the majority of the heads' flags -- also for a caller that does not ask for them."""
+    from paper_2603_25463_amd import binding
+    stride = -(-V // 8) * 8
+    heads = _head_stack(H, V, stride, N, torch.float32, seed=9300 + V).to(dtype).contiguous()
+    raw = torch.stack([_raw_radius(N, stride, V, torch.float32, seed=5800 + V + h) for h in range(H)]).to(dtype).contiguous()
+    ids = torch.randint(0, V, (N,), generator=torch.Generator(device="cuda").manual_seed(16), device="cuda").to(torch.int32)
+    say(f"[vote deal] H={H} V={V} N={N} {dtype}")
+    each = [ciar.quantify(heads[h], ids, ciar.Params(radius_scale=1.0), vocab=V, radius=raw[h]) for h in range(H)]
+    P = ciar.Params(radius_scale=1.0, tau=float(each[0]["score"].median()))
+    g = ciar.quantify_multihead(heads, ids, P, ciar.VOTING, vocab=V, radius_heads=raw)
+    for h in range(H):
+        for k in parity.FLOAT_KEYS:
+            assert torch.equal(g[k][h], each[h][k]), (h, k)
+    want = (2 * g["head_flags"].sum(0, dtype=torch.int32) > H).to(torch.uint8)
+    assert torch.equal(g["flags"], want) and set(want.unique().tolist()) == {0, 1}
+    cp = P.to_c(heads[0], V)
+    ws = torch.empty(int(ciar.lib().ciar_multihead_workspace_bytes(N, H, cp)), dtype=torch.uint8, device="cuda")
+    flags = torch.full((N,), 7, dtype=torch.uint8, device="cuda")
+    p = lambda t: None if t is None else t.data_ptr()
+    rc = ciar.lib().ciar_quantify_multihead(p(heads), p(raw), H, heads.stride(0), p(ids), N, cp, ciar.VOTING, *([None] * 6), p(flags),
+                                            None, p(ws), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    assert rc == 0 and torch.equal(flags, want)
+
+
 @pytest.mark.parametrize("V,dtype", [(1024, torch.float32), (16384, torch.bfloat16)])
 def test_radius_vote_is_the_majority_of_the_flags(ciar, V, dtype):
     """Voting with radius tensors on nearly one-hot rows, whose score is corrected for the token above one half after the
