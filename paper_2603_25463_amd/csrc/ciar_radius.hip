@@ -429,9 +429,15 @@ template <typename T>
 hipError_t launch_radius_typed(const RowArgs& a, int heads, uint8_t* votes, hipStream_t stream, hipEvent_t ev_start,
                                hipEvent_t ev_stop)
 {
+    // As many lanes as the row takes at kRadVecs vectors each -- or, where there is a row per compute unit at most (two, if that
+    // leaves a lane two vectors), at one vector each, up to 256 lanes: then a call waits for one row's chain of instructions, and
+    // fewer tokens per lane make it shorter.  (Without / with, 8 rows of 4096 tokens bf16 12.1 / 9.3 us, fp32 10.0 / 9.1; 300
+    // rows 12.9 / 11.9 and 12.0 / 11.1, of 1024 tokens fp32 9.8 / 9.8, bf16 10.0 / 10.4; 1000 rows of 4096 bf16 13.5 / 16.6.  512
+    // lanes, 8 rows of 4096 bf16: 10.2.)
     const int vecs = (a.V + Elt<T>::kPerVec - 1) / Elt<T>::kPerVec;
-    if (vecs <= 64 * kRadVecs) return launch_radius_tile<T, 64>(a, heads, votes, stream, ev_start, ev_stop);
-    if (vecs <= 128 * kRadVecs) return launch_radius_tile<T, 128>(a, heads, votes, stream, ev_start, ev_stop);
+    const int vecs_per_lane = a.N <= (vecs >= 512 ? 2 : 1) * compute_units() ? 1 : kRadVecs;
+    if (vecs <= 64 * vecs_per_lane) return launch_radius_tile<T, 64>(a, heads, votes, stream, ev_start, ev_stop);
+    if (vecs <= 128 * vecs_per_lane) return launch_radius_tile<T, 128>(a, heads, votes, stream, ev_start, ev_stop);
     if (vecs <= 256 * kRadVecs) return launch_radius_tile<T, 256>(a, heads, votes, stream, ev_start, ev_stop);
     if (vecs <= 512 * kRadVecs) return launch_radius_tile<T, 512>(a, heads, votes, stream, ev_start, ev_stop);
     if (vecs <= 1024 * kRadVecs) return launch_radius_tile<T, 1024>(a, heads, votes, stream, ev_start, ev_stop);

@@ -586,6 +586,10 @@ RADIUS_EDGES = [  # H, V, stride, N, dtype: both sides of every tile's end, seve
     (1, 16385, 16388, 517, torch.float32), (2, 32768, 32768, 70, torch.float32),
     (5, 72, 72, 2000, torch.bfloat16), (1, 4097, 4104, 2100, torch.bfloat16), (3, 8192, 8192, 700, torch.bfloat16),
     (1, 16385, 16392, 1031, torch.bfloat16), (2, 32769, 32776, 270, torch.bfloat16), (1, 65535, 65536, 260, torch.bfloat16),
+    # few rows: one vector to a lane (64, 128, 256 lanes), several where 256 lanes are not enough
+    (1, 256, 256, 9, torch.float32), (2, 257, 260, 60, torch.float32), (1, 513, 516, 256, torch.float32), (3, 1028, 1028, 40, torch.float32),
+    (1, 2048, 2048, 511, torch.float32), (1, 8192, 8192, 60, torch.float32), (1, 513, 520, 7, torch.bfloat16),
+    (1, 2049, 2056, 60, torch.bfloat16), (2, 4097, 4104, 250, torch.bfloat16), (1, 16384, 16384, 60, torch.bfloat16),
 ]
 
 
