@@ -584,11 +584,13 @@ __device__ __forceinline__ int accept_quick(float cx, float tx, float u, float n
 // token (-1: the arg-max token, whose logit is st.mc), cx / tx / rawx = its centre logit, verifier logit and raw
 // radius, u = the row's uniform for the accept test.  Returns whether the drafted token is rejected.
 // raw_top: tensor radius, rows with a token above 1/2: that token's raw radius.  flag: where the row's flag goes besides
-// A.flags, if anywhere.
-template <bool RAD_TOP = false>
+// A.flags, if anywhere.  again(score): whether the row's sums are to be taken anew -- then nothing is written and the
+// result is true.
+struct NeverAgain { __device__ bool operator()(const RowScore&) const { return false; } };
+template <bool RAD_TOP = false, typename Again = NeverAgain>
 __device__ __forceinline__ bool finish_row(const RowArgs& A, int64_t row, const RowStats& st, float cx, float tx,
                                            float rawx, float u, bool do_q, bool do_v, float raw_top = 0.f,
-                                           uint8_t* flag = nullptr)
+                                           uint8_t* flag = nullptr, Again again = {})
 {
     const double S = st.S;
     const float n = st.n;
@@ -641,6 +643,7 @@ __device__ __forceinline__ bool finish_row(const RowArgs& A, int64_t row, const 
             }
         }
         const RowScore rs = finish_score(q, S, st.mode, A, st.kl, st.kw);
+        if (again(rs)) return true;
         if (A.omega) A.omega[row] = (float)rs.omega;
         if (A.sigma) A.sigma[row] = (float)rs.sigma;
         if (A.score) A.score[row] = (float)rs.score;

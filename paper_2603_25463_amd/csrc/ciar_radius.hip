@@ -331,27 +331,28 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
         return st;
     };
     auto row_of = [&](int at) { return (int64_t)(at % H) * P + blockIdx.x + (int64_t)(at / H) * step; };
-    auto finish = [&](int at, const RowStats& st) {
+    auto finish = [&](int at, const RowStats& st, auto again) {
         const int64_t r = row_of(at);
         const int64_t off = row_offset(A, r);
         int xid = ARGMAX ? pk_id[ARGMAX ? at : 0] : A.ids ? A.ids[ids_index(A, r)] : 0;
         xid = xid < 0 ? 0 : (xid >= V ? V - 1 : xid);
         const float cx = load_logit(static_cast<const T*>(A.draft) + off, xid);
         const float rawx = load_logit(static_cast<const T*>(A.radius) + off, xid);
-        finish_row<true>(A, r, st, cx, 0.f, rawx, 0.f, true, false, pk[at].raw_top, &pk_flag[at]);   // (the vote counts the flags as written)
+        // (the vote counts the flags as written)
+        if (finish_row<true>(A, r, st, cx, 0.f, rawx, 0.f, true, false, pk[at].raw_top, &pk_flag[at], again)) return true;
         A.stats[r] = st;
+        return false;
     };
     {
         const int t = my_tid();
         if (t < count) {
             const RowStats st = stats_of(t);
-            const RowScore rs = finish_score(st.q, st.S, st.mode, A, 0.0, 0.0);
-            const double Vd = (double)V, mean = rs.omega / Vd;
             const double etop = (double)exp2_ref(st.mc, st.n == -INFINITY ? 0.f : st.n);
-            const bool fp64 = !(rs.sigma * rs.sigma >= 1e-4 * mean * mean) || (A.precise_flat && etop * Vd <= 2.0 * st.S) ||
-                              (wide && mean > 0.45);
-            pk_fp64[t] = (uint8_t)fp64;
-            if (!fp64) finish(t, st);
+            pk_fp64[t] = (uint8_t)finish(t, st, [&](const RowScore& rs) {
+                const double Vd = (double)V, mean = rs.omega / Vd;
+                return !(rs.sigma * rs.sigma >= 1e-4 * mean * mean) || (A.precise_flat && etop * Vd <= 2.0 * st.S) ||
+                       (wide && mean > 0.45);
+            });
         }
     }
     __syncthreads();
@@ -359,7 +360,7 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
         if (!pk_fp64[at]) continue;                                // uniform
         RowStats st = stats_of(at);
         radius_row_fp64<T, THREADS>(A, row_of(at), sm_red, st);
-        if (my_tid() == 0) finish(at, st);
+        if (my_tid() == 0) finish(at, st, NeverAgain{});
     }
     if (votes) {
         __syncthreads();
