@@ -16,8 +16,8 @@
 // rows and a third for the vote.
 //
 // A row's scalars are parked in LDS; after the workgroup's last row a lane per row turns them into the outputs.  Rows whose
-// widths agree to better than a hundredth of their mean, flat rows of calls whose widths are not small (needs_flat_pass) and
-// rows whose widths crowd against 1 (wide_radius) are swept again in fp64 before that is written.
+// widths (or whose complements) agree to better than a hundredth of their mean and flat rows of calls whose widths are not small
+// (needs_flat_pass) are swept again in fp64 before that is written.
 #include "ciar_device.h"
 
 #include <hip/hip_ext.h>
@@ -26,14 +26,16 @@
 namespace ciar {
 namespace {
 
-constexpr int kRadVecs = 8;                                        // 16-byte vectors of a row per lane
+// 16-byte vectors of a row per lane.  (bf16 rows with complement sums: 32 tokens; with 64 those instances spill 136 to 208 bytes,
+// which is left for the rows above 32768 tokens.)
+constexpr int kRadVecs = 8, kRadVecsWide16 = 4;
 template <int THREADS> constexpr int radius_rows() { return THREADS >= 512 ? 128 : THREADS / 4; }   // most rows of a workgroup
 
-struct RadiusRow { double S, q[5]; float n, mc, raw_top; };        // see RowStats, finish_row
+template <bool WIDE> struct RadiusRow { double S, q[WIDE ? 7 : 5]; float n, mc, raw_top, big; };   // see RowStats, finish_row
 
 // The five sums of a row in fp64 from the logits, about the first token's values, by the whole workgroup; red: 6 doubles per wave.
 template <typename T, int THREADS>
-__device__ void radius_row_fp64(const RowArgs& A, int64_t row, double (*red)[48], RowStats& st)
+__device__ void radius_row_fp64(const RowArgs& A, int64_t row, double (*red)[64], RowStats& st)
 {
     constexpr int NW = THREADS / 64;
     int tid = threadIdx.x;
@@ -78,21 +80,26 @@ __device__ void radius_row_fp64(const RowArgs& A, int64_t row, double (*red)[48]
 // A.N rows: H > 1: [H, P], H heads of P = A.head_rows positions, the H rows of a position one after another in one workgroup,
 // which can then vote; H = 1: P = A.N rows dealt singly, of one head or of several (see row_offset).
 // ARGMAX = no drafted ids: every row reports its arg-max token.  votes: [P] flags by strict majority, or null.
-template <typename T, int THREADS, bool UNIT, bool ARGMAX>
+// WIDE = radii at which the widths can crowd against 1 (wide_radius): rows of which every width is above 1/2 take their Omega and
+// Sigma from the sums of the complements 1 - width (fuse_token_rad_wide), which are formed where they may be wanted: a width
+// above 1/2 has (a + 1) x > 1, and a wave of which one lane's first token has not spares itself the rest.
+template <typename T, int THREADS, int NVEC, bool UNIT, bool ARGMAX, bool WIDE>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)))
-void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __restrict__ votes)
+void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
 {
     using E = Elt<T>;
-    constexpr int EPV = E::kPerVec, NVEC = kRadVecs, EPT = NVEC * EPV, NW = THREADS / 64, ROWS = radius_rows<THREADS>();
+    constexpr int EPV = E::kPerVec, EPT = NVEC * EPV, NW = THREADS / 64, ROWS = radius_rows<THREADS>();
     constexpr int CHUNK = THREADS * EPV;                           // tokens of one vector of every lane
     extern __shared__ u32x4 sm_next[];                             // [NVEC][THREADS]: the row in flight
     // exchange slots of a row: written before its barrier, read behind it; rows alternate between two sets
     __shared__ float sm_ref[2][NW];
-    __shared__ double sm_S[2][NW], sm_tot[2][NW][5];
-    __shared__ double sm_red[NW][48];                              // per wave: [five sums of the row before, S_w][eight groups of lanes]
+    constexpr int NQ = WIDE ? 7 : 5;                               // sums of a row
+    __shared__ double sm_S[2][NW], sm_tot[2][NW][NQ];
+    __shared__ double sm_red[NW][64];                              // per wave: [the sums of the row before, S_w][eight groups of lanes]
+    __shared__ float sm_big[WIDE ? 2 : 1][NW];                     // largest complement
     __shared__ int sm_pi[2][ARGMAX ? NW : 1];
     // parked rows
-    __shared__ RadiusRow pk[ROWS];
+    __shared__ RadiusRow<WIDE> pk[ROWS];
     __shared__ int pk_id[ARGMAX ? ROWS : 1];
     __shared__ uint8_t pk_fp64[ROWS], pk_flag[ROWS];
 
@@ -138,16 +145,20 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
     auto park = [&](int at, int p) {
         const int lane = my_tid() & 63, grp = lane >> 3, part = lane & 7;
         double v = 0.0;
-        if (grp < 5) {
+        if (grp < NQ) {
             if (part < NW) v = sm_tot[p][part][grp];
             if (NW > 8) v += sm_tot[p][part + (NW > 8 ? 8 : 0)][grp];
         }
         v = dpp_add<0xB1, 0xf>(v);                                 // lane ^ 1, lane ^ 2, the other quad of the eight
         v = dpp_add<0x4E, 0xf>(v);
         v = dpp_add<0x141, 0xf>(v);
-        if (grp < 5 && part == 0) pk[at].q[grp] = v;
+        if (grp < NQ && part == 0) pk[at].q[grp] = v;
+        if constexpr (WIDE) {
+            const float big = row16_max(lane < NW ? sm_big[p][lane < NW ? lane : 0] : 0.f);
+            if (lane == 0) pk[at].big = big;
+        }
     };
-    // the six quantities of a wave reduced together: every lane's value -> groups of eight lanes (three DPP steps) -> LDS
+    // the sums of a wave reduced together: every lane's value -> groups of eight lanes (three DPP steps) -> LDS
     auto put = [&](double v, int which, int lane) {
         v = dpp_add<0xB1, 0xf>(v);
         v = dpp_add<0x4E, 0xf>(v);
@@ -155,7 +166,7 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
         if ((lane & 7) == 0) sm_red[wave][which * 8 + (lane >> 3)] = v;
     };
     auto get = [&](int lane) {                                     // lanes 8 q ... 8 q + 7: quantity q over the wave
-        double v = sm_red[wave][lane < 48 ? lane : 0];
+        double v = sm_red[wave][lane < 8 * (NQ + 1) ? lane : 0];
         v = dpp_add<0xB1, 0xf>(v);
         v = dpp_add<0x4E, 0xf>(v);
         return dpp_add<0x141, 0xf>(v);
@@ -214,13 +225,13 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        put(Sl, 5, lane);
+        put(Sl, NQ, lane);
         {
             const double v = get(lane);
             const int grp = lane >> 3;
             if ((lane & 7) == 0) {
-                if (grp < 5) { if (done > 0) sm_tot[p ^ 1][wave][grp] = v; }
-                else if (grp == 5) sm_S[p][wave] = v;
+                if (grp < NQ) { if (done > 0) sm_tot[p ^ 1][wave][grp] = v; }
+                else if (grp == NQ) sm_S[p][wave] = v;
             }
             if (lane == 0) sm_ref[p][wave] = mw;
         }
@@ -252,7 +263,9 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
             if (++nh == H) { nh = 0; npos += step; }
         }
         const gbytes next = row_base(A.draft, npos, nh);
-        double q[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+        double q[NQ];
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) q[i] = 0.0;
         // A row with a token above 1/2: its raw radius is parked for finish_row by the lane that has it, in the wave with the row's
         // largest token.  (No other token has its e: two of them would be all of S.)
         const bool search = top && mw == mc;                       // uniform over the wave
@@ -260,30 +273,54 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
         float raw_top = 0.f;
         bool found = false;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        bool complements = false;                                  // uniform over the wave
+        float big = INFINITY;                                      // largest complement of this lane
+        if constexpr (WIDE) {
+            const float am1 = radius_am1<UNIT>(load_logit(reinterpret_cast<const T*>(sm_next), tid * EPV), kappa, rmax, am1_max);
+            complements = __builtin_amdgcn_ballot_w64(tid * EPV < V && !(-(am1 + 2.0f) * e[0] * fr.nih > 1.0f)) == 0;
+            if (complements) big = 0.f;
+        }
+        constexpr int GROUP = WIDE && sizeof(T) == 2 ? 2 : 4;      // vectors taken at a time
 #pragma unroll
-        for (int g = 0; g < NVEC; g += 4) {
-            u32x4 rb[4];
+        for (int g = 0; g < NVEC; g += GROUP) {
+            u32x4 rb[GROUP];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) rb[u] = sm_next[(g + u) * THREADS + tid];
+            for (int u = 0; u < GROUP; ++u) rb[u] = sm_next[(g + u) * THREADS + tid];
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             if (has_next) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) fetch(next, g + u, tid);
+                for (int u = 0; u < GROUP; ++u) fetch(next, g + u, tid);
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < GROUP; ++u) {
                 const int j = g + u;
                 if (j < nch) {                                     // uniform: the vectors hold tokens
                     if ((j + 1) * CHUNK > V) E::zero_tail(rb[u], (j * THREADS + tid) * EPV, V);
                     float rv[EPV];
                     E::unpack(rb[u], rv);
+                    if (WIDE && complements) {
 #pragma unroll
-                    for (int k = 0; k < EPV; ++k) {
-                        float pl, w;                               // (a slot past the row's end holds e = 0: both are 0)
-                        fuse_token_rad<UNIT>(e[j * EPV + k], rv[k], fr, kappa, rmax, am1_max, pl, w);
-                        const double dl = (double)pl, dw = (double)w;
-                        q[0] += dl; q[1] += dw;
-                        q[2] = fma(dl, dl, q[2]); q[3] = fma(dw, dw, q[3]); q[4] = fma(dl, dw, q[4]);
+                        for (int k = 0; k < EPV; ++k) {
+                            float pl, w, ec;
+                            fuse_token_rad_wide<UNIT>(e[j * EPV + k], rv[k], fr, kappa, rmax, am1_max, pl, w, ec);
+                            if ((j * THREADS + tid) * EPV + k < V) {   // (past the row's end ec is not 0)
+                                const double dc = (double)ec;
+                                q[NQ - 2] += dc; q[NQ - 1] = fma(dc, dc, q[NQ - 1]);
+                                big = fmaxf(big, ec);
+                            }
+                            const double dl = (double)pl, dw = (double)w;
+                            q[0] += dl; q[1] += dw;
+                            q[2] = fma(dl, dl, q[2]); q[3] = fma(dw, dw, q[3]); q[4] = fma(dl, dw, q[4]);
+                        }
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < EPV; ++k) {
+                            float pl, w;                               // (a slot past the row's end holds e = 0: both are 0)
+                            fuse_token_rad<UNIT>(e[j * EPV + k], rv[k], fr, kappa, rmax, am1_max, pl, w);
+                            const double dl = (double)pl, dw = (double)w;
+                            q[0] += dl; q[1] += dw;
+                            q[2] = fma(dl, dl, q[2]); q[3] = fma(dw, dw, q[3]); q[4] = fma(dl, dw, q[4]);
+                        }
                     }
                     if (search) {
 #pragma unroll
@@ -302,6 +339,13 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
             const double f2 = fw * fw;                             // to row units
             put(q[0] * fw, 0, lane); put(q[1] * fw, 1, lane);
             put(q[2] * f2, 2, lane); put(q[3] * f2, 3, lane); put(q[4] * f2, 4, lane);
+            if constexpr (WIDE) {
+                if (complements) {                                 // (else the two sums are whatever their slots hold, and not used)
+                    put(q[NQ - 2], NQ - 2, lane); put(q[NQ - 1], NQ - 1, lane);     // (plain numbers: nothing to rescale)
+                    big = wave_max(big);
+                }
+                if (lane == 0) sm_big[p][wave] = big;
+            }
         }
         if (!has_next) break;
         pos = npos; h = nh;
@@ -316,7 +360,7 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
     {
         const int lane = my_tid() & 63;
         const double v = get(lane);
-        if ((lane & 7) == 0 && lane < 40) sm_tot[(count - 1) & 1][wave][lane >> 3] = v;
+        if ((lane & 7) == 0 && lane < 8 * NQ) sm_tot[(count - 1) & 1][wave][lane >> 3] = v;
     }
     __syncthreads();
     if (wave == 0) park(count - 1, (count - 1) & 1);
@@ -328,6 +372,12 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
 #pragma unroll
         for (int i = 0; i < 5; ++i) st.q[i] = pk[at].q[i];
         st.kl = 0.0; st.kw = 0.0; st.mode = kSumsFull;
+        if constexpr (WIDE) {
+            if (pk[at].big < (float)kComplementBelow) {            // every width above 1/2
+                const RowScore rs = finish_score(st.q, st.S, kSumsFull, A, 0.0, 0.0);
+                if (rs.alpha_l == 1.0 && rs.alpha_u == 1.0) { st.q[1] = pk[at].q[NQ - 2]; st.q[3] = pk[at].q[NQ - 1]; st.mode = kSumsComplement; }
+            }
+        }
         return st;
     };
     auto row_of = [&](int at) { return (int64_t)(at % H) * P + blockIdx.x + (int64_t)(at / H) * step; };
@@ -349,9 +399,8 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
             const RowStats st = stats_of(t);
             const double etop = (double)exp2_ref(st.mc, st.n == -INFINITY ? 0.f : st.n);
             pk_fp64[t] = (uint8_t)finish(t, st, [&](const RowScore& rs) {
-                const double Vd = (double)V, mean = rs.omega / Vd;
-                return !(rs.sigma * rs.sigma >= 1e-4 * mean * mean) || (A.precise_flat && etop * Vd <= 2.0 * st.S) ||
-                       (wide && mean > 0.45);
+                const double Vd = (double)V, mean = (WIDE && st.mode == kSumsComplement ? Vd - rs.omega : rs.omega) / Vd;
+                return !(rs.sigma * rs.sigma >= 1e-4 * mean * mean) || (A.precise_flat && etop * Vd <= 2.0 * st.S);
             });
         }
     }
@@ -373,7 +422,7 @@ void radius_kernel(const RowArgs A, const int H, const int wide, uint8_t* __rest
     }
 }
 
-template <typename T, int THREADS, bool UNIT, bool ARGMAX>
+template <typename T, int THREADS, int NVEC, bool UNIT, bool ARGMAX, bool WIDE>
 hipError_t launch_radius_cfg(const RowArgs& a, int heads, uint8_t* votes, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     constexpr int kPerUnit = 1024 / THREADS;                       // workgroups a compute unit holds
@@ -388,10 +437,10 @@ hipError_t launch_radius_cfg(const RowArgs& a, int heads, uint8_t* votes, hipStr
     const bool by_row = heads > 1 && (THREADS < 512 ? 2 * turns_by_row <= turns : 10 * turns_by_row <= 9 * turns);
     if (by_row && !votes) heads = 1;
     if (by_row && votes) {
-        const hipError_t e = launch_radius_cfg<T, THREADS, UNIT, ARGMAX>(a, 1, nullptr, stream, ev_start, ev_stop);
+        const hipError_t e = launch_radius_cfg<T, THREADS, NVEC, UNIT, ARGMAX, WIDE>(a, 1, nullptr, stream, ev_start, ev_stop);
         return e != hipSuccess ? e : launch_vote(a.flags, heads, positions, votes, stream);
     }
-    constexpr unsigned lds = kRadVecs * 16u * THREADS;             // 8 to 128 KiB
+    constexpr unsigned lds = NVEC * 16u * THREADS;                 // 4 to 128 KiB
     if (lds > 32u * 1024u) {
         // with the static arrays above the default limit: raised once per device and instance
         static std::mutex guard;
@@ -400,7 +449,7 @@ hipError_t launch_radius_cfg(const RowArgs& a, int heads, uint8_t* votes, hipStr
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
         std::lock_guard<std::mutex> lock(guard);
         if (!raised[dev]) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&radius_kernel<T, THREADS, UNIT, ARGMAX>),
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&radius_kernel<T, THREADS, NVEC, UNIT, ARGMAX, WIDE>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
             raised[dev] = true;
@@ -409,40 +458,52 @@ hipError_t launch_radius_cfg(const RowArgs& a, int heads, uint8_t* votes, hipStr
     const int64_t per_wg = radius_rows<THREADS>() / heads;         // positions (>= 2: heads <= 8)
     const int64_t g = whole_rounds(a.N / heads, per_wg, resident);
     const dim3 grid((unsigned)g), block(THREADS);
-    const int wide = wide_radius(a) ? 1 : 0;
     if (ev_start && ev_stop)
-        hipExtLaunchKernelGGL((radius_kernel<T, THREADS, UNIT, ARGMAX>), grid, block, lds, stream, ev_start, ev_stop, 0, a, heads,
-                              wide, votes);
+        hipExtLaunchKernelGGL((radius_kernel<T, THREADS, NVEC, UNIT, ARGMAX, WIDE>), grid, block, lds, stream, ev_start, ev_stop, 0, a, heads,
+                              votes);
     else
-        hipLaunchKernelGGL((radius_kernel<T, THREADS, UNIT, ARGMAX>), grid, block, lds, stream, a, heads, wide, votes);
+        hipLaunchKernelGGL((radius_kernel<T, THREADS, NVEC, UNIT, ARGMAX, WIDE>), grid, block, lds, stream, a, heads, votes);
     return hipGetLastError();
 }
-template <typename T, int THREADS>
+template <typename T, int THREADS, int NVEC, bool WIDE>
 hipError_t launch_radius_tile(const RowArgs& a, int heads, uint8_t* votes, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     const bool argmax = a.ids == nullptr && (a.p_lo || a.p_mid || a.p_hi);
-    if (a.kappa == 1.0) return argmax ? launch_radius_cfg<T, THREADS, true, true>(a, heads, votes, stream, ev_start, ev_stop)
-                                      : launch_radius_cfg<T, THREADS, true, false>(a, heads, votes, stream, ev_start, ev_stop);
-    return argmax ? launch_radius_cfg<T, THREADS, false, true>(a, heads, votes, stream, ev_start, ev_stop)
-                  : launch_radius_cfg<T, THREADS, false, false>(a, heads, votes, stream, ev_start, ev_stop);
+    if (a.kappa == 1.0) return argmax ? launch_radius_cfg<T, THREADS, NVEC, true, true, WIDE>(a, heads, votes, stream, ev_start, ev_stop)
+                                      : launch_radius_cfg<T, THREADS, NVEC, true, false, WIDE>(a, heads, votes, stream, ev_start, ev_stop);
+    return argmax ? launch_radius_cfg<T, THREADS, NVEC, false, true, WIDE>(a, heads, votes, stream, ev_start, ev_stop)
+                  : launch_radius_cfg<T, THREADS, NVEC, false, false, WIDE>(a, heads, votes, stream, ev_start, ev_stop);
 }
-template <typename T>
-hipError_t launch_radius_typed(const RowArgs& a, int heads, uint8_t* votes, hipStream_t stream, hipEvent_t ev_start,
-                               hipEvent_t ev_stop)
+template <typename T, int NVEC, bool WIDE>
+hipError_t launch_radius_lanes(const RowArgs& a, int heads, uint8_t* votes, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
-    // As many lanes as the row takes at kRadVecs vectors each -- or, where there is a row per compute unit at most (two, if that
+    // As many lanes as the row takes at NVEC vectors each -- or, where there is a row per compute unit at most (two, if that
     // leaves a lane two vectors), at one vector each, up to 256 lanes: then a call waits for one row's chain of instructions, and
     // fewer tokens per lane make it shorter.  (Without / with, 8 rows of 4096 tokens bf16 12.1 / 9.3 us, fp32 10.0 / 9.1; 300
     // rows 12.9 / 11.9 and 12.0 / 11.1, of 1024 tokens fp32 9.8 / 9.8, bf16 10.0 / 10.4; 1000 rows of 4096 bf16 13.5 / 16.6.  512
     // lanes, 8 rows of 4096 bf16: 10.2.)
     const int vecs = (a.V + Elt<T>::kPerVec - 1) / Elt<T>::kPerVec;
-    const int vecs_per_lane = a.N <= (vecs >= 512 ? 2 : 1) * compute_units() ? 1 : kRadVecs;
-    if (vecs <= 64 * vecs_per_lane) return launch_radius_tile<T, 64>(a, heads, votes, stream, ev_start, ev_stop);
-    if (vecs <= 128 * vecs_per_lane) return launch_radius_tile<T, 128>(a, heads, votes, stream, ev_start, ev_stop);
-    if (vecs <= 256 * kRadVecs) return launch_radius_tile<T, 256>(a, heads, votes, stream, ev_start, ev_stop);
-    if (vecs <= 512 * kRadVecs) return launch_radius_tile<T, 512>(a, heads, votes, stream, ev_start, ev_stop);
-    if (vecs <= 1024 * kRadVecs) return launch_radius_tile<T, 1024>(a, heads, votes, stream, ev_start, ev_stop);
+    const int vecs_per_lane = a.N <= (vecs >= 512 ? 2 : 1) * compute_units() ? 1 : NVEC;
+    if (vecs <= 64 * vecs_per_lane) return launch_radius_tile<T, 64, NVEC, WIDE>(a, heads, votes, stream, ev_start, ev_stop);
+    if (vecs <= 128 * vecs_per_lane) return launch_radius_tile<T, 128, NVEC, WIDE>(a, heads, votes, stream, ev_start, ev_stop);
+    if (vecs <= 256 * NVEC) return launch_radius_tile<T, 256, NVEC, WIDE>(a, heads, votes, stream, ev_start, ev_stop);
+    if (vecs <= 512 * NVEC) return launch_radius_tile<T, 512, NVEC, WIDE>(a, heads, votes, stream, ev_start, ev_stop);
+    if (vecs <= 1024 * NVEC) return launch_radius_tile<T, 1024, NVEC, WIDE>(a, heads, votes, stream, ev_start, ev_stop);
     return hipErrorInvalidValue;
+}
+template <typename T>
+hipError_t launch_radius_typed(const RowArgs& a, int heads, uint8_t* votes, hipStream_t stream, hipEvent_t ev_start,
+                               hipEvent_t ev_stop)
+{
+    if (!wide_radius(a)) return launch_radius_lanes<T, kRadVecs, false>(a, heads, votes, stream, ev_start, ev_stop);
+    if constexpr (sizeof(T) == 2) {
+        if (a.V <= 1024 * kRadVecsWide16 * Elt<T>::kPerVec)
+            return launch_radius_lanes<T, kRadVecsWide16, true>(a, heads, votes, stream, ev_start, ev_stop);
+        if (a.V > max_vocab(1)) return hipErrorInvalidValue;
+        return launch_radius_tile<T, 1024, kRadVecs, true>(a, heads, votes, stream, ev_start, ev_stop);
+    } else {
+        return launch_radius_lanes<T, kRadVecs, true>(a, heads, votes, stream, ev_start, ev_stop);
+    }
 }
 
 }  // namespace

@@ -677,6 +677,44 @@ def test_top_token_of_a_near_tie(ciar, V, dtype, kw):
             assert torch.equal(x, y), (i, j)
 
 
+RADIUS_WIDE = [  # V, stride, N, dtype, radius_max: the instances with complement sums, at the edges of their tiles
+    (65, 68, 300, torch.float32, 10.0), (1024, 1024, 2000, torch.float32, 10.0), (4097, 4100, 1100, torch.float32, 10.0),
+    (7342, 7344, 300, torch.float32, 10.0), (32768, 32768, 70, torch.float32, 16.0), (520, 520, 60, torch.bfloat16, 10.0),
+    (2049, 2056, 2100, torch.bfloat16, 10.0), (7342, 7344, 600, torch.bfloat16, 10.0), (16385, 16392, 300, torch.bfloat16, 16.0),
+    (32768, 32768, 270, torch.bfloat16, 16.0), (32769, 32776, 270, torch.bfloat16, 16.0), (65536, 65536, 40, torch.bfloat16, 16.0),
+]
+
+
+@pytest.mark.parametrize("V,stride,N,dtype,rmax", RADIUS_WIDE)
+@pytest.mark.parametrize("scale", [1.0, 0.9])
+def test_radius_kernel_wide_rows(ciar, oracle, V, stride, N, dtype, rmax, scale):
+    """The quantifier with a radius tensor on rows whose widths crowd against 1 (sums of the complements), next to rows of which
+    one token or one wave's worth has a narrow interval (sums of the widths), nearly one-hot rows and rows whose complements
+    agree to better than a hundredth (fp64).  Tolerances: those of the oracle comparison (tests/parity.py)."""
+    g = torch.Generator(device="cuda").manual_seed(17 + V)
+    c = torch.randn(N, stride, generator=g, device="cuda") * 0.5
+    raw = (math.log(V) + 3.0) / scale + 0.5 * torch.randn(N, stride, generator=g, device="cuda")
+    raw[1::6, V - 1] = -5.0
+    raw[2::6, : max(1, V // 5)] = -2.0
+    c[3::6, V // 2] += 25.0
+    raw[4::12], c[4::12] = (math.log(V) + 2.0) / scale, c[4::12] * 0.002
+    c[5::12, V // 4:] = float("-inf")
+    if stride > V:
+        c[:, V:] = raw[:, V:] = 1e30
+    c, raw = c.to(dtype), raw.to(dtype)
+    ids = torch.randint(0, V, (N,), generator=g, device="cuda").to(torch.int32)
+    ids[3::6] = V // 2
+    say(f"[radius wide] V={V} N={N} {dtype} rmax={rmax} scale={scale}")
+    kw = dict(radius_scale=scale, radius_max=rmax)
+    for with_ids in (True, False):
+        o = oracle.quantify(c.cpu(), ids.cpu().numpy() if with_ids else None, _oparams(oracle, ciar.Params(**kw)), vocab=V, radius=raw.cpu())
+        tau = float(np.float32(np.median(o["score"])))
+        o["flags"] = (o["score"] > tau).astype(np.uint8)
+        q = ciar.quantify(c, ids if with_ids else None, ciar.Params(tau=tau, **kw), vocab=V, radius=raw)
+        parity.check_floats(q, o)
+        parity.check_flags(q["flags"], o, tau)
+
+
 VOTE_DEALS = [  # H, V, N, dtype: a workgroup per row and the vote behind it (first of a pair) or per position (second)
     (2, 1024, 300, torch.float32), (2, 1024, 2100, torch.float32), (3, 16384, 8, torch.float32), (3, 16384, 2048, torch.float32),
     (8, 4100, 8, torch.bfloat16), (8, 4100, 2048, torch.bfloat16), (2, 33000, 270, torch.bfloat16), (2, 33000, 256, torch.bfloat16),
