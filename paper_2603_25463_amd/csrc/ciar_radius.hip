@@ -16,7 +16,7 @@
 // rows and a third for the vote.
 //
 // A row's scalars are parked in LDS; after the workgroup's last row a lane per row turns them into the outputs.  Rows whose
-// widths (or whose complements) agree to better than a hundredth of their mean and flat rows of calls whose widths are not small
+// widths (or whose complements) agree to better than kCrowded says and flat rows of calls whose widths are not small
 // (needs_flat_pass) are swept again in fp64 before that is written.
 #include "ciar_device.h"
 
@@ -29,6 +29,11 @@ namespace {
 // 16-byte vectors of a row per lane.  (bf16 rows with complement sums: 32 tokens; with 64 those instances spill 136 to 208 bytes,
 // which is left for the rows above 32768 tokens.)
 constexpr int kRadVecs = 8, kRadVecsWide16 = 4;
+// Rows whose Sigma is below three thousandths of the mean width are swept again in fp64.  (What the fp32 rounding of the widths --
+// 1e-7 of each, but alike for like tokens -- leaves in a Sigma at that line: 2e-6 to 7e-6 of it, 256 to 16384 tokens, clamps
+// of 0.5 to 4; 1e-5 to 4e-5 at a third of it.  At a hundredth it would be 5e-7 to 2e-6, but there rows of an untrained head pay
+// for the sweep in calls with a small clamp: 762 x 16384 fp32, radius_max 2, 209 us against 24.5.)
+constexpr double kCrowded = 1e-5;
 template <int THREADS> constexpr int radius_rows() { return THREADS >= 512 ? 128 : THREADS / 4; }   // most rows of a workgroup
 
 template <bool WIDE> struct RadiusRow { double S, q[WIDE ? 7 : 5]; float n, mc, raw_top, big; };   // see RowStats, finish_row
@@ -400,7 +405,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
             const double etop = (double)exp2_ref(st.mc, st.n == -INFINITY ? 0.f : st.n);
             pk_fp64[t] = (uint8_t)finish(t, st, [&](const RowScore& rs) {
                 const double Vd = (double)V, mean = (WIDE && st.mode == kSumsComplement ? Vd - rs.omega : rs.omega) / Vd;
-                return !(rs.sigma * rs.sigma >= 1e-4 * mean * mean) || (A.precise_flat && etop * Vd <= 2.0 * st.S);
+                return !(rs.sigma * rs.sigma >= kCrowded * mean * mean) || (A.precise_flat && etop * Vd <= 2.0 * st.S);
             });
         }
     }

@@ -677,6 +677,21 @@ def test_top_token_of_a_near_tie(ciar, V, dtype, kw):
             assert torch.equal(x, y), (i, j)
 
 
+@pytest.mark.parametrize("V", [256, 4096, 16384])
+@pytest.mark.parametrize("noise", [0.0, 3e-4, 3e-3, 6e-3, 3e-2])
+def test_radius_kernel_crowded_rows(ciar, oracle, V, noise):
+    """Rows of an untrained head in calls with a small clamp: widths that agree to a small part of their mean, on both sides of
+    the line below which the quantifier with a radius tensor takes a row's sums again in fp64.  Tolerances: tests/parity.py."""
+    N = 300
+    g = torch.Generator(device="cuda").manual_seed(18 + V)
+    c = noise * torch.randn(N, V, generator=g, device="cuda")
+    raw = noise * torch.randn(N, V, generator=g, device="cuda")
+    say(f"[radius crowded] V={V} noise={noise}")
+    for rmax in (0.5, 2.0):
+        P = ciar.Params(radius_scale=1.0, radius_max=rmax)
+        parity.check_floats(ciar.quantify(c, None, P, radius=raw), oracle.quantify(c.cpu(), None, _oparams(oracle, P), radius=raw.cpu()))
+
+
 RADIUS_WIDE = [  # V, stride, N, dtype, radius_max: the instances with complement sums, at the edges of their tiles
     (65, 68, 300, torch.float32, 10.0), (1024, 1024, 2000, torch.float32, 10.0), (4097, 4100, 1100, torch.float32, 10.0),
     (7342, 7344, 300, torch.float32, 10.0), (32768, 32768, 70, torch.float32, 16.0), (520, 520, 60, torch.bfloat16, 10.0),
