@@ -400,7 +400,12 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
     };
     {
         const int t = my_tid();
-        if (t < count) {
+        // (the statistics alone, for the Ensemble's second sweep, which looks after its own flat rows)
+        const bool outputs = A.p_lo || A.p_mid || A.p_hi || A.omega || A.sigma || A.score || A.flags;
+        if (t < count && !outputs) {
+            pk_fp64[t] = 0;
+            A.stats[row_of(t)] = stats_of(t);
+        } else if (t < count) {
             const RowStats st = stats_of(t);
             const double etop = (double)exp2_ref(st.mc, st.n == -INFINITY ? 0.f : st.n);
             pk_fp64[t] = (uint8_t)finish(t, st, [&](const RowScore& rs) {
