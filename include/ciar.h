@@ -271,7 +271,7 @@ int ciar_finish_rows(const void* draft_logits, const void* radius, const void* t
  * Any output may be NULL; at least one must be given.  1 <= heads <= 8.  workspace: at least
  * ciar_multihead_workspace_bytes(N, heads, params) bytes, rules as above.  Every head's rows are
  * streamed once; Ensemble sweeps a position's rows a second time where a cap is active or the averaged widths hardly
- * differ, and every row twice for V <= 64 and V > 16384.
+ * differ, and every row twice for V <= 64, for V > 16384 and for few positions of many heads.
  */
 enum { CIAR_VOTING = 0, CIAR_ENSEMBLE = 1 };
 

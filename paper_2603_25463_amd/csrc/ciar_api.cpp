@@ -659,7 +659,7 @@ int ciar_quantify_multihead(const void* draft_heads, const void* radius_heads, i
         a.ids = draft_ids;
         a.p_lo = p_lo; a.p_mid = p_mid; a.p_hi = p_hi; a.omega = omega; a.sigma = sigma; a.score = score; a.flags = flags;
         const bool fused = ciar::ensemble_fused_fits(a, heads);
-        if (fused || ciar::ensemble_sweep_fits(a)) {
+        if (fused || ciar::ensemble_sweep_fits(a, heads)) {
             const hipError_t e = fused ? ciar::launch_ensemble_fused(params->dtype, a, heads, head_stride, stream)
                                        : ciar::launch_ensemble_sweep(params->dtype, a, heads, head_stride, stream);
             if (e != hipSuccess) return hip_fail(e, "ensemble kernel launch");

@@ -770,7 +770,7 @@ void ensemble_sweep_kernel(const RowArgs A, const int H, const int64_t head_stri
     __shared__ float pk_n[ROWS][kMaxHeads], pk_mc[ROWS][kMaxHeads];
     __shared__ int pk_id[ARGMAX ? ROWS : 1];
     __shared__ int pk_state[ROWS];                           // see kDone ...
-    constexpr int kDone = 0, kCaps = 1, kFp64 = 2;                 // finished / an active cap / for ensemble_marked_kernel
+    constexpr int kDone = 0, kCaps = 1, kFp64 = 2;                 // finished / an active cap / to be swept in fp64
 
     // (the lane's index is asked for anew wherever it is used, through an empty asm: no LDS address formed from it is
     // held in registers, or spilled, through the loop -- and a reload would wait for the rows in flight)
@@ -1222,7 +1222,16 @@ hipError_t launch_ensemble(int dtype, const RowArgs& args, int heads, int64_t he
 }
 
 // 32 tokens of a row per lane of at most 512: V <= 16384.  (The fp64 token path of tiny vocabularies is ensemble_kernel's.)
-bool ensemble_sweep_fits(const RowArgs& args) { return args.V > kTinyVocab && args.V <= 512 * kSweepTokens; }
+// Except for many heads of few, short rows: a position's heads take their turn in its workgroup, ~3 us each however short the
+// row, and the two-sweep route has every head's row in a workgroup of its own first.  (8 positions, one sweep / two, scalar
+// radius fp32: 8 heads of 1024 tokens 25.9 / 15.8 us, of 4096 23.9 / 21.7, of 8192 23.9 / 30.3; 5 heads of 1024 17.6 / 13.3, of
+// 2048 16.1 / 13.9, of 4096 16.4 / 17.4.  Radius tensors: 34.4 / 25.5, 35.3 / 33.5; 23.3 / 20.8, 23.6 / 22.2, 24.0 / 26.4.  256
+// positions of 4 heads of 1024 tokens 15.3 / 14.3 and 27.1 / 20.5, of 2048 13.9 / 15.1; 1000 of 5 heads of 1024 26.5 / 27.3.)
+bool ensemble_sweep_fits(const RowArgs& args, int heads)
+{
+    if (args.V <= kTinyVocab || args.V > 512 * kSweepTokens) return false;
+    return !(args.N <= compute_units() && 1024 * (heads - 3) >= args.V);
+}
 
 namespace {
 template <typename T, int THREADS, bool RAD, bool UNIT, bool ARGMAX>
@@ -1276,7 +1285,7 @@ hipError_t launch_sweep_typed(const RowArgs& a, int heads, int64_t head_stride, 
 hipError_t launch_ensemble_sweep(int dtype, const RowArgs& args, int heads, int64_t head_stride, hipStream_t stream)
 {
     if (args.N <= 0) return hipSuccess;
-    if (!ensemble_sweep_fits(args)) return hipErrorInvalidValue;
+    if (!ensemble_sweep_fits(args, heads)) return hipErrorInvalidValue;
     return dtype == 0 ? launch_sweep_typed<float>(args, heads, head_stride, stream)
                       : launch_sweep_typed<bf16_t>(args, heads, head_stride, stream);
 }
@@ -1284,11 +1293,13 @@ hipError_t launch_ensemble_sweep(int dtype, const RowArgs& args, int heads, int6
 // Where its four waves per SIMD beat ensemble_sweep_kernel's two: a lane's share of a row filled with 17 to 32 tokens
 // (2048 positions x 16384 tokens, bf16: 58.8 against 68.2 us with two heads, 83.9 against 96.9 with three; fp32: 73.4 / 78.5,
 // 98.1 / 100.2; with 8192 tokens x 4096 positions the other way round: bf16 80.2 against 72.6, 117 against 103; fp32 87.8 / 75.5,
-// 127 / 107).
+// 127 / 107) -- and where there is a position per compute unit at most, whose heads it takes side by side (8 positions of 3
+// heads of 1024 tokens 9.1 against 12.0, bf16 10.3 / 11.7, of 4096 9.7 / 11.3; 256 of 2 heads of 4096 tokens 7.5 / 9.1; 600 of 3 heads
+// of 4096 20.0 / 17.0).
 bool ensemble_fused_fits(const RowArgs& args, int heads)
 {
-    return !args.radius && !wide_radius(args) && !needs_flat_pass(args) && heads >= 1 && heads <= kFusedHeads &&
-           args.V > 16 * kFusedThreads && args.V <= 32 * kFusedThreads;
+    return !args.radius && !wide_radius(args) && !needs_flat_pass(args) && heads >= 1 && heads <= kFusedHeads && args.V > kTinyVocab &&
+           args.V <= 32 * kFusedThreads && (args.V > 16 * kFusedThreads || args.N <= compute_units());
 }
 
 namespace {
@@ -1335,8 +1346,15 @@ hipError_t launch_ensemble_fused(int dtype, const RowArgs& args, int heads, int6
 {
     if (args.N <= 0) return hipSuccess;
     if (!ensemble_fused_fits(args, heads)) return hipErrorInvalidValue;
-    return dtype == 0 ? launch_ensemble_fused_cfg<float, 8>(args, heads, head_stride, stream)
-                      : launch_ensemble_fused_cfg<bf16_t, 4>(args, heads, head_stride, stream);
+    const int epv = dtype == 0 ? 4 : 8, vecs = (args.V + epv - 1) / epv;
+    const int per_lane = (vecs + kFusedThreads - 1) / kFusedThreads;
+    if (dtype == 0) {
+        if (per_lane <= 2) return launch_ensemble_fused_cfg<float, 2>(args, heads, head_stride, stream);
+        if (per_lane <= 4) return launch_ensemble_fused_cfg<float, 4>(args, heads, head_stride, stream);
+        return launch_ensemble_fused_cfg<float, 8>(args, heads, head_stride, stream);
+    }
+    if (per_lane <= 2) return launch_ensemble_fused_cfg<bf16_t, 2>(args, heads, head_stride, stream);
+    return launch_ensemble_fused_cfg<bf16_t, 4>(args, heads, head_stride, stream);
 }
 
 hipError_t launch_vote(const uint8_t* head_flags, int heads, int64_t N, uint8_t* flags, hipStream_t stream)

@@ -172,11 +172,12 @@ hipError_t launch_radius_quantify(int dtype, const RowArgs& args, int heads, uin
 int max_heads();
 // Ensemble: token-wise mean of the heads' curves -> the [N] outputs in args.
 hipError_t launch_ensemble(int dtype, const RowArgs& args, int heads, int64_t head_stride, hipStream_t stream);
-// Ensemble in one sweep (64 < V <= 16384; no streaming pass before it, no RowStats): every row is read once.
-bool ensemble_sweep_fits(const RowArgs& args);
+// Ensemble in one sweep (64 < V <= 16384 and not many heads of few short rows; no streaming pass before it, no RowStats):
+// every row is read once.
+bool ensemble_sweep_fits(const RowArgs& args, int heads);
 hipError_t launch_ensemble_sweep(int dtype, const RowArgs& args, int heads, int64_t head_stride, hipStream_t stream);
 // The same with the rows of all heads of a position in one workgroup's registers (and LDS) at once: up to three heads, scalar
-// radius, 8192 < V <= 16384.
+// radius, few positions or 8192 < V <= 16384.
 bool ensemble_fused_fits(const RowArgs& args, int heads);
 hipError_t launch_ensemble_fused(int dtype, const RowArgs& args, int heads, int64_t head_stride, hipStream_t stream);
 // Voting: flags[row] = strict majority of head_flags[h * N + row].

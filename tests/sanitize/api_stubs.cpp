@@ -101,7 +101,7 @@ hipError_t launch_ensemble(int, const RowArgs& a, int heads, int64_t, hipStream_
     return hipSuccess;
 }
 // (the one-sweep route is taken for the vocabularies it is taken for in the library)
-bool ensemble_sweep_fits(const RowArgs& a) { return a.V > 64 && a.V <= 16384; }
+bool ensemble_sweep_fits(const RowArgs& a, int) { return a.V > 64 && a.V <= 16384; }
 hipError_t launch_ensemble_sweep(int, const RowArgs& a, int, int64_t, hipStream_t)
 {
     ++stubs::launches; stubs::last_args = a;

@@ -535,6 +535,11 @@ SWEEP_EDGES = [  # H, V, stride, N, dtype: both sides of every tile's end, sever
     (4, 65, 68, 2600, torch.float32), (2, 2048, 2048, 2100, torch.float32), (5, 2049, 2052, 1100, torch.float32),
     (3, 4096, 4096, 1100, torch.bfloat16), (4, 4097, 4104, 530, torch.bfloat16), (2, 8192, 8192, 600, torch.float32),
     (8, 8193, 8196, 40, torch.float32), (2, 16384, 16384, 300, torch.bfloat16), (4, 16384, 16384, 70, torch.float32),
+    # few positions: side by side in registers (up to three heads, scalar radius), two sweeps (many heads of short rows), one sweep
+    (3, 65, 68, 40, torch.float32), (2, 4096, 4096, 256, torch.float32), (3, 4097, 4100, 257, torch.float32),
+    (3, 8192, 8192, 40, torch.bfloat16), (1, 8193, 8200, 30, torch.bfloat16), (4, 1024, 1024, 256, torch.float32),
+    (4, 1025, 1028, 60, torch.float32), (8, 5120, 5120, 40, torch.bfloat16), (8, 5121, 5128, 40, torch.bfloat16),
+    (3, 16385, 16388, 60, torch.float32), (2, 32776, 32776, 60, torch.bfloat16),
 ]
 
 
