@@ -658,6 +658,11 @@ int ciar_quantify_multihead(const void* draft_heads, const void* radius_heads, i
         a.radius = radius_heads;
         a.ids = draft_ids;
         a.p_lo = p_lo; a.p_mid = p_mid; a.p_hi = p_hi; a.omega = omega; a.sigma = sigma; a.score = score; a.flags = flags;
+        // (more rows than the two-sweep route numbers are refused here as well, except where one sweep has always taken them: up
+        // to three heads with an ordinary scalar radius)
+        const bool any_rows = !radius_heads && heads <= 3 && !ciar::wide_radius(a) && !ciar::needs_flat_pass(a);
+        if (!any_rows && (int64_t)heads * N > 0x7fffffffLL)
+            return fail(CIAR_EUNSUPPORTED, "heads * N exceeds 2^31 - 1 rows per call");
         const bool fused = ciar::ensemble_fused_fits(a, heads);
         if (fused || ciar::ensemble_sweep_fits(a, heads)) {
             const hipError_t e = fused ? ciar::launch_ensemble_fused(params->dtype, a, heads, head_stride, stream)

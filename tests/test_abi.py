@@ -274,3 +274,15 @@ def test_interhead_argument_errors_and_workspace(L):
     # the timed form needs both events
     assert L.ciar_interhead_logits_timed(FAKE, FAKE + 4096, None, 128, 4, a, FAKE + 8192, FAKE + 12288, None, None,
                                          None) == EINVAL
+
+
+@pytest.mark.parametrize("strategy,radius,heads,vocab", [(0, None, 2, 1024), (1, FAKE, 2, 1024), (1, FAKE, 8, 16384), (1, None, 4, 1024),
+                                                        (1, None, 2, 20000)])
+def test_multihead_refuses_more_rows_than_it_numbers(L, strategy, radius, heads, vocab):
+    """heads * N above 2^31 - 1: refused by whichever route the call would take."""
+    from paper_2603_25463_amd.binding import last_error
+    N = (1 << 31) // heads
+    p = _params(L, vocab=vocab, row_stride=vocab)
+    rc = L.ciar_quantify_multihead(FAKE, radius, heads, N * vocab, None, N, ctypes.byref(p), strategy, FAKE, None, None, None, None, None,
+                                   None, None, FAKE, 1 << 62, None)
+    assert rc == -4 and "2^31" in last_error()
