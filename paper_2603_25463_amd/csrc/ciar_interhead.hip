@@ -4,7 +4,7 @@
 // bf16 operands, fp32 accumulation on the matrix cores (v_mfma_f32_32x32x16_bf16), fp32 logits out: columns
 // [0, V) go to the centre rows, [V, 2V) to the raw-radius rows, which the tensor-radius quantifier reads next.
 #include <mutex>
-#include "ciar_internal.h"
+#include "ciar_device.h"
 #include <hip/hip_ext.h>
 
 namespace ciar {
@@ -32,7 +32,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int BK = kHeadTileDepth;
 constexpr int ROWB = BK * 2;            // bytes of a tile row in LDS
 static_assert(BK == 64, "a tile row is eight 16-byte chunks");
-using gbytes = const __attribute__((address_space(1))) char*;
 using gptr = const __attribute__((address_space(1))) void*;
 using lptr = __attribute__((address_space(3))) void*;
 
@@ -590,9 +589,10 @@ hipError_t launch_few(const HeadArgs& a, hipStream_t stream, hipEvent_t ev_start
 template <int HB>
 hipError_t launch_few_split(const HeadArgs& a, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
-    // 2 V / 32 column blocks, four waves per compute unit wanted: the depth is divided where there are fewer
-    if (a.V >= 12288) return launch_few<HB, 1>(a, stream, ev_start, ev_stop);
-    if (a.V >= 6144) return launch_few<HB, 2>(a, stream, ev_start, ev_stop);
+    // 2 V / 32 column blocks, a wave each: the depth is divided where they leave a compute unit less than three waves
+    const int blocks = 2 * a.V / 32, wanted = 3 * compute_units();
+    if (blocks >= wanted) return launch_few<HB, 1>(a, stream, ev_start, ev_stop);
+    if (2 * blocks >= wanted) return launch_few<HB, 2>(a, stream, ev_start, ev_stop);
     return launch_few<HB, 4>(a, stream, ev_start, ev_stop);
 }
 
@@ -609,9 +609,7 @@ hipError_t launch_interhead(const HeadArgs& args, hipStream_t stream, hipEvent_t
     // 256 x 256 tiles read the least per matrix instruction; where they are fewer than the compute units, two 256 x 128 workgroups
     // per compute unit do better (785 x 2240 x 2 * 2560: 51 -> 34.5 us, 256 x 1280 x 2 * 16384: 49 -> 41.6 us; with one tile per
     // compute unit, 512 x 1280 x 2 * 16384, 66 against 59 us, with four 236 against 200 us)
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        cus = 256;
+    const int cus = compute_units();
     const int64_t tiles = (args.N + 255) / 256 * (2 * (int64_t)args.V / 256);
     if (args.V % 256 == 0 && tiles >= cus) return launch_tile<4, 4>(args, stream, ev_start, ev_stop);
     return launch_pair(args, stream, ev_start, ev_stop);
