@@ -17,7 +17,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // Workgroup tile (64 MB) x (64 NB) x 64 with four waves in a 2 x 2 grid, each wave (32 MB) x (32 NB) = MB x NB MFMA
 // blocks of 32 x 32.  MB = NB = 4 (256 x 256, a wave 128 x 128) is the shape for real vocabularies: a wave then
 // reads 8 operand vectors from LDS for 16 matrix instructions, half the LDS traffic per instruction of the
-// 128 x 128 tile (MB = NB = 2), which serves 33 to 128 rows.
+// 128 x 128 tile (MB = NB = 2), which serves 33 to 128 rows, and up to 256 of vocabularies that are an odd multiple of 128.
 // Measured (2048 rows, V = 16384): D = 1280 202 -> 192 us, D = 4096 510 -> 463 us when the requests moved between the matrix
 // instructions of the fourth slice and the epilogue lost its barriers.
 //
@@ -281,8 +281,7 @@ hipError_t launch_tile(const HeadArgs& a, hipStream_t stream, hipEvent_t ev_star
 
 // 256 x 128 workgroup tiles, 32 deep, four waves in a 2 x 2 grid of 128 x 64 (4 x 2 matrix blocks, 128 accumulator registers): two
 // workgroups share a compute unit, so that one multiplies while the other waits at a barrier, starts a tile or writes one
-// out.  For batches whose 256 x 256 tiles would leave compute units without work, and vocabularies that are not a multiple of
-// 256; a large batch does better with the larger tile, which brings a third less into LDS per matrix instruction.
+// out.  For batches whose tiles have a compute unit each, and vocabularies that are not a multiple of 256; a large batch does better with the larger tile, which brings a third less into LDS per matrix instruction.
 // Three stages of 24 KiB: a slice is requested two slices ahead and awaited by count (the one behind it may still be under
 // way).  A tile row is four 16-byte chunks, chunk q of row r at position q ^ ((r / 4) % 4): four rows fill the 64 banks, and
 // any 16 consecutive rows at the same k cover every bank once.
@@ -606,12 +605,16 @@ hipError_t launch_interhead(const HeadArgs& args, hipStream_t stream, hipEvent_t
     if (args.N <= 16) return launch_few_split<2>(args, stream, ev_start, ev_stop);
     if (args.N <= 32) return launch_few_split<4>(args, stream, ev_start, ev_stop);
     if (args.N <= 128) return launch_tile<2, 2>(args, stream, ev_start, ev_stop);
-    // 256 x 256 tiles read the least per matrix instruction; where they are fewer than the compute units, two 256 x 128 workgroups
-    // per compute unit do better (785 x 2240 x 2 * 2560: 51 -> 34.5 us, 256 x 1280 x 2 * 16384: 49 -> 41.6 us; with one tile per
-    // compute unit, 512 x 1280 x 2 * 16384, 66 against 59 us, with four 236 against 200 us)
-    const int cus = compute_units();
-    const int64_t tiles = (args.N + 255) / 256 * (2 * (int64_t)args.V / 256);
-    if (args.V % 256 == 0 && tiles >= cus) return launch_tile<4, 4>(args, stream, ev_start, ev_stop);
+    // 256 x 256 tiles read the least per matrix instruction.  Where they are so few that 256 x 128 ones have a compute unit each,
+    // those are as quick and twice as many (785 x 2240 x 2 * 2560: 51 -> 34.5 us, 512 x 1280 x 2 * 8192 51 -> 44, x 4096 98 -> 86);
+    // two of them to a compute unit are slower than one large tile (512 rows, x 1280 x 2 * 10240 53.2 against 58.4, x 4096 101 /
+    // 127, x 4096 x 2 * 14336 125 / 148).  An odd multiple of 128 has no large tiles: there, up to 256 rows, one round of
+    // 128 x 128 (256 rows, x 4096 x 2 * 7296 57.4 against 66.7, x 4096 x 2 * 2176 50.5 / 60.9, x 1280 25.8 / 28.6, x 512 23.9 / 23.6),
+    // or of half the compute units with it where the second row of tiles is half empty (160 rows, x 1280 x 2 * 7296 32.4 / 31.9,
+    // x 3072 53.6 / 50.5, x 4096 x 2 * 2176 50.4 / 55.3).
+    const int64_t cus = compute_units(), tiles = (args.N + 255) / 256 * (2 * (int64_t)args.V / 256);
+    if (args.V % 256 == 0 && 2 * tiles > cus) return launch_tile<4, 4>(args, stream, ev_start, ev_stop);
+    if (args.V % 256 != 0 && args.N <= 256 && 4 * (int64_t)args.V / 128 <= (args.N >= 192 ? cus : cus / 2)) return launch_tile<2, 2>(args, stream, ev_start, ev_stop);
     return launch_pair(args, stream, ev_start, ev_stop);
 }
 

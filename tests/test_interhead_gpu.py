@@ -204,12 +204,14 @@ def test_interhead_few_rows(ciar, oracle, N, D, V):
         assert bool((c[:, V:] == 7.5).all()) and bool((r[:, V:] == 7.5).all())
 
 
-@pytest.mark.parametrize("N,V", [(129, 128), (129, 256), (255, 384), (256, 640), (257, 1152), (511, 256), (770, 896)])
+@pytest.mark.parametrize("N,V", [(129, 128), (129, 256), (255, 384), (256, 640), (257, 1152), (511, 256), (770, 896),
+                                 (200, 8192), (256, 8320), (300, 8448)])
 @pytest.mark.parametrize("D", [64, 128, 320])
 def test_interhead_two_workgroups_per_unit(ciar, oracle, N, V, D):
-    """The kernel for batches that leave compute units without a 256 x 256 tile, or vocabularies that are no multiple of 256:
-    ragged last rows, tiles that straddle the centre and the radius half's end, fewer depth slices than stages; integer
-    operands, so any wrong element shows exactly."""
+    """The kernel for batches that leave compute units without a 256 x 256 tile, and its neighbours: vocabularies that are an odd
+    multiple of 128 (no 256-column tile ends where the centre half does), up to 256 rows of them in 128 x 128 tiles, batches with
+    just enough large tiles; ragged last rows, fewer depth slices than stages; integer operands, so any wrong element shows
+    exactly."""
     g = torch.Generator().manual_seed(100 * N + D + V)
     h = torch.randint(-4, 5, (N, D), generator=g).bfloat16()
     w = torch.randint(-4, 5, (2 * V, D), generator=g).bfloat16()
