@@ -1115,7 +1115,7 @@ void ensemble_sweep_kernel(const RowArgs A, const int H, const int64_t head_stri
                 const int64_t off = (int64_t)h * head_stride + r * A.stride;
                 const double S = pk_S[at][h];
                 const double ed = exp((double)load_logit(static_cast<const T*>(A.draft) + off, i) - (double)pk_n[at][h] * kLn2);
-                const double x = ed / S, omx = fmax(0.0, S - ed) / S;
+                const double inv = recip(S), x = ed * inv, omx = fmax(0.0, S - ed) * inv;
                 double a = A.a, b = A.b;
                 if constexpr (RAD) {
                     const double rr = radius_of((double)load_logit(static_cast<const T*>(A.radius) + off, i), A.kappa, A.rmax);
