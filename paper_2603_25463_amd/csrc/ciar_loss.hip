@@ -74,7 +74,10 @@ constexpr uint32_t kRuledOutBits = 0xf1800000u;                    // (its upper
 // the optimiser holds in vector registers, or spills, through the whole row loop.)
 struct DroRadius { float kappa, rmax, scalar; };                   // scalar = min(kappa, rmax), the radius without a tensor
 
-template <typename T, int NVEC, int THREADS>
+// RAD = 1 / 0: with / without a radius tensor, -1: to be asked.  (Told apart where the three rows do not fit the registers, eight
+// vectors of bf16: one kernel for both spilled 1808 bytes per lane, 1250 x 40000 8992 us with a radius tensor, 1746 without;
+// two spill 616 and 484, 809 and 367 us.)
+template <typename T, int NVEC, int THREADS, int RAD = -1>
 __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadius R, double* fin,
                                                 u32x4 (&cw)[NVEC], u32x4 (&tw)[NVEC], u32x4 (&rw)[NVEC], double* sm_d,
                                                 const int tid)
@@ -83,7 +86,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     constexpr int EPV = E::kPerVec, NW = THREADS / 64;
     const int lane = tid & 63, wave = tid >> 6;
     const int V = A.V;
-    const bool rad = A.radius != nullptr;                          // uniform
+    const bool rad = RAD < 0 ? A.radius != nullptr : RAD == 1;     // uniform
     auto uniform = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
     const float kap = R.kappa, rmax = R.rmax, r0 = R.scalar;
     if (V < NVEC * THREADS * EPV) {                                // uniform: the row does not fill the tile
@@ -488,7 +491,7 @@ __device__ __forceinline__ void dro_finish_row(const RowArgs& A, float* __restri
     terms[6 * N + row] = (float)kl;
 }
 
-template <typename T, int NVEC>
+template <typename T, int NVEC, int RAD = -1>
 __global__ __launch_bounds__(1024) void dro_row_kernel(const RowArgs A, const DroRadius R, float* __restrict__ terms)
 {
     constexpr int THREADS = 1024, NW = 16;
@@ -496,7 +499,7 @@ __global__ __launch_bounds__(1024) void dro_row_kernel(const RowArgs A, const Dr
     const int tid = threadIdx.x;
     const int64_t row = blockIdx.x;
     const int last_vec = (A.V + Elt<T>::kPerVec - 1) / Elt<T>::kPerVec - 1;
-    const bool rad = A.radius != nullptr;                          // uniform
+    const bool rad = RAD < 0 ? A.radius != nullptr : RAD == 1;     // uniform
     const gbytes cb = (gbytes)(static_cast<const T*>(A.draft) + row * A.stride);
     const gbytes tb = (gbytes)(static_cast<const T*>(A.target) + row * A.stride);
     const gbytes rb = (gbytes)(static_cast<const T*>(rad ? A.radius : A.draft) + row * A.stride);
@@ -509,7 +512,7 @@ __global__ __launch_bounds__(1024) void dro_row_kernel(const RowArgs A, const Dr
         if (rad) rw[j] = __builtin_nontemporal_load((gvec)(rb + off));
     }
     __shared__ double sm_fin[kDroTotals];
-    dro_row_compute<T, NVEC, THREADS>(A, R, sm_fin, cw, tw, rw, sm_d, tid);
+    dro_row_compute<T, NVEC, THREADS, RAD>(A, R, sm_fin, cw, tw, rw, sm_d, tid);
     if (tid == 0) dro_finish_row(A, terms, row, sm_fin);           // (the lane that has written the totals)
 }
 
@@ -777,7 +780,9 @@ hipError_t launch_dro(int dtype, const RowArgs& args, float* terms, double lambd
     } else if (vecs <= 1024) CIAR_DRO_LAUNCH(1);
     else if (vecs <= 2048) CIAR_DRO_LAUNCH(2);
     else if (vecs <= 4096) CIAR_DRO_LAUNCH(4);
-    else if (vecs <= 8192) CIAR_DRO_LAUNCH(8);
+    else if (vecs <= 8192 && dtype == 0) hipLaunchKernelGGL((dro_row_kernel<float, 8>), grid, block, 0, stream, args, R, terms);
+    else if (vecs <= 8192 && args.radius) hipLaunchKernelGGL((dro_row_kernel<bf16_t, 8, 1>), grid, block, 0, stream, args, R, terms);
+    else if (vecs <= 8192) hipLaunchKernelGGL((dro_row_kernel<bf16_t, 8, 0>), grid, block, 0, stream, args, R, terms);
     else return hipErrorInvalidValue;
 #undef CIAR_DRO_LAUNCH
     hipError_t e = hipGetLastError();
