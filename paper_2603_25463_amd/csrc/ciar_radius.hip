@@ -102,6 +102,8 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
     __shared__ double sm_S[2][NW], sm_tot[2][NW][NQ];
     __shared__ double sm_red[NW][64];                              // per wave: [the sums of the row before, S_w][eight groups of lanes]
     __shared__ float sm_big[WIDE ? 2 : 1][NW];                     // largest complement
+    // (LDS is what the places on a compute unit are counted by: a slot per wave and parked row instead of this pair costs the
+    // 128-lane instances one of eight, 58333 x 3000 fp32 270 -> 350 us)
     __shared__ int sm_pi[2][ARGMAX ? NW : 1];
     // parked rows
     __shared__ RadiusRow<WIDE> pk[ROWS];
@@ -280,11 +282,6 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         bool complements = false;                                  // uniform over the wave
         float big = INFINITY;                                      // largest complement of this lane
-        if constexpr (WIDE) {
-            const float am1 = radius_am1<UNIT>(load_logit(reinterpret_cast<const T*>(sm_next), tid * EPV), kappa, rmax, am1_max);
-            complements = __builtin_amdgcn_ballot_w64(tid * EPV < V && !(-(am1 + 2.0f) * e[0] * fr.nih > 1.0f)) == 0;
-            if (complements) big = 0.f;
-        }
         constexpr int GROUP = WIDE && sizeof(T) == 2 ? 2 : 4;      // vectors taken at a time
 #pragma unroll
         for (int g = 0; g < NVEC; g += GROUP) {
@@ -303,6 +300,11 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
                     if ((j + 1) * CHUNK > V) E::zero_tail(rb[u], (j * THREADS + tid) * EPV, V);
                     float rv[EPV];
                     E::unpack(rb[u], rv);
+                    if (WIDE && j == 0) {
+                        const float am1 = radius_am1<UNIT>(rv[0], kappa, rmax, am1_max);
+                        complements = __builtin_amdgcn_ballot_w64(tid * EPV < V && !(-(am1 + 2.0f) * e[0] * fr.nih > 1.0f)) == 0;
+                        if (complements) big = 0.f;
+                    }
                     if (WIDE && complements) {
 #pragma unroll
                         for (int k = 0; k < EPV; ++k) {
