@@ -742,8 +742,10 @@ void stream_kernel(const RowArgs A)
                 // (n is the largest of the waves' references.  It is ref_of(mc) as well, but formed from mc it comes later and in a
                 // vector register: one 1024-token row verified 5.45 -> 5.63 us, 36621 of them 109 -> 116, 65104 bf16 rows
                 // quantified and verified with a radius tensor 529 -> 620)
+                // (... except in the fused bf16 instances of 1024 lanes with a scalar radius: 32768 x 65536 1875 us so, 1894 from the
+                // references)
                 const float mc_l = sm_ref[src * 2], n_l = sm_ref[src * 2 + 1];
-                mc = row16_max(mc_l); n = row16_max(n_l);
+                mc = row16_max(mc_l); n = BATCH3 && THREADS == 1024 ? ref_of(mc) : row16_max(n_l);
                 S = row16_sum(lane < NW && n_l != -INFINITY ? sm_S[src] * pow2_of(n_l - n) : 0.0);
             } else {
                 mc = sm_ref[0]; n = sm_ref[1];
