@@ -548,7 +548,7 @@ SWEEP_EDGES = [  # H, V, stride, N, dtype: both sides of every tile's end, sever
                                 dict(tensor=True, radius_scale=0.7, radius_max=3.0)])
 def test_ensemble_sweep_edges(ciar, oracle, H, V, stride, N, dtype, kw):
     """The one-sweep Ensemble kernel at the edges of its tiles, on ordinary rows among those it treats apart: active caps
-    (nearly one-hot rows, radii next to nothing) and, for the fp64 kernel behind it, rows flat in every head and widths
+    (nearly one-hot rows, radii next to nothing) and, for its fp64 sweep, rows flat in every head and widths
     that agree to within a hundredth; with and without drafted ids."""
     kw = dict(kw)
     tensor = kw.pop("tensor", False)
