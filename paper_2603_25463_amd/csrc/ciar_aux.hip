@@ -34,10 +34,10 @@ __global__ __launch_bounds__(256) void dense_kernel(const RowArgs A, float* __re
     if (lane == 0) smem[wave] = (double)m;
     __syncthreads();
     m = fmaxf(fmaxf((float)smem[0], (float)smem[1]), fmaxf((float)smem[2], (float)smem[3]));
-    const float n = ref_of(m);
+    const float n = Elt<T>::ref_of(m);
 
     double acc = 0.0;
-    for (int i = tid; i < V; i += 256) acc += (double)exp2_ref(load_logit(c, i), n);
+    for (int i = tid; i < V; i += 256) acc += (double)Elt<T>::exp2_ref(load_logit(c, i), n);
     const double S = block_sum(acc);
 
     const FuseRow fr = fuse_row(S, A.a, A.b);
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(256) void dense_kernel(const RowArgs A, float* __re
     const RadiusMode rm = radius_mode(A);
     // gl, gw of one token: p^l = Bc gl, p^u - p^l = Wc gw (tensor-radius mode: Bc = Wc = 1 / S)
     auto token = [&](int i, float& e, float& gl, float& gw) {
-        e = exp2_ref(load_logit(c, i), n);
+        e = Elt<T>::exp2_ref(load_logit(c, i), n);
         if (rad) fuse_token_rad(e, load_logit(rad, i), fr, rm, gl, gw);
         else fuse_token(e, fr, gl, gw);
     };

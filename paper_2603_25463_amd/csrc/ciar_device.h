@@ -8,6 +8,7 @@
 #include <limits.h>
 #include <atomic>
 #include <math.h>
+#include <type_traits>
 
 namespace ciar {
 namespace {
@@ -77,9 +78,21 @@ __device__ __forceinline__ double recip(double x)
 // 2^k as a double for an integer-valued float difference k <= 0 (clamped: below 2^-1000 it is 0 anyway)
 __device__ __forceinline__ double pow2_of(float k) { return ldexp(1.0, (int)fmaxf(k, -1000.f)); }
 
+// bf16 logits x: kBf16Scale (15 significant bits) times x is exact in fp32, and kBf16Scale * kBf16ToLog2e is log2(e) to 1.2e-13
+// relative, so 2^(x log2(e) - n) takes one FMA whose only error is its own rounding.  (fp32 logits: exp2_ref.)
+constexpr float kBf16Scale = 1.52874755859375f;        // = kBf16ScaleHi + kBf16ScaleLo, each a bf16 number
+constexpr float kBf16ToLog2e = 0.94371045f;
+constexpr uint32_t kBf16ScaleHi = 0x3fc4u, kBf16ScaleLo = 0xbb24u;
+__device__ __forceinline__ float exp2_scaled(float z, float n)         // z = kBf16Scale x
+{
+    return __builtin_amdgcn_exp2f(fmaf(z, kBf16ToLog2e, -n));
+}
+
 template <typename T> struct Elt;
 template <> struct Elt<float> {
     static constexpr int kPerVec = 4;
+    __device__ static __forceinline__ float exp2_ref(float x, float n) { return ciar::exp2_ref(x, n); }
+    __device__ static __forceinline__ float ref_of(float m) { return ciar::ref_of(m); }
     static constexpr uint32_t kNegInfWord = 0xff800000u;
     __device__ static __forceinline__ void unpack(const u32x4& r, float* o)
     {
@@ -105,6 +118,15 @@ template <> struct Elt<float> {
 struct bf16_t { uint16_t bits; };
 template <> struct Elt<bf16_t> {
     static constexpr int kPerVec = 8;
+    // ref_of, and where a reference that large is no longer good to an integer (masked tokens at -1e37, say) a little above it: no
+    // exponential of its tokens overflows, as with the two-part log2(e) of fp32 logits.
+    __device__ static __forceinline__ float ref_of(float m)
+    {
+        const float n = ciar::ref_of(m);
+        return fabsf(n) < 0x1p24f || n == -INFINITY ? n : fmaf(fabsf(n), 0x1p-22f, n);
+    }
+    // (the same number, bit for bit, as from the matrix cores' product: see bf16_scaled)
+    __device__ static __forceinline__ float exp2_ref(float x, float n) { return exp2_scaled(x * kBf16Scale, n); }
     static constexpr uint32_t kNegInfWord = 0xff80ff80u;
     __device__ static __forceinline__ void unpack(const u32x4& r, float* o)
     {
@@ -113,16 +135,17 @@ template <> struct Elt<bf16_t> {
         o[4] = bits_f(r.z << 16); o[5] = bits_f(r.z & 0xffff0000u);
         o[6] = bits_f(r.w << 16); o[7] = bits_f(r.w & 0xffff0000u);
     }
-    __device__ static __forceinline__ uint32_t mask_word(uint32_t w, int base, int V)
+    // (by -inf, or by the pattern whose word is `fill`)
+    __device__ static __forceinline__ uint32_t mask_word(uint32_t w, int base, int V, uint32_t fill)
     {
-        if (base >= V) return kNegInfWord;
-        if (base + 1 >= V) return (w & 0x0000ffffu) | 0xff800000u;
+        if (base >= V) return fill;
+        if (base + 1 >= V) return (w & 0x0000ffffu) | (fill & 0xffff0000u);
         return w;
     }
-    __device__ static __forceinline__ void mask_tail(u32x4& r, int base, int V)
+    __device__ static __forceinline__ void mask_tail(u32x4& r, int base, int V, uint32_t fill = kNegInfWord)
     {
-        r.x = mask_word(r.x, base + 0, V); r.y = mask_word(r.y, base + 2, V);
-        r.z = mask_word(r.z, base + 4, V); r.w = mask_word(r.w, base + 6, V);
+        r.x = mask_word(r.x, base + 0, V, fill); r.y = mask_word(r.y, base + 2, V, fill);
+        r.z = mask_word(r.z, base + 4, V, fill); r.w = mask_word(r.w, base + 6, V, fill);
     }
     __device__ static __forceinline__ uint32_t zero_word(uint32_t w, int base, int V)
     {
@@ -134,6 +157,84 @@ template <> struct Elt<bf16_t> {
         r.z = zero_word(r.z, base + 4, V); r.w = zero_word(r.w, base + 6, V);
     }
 };
+
+// bf16 rows widened by the matrix cores.  What a token of a bf16 row costs on the vector ALUs beyond its exponential and its
+// sums is unpacking it from its half of a word and taking it to base 2 (two multiply-adds): three issues of eight.  A 4 x 4
+// matrix product per four lanes, (the lanes' four tokens each) x (kBf16Scale on the diagonal), does the unpacking and the exact
+// scaling of four tokens per lane in one issue per bf16 part of kBf16Scale, next to the vector ALUs' work: with the FMA
+// that is left, one and a half issues per token for three.  The products are exact, so the result is the number that
+// x * kBf16Scale gives, bit for bit.
+// Slots: the tokens of a quad's four lanes come back transposed: slot 4 g + r of lane l holds token 4 g + (l & 3) of lane
+// (l & ~3) + r's vector.  Sums over a row do not care; whoever wants a slot's token index asks slot_base and slot_step.
+// An infinity would make its three neighbours 0 * inf: rows that may hold one are widened on the vector ALUs (ordinary_top; sums
+// that come out as no number).
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+struct Bf16Scale { s16x4 hi, lo; };                                // this lane's column of the two diagonal matrices
+__device__ __forceinline__ Bf16Scale bf16_scale(int lane)
+{
+    const uint32_t up = (uint32_t)(lane & 1) * 16u;
+    const bool first = (lane & 2) == 0;
+    const uint32_t h = kBf16ScaleHi << up, l = kBf16ScaleLo << up;
+    return {__builtin_bit_cast(s16x4, u32x2{first ? h : 0u, first ? 0u : h}),
+            __builtin_bit_cast(s16x4, u32x2{first ? l : 0u, first ? 0u : l})};
+}
+__device__ __forceinline__ void bf16_scaled(const u32x4& r, const Bf16Scale& m, float* z)
+{
+    const s16x4 a = __builtin_bit_cast(s16x4, u32x2{r.x, r.y}), b = __builtin_bit_cast(s16x4, u32x2{r.z, r.w});
+    f32x4 za = {0.f, 0.f, 0.f, 0.f}, zb = za;
+    za = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a, m.hi, za, 0, 0, 0);
+    zb = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(b, m.hi, zb, 0, 0, 0);
+    za = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a, m.lo, za, 0, 0, 0);
+    zb = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(b, m.lo, zb, 0, 0, 0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) { z[k] = za[k]; z[4 + k] = zb[k]; }
+}
+// Token index of slot k (of 4 g + r) of this thread's vector, from the first token of the workgroup's vectors: slot_base + 4 g +
+// slot_step r; `quads` = the slots are transposed.
+__device__ __forceinline__ int slot_base(bool quads, int tid, int per_vec)
+{
+    return quads ? (tid & ~3) * per_vec + (tid & 3) : tid * per_vec;
+}
+__device__ __forceinline__ int slot_step(bool quads, int per_vec) { return quads ? per_vec : 1; }
+
+// v[i] of lane j of a quad <-> v[j] of lane i: slots to tokens in order and back (two exchanges with a neighbour lane)
+__device__ __forceinline__ void quad_transpose(float& v0, float& v1, float& v2, float& v3, int lane)
+{
+    auto swap = [](float& a, float& b, bool upper, auto ctrl) {   // the pair's lower lane gives b for the upper lane's a
+        const float give = upper ? a : b;
+        const float got = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(give), decltype(ctrl)::value, 0xf, 0xf, true));
+        if (upper) a = got; else b = got;
+    };
+    const bool odd = (lane & 1) != 0, high = (lane & 2) != 0;
+    constexpr std::integral_constant<int, 0xB1> by1{};             // quad_perm 1,0,3,2
+    constexpr std::integral_constant<int, 0x4E> by2{};             // quad_perm 2,3,0,1
+    swap(v0, v1, odd, by1);
+    swap(v2, v3, odd, by1);
+    swap(v0, v2, high, by2);
+    swap(v1, v3, high, by2);
+}
+
+// The largest logit of a wave's bf16 words without unpacking them: as fp16 numbers bf16 patterns have the same order, and gfx950
+// takes the maximum of three packed pairs in one issue (a quarter of an issue per token; unpacked: a half, and the
+// unpacking).  Patterns that are infinities or no numbers in fp16 -- bf16 magnitudes from 2^121 on, masked tokens at -inf or the
+// type's lowest value among them -- come through as such (ordinary_top is false): then the wave's tokens are unpacked.
+constexpr uint32_t kNoTokenWord = 0xfbfffbffu;                     // below every ordinary logit: padding
+__device__ __forceinline__ uint32_t pk_max3(uint32_t a, uint32_t b, uint32_t c)
+{
+    uint32_t m;
+    asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));
+    return m;
+}
+template <int N>
+__device__ __forceinline__ uint32_t top_words(const u32x4 (&v)[N])
+{
+    uint32_t m = kNoTokenWord;
+#pragma unroll
+    for (int j = 0; j < N; ++j) m = pk_max3(pk_max3(m, v[j].x, v[j].y), v[j].z, v[j].w);
+    return m;
+}
 
 template <typename T>
 __device__ __forceinline__ float load_logit(const T* row, int i)
@@ -275,6 +376,27 @@ __device__ __forceinline__ float wave_max(float v)
     v = dpp_max<kRowBcast15, 0xa>(v);
     v = dpp_max<kRowBcast31, 0xc>(v);
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+// the same for top_words: the larger of the wave's two halves as a float; `ordinary` as above
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp_pk_max(uint32_t v)
+{
+    const uint32_t o = (uint32_t)dpp_or<CTRL, ROW_MASK>((int)v, (int)v);
+    return pk_max3(v, o, o);
+}
+__device__ __forceinline__ float wave_top(uint32_t v, bool& ordinary)
+{
+    v = dpp_pk_max<kRowShr1, 0xf>(v);
+    v = dpp_pk_max<kRowShr2, 0xf>(v);
+    v = dpp_pk_max<kRowShr4, 0xf>(v);
+    v = dpp_pk_max<kRowShr8, 0xf>(v);
+    v = dpp_pk_max<kRowBcast15, 0xa>(v);
+    v = dpp_pk_max<kRowBcast31, 0xc>(v);
+    const uint32_t u = (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+    const float m = fmaxf(bits_f(u & 0xffff0000u), bits_f(u << 16));
+    ordinary = (u & 0x7c00u) != 0x7c00u && (u & 0x7c000000u) != 0x7c000000u && m > bits_f(kNoTokenWord & 0xffff0000u);
+    return m;
 }
 
 // maximum over lanes 0..15 (the first DPP row), handed to every lane of the wave
@@ -583,11 +705,11 @@ __device__ __forceinline__ int accept_quick(float cx, float tx, float u, float n
 // steps): score, flag, the reported token's interval, the accept test in the log domain.  xid = the reported
 // token (-1: the arg-max token, whose logit is st.mc), cx / tx / rawx = its centre logit, verifier logit and raw
 // radius, u = the row's uniform for the accept test.  Returns whether the drafted token is rejected.
-// raw_top: tensor radius, rows with a token above 1/2: that token's raw radius.  flag: where the row's flag goes besides
+// T: the logits' type (the exponentials of its rows).  raw_top: tensor radius, rows with a token above 1/2: that token's raw radius.  flag: where the row's flag goes besides
 // A.flags, if anywhere.  again(score): whether the row's sums are to be taken anew -- then nothing is written and the
 // result is true.
 struct NeverAgain { __device__ bool operator()(const RowScore&) const { return false; } };
-template <bool RAD_TOP = false, typename Again = NeverAgain>
+template <typename T, bool RAD_TOP = false, typename Again = NeverAgain>
 __device__ __forceinline__ bool finish_row(const RowArgs& A, int64_t row, const RowStats& st, float cx, float tx,
                                            float rawx, float u, bool do_q, bool do_v, float raw_top = 0.f,
                                            uint8_t* flag = nullptr, Again again = {})
@@ -614,7 +736,7 @@ __device__ __forceinline__ bool finish_row(const RowArgs& A, int64_t row, const 
         asm volatile("" : "+s"(fa), "+s"(fb), "+s"(fv));
         if (st.mode == kSumsFull && A.normalize && fv > kTinyVocab && (RAD_TOP || (!A.radius && fa < 3.0 * (double)fv)) &&
             st.kl == 0.0 && st.kw == 0.0) {
-            const float etop = exp2_ref(st.mc, n == -INFINITY ? 0.f : n);
+            const float etop = Elt<T>::exp2_ref(st.mc, n == -INFINITY ? 0.f : n);
             if ((double)etop > 0.5 * S) {
                 const double ed = (double)etop, invS = 1.0 / S;
                 const double x = ed * invS, om = fmax(0.0, S - ed) * invS;      // 1 - x from the sum of the other tokens
@@ -654,7 +776,7 @@ __device__ __forceinline__ bool finish_row(const RowArgs& A, int64_t row, const 
             // probability can approach 1, sits in a wave whose reference is n), so that S - e_x is the
             // sum of the other tokens to fp64 rounding and 1 - x keeps its relative accuracy as x -> 1:
             // the lower bound's denominator b + (1-b)(1-x) is that small number when b is small too.
-            const double ex = (double)exp2_ref(cx, n == -INFINITY ? 0.f : n);
+            const double ex = (double)Elt<T>::exp2_ref(cx, n == -INFINITY ? 0.f : n);
             const double x = ex / S, omx = fmax(0.0, S - ex) / S;
             double a = A.a, b = A.b;
             if (A.radius) {

@@ -145,7 +145,7 @@ __global__ __launch_bounds__(THREADS) void resample_kernel(const RowArgs A, cons
             // exponentials carry anyway) and the FMA forms the difference from the exact product et / Z
 #pragma unroll
             for (int k = 0; k < EPV; ++k)
-                r[k] = fmaxf(fmaf(exp2_ref(tv[k], nt), invZf, -(exp2_ref(cv[k], n) * invSf)), 0.f);
+                r[k] = fmaxf(fmaf(E::exp2_ref(tv[k], nt), invZf, -(E::exp2_ref(cv[k], n) * invSf)), 0.f);
         };
         // E1: workgroup totals of the residual over each chunk of CHUNK tokens, eight chunks at a time (UB of each row
         // in flight).  The eight lane sums are reduced over the wave together: two DPP steps leave every quad's sums
@@ -364,7 +364,7 @@ __global__ __launch_bounds__(256) void flatrow_kernel(const RowArgs A, const int
                     cx = load_logit(crow, xid);
                     if (rrow) rawx = load_logit(rrow, xid);
                 }
-                finish_row(A, row, o, cx, 0.f, rawx, 0.f, true, false);
+                finish_row<T>(A, row, o, cx, 0.f, rawx, 0.f, true, false);
             }
         }
     }

@@ -40,7 +40,7 @@ __global__ __launch_bounds__(256) void ensemble_kernel(const RowArgs A, const in
     bool flat_h = true;                                            // this lane's head: a flat row (see below)
     if (tid < H) {
         const RowStats st = A.stats[(int64_t)tid * A.N + row];
-        flat_h = (double)exp2_ref(st.mc, st.n == -INFINITY ? 0.f : st.n) * (double)V <= 2.0 * st.S;
+        flat_h = (double)Elt<T>::exp2_ref(st.mc, st.n == -INFINITY ? 0.f : st.n) * (double)V <= 2.0 * st.S;
         const RowScore rs = finish_score(st.q, st.S, st.mode, A, st.kl, st.kw);
         const double Bc = (rad ? 1.0 : A.b) / st.S, Wc = (rad ? 1.0 : A.a - A.b) / st.S;
         sm_fr[tid] = fuse_row(st.S, A.a, A.b);
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256) void ensemble_kernel(const RowArgs A, const in
     const int nvec = (V + EPV - 1) / EPV;
     // One head's share of a token: its width after the head's caps (added to d) and, WIDE, its complement (to c).
     auto head_token = [&](int h, float cval, float rval, const FuseRow& fr, double& d, double& c) {
-        const float e = exp2_ref(cval, sm_n[h]);
+        const float e = Elt<T>::exp2_ref(cval, sm_n[h]);
         float gl, gw;
         if constexpr (WIDE) {
             float ec;
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(256) void ensemble_kernel(const RowArgs A, const in
         // A handful of tokens: e as the streaming kernel summed it into S, so that 1 - x stays accurate as x -> 1.
         // A flat row: the fp64 exponential (every x is tiny; the fp32 one would leave 6e-8 of each width behind,
         // uncorrelated from token to token, where the widths themselves agree to 1e-6).
-        const double ed = V <= 64 ? (double)exp2_ref(cval, sm_n[h]) : exp((double)cval - (double)sm_n[h] * kLn2);
+        const double ed = V <= 64 ? (double)Elt<T>::exp2_ref(cval, sm_n[h]) : exp((double)cval - (double)sm_n[h] * kLn2);
         const double x = ed / sm_S[h], omx = fmax(0.0, sm_S[h] - ed) / sm_S[h];
         double a = A.a, b = A.b;
         if (rad) {
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(256) void ensemble_kernel(const RowArgs A, const in
                 const float invS = sm_invS[h], nh = sm_n[h];
                 const double cw = sm_cw[h], cl = sm_cl[h];
                 auto token = [&](float cval, float rval, double& d, double& cc, float& p) {
-                    const float e = exp2_ref(cval, nh);
+                    const float e = Elt<T>::exp2_ref(cval, nh);
                     float gl, gw;
                     if constexpr (WIDE) {
                         float ec;
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(256) void ensemble_kernel(const RowArgs A, const in
             double lo = 0.0, mid = 0.0, hi = 0.0;
             for (int h = 0; h < H; ++h) {
                 const T* crow = static_cast<const T*>(A.draft) + (int64_t)h * head_stride + row * A.stride;
-                const double ex = (double)exp2_ref(load_logit(crow, xid), sm_n[h]);
+                const double ex = (double)Elt<T>::exp2_ref(load_logit(crow, xid), sm_n[h]);
                 const double x = ex / sm_S[h], omx = fmax(0.0, sm_S[h] - ex) / sm_S[h];
                 double a = A.a, b = A.b;
                 if (rad) {
@@ -455,21 +455,21 @@ void ensemble_fused_kernel(const RowArgs A, const int64_t head_stride)
 #pragma unroll
             for (int i = 1; i < EPT; ++i) ml = fmaxf(ml, e[i]);
             const float mw = wave_max(ml);
-            const float nw = ref_of(mw);
+            const float nw = Elt<T>::ref_of(mw);
             const float nref = nw == -INFINITY ? 0.f : nw;
             double sacc = 0.0;                                     // (one accumulator: registers are scarcer here than issue slots)
 #pragma unroll
             for (int j = 0; j < NVEC; ++j) {
 #pragma unroll
                 for (int k = 0; k < EPV; ++k) {
-                    e[j * EPV + k] = exp2_ref(e[j * EPV + k], nref);
+                    e[j * EPV + k] = Elt<T>::exp2_ref(e[j * EPV + k], nref);
                     sacc += (double)e[j * EPV + k];
                 }
                 __builtin_amdgcn_sched_barrier(0);                 // keep the working set to one vector at a time
             }
             const double Sw = wave_sum(sacc);
             if (lane == 0) { sm_ref[h][wave][0] = mw; sm_ref[h][wave][1] = nw; sm_S[h][wave] = Sw; }
-            emax_w = uniform_f(exp2_ref(mw, nref));                // the wave's largest e_i, in its own units
+            emax_w = uniform_f(Elt<T>::exp2_ref(mw, nref));                // the wave's largest e_i, in its own units
             return uniform_f(nw);
         };
         float e[RH][EPT];
@@ -529,7 +529,7 @@ void ensemble_fused_kernel(const RowArgs A, const int64_t head_stride)
                 if (rn != -INFINITY) s += sm_S[h][w] * pow2_of(rn - nn);
             }
             S[h] = uniform_d(s); n[h] = uniform_f(nn);
-            const double emax = (double)exp2_ref(uniform_f(mc), n[h]);
+            const double emax = (double)Elt<T>::exp2_ref(uniform_f(mc), n[h]);
             all_capless = all_capless && (!A.normalize || emax <= A.capless_xmax * S[h]);
             any_split = any_split || emax > 0.5 * S[h];
             __builtin_amdgcn_sched_barrier(0);                     // one head at a time: the LDS reads of all heads at once
@@ -586,7 +586,7 @@ void ensemble_fused_kernel(const RowArgs A, const int64_t head_stride)
 #pragma unroll
         for (int h = 0; h < H; ++h) {
             const T* crow = static_cast<const T*>(A.draft) + (int64_t)h * head_stride + row * A.stride;
-            const float e0 = exp2_ref(load_logit(crow, 0), n[h]);
+            const float e0 = Elt<T>::exp2_ref(load_logit(crow, 0), n[h]);
             float gl, gw;
             fuse_token(e0, fuse_row(S[h], ra, rb), gl, gw);
             KD = fma(au[h] * (ra - rb) / S[h], (double)gw, fma((au[h] - al[h]) * rb / S[h], (double)gl, KD));
@@ -713,7 +713,7 @@ void ensemble_fused_kernel(const RowArgs A, const int64_t head_stride)
                 for (int h = 0; h < H; ++h) {
                     const T* crow = static_cast<const T*>(A.draft) + (int64_t)h * head_stride + row * A.stride;
                     const double Sh = sm_Sh[h];
-                    const double ex = (double)exp2_ref(load_logit(crow, xid), sm_nh[h]);
+                    const double ex = (double)Elt<T>::exp2_ref(load_logit(crow, xid), sm_nh[h]);
                     const double x = ex / Sh, omx = fmax(0.0, Sh - ex) / Sh;
                     mid += x;
                     lo += sm_alh[h] * rb * x / (rb + (1.0 - rb) * omx);
@@ -928,11 +928,11 @@ void ensemble_sweep_kernel(const RowArgs A, const int H, const int64_t head_stri
                 fetch(RAD ? 0 : p, A.draft, next_row, next_h, has_next, tid);
                 unpack_row(cbuf, e, true, tid);
             }
-            const float mw = wave_max(max_of(e)), nw = ref_of(mw), nref = nw == -INFINITY ? 0.f : nw;
+            const float mw = wave_max(max_of(e)), nw = Elt<T>::ref_of(mw), nref = nw == -INFINITY ? 0.f : nw;
             double sacc[2] = {0.0, 0.0};
 #pragma unroll
             for (int i = 0; i < kSweepTokens; ++i) {
-                e[i] = exp2_ref(e[i], nref);
+                e[i] = Elt<T>::exp2_ref(e[i], nref);
                 sacc[i & 1] += (double)e[i];
             }
             // S_w over the wave, together with the cap sums of the head before (in their slots since its end)
@@ -951,14 +951,14 @@ void ensemble_sweep_kernel(const RowArgs A, const int H, const int64_t head_stri
             // the waves' results combined, across the first lanes of every wave
             const int src = lane < NW ? lane : 0;
             // (the row's reference is the largest of the waves': the reference of the largest logit)
-            const float m_l = sm_ref[p][src], n_l = ref_of(m_l), mc = row16_max(m_l), n = ref_of(mc);
+            const float m_l = sm_ref[p][src], n_l = Elt<T>::ref_of(m_l), mc = row16_max(m_l), n = Elt<T>::ref_of(mc);
             const double S = row16_sum(lane < NW && n_l != -INFINITY ? sm_S[p][src] * pow2_of(n_l - n) : 0.0);
             // (the radius constants through an empty asm, formed anew for every row, and what is the same in every lane of
             // the wave moved to scalar registers: nothing of it is held in vector registers, or spilled, through the loop)
             double ra = A.a, rb = A.b;
             asm volatile("" : "+s"(ra), "+s"(rb));
             if (tid == 0) { pk_S[done][h] = S; pk_n[done][h] = n; pk_mc[done][h] = mc; }
-            const double emax = (double)exp2_ref(mc, n == -INFINITY ? 0.f : n);
+            const double emax = (double)Elt<T>::exp2_ref(mc, n == -INFINITY ? 0.f : n);
             all_flat = all_flat && emax * (double)V <= 2.0 * S;
             const double Su = nw == -INFINITY ? 1.0 : ldexp(S, (int)fminf(n - nw, 1000.f));   // S in this wave's units
             const double inv = uniform_d(recip(Su));
@@ -999,7 +999,7 @@ void ensemble_sweep_kernel(const RowArgs A, const int H, const int64_t head_stri
                 // (the host's bound on the largest probability, as in the streaming kernel)
                 const bool capless = !A.normalize || emax <= A.capless_xmax * S;          // uniform over the workgroup
                 const float is = -fr.nih, is2 = is * is;
-                const bool poly = capless && A.wpoly_x >= 0.f && (double)exp2_ref(mw, nref) <= (double)A.wpoly_x * Su;
+                const bool poly = capless && A.wpoly_x >= 0.f && (double)Elt<T>::exp2_ref(mw, nref) <= (double)A.wpoly_x * Su;
                 if (poly) {                                        // uniform over the wave: see RowArgs::wpoly
                     const float d0 = uniform_f(A.wpoly[0] * is), d1 = uniform_f(A.wpoly[1] * is2);
                     const float d2 = uniform_f(A.wpoly[2] * (is2 * is)), d3 = uniform_f(A.wpoly[3] * (is2 * is2));
@@ -1085,7 +1085,7 @@ void ensemble_sweep_kernel(const RowArgs A, const int H, const int64_t head_stri
             if constexpr (RAD) unpack_row(rbuf, rv, false, tid);
 #pragma unroll
             for (int i = 0; i < kSweepTokens; ++i) {
-                const float ek = exp2_ref(e[i], n == -INFINITY ? 0.f : n);
+                const float ek = Elt<T>::exp2_ref(e[i], n == -INFINITY ? 0.f : n);
                 float gl, gw;
                 if constexpr (RAD) fuse_token_rad<UNIT>(ek, rv[i], fr, rm.kappa, rm.rmax, rm.am1_max, gl, gw);
                 else fuse_token(ek, fr, gl, gw);
@@ -1174,7 +1174,7 @@ void ensemble_sweep_kernel(const RowArgs A, const int H, const int64_t head_stri
         double lo = 0.0, mid = 0.0, hi = 0.0;
         for (int h = 0; h < H; ++h) {
             const T* crow = static_cast<const T*>(A.draft) + (int64_t)h * head_stride + r * A.stride;
-            const double Sh = pk_S[t][h], ex = (double)exp2_ref(load_logit(crow, xid), pk_n[t][h]);
+            const double Sh = pk_S[t][h], ex = (double)Elt<T>::exp2_ref(load_logit(crow, xid), pk_n[t][h]);
             const double x = ex / Sh, omx = fmax(0.0, Sh - ex) / Sh;
             double a = A.a, b = A.b;
             if constexpr (RAD) {

@@ -211,7 +211,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
                 E::unpack(buf[j], &e[j * EPV]);
             }
         }
-        const float mw = wave_max(max_of(e)), nw = ref_of(mw), nref = nw == -INFINITY ? 0.f : nw;
+        const float mw = wave_max(max_of(e)), nw = Elt<T>::ref_of(mw), nref = nw == -INFINITY ? 0.f : nw;
         if constexpr (ARGMAX) {
             int at = INT_MAX;
 #pragma unroll
@@ -226,7 +226,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
             if (j < nch) {
 #pragma unroll
                 for (int k = 0; k < EPV; ++k) {
-                    e[j * EPV + k] = exp2_ref(e[j * EPV + k], nref);
+                    e[j * EPV + k] = Elt<T>::exp2_ref(e[j * EPV + k], nref);
                     Sl += (double)e[j * EPV + k];
                 }
             }
@@ -245,7 +245,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
         lds_barrier();
         if (wave == 0 && done > 0) park(done - 1, p ^ 1);
         const int src = lane < NW ? lane : 0;
-        const float m_l = sm_ref[p][src], n_l = ref_of(m_l), mc = row16_max(m_l), n = ref_of(mc);
+        const float m_l = sm_ref[p][src], n_l = Elt<T>::ref_of(m_l), mc = row16_max(m_l), n = Elt<T>::ref_of(mc);
         const double S = row16_sum(lane < NW && n_l != -INFINITY ? sm_S[p][src] * pow2_of(n_l - n) : 0.0);
         if constexpr (ARGMAX) {
             if (wave == 0) {                                       // the lowest index of the waves that hold the maximum
@@ -256,7 +256,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
         if (tid == 0) { pk[done].S = S; pk[done].n = n; pk[done].mc = mc; }
         const double fw = nw == -INFINITY ? 0.0 : pow2_of(nw - n);                         // this wave's e_i are 1 / fw too large
         const double Su = nw == -INFINITY ? 1.0 : ldexp(S, (int)fminf(n - nw, 1000.f));   // S in this wave's units
-        const bool top = (double)exp2_ref(mc, n == -INFINITY ? 0.f : n) > 0.5 * S;         // uniform over the workgroup
+        const bool top = (double)Elt<T>::exp2_ref(mc, n == -INFINITY ? 0.f : n) > 0.5 * S;         // uniform over the workgroup
         FuseRow fr;
         {
             const double inv = recip(Su);
@@ -276,7 +276,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
         // A row with a token above 1/2: its raw radius is parked for finish_row by the lane that has it, in the wave with the row's
         // largest token.  (No other token has its e: two of them would be all of S.)
         const bool search = top && mw == mc;                       // uniform over the wave
-        const float etop = uniform(exp2_ref(mw, nref));
+        const float etop = uniform(Elt<T>::exp2_ref(mw, nref));
         float raw_top = 0.f;
         bool found = false;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -396,7 +396,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
         const float cx = load_logit(static_cast<const T*>(A.draft) + off, xid);
         const float rawx = load_logit(static_cast<const T*>(A.radius) + off, xid);
         // (the vote counts the flags as written)
-        if (finish_row<true>(A, r, st, cx, 0.f, rawx, 0.f, true, false, pk[at].raw_top, &pk_flag[at], again)) return true;
+        if (finish_row<T, true>(A, r, st, cx, 0.f, rawx, 0.f, true, false, pk[at].raw_top, &pk_flag[at], again)) return true;
         A.stats[r] = st;
         return false;
     };
@@ -409,7 +409,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
             A.stats[row_of(t)] = stats_of(t);
         } else if (t < count) {
             const RowStats st = stats_of(t);
-            const double etop = (double)exp2_ref(st.mc, st.n == -INFINITY ? 0.f : st.n);
+            const double etop = (double)Elt<T>::exp2_ref(st.mc, st.n == -INFINITY ? 0.f : st.n);
             pk_fp64[t] = (uint8_t)finish(t, st, [&](const RowScore& rs) {
                 const double Vd = (double)V, mean = (WIDE && st.mode == kSumsComplement ? Vd - rs.omega : rs.omega) / Vd;
                 return !(rs.sigma * rs.sigma >= kCrowded * mean * mean) || (A.precise_flat && etop * Vd <= 2.0 * st.S);

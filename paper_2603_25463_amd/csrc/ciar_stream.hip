@@ -91,7 +91,7 @@ struct Shift { float kl, kw, kc; };
 // delta_i = w_i and only the sums of gw are needed.
 // SPLIT = see fuse_parts.
 // MASK = the row does not fill the tile: slots past its end contribute nothing (they hold e = 0, which would
-// otherwise enter as 0 - k).
+// otherwise enter as 0 - k).  base, step: see slot_base.
 //
 // Small probabilities (WIDTH_ONLY instances).  The raw width per unit of e,
 //   G(x) = (1 - x) / ((1 + (a-1) x)(1 - (1-b) x)),   gw = e G(x),
@@ -104,8 +104,9 @@ struct WidthPoly { float d0, d1, d2, d3, ethr; };   // gw = e (1 + e (d0 + e (d1
 
 template <int THREADS, int NVEC, int EPV, bool WIDTH_ONLY, bool SPLIT, bool MASK>
 __device__ __forceinline__ void fuse_sums(const float (&e)[NVEC * EPV], const FuseRow& fr_in, const WidthPoly& wp,
-                                          const Shift& sh, int V, int tid, double (&q5)[5])
+                                          const Shift& sh, int V, int base, int step, double (&q5)[5])
 {
+    auto live_slot = [&](int j, int k) { return j * THREADS * EPV + base + (k & ~3) + step * (k & 3) < V; };
     // The caller branches between several instances of this pass.  The row constants go through an empty asm
     // so that each instance has its own: otherwise the optimiser hoists the sub-expressions the instances share
     // (1 + cu e for every token of the lane) above the branch and spills them.
@@ -129,7 +130,7 @@ __device__ __forceinline__ void fuse_sums(const float (&e)[NVEC * EPV], const Fu
                     const float ek = e[j * EPV + k];
                     const float G = fmaf(fmaf(fmaf(fmaf(wp.d3, ek, wp.d2), ek, wp.d1), ek, wp.d0), ek, 1.0f);
                     float sw = fmaf(ek, G, -sh.kw);
-                    if (MASK && (j * THREADS + tid) * EPV + k >= V) sw = 0.f;
+                    if (MASK && !live_slot(j, k)) sw = 0.f;
                     const double dw = (double)sw;
                     a1[k & 1] += dw;
                     a3[k & 1] = fma(dw, dw, a3[k & 1]);
@@ -142,7 +143,7 @@ __device__ __forceinline__ void fuse_sums(const float (&e)[NVEC * EPV], const Fu
         for (int k = 0; k < EPV; ++k) {
             float g, du, om;
             fuse_parts<SPLIT>(e[j * EPV + k], fr, g, du, om);
-            const bool live = !MASK || (j * THREADS + tid) * EPV + k < V;
+            const bool live = !MASK || live_slot(j, k);
             float sw = fmaf(g, om, -sh.kw);
             if (!live) sw = 0.f;
             const double dw = (double)sw;
@@ -171,7 +172,7 @@ __device__ __forceinline__ void fuse_sums(const float (&e)[NVEC * EPV], const Fu
 // lane's largest ec.
 template <int THREADS, int NVEC, int EPV>
 __device__ __forceinline__ void fuse_sums_wide(const float (&e)[NVEC * EPV], const FuseRow& fr, const Shift& sh,
-                                               int V, int tid, double (&q)[8])
+                                               int V, int base, int step, double (&q)[8])
 {
     double acc[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     float big = 0.f;
@@ -182,7 +183,7 @@ __device__ __forceinline__ void fuse_sums_wide(const float (&e)[NVEC * EPV], con
         for (int k = 0; k < EPV; ++k) {
             float gl, gw, ec;
             fuse_token_wide(e[j * EPV + k], fr, gl, gw, ec);
-            if ((j * THREADS + tid) * EPV + k < V) {
+            if (j * THREADS * EPV + base + (k & ~3) + step * (k & 3) < V) {
                 const double dl = (double)(gl - sh.kl), dw = (double)(gw - sh.kw), dc = (double)(ec - sh.kc);
                 acc[0] += dl; acc[1] += dw;
                 acc[2] = fma(dl, dl, acc[2]); acc[3] = fma(dw, dw, acc[3]); acc[4] = fma(dl, dw, acc[4]);
@@ -356,6 +357,7 @@ void stream_kernel(const RowArgs A)
     // verifier row's partition sum are reduced over the wave together (wave_sum3) once the verifier row has been summed.
     // (These instances are bound by their vector instructions: workload 5 1951 -> 1905 us.  The fp32 instances, which
     // wait for memory, measured 1 % slower with it and keep one reduction per sum.)
+    constexpr bool MATRIX = sizeof(T) == 2 && !RAD; // the centre row through the matrix cores (see bf16_scaled)
     constexpr bool BATCH3 = DO_Q && DO_V && !RAD && !WIDE && sizeof(T) == 2;
     constexpr int NQ = WIDE ? 8 : 5;                // interval sums a wave hands over
     // A row with a token above 1/2 and a radius tensor: finish_row wants that token's raw radius.  It is picked up in the
@@ -442,34 +444,71 @@ void stream_kernel(const RowArgs A)
             for (int j = 0; j < NVEC; ++j) buf[j] = __builtin_nontemporal_load((gvec)(base + (uint64_t)j * (THREADS * 16u) + off));
         }
     };
+    // (constants of the matrix cores' products are formed where they are used, from an opaque copy of the thread index: an
+    // instruction or two per register and row, where they would otherwise be held through the row loop)
+    auto opaque_tid = [&]() {
+        int t = tid;
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+    auto mask_with = [&](u32x4& r, int first, uint32_t fill) {
+        if constexpr (sizeof(T) == 2) E::mask_tail(r, first, V, fill);
+        else E::mask_tail(r, first, V);
+    };
     // Verifier row statistics of one wave from the row as loaded: nt_w and Z_w = sum 2^(t_i log2e - nt_w).
     // Any integer reference serves as long as no term overflows and the large terms stay normal numbers, so the
     // sum is first taken about the reference of the centre row's tokens in the same wave (`guess`: verifier
     // logits follow the device model's), which saves the pass for the maximum; a sum outside [2^-40, 2^100]
     // (a verifier row far from its centre row, or a wave without tokens: sum 0) is redone about the wave's own
     // maximum.
-    auto verifier_mask = [&](u32x4 (&tb)[NVEC]) {
+    auto verifier_mask = [&](u32x4 (&tb)[NVEC], uint32_t fill) {
         if (partial) {
+            const int ot = sizeof(T) == 2 ? opaque_tid() : tid;
 #pragma unroll
-            for (int j = 0; j < NVEC; ++j) E::mask_tail(tb[j], (j * THREADS + tid) * EPV, V);
+            for (int j = 0; j < NVEC; ++j) mask_with(tb[j], (j * THREADS + ot) * EPV, fill);
         }
     };
-    // (the lane's share of the sum about the reference nref)
-    auto verifier_lane_sum = [&](u32x4 (&tb)[NVEC], float nref) {
+    // (the lane's share of the sum about the reference nref; quads: the tokens widened by the matrix cores)
+    auto verifier_lane_sum = [&](u32x4 (&tb)[NVEC], float nref, bool quads) {
         float zacc[4] = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (sizeof(T) == 2) {
+            if (quads) {
+                const Bf16Scale bs = bf16_scale(opaque_tid());
+                float z[2][EPV];
+                bf16_scaled(tb[0], bs, z[0]);
+#pragma unroll
+                for (int j = 0; j < NVEC; ++j) {
+                    if (j + 1 < NVEC) bf16_scaled(tb[j + 1], bs, z[(j + 1) & 1]);   // (the matrix cores one vector ahead)
+#pragma unroll
+                    for (int k = 0; k < EPV; ++k) zacc[k & 3] += exp2_scaled(z[j & 1][k], nref);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                return (double)((zacc[0] + zacc[1]) + (zacc[2] + zacc[3]));
+            }
+        }
 #pragma unroll
         for (int j = 0; j < NVEC; ++j) {
             float tv[EPV];
             E::unpack(tb[j], tv);
 #pragma unroll
-            for (int k = 0; k < EPV; ++k) zacc[k & 3] += exp2_ref(tv[k], nref);
+            for (int k = 0; k < EPV; ++k) zacc[k & 3] += E::exp2_ref(tv[k], nref);
             __builtin_amdgcn_sched_barrier(0);
         }
         return (double)((zacc[0] + zacc[1]) + (zacc[2] + zacc[3]));
     };
-    // (the sum about the guess was out of range: about the wave's own maximum)
-    auto verifier_redo = [&](u32x4 (&tb)[NVEC], float& ntw, double& Zw) {
-        if (!(Zw >= 0x1p-40 && Zw <= 0x1p100)) {                   // uniform over the wave; also taken by NaN
+    // (the sum about the guess was out of range: about the wave's own maximum -- after a second look without the matrix cores
+    // where a masked token can have got into the way)
+    // (`quads` is false afterwards)
+    auto verifier_redo = [&](u32x4 (&tb)[NVEC], float& ntw, double& Zw, bool& quads) {
+        auto in_range = [&]() { return Zw >= 0x1p-40 && Zw <= 0x1p100; };   // (false for NaN)
+        if constexpr (sizeof(T) == 2) {
+            if (quads && !in_range()) {                            // uniform over the wave
+                quads = false;
+                verifier_mask(tb, E::kNegInfWord);
+                Zw = wave_sum(verifier_lane_sum(tb, ntw, false));
+            }
+        }
+        if (!in_range()) {                                         // uniform over the wave
             float mt = -INFINITY;
 #pragma unroll
             for (int j = 0; j < NVEC; ++j) {
@@ -478,15 +517,15 @@ void stream_kernel(const RowArgs A)
 #pragma unroll
                 for (int k = 0; k < EPV; ++k) mt = fmaxf(mt, tv[k]);
             }
-            ntw = ref_of(wave_max(mt));
-            Zw = wave_sum(verifier_lane_sum(tb, ntw == -INFINITY ? 0.f : ntw));   // an all-masked wave: every term is 2^-inf = 0
+            ntw = Elt<T>::ref_of(wave_max(mt));
+            Zw = wave_sum(verifier_lane_sum(tb, ntw == -INFINITY ? 0.f : ntw, false));   // an all-masked wave: every term is 2^-inf = 0
         }
     };
-    auto verifier_stats = [&](u32x4 (&tb)[NVEC], float guess, float& ntw, double& Zw) {
-        verifier_mask(tb);
+    auto verifier_stats = [&](u32x4 (&tb)[NVEC], float guess, float& ntw, double& Zw, bool& quads) {
+        verifier_mask(tb, quads ? kNoTokenWord : E::kNegInfWord);
         ntw = guess == -INFINITY ? 0.f : guess;
-        Zw = wave_sum(verifier_lane_sum(tb, ntw));
-        verifier_redo(tb, ntw, Zw);
+        Zw = wave_sum(verifier_lane_sum(tb, ntw, quads));
+        verifier_redo(tb, ntw, Zw, quads);
     };
 
     // ---- which rows this workgroup takes ---------------------------------------------------------------------
@@ -556,9 +595,9 @@ void stream_kernel(const RowArgs A)
                 if constexpr (DO_Q) {
                     const float cx = A.ids ? sm_fx[i][0] : st.mc;  // no ids: the arg-max token is reported
                     float raw_top = RAD && !TOP_INDEX ? sm_rtop[RAD && !TOP_INDEX ? i : 0] : 0.f;
-                    if (TOP_INDEX && (double)exp2_ref(st.mc, st.n == -INFINITY ? 0.f : st.n) > 0.5 * st.S)
+                    if (TOP_INDEX && (double)E::exp2_ref(st.mc, st.n == -INFINITY ? 0.f : st.n) > 0.5 * st.S)
                         raw_top = load_logit(static_cast<const T*>(A.radius) + row_offset(A, r), sm_top[TOP_INDEX ? i : 0]);
-                    finish_row<RAD>(A, r, st, cx, 0.f, sm_fx[i][1], 0.f, true, false, raw_top);
+                    finish_row<T, RAD>(A, r, st, cx, 0.f, sm_fx[i][1], 0.f, true, false, raw_top);
                 }
             }
         };
@@ -691,36 +730,65 @@ void stream_kernel(const RowArgs A)
 
         // ---- B: centre row: per-wave max, e_i = 2^(c_i log2e - n_w), S_w -------------------------------
         float e[EPT];
-        if (partial) {
-#pragma unroll
-            for (int j = 0; j < NVEC; ++j) E::mask_tail(buf[j], (j * THREADS + tid) * EPV, V);
-        }
-#pragma unroll
-        for (int j = 0; j < NVEC; ++j) E::unpack(buf[j], &e[j * EPV]);
-        const float mcw = wave_max(max_of(e));
-        const float nw = ref_of(mcw);
+        float mcw, nw;
         double Sw;
-        {
-            // S is accumulated in fp64 from the first add: on a nearly one-hot row the bounds of the top
-            // token react to a relative error in S about five times over, and on a two-token row Sigma is
-            // a difference of two nearly equal widths; even one fp32 add of two comparable terms (6e-8)
-            // shows there (measured against the fp64 definition).  Adding the tokens of a 16-byte vector pairwise in
-            // fp32 first (fp64 only across vectors: 0.9 instructions less per token) was tried and fails parity: where a
-            // cap is active Omega = alpha_u S_u - alpha_l S_l is a small difference of numbers near 1 (0.022 from
-            // 1.012 - 0.99 in the failing case), which multiplies the 1e-8 that a dominant token's vector loses by 45.
+        // S is accumulated in fp64 from the first add: on a nearly one-hot row the bounds of the top
+        // token react to a relative error in S about five times over, and on a two-token row Sigma is
+        // a difference of two nearly equal widths; even one fp32 add of two comparable terms (6e-8)
+        // shows there (measured against the fp64 definition).  Adding the tokens of a 16-byte vector pairwise in
+        // fp32 first (fp64 only across vectors: 0.9 instructions less per token) was tried and fails parity: where a
+        // cap is active Omega = alpha_u S_u - alpha_l S_l is a small difference of numbers near 1 (0.022 from
+        // 1.012 - 0.99 in the failing case), which multiplies the 1e-8 that a dominant token's vector loses by 45.
+        double sacc[2] = {0.0, 0.0};
+        // bf16 rows: the maximum from the packed words, the tokens widened by the matrix cores (`quads`: the slots of e[] are
+        // transposed, see bf16_scaled; uniform over the wave).  Not where the slots meet a radius tensor's, nor for a handful of
+        // tokens (their pass wants them in order).
+        bool quads = false;
+        if constexpr (MATRIX) {
+            if (partial) {
+                const int ot = opaque_tid();
+#pragma unroll
+                for (int j = 0; j < NVEC; ++j) mask_with(buf[j], (j * THREADS + ot) * EPV, kNoTokenWord);
+            }
+            mcw = wave_top(top_words(buf), quads);
+            if (NVEC == 1 && V <= kTinyVocab) quads = false;
+        }
+        if (MATRIX && quads) {
+            nw = Elt<T>::ref_of(mcw);
+            const Bf16Scale bs = bf16_scale(opaque_tid());
+            bf16_scaled(buf[0], bs, &e[0]);
+#pragma unroll
+            for (int j = 0; j < NVEC; ++j) {
+                if (j + 1 < NVEC) bf16_scaled(buf[j + 1], bs, &e[(j + 1) * EPV]);   // (the matrix cores one vector ahead)
+#pragma unroll
+                for (int k = 0; k < EPV; ++k) {
+                    e[j * EPV + k] = exp2_scaled(e[j * EPV + k], nw);
+                    sacc[k & 1] += (double)e[j * EPV + k];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+            if (partial) {
+                const int ot = sizeof(T) == 2 ? opaque_tid() : tid;
+#pragma unroll
+                for (int j = 0; j < NVEC; ++j) E::mask_tail(buf[j], (j * THREADS + ot) * EPV, V);
+            }
+#pragma unroll
+            for (int j = 0; j < NVEC; ++j) E::unpack(buf[j], &e[j * EPV]);
+            mcw = wave_max(max_of(e));
+            nw = Elt<T>::ref_of(mcw);
             const float nref = nw == -INFINITY ? 0.f : nw;
-            double sacc[2] = {0.0, 0.0};
 #pragma unroll
             for (int j = 0; j < NVEC; ++j) {
 #pragma unroll
                 for (int k = 0; k < EPV; ++k) {
-                    e[j * EPV + k] = exp2_ref(e[j * EPV + k], nref);
+                    e[j * EPV + k] = E::exp2_ref(e[j * EPV + k], nref);
                     sacc[k & 1] += (double)e[j * EPV + k];
                 }
                 __builtin_amdgcn_sched_barrier(0);                 // keep the working set to one vector at a time
             }
-            Sw = wave_sum(sacc[0] + sacc[1]);
         }
+        Sw = wave_sum(sacc[0] + sacc[1]);
 
         // ---- the waves exchange the centre row's statistics ----------------------------------------------
         float (&sm_ref)[NW * 2] = sm_ref2[done & 1];
@@ -735,7 +803,9 @@ void stream_kernel(const RowArgs A)
         // l < NW takes wave l; the other lanes of the DPP row repeat wave 0, which changes no maximum, and add
         // nothing); with four a short loop is as quick (measured).
         constexpr bool LANES = NW >= 8;
-        const int src = lane < NW ? lane : 0;
+        // (bf16: from an opaque copy of the lane index, so that the slots' addresses are not held, or spilled, through the row loop)
+        const int ln = sizeof(T) == 2 ? opaque_tid() & 63 : lane;
+        const int src = ln < NW ? ln : 0;
         // (by_lanes: across the first lanes of the wave, which must all be active; else in a loop)
         auto combine_S = [&](auto by_lanes, float& mc, float& n, double& S) {
             if constexpr (decltype(by_lanes)::value) {
@@ -745,8 +815,8 @@ void stream_kernel(const RowArgs A)
                 // (... except in the fused bf16 instances of 1024 lanes with a scalar radius: 32768 x 65536 1875 us so, 1894 from the
                 // references)
                 const float mc_l = sm_ref[src * 2], n_l = sm_ref[src * 2 + 1];
-                mc = row16_max(mc_l); n = BATCH3 && THREADS == 1024 ? ref_of(mc) : row16_max(n_l);
-                S = row16_sum(lane < NW && n_l != -INFINITY ? sm_S[src] * pow2_of(n_l - n) : 0.0);
+                mc = row16_max(mc_l); n = BATCH3 && THREADS == 1024 ? Elt<T>::ref_of(mc) : row16_max(n_l);
+                S = row16_sum(ln < NW && n_l != -INFINITY ? sm_S[src] * pow2_of(n_l - n) : 0.0);
             } else {
                 mc = sm_ref[0]; n = sm_ref[1];
 #pragma unroll
@@ -772,7 +842,7 @@ void stream_kernel(const RowArgs A)
         // Caps: S_l <= b / (1 - (1-b) x_max) and S_u >= a / (1 + (a-1) x_max) for the largest probability
         // x_max of the row, so below the host-computed bound on x_max both caps are inactive and the
         // cheaper width-only pass is exact.  Uniform over the workgroup.
-        const double emax = (double)exp2_ref(mc, n);               // the row's largest e_i, in row units
+        const double emax = (double)E::exp2_ref(mc, n);               // the row's largest e_i, in row units
         const bool capless = !A.normalize || (!RAD && emax <= A.capless_xmax * S);
         const bool split = emax > 0.5 * S;                         // some x_i above 1/2: 1 - x needs the two-float 1/S
         const bool flat = emax * (double)V <= 2.0 * S;             // largest probability <= 2 / V (see Shift)
@@ -789,6 +859,7 @@ void stream_kernel(const RowArgs A)
             __builtin_amdgcn_sched_barrier(0);
         }
         float ntw = -INFINITY;                                     // the reference this wave's Z_w is taken about
+        bool tquads = MATRIX ? quads : sizeof(T) == 2;             // the verifier row goes through the matrix cores
         bool lane_sums = false;                                    // uniform: q5[1], q5[3] are still the lanes' own sums
         if constexpr (DO_Q) {
             // x_i = e_i fw / S: hand fuse_row the partition sum expressed in this wave's units
@@ -842,6 +913,7 @@ void stream_kernel(const RowArgs A)
                 wp.d0 = uniform(wp.d0); wp.d1 = uniform(wp.d1); wp.d3 = uniform(wp.d3); wp.ethr = uniform(wp.ethr);
             }
             double kq[3] = {(double)sh.kl, (double)sh.kw, (double)sh.kc};   // fp64 copy (the tiny path sets its own)
+            const int base = slot_base(MATRIX && quads, MATRIX ? opaque_tid() : tid, EPV), step4 = slot_step(MATRIX && quads, EPV);
             bool tiny = false;
             if constexpr (NVEC == 1) tiny = V <= kTinyVocab;       // uniform
             if (tiny) {
@@ -863,7 +935,7 @@ void stream_kernel(const RowArgs A)
                 load_row(buf, A.radius, row);
                 if (TOP_INDEX && split && mcw == mc) {
                     // (uniform over the wave: it holds the row's largest token; as for TopToken)
-                    const float etop = exp2_ref(mcw, nw);
+                    const float etop = E::exp2_ref(mcw, nw);
                     int at = -1;
 #pragma unroll
                     for (int i = 0; i < EPT; ++i) at = e[i] == etop ? i : at;
@@ -873,20 +945,20 @@ void stream_kernel(const RowArgs A)
 #pragma unroll
                     for (int j = 0; j < NVEC; ++j) E::zero_tail(buf[j], (j * THREADS + tid) * EPV, V);
                 }
-                TopToken top = {!TOP_INDEX && split && mcw == mc, false, uniform_f(exp2_ref(mcw, nw)), 0.f};
+                TopToken top = {!TOP_INDEX && split && mcw == mc, false, uniform_f(E::exp2_ref(mcw, nw)), 0.f};
                 if (rm.unit) fuse_sums_rad<T, THREADS, NVEC, WIDE, true>(e, buf, fr, rm, sh, V, tid, q5, top);
                 else         fuse_sums_rad<T, THREADS, NVEC, WIDE, false>(e, buf, fr, rm, sh, V, tid, q5, top);
                 if (top.found) sm_rtop[TOP_INDEX ? 0 : done] = top.raw;            // (one lane of the workgroup), for finish_row
 #pragma unroll
                 for (int i = 0; i < 5; ++i) q5[i] = wave_sum(q5[i]);
             } else if constexpr (WIDE) {
-                fuse_sums_wide<THREADS, NVEC, EPV>(e, fr, sh, V, tid, q5);
+                fuse_sums_wide<THREADS, NVEC, EPV>(e, fr, sh, V, base, step4, q5);
 #pragma unroll
                 for (int i = 0; i < 5; ++i) q5[i] = wave_sum(q5[i]);
             } else if (capless) {
-                if (partial)    fuse_sums<THREADS, NVEC, EPV, true, true, true>(e, fr, wp, sh, V, tid, q5);
-                else if (split) fuse_sums<THREADS, NVEC, EPV, true, true, false>(e, fr, wp, sh, V, tid, q5);
-                else            fuse_sums<THREADS, NVEC, EPV, true, false, false>(e, fr, wp, sh, V, tid, q5);
+                if (partial)    fuse_sums<THREADS, NVEC, EPV, true, true, true>(e, fr, wp, sh, V, base, step4, q5);
+                else if (split) fuse_sums<THREADS, NVEC, EPV, true, true, false>(e, fr, wp, sh, V, base, step4, q5);
+                else            fuse_sums<THREADS, NVEC, EPV, true, false, false>(e, fr, wp, sh, V, base, step4, q5);
                 if constexpr (BATCH3) {
                     // reduced below, together with the verifier row's sum; until then the quads' sums wait in LDS
                     // (slot addresses from an opaque copy of the lane index: hoisted out of the row loop they are spilled)
@@ -900,8 +972,8 @@ void stream_kernel(const RowArgs A)
                     q5[3] = wave_sum(q5[3]);
                 }
             } else {
-                if (partial) fuse_sums<THREADS, NVEC, EPV, false, true, true>(e, fr, wp, sh, V, tid, q5);
-                else         fuse_sums<THREADS, NVEC, EPV, false, true, false>(e, fr, wp, sh, V, tid, q5);
+                if (partial) fuse_sums<THREADS, NVEC, EPV, false, true, true>(e, fr, wp, sh, V, base, step4, q5);
+                else         fuse_sums<THREADS, NVEC, EPV, false, true, false>(e, fr, wp, sh, V, base, step4, q5);
 #pragma unroll
                 for (int i = 0; i < 5; ++i) q5[i] = wave_sum(q5[i]);
             }
@@ -917,9 +989,9 @@ void stream_kernel(const RowArgs A)
                     __builtin_amdgcn_sched_barrier(0);
                     load_row(buf, A.target, row);
                 }
-                verifier_mask(buf);
+                verifier_mask(buf, quads ? kNoTokenWord : E::kNegInfWord);
                 ntw = nw == -INFINITY ? 0.f : nw;
-                double Zw = verifier_lane_sum(buf, ntw);
+                double Zw = verifier_lane_sum(buf, ntw, quads);
                 if (lane_sums) {
                     int ol = tid;
                     asm volatile("" : "+v"(ol));
@@ -928,7 +1000,7 @@ void stream_kernel(const RowArgs A)
                 } else {
                     Zw = wave_sum(Zw);
                 }
-                verifier_redo(buf, ntw, Zw);
+                verifier_redo(buf, ntw, Zw, tquads);
                 if (lane == 0) { sm_nt[wave] = ntw; sm_Z[wave] = Zw; }
             }
             if (lane == 0) {
@@ -945,9 +1017,9 @@ void stream_kernel(const RowArgs A)
                     Shift k0;
                     if constexpr (RAD) {
                         fw0 = pow2_of(sm_ref[1] - n);
-                        k0 = shift_of(sm_e0, fuse_row(S / fw0, A.a, A.b));
+                        k0 = shift_of(sm_e0, fuse_row(S / fw0, ra, rb));
                     } else {
-                        k0 = shift_of((float)(S / (double)V), fuse_row(S, A.a, A.b));
+                        k0 = shift_of((float)(S / (double)V), fuse_row(S, ra, rb));
                     }
                     kq[0] = (double)k0.kl * fw0; kq[1] = (double)k0.kw * fw0; kq[2] = (double)k0.kc;
                     ku = 1.0;
@@ -984,7 +1056,7 @@ void stream_kernel(const RowArgs A)
                 __builtin_amdgcn_sched_barrier(0);
                 load_row(buf, A.target, row);
             }
-            verifier_stats(buf, nw, ntw, Zw);
+            verifier_stats(buf, nw, ntw, Zw, tquads);
             if (lane == 0) { sm_nt[wave] = ntw; sm_Z[wave] = Zw; }
         }
         // The next centre row goes in flight before the barrier and thread 0's bookkeeping -- except where this
@@ -1011,7 +1083,7 @@ void stream_kernel(const RowArgs A)
             if constexpr (decltype(by_lanes)::value) {
                 const float nt_l = sm_nt[src];
                 nt = row16_max(nt_l);
-                Z = row16_sum(lane < NW && nt_l != -INFINITY ? sm_Z[src] * pow2_of(nt_l - nt) : 0.0);
+                Z = row16_sum(ln < NW && nt_l != -INFINITY ? sm_Z[src] * pow2_of(nt_l - nt) : 0.0);
             } else {
 #pragma unroll
                 for (int w = 0; w < NW; ++w) nt = fmaxf(nt, sm_nt[w]);
@@ -1030,7 +1102,7 @@ void stream_kernel(const RowArgs A)
             if constexpr (LANES) {
                 const float nt_l = sm_nt[src];
                 ntq = row16_max(nt_l);
-                Zq = row16_sum_f(lane < NW && nt_l != -INFINITY ? ldexpf((float)sm_Z[src], (int)fmaxf(nt_l - ntq, -200.f)) : 0.f);
+                Zq = row16_sum_f(ln < NW && nt_l != -INFINITY ? ldexpf((float)sm_Z[src], (int)fmaxf(nt_l - ntq, -200.f)) : 0.f);
             } else {
 #pragma unroll
                 for (int w = 0; w < NW; ++w) ntq = fmaxf(ntq, sm_nt[w]);
@@ -1073,14 +1145,37 @@ void stream_kernel(const RowArgs A)
                 // and exponentials of every token alive for this branch, in registers the hot path does not have)
                 asm volatile("" : "+v"(ntref));
                 const float qfac = (float)((ntw == -INFINITY ? 0.0 : pow2_of(ntw - nt)) / Z);
+                // (a centre row in transposed slots: the verifier row's tokens likewise, or, where that row may not go through
+                // the matrix cores, the centre row's put in order)
                 auto residuals = [&](int j, float (&r)[EPV]) {
-                    float tv[EPV];
+                    if constexpr (MATRIX) {
+                        if (quads && tquads) {
+                            float tz[EPV];
+                            bf16_scaled(buf[j], bf16_scale(dt), tz);
+#pragma unroll
+                            for (int k = 0; k < EPV; ++k) {
+                                float ek = e[j * EPV + k];
+                                asm volatile("" : "+v"(ek));
+                                r[k] = fmaxf(fmaf(exp2_scaled(tz[k], ntref), qfac, -(ek * pfac)), 0.f);
+                            }
+                            return;
+                        }
+                    }
+                    float tv[EPV], ev[EPV];
                     E::unpack(buf[j], tv);
 #pragma unroll
+                    for (int k = 0; k < EPV; ++k) ev[k] = e[j * EPV + k];
+                    if constexpr (MATRIX) {
+                        if (quads) {
+#pragma unroll
+                            for (int g = 0; g < EPV; g += 4) quad_transpose(ev[g], ev[g + 1], ev[g + 2], ev[g + 3], dt);
+                        }
+                    }
+#pragma unroll
                     for (int k = 0; k < EPV; ++k) {
-                        float ek = e[j * EPV + k];
+                        float ek = ev[k];
                         asm volatile("" : "+v"(ek));
-                        r[k] = fmaxf(fmaf(exp2_ref(tv[k], ntref), qfac, -(ek * pfac)), 0.f);
+                        r[k] = fmaxf(fmaf(E::exp2_ref(tv[k], ntref), qfac, -(ek * pfac)), 0.f);
                     }
                 };
                 // Piece totals.  Eight vectors per lane: the eight lane sums are reduced over the wave together -- two DPP
@@ -1165,6 +1260,12 @@ void stream_kernel(const RowArgs A)
                             if (j == jstar) {                      // uniform; the register arrays keep constant indices
                                 float r[EPV];
                                 residuals(j, r);
+                                if constexpr (MATRIX) {
+                                    if (quads && tquads) {
+#pragma unroll
+                                        for (int g = 0; g < EPV; g += 4) quad_transpose(r[g], r[g + 1], r[g + 2], r[g + 3], dt);
+                                    }
+                                }
                                 float s = 0.f;
 #pragma unroll
                                 for (int k = 0; k < EPV; ++k) s += r[k];
@@ -1251,7 +1352,7 @@ void stream_kernel(const RowArgs A)
                 if constexpr (NW >= 16) {
 #pragma unroll
                     for (int i = 0; i < NQ; ++i) {
-                        const double mine = lane < NW ? sm_q5[src * NQ + i] : 0.0;
+                        const double mine = ln < NW ? sm_q5[src * NQ + i] : 0.0;
                         t[i] = i == 7 ? (double)row16_max((float)mine) : row16_sum(mine);
                     }
                 } else {

@@ -1623,3 +1623,44 @@ def test_bad_arguments_raise(ciar):
         ciar.quantify(c, None, ciar.Params(radius_max=16.5))
     with pytest.raises(TypeError):
         ciar.quantify(c.half(), None, ciar.Params())
+
+
+# ---- bf16 rows widened by the matrix cores -----------------------------------------------------------------------
+
+@pytest.mark.parametrize("V,stride", [(65, 72), (2047, 2048), (2056, 2056), (4097, 4104), (8191, 8192), (16384, 16384),
+                                      (32003, 32008), (65529, 65536)])
+@pytest.mark.parametrize("tensor_radius", [False, True])
+def test_bf16_rows_with_masked_and_extreme_tokens(ciar, oracle, V, stride, tensor_radius):
+    """A token that is an infinity, or too large for the packed maximum, sends its wave's tokens over the vector ALUs: rows
+    with such tokens in the centre row, the verifier row or both, next to ordinary ones, at the edges of the tiles."""
+    g = torch.Generator(device="cuda").manual_seed(V)
+    rand = lambda *s: torch.rand(*s, device="cuda", generator=g)
+    low = torch.finfo(torch.bfloat16).min
+    masks = [(None, ""), (-math.inf, "c"), (-math.inf, "t"), (-math.inf, "ct"), (low, "ct"), (low, "t"), (-1e37, "c"), (-3e36, "ct"),
+             (-2.65e36, "ct"), (-1e30, "c")]
+    N = 3 * len(masks)
+    c = torch.zeros(N, stride, device="cuda")
+    c[:, :V] = 2.0 * torch.randn(N, V, device="cuda", generator=g)
+    c[1] -= 90.0                                                          # nothing but negative logits
+    c[2] = 40.0 * c[2]                                                    # very spread
+    t = c + 0.7 * torch.randn(N, stride, device="cuda", generator=g)
+    for i, (m, where) in enumerate(masks):
+        if m is None:
+            continue
+        for r, hit in ((3 * i, rand(V) < 0.3), (3 * i + 1, torch.arange(V, device="cuda") < min(600, V - 8)),
+                       (3 * i + 2, torch.arange(V, device="cuda") == V - 1)):
+            if "c" in where:
+                c[r, :V] = torch.where(hit, torch.full_like(c[r, :V], m), c[r, :V])
+            if "t" in where:
+                t[r, :V] = torch.where(hit, torch.full_like(t[r, :V], m), t[r, :V])
+    c, t = c.to(torch.bfloat16), t.to(torch.bfloat16)
+    if stride > V:
+        c[:, V:] = float("nan")
+        t[:, V:] = float("nan")
+    live = torch.where(torch.isfinite(c[:, :V]) & (c[:, :V] > -1e20), c[:, :V].float(), torch.full((), -1e30, device="cuda"))
+    ids = torch.argmax(live + torch.where(live > -1e20, 3.0 * rand(N, V), torch.zeros((), device="cuda")), 1).to(torch.int32)
+    ua = 0.3 + 0.7 * torch.randint(0, 1 << 20, (N,), device="cuda", generator=g).float() / (1 << 20)
+    ur = torch.randint(0, 1 << 24, (N,), device="cuda", generator=g).float() / (1 << 24)
+    raw = _raw_radius(N, stride, V, torch.bfloat16, seed=V) if tensor_radius else None
+    P = ciar.Params(radius_scale=1.0, window=4, tau=1e-3) if tensor_radius else ciar.Params(confidence=0.9, window=4, tau=1e-3)
+    _run_case(ciar, oracle, c[:, :V] if stride == V else c, t, ids, ua, ur, P, vocab=V, tag=f"masks V={V}", radius=raw)
