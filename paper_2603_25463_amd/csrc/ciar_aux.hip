@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256) void dense_kernel(const RowArgs A, float* __re
     // gl, gw of one token: p^l = Bc gl, p^u - p^l = Wc gw (tensor-radius mode: Bc = Wc = 1 / S)
     auto token = [&](int i, float& e, float& gl, float& gw) {
         e = Elt<T>::exp2_ref(load_logit(c, i), n);
-        if (rad) fuse_token_rad(e, load_logit(rad, i), fr, rm, gl, gw);
+        if (rad) fuse_token_rad<T>(e, load_logit(rad, i), fr, rm, gl, gw);
         else fuse_token(e, fr, gl, gw);
     };
     double q5[5];

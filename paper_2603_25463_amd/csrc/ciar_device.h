@@ -191,6 +191,21 @@ __device__ __forceinline__ void bf16_scaled(const u32x4& r, const Bf16Scale& m, 
 #pragma unroll
     for (int k = 0; k < 4; ++k) { z[k] = za[k]; z[4 + k] = zb[k]; }
 }
+// the tokens as they are, in the same slots (a diagonal of ones: one product)
+__device__ __forceinline__ s16x4 bf16_unit(int lane)
+{
+    const uint32_t h = 0x3f80u << ((uint32_t)(lane & 1) * 16u);
+    const bool first = (lane & 2) == 0;
+    return __builtin_bit_cast(s16x4, u32x2{first ? h : 0u, first ? 0u : h});
+}
+__device__ __forceinline__ void bf16_widened(const u32x4& r, const s16x4& m, float* z)
+{
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    const f32x4 za = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(s16x4, u32x2{r.x, r.y}), m, zero, 0, 0, 0);
+    const f32x4 zb = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(s16x4, u32x2{r.z, r.w}), m, zero, 0, 0, 0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) { z[k] = za[k]; z[4 + k] = zb[k]; }
+}
 // Token index of slot k (of 4 g + r) of this thread's vector, from the first token of the workgroup's vectors: slot_base + 4 g +
 // slot_step r; `quads` = the slots are transposed.
 __device__ __forceinline__ int slot_base(bool quads, int tid, int per_vec)
@@ -227,6 +242,7 @@ __device__ __forceinline__ uint32_t pk_max3(uint32_t a, uint32_t b, uint32_t c)
     asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(m) : "v"(a), "v"(b), "v"(c));
     return m;
 }
+__device__ __forceinline__ bool any_huge(uint32_t w) { return (w & 0x7c00u) == 0x7c00u || (w & 0x7c000000u) == 0x7c000000u; }
 template <int N>
 __device__ __forceinline__ uint32_t top_words(const u32x4 (&v)[N])
 {
@@ -395,7 +411,7 @@ __device__ __forceinline__ float wave_top(uint32_t v, bool& ordinary)
     v = dpp_pk_max<kRowBcast31, 0xc>(v);
     const uint32_t u = (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
     const float m = fmaxf(bits_f(u & 0xffff0000u), bits_f(u << 16));
-    ordinary = (u & 0x7c00u) != 0x7c00u && (u & 0x7c000000u) != 0x7c000000u && m > bits_f(kNoTokenWord & 0xffff0000u);
+    ordinary = !any_huge(u) && m > bits_f(kNoTokenWord & 0xffff0000u);
     return m;
 }
 
@@ -545,11 +561,17 @@ __device__ __forceinline__ double radius_of(double raw, double kappa, double rma
 
 // a - 1 = e^r - 1 of a tensor-radius token, r = min(kappa Softplus(raw), rmax); am1_max = e^rmax - 1.
 // UNIT (kappa = 1, the Interval Head as the paper defines it): e^Softplus(raw) = 1 + e^raw, so a - 1 = e^raw, capped:
-// one exponential, no logarithm, and no cancellation in a - 1 however small the radius is.
-template <bool UNIT>
+// one exponential, no logarithm, and no cancellation in a - 1 however small the radius is.  (bf16: the same floats from the
+// matrix cores' products, am1_scaled.)
+__device__ __forceinline__ float am1_scaled(float z, float am1_max)     // z = kBf16Scale raw
+{
+    return fminf(__builtin_amdgcn_exp2f(z * kBf16ToLog2e), am1_max);
+}
+template <typename T, bool UNIT>
 __device__ __forceinline__ float radius_am1(float raw, float kappa, float rmax, float am1_max)
 {
-    if constexpr (UNIT) return fminf(__builtin_amdgcn_exp2f(fmaf(raw, kLog2eLo, raw * kLog2eHi)), am1_max);
+    if constexpr (UNIT && sizeof(T) == 2) return am1_scaled(raw * kBf16Scale, am1_max);
+    else if constexpr (UNIT) return fminf(__builtin_amdgcn_exp2f(fmaf(raw, kLog2eLo, raw * kLog2eHi)), am1_max);
     else return __builtin_amdgcn_exp2f(radius_r(raw, kappa, rmax) * 1.44269504f) - 1.0f;
 }
 
@@ -557,11 +579,8 @@ __device__ __forceinline__ float radius_am1(float raw, float kappa, float rmax, 
 // b = 1/a the lower bound's denominator times a is dl = 1 + (a-1)(1-x) (no cancellation: both terms >= 0), and
 //   p^l S = e / dl,   p^u S = a e / du (du = 1 + (a-1) x),   (p^u - p^l) S = (a-1)(a+1) e (1-x) / (du dl),
 // so that neither b nor a second reciprocal is needed.
-template <bool UNIT>
-__device__ __forceinline__ void fuse_token_rad(float e, float raw, const FuseRow& r, float kappa, float rmax,
-                                               float am1_max, float& pl, float& w)
+__device__ __forceinline__ void fuse_token_am1(float e, float am1, const FuseRow& r, float& pl, float& w)
 {
-    const float am1 = radius_am1<UNIT>(raw, kappa, rmax, am1_max);
     const float om = fmaf(e, r.nil, fmaf(e, r.nih, 1.0f));        // 1 - x
     const float x = -e * r.nih;
     const float du = fmaf(am1, x, 1.0f);
@@ -570,14 +589,20 @@ __device__ __forceinline__ void fuse_token_rad(float e, float raw, const FuseRow
     pl = g * du;
     w = (am1 * (am1 + 2.0f)) * (g * om);
 }
+template <typename T, bool UNIT>
+__device__ __forceinline__ void fuse_token_rad(float e, float raw, const FuseRow& r, float kappa, float rmax,
+                                               float am1_max, float& pl, float& w)
+{
+    fuse_token_am1(e, radius_am1<T, UNIT>(raw, kappa, rmax, am1_max), r, pl, w);
+}
 
 // The same with the complement of the width (see fuse_token_wide), in the same units:
 // ec = 1 - (p^u_i - p^l_i) = (a - 2 (a-1) x (1-x)) / (du dl).
-template <bool UNIT>
+template <typename T, bool UNIT>
 __device__ __forceinline__ void fuse_token_rad_wide(float e, float raw, const FuseRow& r, float kappa, float rmax,
                                                     float am1_max, float& pl, float& w, float& ec)
 {
-    const float am1 = radius_am1<UNIT>(raw, kappa, rmax, am1_max);
+    const float am1 = radius_am1<T, UNIT>(raw, kappa, rmax, am1_max);
     const float om = fmaf(e, r.nil, fmaf(e, r.nih, 1.0f));        // 1 - x
     const float x = -e * r.nih;
     const float du = fmaf(am1, x, 1.0f);
@@ -595,17 +620,19 @@ __device__ __forceinline__ RadiusMode radius_mode(const RowArgs& A)
 {
     return {A.kappa == 1.0, (float)A.kappa, (float)A.rmax, A.am1_max};
 }
+template <typename T>
 __device__ __forceinline__ void fuse_token_rad(float e, float raw, const FuseRow& r, const RadiusMode& m, float& pl,
                                                float& w)
 {
-    if (m.unit) fuse_token_rad<true>(e, raw, r, m.kappa, m.rmax, m.am1_max, pl, w);
-    else fuse_token_rad<false>(e, raw, r, m.kappa, m.rmax, m.am1_max, pl, w);
+    if (m.unit) fuse_token_rad<T, true>(e, raw, r, m.kappa, m.rmax, m.am1_max, pl, w);
+    else fuse_token_rad<T, false>(e, raw, r, m.kappa, m.rmax, m.am1_max, pl, w);
 }
+template <typename T>
 __device__ __forceinline__ void fuse_token_rad_wide(float e, float raw, const FuseRow& r, const RadiusMode& m,
                                                     float& pl, float& w, float& ec)
 {
-    if (m.unit) fuse_token_rad_wide<true>(e, raw, r, m.kappa, m.rmax, m.am1_max, pl, w, ec);
-    else fuse_token_rad_wide<false>(e, raw, r, m.kappa, m.rmax, m.am1_max, pl, w, ec);
+    if (m.unit) fuse_token_rad_wide<T, true>(e, raw, r, m.kappa, m.rmax, m.am1_max, pl, w, ec);
+    else fuse_token_rad_wide<T, false>(e, raw, r, m.kappa, m.rmax, m.am1_max, pl, w, ec);
 }
 
 // Vocabularies of at most this many tokens take fp64 token arithmetic (see fuse_sums_tiny, dro_row_tiny_kernel).
@@ -744,10 +771,10 @@ __device__ __forceinline__ bool finish_row(const RowArgs& A, int64_t row, const 
                 if constexpr (RAD_TOP) {
                     const RadiusMode rm = radius_mode(A);
                     float plf, wf;
-                    fuse_token_rad(etop, raw_top, fuse_row_inv(recip(S), fa, fb), rm, plf, wf);
+                    fuse_token_rad<T>(etop, raw_top, fuse_row_inv(recip(S), fa, fb), rm, plf, wf);
                     glf = (double)plf; gwf = (double)wf;
-                    const double am1 = (double)(rm.unit ? radius_am1<true>(raw_top, rm.kappa, rm.rmax, rm.am1_max)
-                                                        : radius_am1<false>(raw_top, rm.kappa, rm.rmax, rm.am1_max));
+                    const double am1 = (double)(rm.unit ? radius_am1<T, true>(raw_top, rm.kappa, rm.rmax, rm.am1_max)
+                                                        : radius_am1<T, false>(raw_top, rm.kappa, rm.rmax, rm.am1_max));
                     gl = ed / (1.0 + am1 * om);
                     gw = am1 * (am1 + 2.0) * om * gl / (1.0 + am1 * x);
                 } else {

@@ -66,11 +66,11 @@ __global__ __launch_bounds__(256) void ensemble_kernel(const RowArgs A, const in
         float gl, gw;
         if constexpr (WIDE) {
             float ec;
-            if (rad) fuse_token_rad_wide(e, rval, fr, rm, gl, gw, ec);
+            if (rad) fuse_token_rad_wide<T>(e, rval, fr, rm, gl, gw, ec);
             else fuse_token_wide(e, fr, gl, gw, ec);
             c += (double)ec;
         } else {
-            if (rad) fuse_token_rad(e, rval, fr, rm, gl, gw);
+            if (rad) fuse_token_rad<T>(e, rval, fr, rm, gl, gw);
             else fuse_token(e, fr, gl, gw);
         }
         d = fma(sm_cw[h], (double)gw, fma(sm_cl[h], (double)gl, d));
@@ -187,11 +187,11 @@ __global__ __launch_bounds__(256) void ensemble_kernel(const RowArgs A, const in
                     float gl, gw;
                     if constexpr (WIDE) {
                         float ec;
-                        if constexpr (RADc) fuse_token_rad_wide<UNITc>(e, rval, fr, rm.kappa, rm.rmax, rm.am1_max, gl, gw, ec);
+                        if constexpr (RADc) fuse_token_rad_wide<T, UNITc>(e, rval, fr, rm.kappa, rm.rmax, rm.am1_max, gl, gw, ec);
                         else fuse_token_wide(e, fr, gl, gw, ec);
                         cc += (double)ec;
                     } else {
-                        if constexpr (RADc) fuse_token_rad<UNITc>(e, rval, fr, rm.kappa, rm.rmax, rm.am1_max, gl, gw);
+                        if constexpr (RADc) fuse_token_rad<T, UNITc>(e, rval, fr, rm.kappa, rm.rmax, rm.am1_max, gl, gw);
                         else fuse_token(e, fr, gl, gw);
                     }
                     if constexpr (NOLOW) d = fma(cw, (double)gw, d);
@@ -985,7 +985,7 @@ void ensemble_sweep_kernel(const RowArgs A, const int H, const int64_t head_stri
 #pragma unroll
                         for (int k = 0; k < EPV; ++k) {
                             float gl, gw;                          // (a slot past the row's end holds e = 0: both are 0)
-                            fuse_token_rad<UNIT>(e[j * EPV + k], rv[j * EPV + k], fr, rm.kappa, rm.rmax, rm.am1_max, gl, gw);
+                            fuse_token_rad<T, UNIT>(e[j * EPV + k], rv[j * EPV + k], fr, rm.kappa, rm.rmax, rm.am1_max, gl, gw);
                             const double w = (double)gw;
                             g0 += (double)gl; g1 += w;
                             D[j * EPV + k] = fma(cw, w, D[j * EPV + k]);
@@ -1087,7 +1087,7 @@ void ensemble_sweep_kernel(const RowArgs A, const int H, const int64_t head_stri
             for (int i = 0; i < kSweepTokens; ++i) {
                 const float ek = Elt<T>::exp2_ref(e[i], n == -INFINITY ? 0.f : n);
                 float gl, gw;
-                if constexpr (RAD) fuse_token_rad<UNIT>(ek, rv[i], fr, rm.kappa, rm.rmax, rm.am1_max, gl, gw);
+                if constexpr (RAD) fuse_token_rad<T, UNIT>(ek, rv[i], fr, rm.kappa, rm.rmax, rm.am1_max, gl, gw);
                 else fuse_token(ek, fr, gl, gw);
                 D[i] = fma(cw, (double)gw, fma(cl, (double)gl, D[i]));
                 if ((i & 1) == 1) __builtin_amdgcn_sched_barrier(0);

@@ -34,6 +34,7 @@ constexpr int kRadVecs = 8, kRadVecsWide16 = 4;
 // of 0.5 to 4; 1e-5 to 4e-5 at a third of it.  At a hundredth it would be 5e-7 to 2e-6, but there rows of an untrained head pay
 // for the sweep in calls with a small clamp: 762 x 16384 fp32, radius_max 2, 209 us against 24.5.)
 constexpr double kCrowded = 1e-5;
+constexpr double kCapGuard = 1e-5;     // how far from its cap a sum of bounds taken in fp32 (good to ~1e-6) has to be to settle it
 template <int THREADS> constexpr int radius_rows() { return THREADS >= 512 ? 128 : THREADS / 4; }   // most rows of a workgroup
 
 template <bool WIDE> struct RadiusRow { double S, q[WIDE ? 7 : 5]; float n, mc, raw_top, big; };   // see RowStats, finish_row
@@ -80,6 +81,51 @@ __device__ void radius_row_fp64(const RowArgs& A, int64_t row, double (*red)[64]
     for (int i = 0; i < 5; ++i) st.q[i] = total(q[i]);
     st.kl = kl; st.kw = kw;
     st.mode = kSumsDirect;
+}
+
+// The five sums of a row in the units of its logits' reference, by the whole workgroup from the logits: the token arithmetic of
+// radius_kernel, for a row whose caps turned out not to be inactive.
+template <typename T, int THREADS, bool UNIT>
+__device__ void radius_row_full(const RowArgs& A, int64_t row, double (*red)[64], RowStats& st)
+{
+    using E = Elt<T>;
+    constexpr int EPV = E::kPerVec, NW = THREADS / 64;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = tid >> 6, V = A.V;
+    const gbytes crow = (gbytes)(static_cast<const T*>(A.draft) + row_offset(A, row));
+    const gbytes rrow = (gbytes)(static_cast<const T*>(A.radius) + row_offset(A, row));
+    const float n = st.n == -INFINITY ? 0.f : st.n, kappa = (float)A.kappa, rmax = (float)A.rmax;
+    const FuseRow fr = fuse_row_inv(recip(st.S), A.a, A.b);
+    double q[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int j = tid; j * EPV < V; j += THREADS) {
+        u32x4 cb = *(gvec)(crow + (uint32_t)j * 16u), rb = *(gvec)(rrow + (uint32_t)j * 16u);
+        E::mask_tail(cb, j * EPV, V);
+        E::zero_tail(rb, j * EPV, V);
+        float cv[EPV], rv[EPV];
+        E::unpack(cb, cv);
+        E::unpack(rb, rv);
+#pragma unroll
+        for (int k = 0; k < EPV; ++k) {
+            float pl, w;
+            fuse_token_rad<T, UNIT>(E::exp2_ref(cv[k], n), rv[k], fr, kappa, rmax, A.am1_max, pl, w);
+            const double dl = (double)pl, dw = (double)w;
+            q[0] += dl; q[1] += dw;
+            q[2] = fma(dl, dl, q[2]); q[3] = fma(dw, dw, q[3]); q[4] = fma(dl, dw, q[4]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 5; ++i) q[i] = wave_sum(q[i]);
+    __syncthreads();                                               // the slots may still be read from the last use
+    if (lane == 0) {
+#pragma unroll
+        for (int i = 0; i < 5; ++i) red[wave][i] = q[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 5; ++i) st.q[i] = row16_sum(lane < NW ? red[lane < NW ? lane : 0][i] : 0.0);
+    st.kl = 0.0; st.kw = 0.0;
+    st.mode = kSumsFull;
 }
 
 // A.N rows: H > 1: [H, P], H heads of P = A.head_rows positions, the H rows of a position one after another in one workgroup,
@@ -301,7 +347,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
                     float rv[EPV];
                     E::unpack(rb[u], rv);
                     if (WIDE && j == 0) {
-                        const float am1 = radius_am1<UNIT>(rv[0], kappa, rmax, am1_max);
+                        const float am1 = radius_am1<T, UNIT>(rv[0], kappa, rmax, am1_max);
                         complements = __builtin_amdgcn_ballot_w64(tid * EPV < V && !(-(am1 + 2.0f) * e[0] * fr.nih > 1.0f)) == 0;
                         if (complements) big = 0.f;
                     }
@@ -309,7 +355,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
 #pragma unroll
                         for (int k = 0; k < EPV; ++k) {
                             float pl, w, ec;
-                            fuse_token_rad_wide<UNIT>(e[j * EPV + k], rv[k], fr, kappa, rmax, am1_max, pl, w, ec);
+                            fuse_token_rad_wide<T, UNIT>(e[j * EPV + k], rv[k], fr, kappa, rmax, am1_max, pl, w, ec);
                             if ((j * THREADS + tid) * EPV + k < V) {   // (past the row's end ec is not 0)
                                 const double dc = (double)ec;
                                 q[NQ - 2] += dc; q[NQ - 1] = fma(dc, dc, q[NQ - 1]);
@@ -323,7 +369,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
 #pragma unroll
                         for (int k = 0; k < EPV; ++k) {
                             float pl, w;                               // (a slot past the row's end holds e = 0: both are 0)
-                            fuse_token_rad<UNIT>(e[j * EPV + k], rv[k], fr, kappa, rmax, am1_max, pl, w);
+                            fuse_token_rad<T, UNIT>(e[j * EPV + k], rv[k], fr, kappa, rmax, am1_max, pl, w);
                             const double dl = (double)pl, dw = (double)w;
                             q[0] += dl; q[1] += dw;
                             q[2] = fma(dl, dl, q[2]); q[3] = fma(dw, dw, q[3]); q[4] = fma(dl, dw, q[4]);
@@ -434,11 +480,481 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
     }
 }
 
-template <typename T, int THREADS, int NVEC, bool UNIT, bool ARGMAX, bool WIDE>
+// The same for calls whose rows follow one another (see launch_radius_tile): where a row's caps are expected to be inactive a wave
+// takes the sums of the widths alone (`lean` below), and bf16 rows go through the matrix cores.  2048 x 16384, three heads, bf16
+// 112.4 -> 102.5 us; 1531 x 12345 fp32 36.3 -> 35.2.
+template <typename T, int THREADS, int NVEC, bool UNIT, bool ARGMAX>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4)))
+void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
+{
+    using E = Elt<T>;
+    constexpr int EPV = E::kPerVec, EPT = NVEC * EPV, NW = THREADS / 64, ROWS = radius_rows<THREADS>();
+    constexpr int CHUNK = THREADS * EPV;                           // tokens of one vector of every lane
+    constexpr bool MATRIX = sizeof(T) == 2;                        // rows go through the matrix cores (see bf16_scaled)
+    constexpr bool SCALED = MATRIX && UNIT;                        // the radius row's tokens are taken times kBf16Scale
+    extern __shared__ u32x4 sm_next[];                             // [NVEC][THREADS]: the row in flight
+    // exchange slots of a row: written before its barrier, read behind it; rows alternate between two sets
+    __shared__ float sm_ref[2][NW];
+    constexpr int NQ = 5;                                          // sums of a row
+    __shared__ double sm_S[2][NW], sm_tot[2][NW][NQ];
+    __shared__ double sm_red[NW][64];                              // per wave: [the sums of the row before, S_w][eight groups of lanes]
+    // (LDS is what the places on a compute unit are counted by: a slot per wave and parked row instead of this pair costs the
+    // 128-lane instances one of eight, 58333 x 3000 fp32 270 -> 350 us)
+    __shared__ int sm_pi[2][ARGMAX ? NW : 1];
+    // parked rows
+    __shared__ RadiusRow<false> pk[ROWS];
+    __shared__ int pk_id[ARGMAX ? ROWS : 1];
+    __shared__ uint8_t pk_fp64[ROWS], pk_flag[ROWS];
+
+    // (the lane's index is asked for anew wherever it is used, through an empty asm: no LDS address formed from it is held in
+    // registers, or spilled, through the loop -- and a reload would wait for the row in flight)
+    auto my_tid = []() {
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+    auto uniform = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int V = A.V;
+    const int nch = (V + CHUNK - 1) / CHUNK;                       // vectors of a lane that hold tokens at all
+    const int last_vec = (V + EPV - 1) / EPV - 1;
+    const uint32_t P = (uint32_t)(H > 1 ? A.head_rows : A.N), step = gridDim.x;
+    const float kappa = uniform((float)A.kappa), rmax = uniform((float)A.rmax), am1_max = A.am1_max;
+    // this workgroup's rows: H of each of its positions blockIdx.x, blockIdx.x + step, ...
+    const uint32_t mine = blockIdx.x < P ? (P - blockIdx.x + step - 1u) / step : 0u;
+    const int count = (int)mine * H;                               // <= ROWS: the launcher sizes the grid accordingly
+    if (count == 0) return;
+
+    using lds_ptr = __attribute__((address_space(3))) void*;
+    using glb_ptr = const __attribute__((address_space(1))) void*;
+    auto offset_of = [&](uint32_t pos, int h) {
+        return H > 1 ? (int64_t)h * A.head_stride + (int64_t)pos * A.stride : row_offset(A, pos);
+    };
+    auto row_base = [&](const void* rows, uint32_t pos, int h) {
+        const uint64_t b = (uint64_t)(static_cast<const T*>(rows) + offset_of(pos, h));
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+        const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+        return (gbytes)(((uint64_t)hi << 32) | lo);
+    };
+    // vector j of a row goes in flight (lane l of a wave lands 16 l bytes behind the address the wave names); lanes past the end
+    // of the row fetch its last vector
+    const uint32_t last_off = (uint32_t)last_vec * 16u;
+    auto fetch = [&](gbytes base, int j, int tid) {
+        if (j < nch)                                               // uniform
+            __builtin_amdgcn_global_load_lds((glb_ptr)(base + min((uint32_t)(j * THREADS + tid) * 16u, last_off)),
+                                             (lds_ptr)(sm_next + j * THREADS + wave * 64), 16, 0, kNonTemporal);
+    };
+    // wave 0: a row's sums over the waves, parked
+    auto park = [&](int at, int p) {
+        const int lane = my_tid() & 63, grp = lane >> 3, part = lane & 7;
+        double v = 0.0;
+        if (grp < NQ) {
+            if (part < NW) v = sm_tot[p][part][grp];
+            if (NW > 8) v += sm_tot[p][part + (NW > 8 ? 8 : 0)][grp];
+        }
+        v = dpp_add<0xB1, 0xf>(v);                                 // lane ^ 1, lane ^ 2, the other quad of the eight
+        v = dpp_add<0x4E, 0xf>(v);
+        v = dpp_add<0x141, 0xf>(v);
+        if (grp < NQ && part == 0) pk[at].q[grp] = v;
+    };
+    // the sums of a wave reduced together: every lane's value -> groups of eight lanes (three DPP steps) -> LDS
+    auto put = [&](double v, int which, int lane) {
+        v = dpp_add<0xB1, 0xf>(v);
+        v = dpp_add<0x4E, 0xf>(v);
+        v = dpp_add<0x141, 0xf>(v);
+        if ((lane & 7) == 0) sm_red[wave][which * 8 + (lane >> 3)] = v;
+    };
+    auto get = [&](int lane) {                                     // lanes 8 q ... 8 q + 7: quantity q over the wave
+        double v = sm_red[wave][lane < 8 * (NQ + 1) ? lane : 0];
+        v = dpp_add<0xB1, 0xf>(v);
+        v = dpp_add<0x4E, 0xf>(v);
+        return dpp_add<0x141, 0xf>(v);
+    };
+
+    uint32_t pos = blockIdx.x;
+    int h = 0;
+    {
+        const gbytes base = row_base(A.draft, pos, h);
+        const int tid = my_tid();
+#pragma unroll
+        for (int j = 0; j < NVEC; ++j) fetch(base, j, tid);
+    }
+    if constexpr (THREADS < 1024) {
+        if (count > 1) __builtin_amdgcn_s_setprio(3);
+    }
+    for (int done = 0;; ++done) {
+        const int p = done & 1;
+        const int tid = my_tid(), lane = tid & 63;
+        const bool has_next = done + 1 < count;                    // uniform
+        // ---- 1: the centre row ------------------------------------------------------------------------------------------
+        float e[EPT];
+        float mw, nw;
+        bool quads = false;                                        // the slots of e[] are transposed (uniform over the wave)
+        double Sl = 0.0;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        {
+            u32x4 buf[NVEC];
+#pragma unroll
+            for (int j = 0; j < NVEC; ++j) buf[j] = sm_next[j * THREADS + tid];
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            const gbytes base = row_base(A.radius, pos, h);
+#pragma unroll
+            for (int j = 0; j < NVEC; ++j) fetch(base, j, tid);
+            if constexpr (MATRIX) {
+#pragma unroll
+                for (int j = 0; j < NVEC; ++j)
+                    if ((j + 1) * CHUNK > V) E::mask_tail(buf[j], (j * THREADS + tid) * EPV, V, kNoTokenWord);   // uniform
+                mw = wave_top(top_words(buf), quads);
+            }
+            if (MATRIX && __builtin_expect(quads, true)) {
+                nw = E::ref_of(mw);
+                if constexpr (ARGMAX) {
+                    int at = INT_MAX;
+#pragma unroll
+                    for (int j = NVEC - 1; j >= 0; --j) {
+                        float v[EPV];
+                        E::unpack(buf[j], v);
+#pragma unroll
+                        for (int k = EPV - 1; k >= 0; --k)
+                            if (v[k] == mw) at = j * EPV + k;
+                    }
+                    at = wave_min_i(at == INT_MAX ? INT_MAX : (at / EPV * THREADS + tid) * EPV + at % EPV);
+                    if (lane == 0) sm_pi[p][wave] = at;
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                const Bf16Scale bs = bf16_scale(tid);
+                bf16_scaled(buf[0], bs, &e[0]);
+#pragma unroll
+                for (int j = 0; j < NVEC; ++j) {
+                    if (j + 1 < NVEC) bf16_scaled(buf[j + 1], bs, &e[(j + 1) * EPV]);   // (the matrix cores one vector ahead)
+                    if (j < nch) {
+#pragma unroll
+                        for (int k = 0; k < EPV; ++k) {
+                            e[j * EPV + k] = exp2_scaled(e[j * EPV + k], nw);
+                            Sl += (double)e[j * EPV + k];
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < NVEC; ++j) {
+                    if ((j + 1) * CHUNK > V) E::mask_tail(buf[j], (j * THREADS + tid) * EPV, V);      // uniform
+                    E::unpack(buf[j], &e[j * EPV]);
+                }
+                mw = wave_max(max_of(e));
+                nw = E::ref_of(mw);
+                const float nref = nw == -INFINITY ? 0.f : nw;
+                if constexpr (ARGMAX) {
+                    int at = INT_MAX;
+#pragma unroll
+                    for (int i = EPT - 1; i >= 0; --i)
+                        if (e[i] == mw) at = i;
+                    at = wave_min_i(at == INT_MAX ? INT_MAX : (at / EPV * THREADS + tid) * EPV + at % EPV);
+                    if (lane == 0) sm_pi[p][wave] = at;
+                }
+#pragma unroll
+                for (int j = 0; j < NVEC; ++j) {
+                    if (j < nch) {
+#pragma unroll
+                        for (int k = 0; k < EPV; ++k) {
+                            e[j * EPV + k] = Elt<T>::exp2_ref(e[j * EPV + k], nref);
+                            Sl += (double)e[j * EPV + k];
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+        put(Sl, NQ, lane);
+        {
+            const double v = get(lane);
+            const int grp = lane >> 3;
+            if ((lane & 7) == 0) {
+                if (grp < NQ) { if (done > 0) sm_tot[p ^ 1][wave][grp] = v; }
+                else if (grp == NQ) sm_S[p][wave] = v;
+            }
+            if (lane == 0) sm_ref[p][wave] = mw;
+        }
+        lds_barrier();
+        if (wave == 0 && done > 0) park(done - 1, p ^ 1);
+        const int src = lane < NW ? lane : 0;
+        const float m_l = sm_ref[p][src], n_l = Elt<T>::ref_of(m_l), mc = row16_max(m_l), n = Elt<T>::ref_of(mc);
+        const double S = row16_sum(lane < NW && n_l != -INFINITY ? sm_S[p][src] * pow2_of(n_l - n) : 0.0);
+        if constexpr (ARGMAX) {
+            if (wave == 0) {                                       // the lowest index of the waves that hold the maximum
+                const int best = wave_min_i(lane < NW && m_l == mc ? sm_pi[p][src] : INT_MAX);
+                if (lane == 0) pk_id[done] = best == INT_MAX ? 0 : best;
+            }
+        }
+        if (tid == 0) { pk[done].S = S; pk[done].n = n; pk[done].mc = mc; }
+        const double fw = nw == -INFINITY ? 0.0 : pow2_of(nw - n);                         // this wave's e_i are 1 / fw too large
+        const double Su = nw == -INFINITY ? 1.0 : ldexp(S, (int)fminf(n - nw, 1000.f));   // S in this wave's units
+        const bool top = (double)Elt<T>::exp2_ref(mc, n == -INFINITY ? 0.f : n) > 0.5 * S;         // uniform over the workgroup
+        FuseRow fr;
+        {
+            const double inv = recip(Su);
+            const float nih = (float)-inv;
+            fr = {0.f, uniform(nih), uniform((float)(-inv - (double)nih)), 0.f, 0.f};
+        }
+        // ---- 2: the radius row; its slots take the next centre row as they are read ---------------------------------------
+        uint32_t npos = pos;
+        int nh = h;
+        if (has_next) {
+            if (++nh == H) { nh = 0; npos += step; }
+        }
+        const gbytes next = row_base(A.draft, npos, nh);
+        double q[NQ];
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) q[i] = 0.0;
+        // A row with a token above 1/2: its raw radius is parked for finish_row by the lane that has it, in the wave with the row's
+        // largest token.  (No other token has its e: two of them would be all of S.)
+        const bool search = top && mw == mc;                       // uniform over the wave
+        const float etop = uniform(Elt<T>::exp2_ref(mw, nw == -INFINITY ? 0.f : nw));
+        float raw_top = 0.f;
+        bool found = false;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        // Where the caps are inactive -- they are on almost every row -- Omega and Sigma want the sums of the widths alone (see
+        // kSumsWidthOnly).  Whether they are is known when the row is summed, so a wave that expects it (no token above 1/2, radii
+        // that are not all small: half of its lanes' first tokens have a - 1 > 1/8) takes those two in fp64 and sum p^l in fp32,
+        // which tells (kCapGuard), and marks the row by a sum that is no number; a row that was expected wrong is taken again
+        // (radius_row_full).  21 instead of 27 issues per token.
+        // Token widths of a row whose largest probability is at most 1/8 need 1/S as one float (1 - x to 1e-8).
+        const bool split = (double)Elt<T>::exp2_ref(mc, n == -INFINITY ? 0.f : n) > 0.125 * S;
+        auto am1_of = [&](float v) {
+            if constexpr (SCALED) return am1_scaled(v, am1_max);
+            else return radius_am1<T, UNIT>(v, kappa, rmax, am1_max);
+        };
+        // (an infinite radius may not go through the matrix cores; looked for ahead of the pass, all vectors at once)
+        bool widen = MATRIX && quads;                              // uniform over the wave
+        if (MATRIX && quads) {
+            uint32_t huge = 0u;
+#pragma unroll
+            for (int j = 0; j < NVEC; ++j) {
+                if (j < nch) {
+                    const u32x4 r = sm_next[j * THREADS + tid];
+                    huge = pk_max3(j == 0 ? pk_max3(r.x, r.x, r.y) : pk_max3(huge, r.x, r.y), r.z, r.w);
+                }
+                if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+            widen = __builtin_amdgcn_ballot_w64(any_huge(huge)) == 0;
+        }
+        bool lean = false;                                         // uniform over the wave
+        if (!top && (!MATRIX || widen)) {
+            const float raw = sizeof(T) == 4 ? bits_f(sm_next[tid].x) : bits_f(sm_next[tid].x << 16);
+            lean = !A.normalize || __popcll(__builtin_amdgcn_ballot_w64(am1_of(SCALED ? raw * kBf16Scale : raw) > 0.125f)) >= 32;
+        }
+        float sum_pl = 0.f;
+        constexpr int GROUP = sizeof(T) == 2 ? 2 : 4;              // vectors taken at a time
+        // the pass over the vectors, in an instance of its own per kind (0: all five sums, 1: the widths', 2: those with 1 - x from
+        // the two-part 1 / S), each with row constants of its own: what the instances have in common is otherwise formed for all
+        // tokens ahead of the branch, and spilled
+        auto pass = [&](auto kind) {
+            constexpr int KIND = decltype(kind)::value;
+            FuseRow f = fr;
+            asm volatile("" : "+v"(f.nih), "+v"(f.nil));
+#pragma unroll
+            for (int g = 0; g < NVEC; g += GROUP) {
+                u32x4 rb[GROUP];
+#pragma unroll
+                for (int u = 0; u < GROUP; ++u) rb[u] = sm_next[(g + u) * THREADS + tid];
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                if (has_next) {
+#pragma unroll
+                    for (int u = 0; u < GROUP; ++u) fetch(next, g + u, tid);
+                }
+#pragma unroll
+                for (int u = 0; u < GROUP; ++u) {
+                    const int j = g + u;
+                    if (j < nch) {                                     // uniform: the vectors hold tokens
+                        if ((j + 1) * CHUNK > V) E::zero_tail(rb[u], (j * THREADS + tid) * EPV, V);
+                        float rv[EPV];                                 // SCALED: times kBf16Scale
+                        if (MATRIX && (KIND > 0 || __builtin_expect(widen, true))) {
+                            if constexpr (SCALED) bf16_scaled(rb[u], bf16_scale(tid), rv);
+                            else if constexpr (MATRIX) bf16_widened(rb[u], bf16_unit(tid), rv);
+                        } else {
+                            E::unpack(rb[u], rv);
+                            if (MATRIX && quads) {
+#pragma unroll
+                                for (int k = 0; k < EPV; k += 4) quad_transpose(rv[k], rv[(k + 1) % EPV], rv[(k + 2) % EPV], rv[(k + 3) % EPV], tid);
+                            }
+                            if constexpr (SCALED) {
+#pragma unroll
+                                for (int k = 0; k < EPV; ++k) rv[k] *= kBf16Scale;
+                            }
+                        }
+                        if constexpr (KIND > 0) {
+#pragma unroll
+                            for (int k = 0; k < EPV; ++k) {
+                                const float ek = e[j * EPV + k], am1 = am1_of(rv[k]);
+                                float om = fmaf(ek, f.nih, 1.0f);
+                                if constexpr (KIND == 2) om = fmaf(ek, f.nil, om);
+                                const float du = fmaf(am1, -ek * f.nih, 1.0f), dl = fmaf(am1, om, 1.0f);
+                                const float g1 = ek * __builtin_amdgcn_rcpf(du * dl);
+                                sum_pl = fmaf(g1, du, sum_pl);
+                                const double dw = (double)((am1 * (am1 + 2.0f)) * (g1 * om));
+                                q[1] += dw;
+                                q[3] = fma(dw, dw, q[3]);
+                            }
+                        } else {
+#pragma unroll
+                            for (int k = 0; k < EPV; ++k) {
+                                float pl, w;                               // (a slot past the row's end holds e = 0: both are 0)
+                                fuse_token_am1(e[j * EPV + k], am1_of(rv[k]), f, pl, w);
+                                const double dl = (double)pl, dw = (double)w;
+                                q[0] += dl; q[1] += dw;
+                                q[2] = fma(dl, dl, q[2]); q[3] = fma(dw, dw, q[3]); q[4] = fma(dl, dw, q[4]);
+                            }
+                        if (__builtin_expect(search, false)) {
+#pragma unroll
+                            for (int k = 0; k < EPV; ++k) {
+                                const bool is = e[j * EPV + k] == etop;
+                                raw_top = is ? rv[k] : raw_top;
+                                found = found || is;
+                            }
+                        }
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        };
+        // (what the branches expect decides what lies next to each other: a call of a few rows waits for its instructions to
+        // arrive, and longer for those behind a jump)
+        if (__builtin_expect(lean, true)) {
+            if (ARGMAX || __builtin_expect(split, false)) pass(std::integral_constant<int, 2>{});
+            else pass(std::integral_constant<int, 1>{});
+        } else {
+            pass(std::integral_constant<int, 0>{});
+        }
+        if (found) pk[done].raw_top = SCALED ? raw_top / kBf16Scale : raw_top;   // (one lane of the workgroup; the quotient is exact)
+        {
+            const double f2 = fw * fw;                             // to row units
+            if (lean) {
+                put((double)sum_pl * fw, 0, lane); put(q[1] * fw, 1, lane); put(q[3] * f2, 3, lane);
+                // (the fifth sum's slots hold anything; the constant through an empty asm, or it is held through the row loop)
+                int nan_hi = 0x7ff80000;
+                asm volatile("" : "+v"(nan_hi));
+                if ((lane & 7) == 0) sm_red[wave][2 * 8 + (lane >> 3)] = __hiloint2double(nan_hi, nan_hi);
+            } else {
+                put(q[0] * fw, 0, lane); put(q[1] * fw, 1, lane);
+                put(q[2] * f2, 2, lane); put(q[3] * f2, 3, lane); put(q[4] * f2, 4, lane);
+            }
+        }
+        if (!has_next) break;
+        pos = npos; h = nh;
+        // wave priority by progress: whoever of the workgroups of a compute unit is behind is served first
+        if constexpr (THREADS < 1024) {
+            if (done + 1 < (count + 3) >> 2) __builtin_amdgcn_s_setprio(3);
+            else if (done + 1 < (count + 1) >> 1) __builtin_amdgcn_s_setprio(2);
+            else if (done + 1 < (3 * count + 3) >> 2) __builtin_amdgcn_s_setprio(1);
+            else __builtin_amdgcn_s_setprio(0);
+        }
+    }
+    {
+        const int lane = my_tid() & 63;
+        const double v = get(lane);
+        if ((lane & 7) == 0 && lane < 8 * NQ) sm_tot[(count - 1) & 1][wave][lane >> 3] = v;
+    }
+    __syncthreads();
+    if (wave == 0) park(count - 1, (count - 1) & 1);
+    __syncthreads();
+    // ---- a lane per row ---------------------------------------------------------------------------------------------------
+    auto stats_of = [&](int at, bool& known) {
+        RowStats st;
+        known = true;
+        st.S = pk[at].S; st.Z = 0.0; st.n = pk[at].n; st.nt = 0.f; st.mc = pk[at].mc;
+#pragma unroll
+        for (int i = 0; i < 5; ++i) st.q[i] = pk[at].q[i];
+        st.kl = 0.0; st.kw = 0.0; st.mode = kSumsFull;
+        if (st.q[2] != st.q[2]) {                         // the widths' sums, and whether they do
+            const double Sl = st.q[0] / st.S, Su = Sl + st.q[1] / st.S;
+            known = !A.normalize || (Sl <= A.cap_lo * (1.0 - kCapGuard) && Su >= A.cap_hi * (1.0 + kCapGuard));
+            st.mode = kSumsWidthOnly;
+            st.q[0] = 0.0; st.q[2] = 0.0; st.q[4] = 0.0;
+        }
+        return st;
+    };
+    auto row_of = [&](int at) { return (int64_t)(at % H) * P + blockIdx.x + (int64_t)(at / H) * step; };
+    auto finish = [&](int at, const RowStats& st, auto again) {
+        const int64_t r = row_of(at);
+        const int64_t off = row_offset(A, r);
+        int xid = ARGMAX ? pk_id[ARGMAX ? at : 0] : A.ids ? A.ids[ids_index(A, r)] : 0;
+        xid = xid < 0 ? 0 : (xid >= V ? V - 1 : xid);
+        const float cx = load_logit(static_cast<const T*>(A.draft) + off, xid);
+        const float rawx = load_logit(static_cast<const T*>(A.radius) + off, xid);
+        // (the vote counts the flags as written)
+        if (finish_row<T, true>(A, r, st, cx, 0.f, rawx, 0.f, true, false, pk[at].raw_top, &pk_flag[at], again)) return true;
+        A.stats[r] = st;
+        return false;
+    };
+    constexpr uint8_t kFull = 1, kExact = 2;                       // what a row is taken again with: all sums in fp32, in fp64
+    auto crowded = [&](const RowStats& st) {
+        return [&](const RowScore& rs) {
+            const double etop = (double)Elt<T>::exp2_ref(st.mc, st.n == -INFINITY ? 0.f : st.n);
+            const double Vd = (double)V, mean = rs.omega / Vd;
+            return !(rs.sigma * rs.sigma >= kCrowded * mean * mean) || (A.precise_flat && etop * Vd <= 2.0 * st.S);
+        };
+    };
+    // (no outputs: the statistics alone, for the Ensemble's second sweep, which looks after its own flat rows)
+    const bool outputs = A.p_lo || A.p_mid || A.p_hi || A.omega || A.sigma || A.score || A.flags;
+    {
+        const int t = my_tid();
+        if (t < count) {
+            bool known;
+            const RowStats st = stats_of(t, known);
+            if (!known) {
+                pk_fp64[t] = kFull;
+            } else if (!outputs) {
+                pk_fp64[t] = 0;
+                A.stats[row_of(t)] = st;
+            } else {
+                pk_fp64[t] = finish(t, st, crowded(st)) ? kExact : 0;
+            }
+        }
+    }
+    __syncthreads();
+    for (int at = 0; at < count; ++at) {
+        if (!pk_fp64[at]) continue;                                // uniform
+        bool known;
+        RowStats st = stats_of(at, known);
+        if (pk_fp64[at] == kFull) {
+            radius_row_full<T, THREADS, UNIT>(A, row_of(at), sm_red, st);
+            __syncthreads();
+            if (my_tid() == 0) {
+                pk_fp64[at] = outputs && finish(at, st, crowded(st)) ? kExact : 0;
+                if (!outputs) A.stats[row_of(at)] = st;
+            }
+            __syncthreads();
+            if (!pk_fp64[at]) continue;
+        }
+        radius_row_fp64<T, THREADS>(A, row_of(at), sm_red, st);
+        if (my_tid() == 0) finish(at, st, NeverAgain{});
+    }
+    if (votes) {
+        __syncthreads();
+        const int t = my_tid();
+        if (t < (int)mine) {
+            int yes = 0;
+            for (int i = 0; i < H; ++i) yes += pk_flag[t * H + i];
+            votes[blockIdx.x + (int64_t)t * step] = (uint8_t)(2 * yes > H);
+        }
+    }
+}
+
+template <typename T, int THREADS, int NVEC, bool UNIT, bool ARGMAX, bool WIDE, bool LEAN>
+constexpr auto radius_entry()
+{
+    if constexpr (LEAN) return &radius_lean_kernel<T, THREADS, NVEC, UNIT, ARGMAX>;
+    else return &radius_kernel<T, THREADS, NVEC, UNIT, ARGMAX, WIDE>;
+}
+
+template <typename T, int THREADS, int NVEC, bool UNIT, bool ARGMAX, bool WIDE, bool LEAN>
 hipError_t launch_radius_cfg(const RowArgs& a, int heads, uint8_t* votes, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     constexpr int kPerUnit = 1024 / THREADS;                       // workgroups a compute unit holds
     const int64_t resident = (int64_t)kPerUnit * compute_units(), positions = a.N / heads;
+    constexpr auto kernel = radius_entry<T, THREADS, NVEC, UNIT, ARGMAX, WIDE, LEAN>();
     // Several heads: the rows of a position in one workgroup, which takes the vote, or -- where the chip then goes through
     // fewer rows in turn -- every row for itself and the vote in a launch of its own.  (fp32, by position / by row: 8 positions
     // of 8 heads 1024 tokens 31.8 / 10.8 us, 16384 tokens 49.2 / 13.5, 32768 tokens 79.8 / 19.4; 300 of 5 heads 1024 tokens
@@ -449,7 +965,7 @@ hipError_t launch_radius_cfg(const RowArgs& a, int heads, uint8_t* votes, hipStr
     const bool by_row = heads > 1 && (THREADS < 512 ? 2 * turns_by_row <= turns : 10 * turns_by_row <= 9 * turns);
     if (by_row && !votes) heads = 1;
     if (by_row && votes) {
-        const hipError_t e = launch_radius_cfg<T, THREADS, NVEC, UNIT, ARGMAX, WIDE>(a, 1, nullptr, stream, ev_start, ev_stop);
+        const hipError_t e = launch_radius_cfg<T, THREADS, NVEC, UNIT, ARGMAX, WIDE, LEAN>(a, 1, nullptr, stream, ev_start, ev_stop);
         return e != hipSuccess ? e : launch_vote(a.flags, heads, positions, votes, stream);
     }
     constexpr unsigned lds = NVEC * 16u * THREADS;                 // 4 to 128 KiB
@@ -461,7 +977,7 @@ hipError_t launch_radius_cfg(const RowArgs& a, int heads, uint8_t* votes, hipStr
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
         std::lock_guard<std::mutex> lock(guard);
         if (!raised[dev]) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&radius_kernel<T, THREADS, NVEC, UNIT, ARGMAX, WIDE>),
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
             raised[dev] = true;
@@ -471,20 +987,34 @@ hipError_t launch_radius_cfg(const RowArgs& a, int heads, uint8_t* votes, hipStr
     const int64_t g = whole_rounds(a.N / heads, per_wg, resident);
     const dim3 grid((unsigned)g), block(THREADS);
     if (ev_start && ev_stop)
-        hipExtLaunchKernelGGL((radius_kernel<T, THREADS, NVEC, UNIT, ARGMAX, WIDE>), grid, block, lds, stream, ev_start, ev_stop, 0, a, heads,
+        hipExtLaunchKernelGGL(kernel, grid, block, lds, stream, ev_start, ev_stop, 0, a, heads,
                               votes);
     else
-        hipLaunchKernelGGL((radius_kernel<T, THREADS, NVEC, UNIT, ARGMAX, WIDE>), grid, block, lds, stream, a, heads, votes);
+        hipLaunchKernelGGL(kernel, grid, block, lds, stream, a, heads, votes);
     return hipGetLastError();
 }
 template <typename T, int THREADS, int NVEC, bool WIDE>
 hipError_t launch_radius_tile(const RowArgs& a, int heads, uint8_t* votes, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     const bool argmax = a.ids == nullptr && (a.p_lo || a.p_mid || a.p_hi);
-    if (a.kappa == 1.0) return argmax ? launch_radius_cfg<T, THREADS, NVEC, true, true, WIDE>(a, heads, votes, stream, ev_start, ev_stop)
-                                      : launch_radius_cfg<T, THREADS, NVEC, true, false, WIDE>(a, heads, votes, stream, ev_start, ev_stop);
-    return argmax ? launch_radius_cfg<T, THREADS, NVEC, false, true, WIDE>(a, heads, votes, stream, ev_start, ev_stop)
-                  : launch_radius_cfg<T, THREADS, NVEC, false, false, WIDE>(a, heads, votes, stream, ev_start, ev_stop);
+    // The widths' sums alone where rows follow one another.  With a row per compute unit at most, a call waits for one row's
+    // instructions to arrive, of which there are more then (8 x 16384 fp32 with small radii 11.3 us without, 12.2 with; bf16 11.6 and
+    // 12.4); fp32 rows without drafted ids spill with it (2048 x 4096 22.8 and 25.3);
+    // with a clamp that small no wave would expect inactive caps (2048 x 16384 bf16 44.3 and 46.6).
+    if constexpr (!WIDE) {
+        if (a.N > compute_units() && !(argmax && sizeof(T) == 4) && (a.am1_max > 0.125f || !a.normalize)) {
+            if constexpr (sizeof(T) == 2) {
+                if (argmax) return a.kappa == 1.0 ? launch_radius_cfg<T, THREADS, NVEC, true, true, false, true>(a, heads, votes, stream, ev_start, ev_stop)
+                                                  : launch_radius_cfg<T, THREADS, NVEC, false, true, false, true>(a, heads, votes, stream, ev_start, ev_stop);
+            }
+            return a.kappa == 1.0 ? launch_radius_cfg<T, THREADS, NVEC, true, false, false, true>(a, heads, votes, stream, ev_start, ev_stop)
+                                  : launch_radius_cfg<T, THREADS, NVEC, false, false, false, true>(a, heads, votes, stream, ev_start, ev_stop);
+        }
+    }
+    if (a.kappa == 1.0) return argmax ? launch_radius_cfg<T, THREADS, NVEC, true, true, WIDE, false>(a, heads, votes, stream, ev_start, ev_stop)
+                                      : launch_radius_cfg<T, THREADS, NVEC, true, false, WIDE, false>(a, heads, votes, stream, ev_start, ev_stop);
+    return argmax ? launch_radius_cfg<T, THREADS, NVEC, false, true, WIDE, false>(a, heads, votes, stream, ev_start, ev_stop)
+                  : launch_radius_cfg<T, THREADS, NVEC, false, false, WIDE, false>(a, heads, votes, stream, ev_start, ev_stop);
 }
 template <typename T, int NVEC, bool WIDE>
 hipError_t launch_radius_lanes(const RowArgs& a, int heads, uint8_t* votes, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop)

@@ -275,14 +275,14 @@ __device__ __forceinline__ void fuse_sums_rad(const float (&e)[NVEC * Elt<T>::kP
             const bool live = (j * THREADS + tid) * EPV + k < V;
             if constexpr (WIDE) {
                 float ec;
-                fuse_token_rad_wide<UNIT>(e[j * EPV + k], raw[k], fr, kappa, rmax, am1_max, pl, w, ec);
+                fuse_token_rad_wide<T, UNIT>(e[j * EPV + k], raw[k], fr, kappa, rmax, am1_max, pl, w, ec);
                 if (live) {
                     const double dc = (double)(ec - sh.kc);
                     c1 += dc; c2 = fma(dc, dc, c2);
                     big = fmaxf(big, ec);
                 }
             } else {
-                fuse_token_rad<UNIT>(e[j * EPV + k], raw[k], fr, kappa, rmax, am1_max, pl, w);
+                fuse_token_rad<T, UNIT>(e[j * EPV + k], raw[k], fr, kappa, rmax, am1_max, pl, w);
             }
             const double dl = live ? (double)(pl - sh.kl) : 0.0, dw = live ? (double)(w - sh.kw) : 0.0;
             a0[k & 1] += dl;
@@ -878,8 +878,8 @@ void stream_kernel(const RowArgs A)
                 Shift k;
                 k.kc = 0.f;
                 if constexpr (RAD) {
-                    if constexpr (WIDE) fuse_token_rad_wide(eref, raw0, r, rm, k.kl, k.kw, k.kc);
-                    else fuse_token_rad(eref, raw0, r, rm, k.kl, k.kw);
+                    if constexpr (WIDE) fuse_token_rad_wide<T>(eref, raw0, r, rm, k.kl, k.kw, k.kc);
+                    else fuse_token_rad<T>(eref, raw0, r, rm, k.kl, k.kw);
                 } else {
                     if constexpr (WIDE) fuse_token_wide(eref, r, k.kl, k.kw, k.kc);
                     else fuse_token<true>(eref, r, k.kl, k.kw);

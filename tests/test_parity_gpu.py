@@ -1664,3 +1664,39 @@ def test_bf16_rows_with_masked_and_extreme_tokens(ciar, oracle, V, stride, tenso
     raw = _raw_radius(N, stride, V, torch.bfloat16, seed=V) if tensor_radius else None
     P = ciar.Params(radius_scale=1.0, window=4, tau=1e-3) if tensor_radius else ciar.Params(confidence=0.9, window=4, tau=1e-3)
     _run_case(ciar, oracle, c[:, :V] if stride == V else c, t, ids, ua, ur, P, vocab=V, tag=f"masks V={V}", radius=raw)
+
+
+@pytest.mark.parametrize("V,dtype", [(1000, torch.float32), (4096, torch.bfloat16), (16384, torch.float32), (20001, torch.bfloat16)])
+@pytest.mark.parametrize("kw", [dict(), dict(radius_scale=0.7), dict(normalize=False)])
+def test_radius_rows_whose_caps_are_not_what_they_look_like(ciar, oracle, V, dtype, kw):
+    """The quantifier's waves expect inactive caps from the row's largest probability and the radii of a few of its tokens:
+    rows that look so and have an active cap (small radii on the likely tokens, large ones elsewhere), rows that look the
+    other way round, rows whose waves disagree, infinite raw radii; more rows than compute units and fewer."""
+    stride = -(-V // 8) * 8
+    g = torch.Generator(device="cuda").manual_seed(V)
+    N = 600
+    c = 0.5 * torch.randn(N, stride, device="cuda", generator=g)
+    raw = torch.randn(N, stride, device="cuda", generator=g)
+    at = torch.randint(0, V, (N, 3), device="cuda", generator=g)
+    kind = torch.arange(N, device="cuda") % 7
+    for k in range(3):                                                     # three likely tokens of about 1/3 each
+        c.scatter_(1, at[:, k:k + 1], torch.where(kind < 4, 9.0 + math.log(V / 1000.0) + 0.01 * k, 0.5)[:, None].expand(N, 1))
+    tiny = torch.full((N, 1), -9.0, device="cuda")
+    for k in range(3):
+        raw.scatter_(1, at[:, k:k + 1], torch.where((kind < 2)[:, None], tiny, raw.gather(1, at[:, k:k + 1])))
+    raw[kind == 2] -= 9.0                                                  # small radii throughout
+    raw[kind == 4] = torch.where(torch.arange(stride, device="cuda") < V // 2, raw[kind == 4], raw[kind == 4] - 9.0)
+    raw[kind == 5] = torch.where(torch.rand(raw[kind == 5].shape, device="cuda", generator=g) < 0.1, -math.inf, raw[kind == 5])
+    raw[kind == 6] = torch.where(torch.rand(raw[kind == 6].shape, device="cuda", generator=g) < 0.1, 60.0, raw[kind == 6])
+    c, raw = c.to(dtype), raw.to(dtype)
+    ids = at[:, 0].to(torch.int32)
+    P = ciar.Params(**{"radius_scale": 1.0, "tau": 0.01, **kw})
+    OP = _oparams(oracle, P)
+    for rows in (N, 40):
+        say(f"[caps] V={V} {dtype} rows={rows} {kw}")
+        o = oracle.quantify(c[:rows].cpu(), ids[:rows].cpu().numpy(), OP, vocab=V, radius=raw[:rows].cpu())
+        for use in (ids[:rows], None):
+            q = ciar.quantify(c[:rows], use, P, vocab=V, radius=raw[:rows])
+            torch.cuda.synchronize()
+            parity.check_floats(q, o, keys=parity.FLOAT_KEYS if use is not None else ("omega", "sigma", "score"))
+            parity.check_flags(q["flags"], o, float(np.float32(P.tau)))
