@@ -329,7 +329,11 @@ constexpr bool draws_in_stream()
 // sm_draw / row_id of a rejected row whose draw is still to be made (by resample_kernel)
 constexpr int kDrawPending = -2;
 
-template <typename T, int THREADS, int NVEC, bool DO_Q, bool DO_V, bool RAD, bool WIDE>
+// WHOLE: every row fills the tile.  Such calls have instances of their own, without the code for rows that do not (vectors past the
+// end clamped, tokens masked): a call of a few rows waits for its instructions to arrive, and longer for those behind a jump (8 x
+// 16384 fp32 13.8 -> 13.0 us, 256 rows 16.1 -> 15.5, 2048 rows 51.5 -> 50.4).  The others tell at run time: with masks that are
+// wanted in any case the compiler forms them ahead of the row loop and spills them (up to 500 B).
+template <typename T, int THREADS, int NVEC, bool DO_Q, bool DO_V, bool RAD, bool WIDE, bool WHOLE>
 __global__ __launch_bounds__(THREADS)
 __attribute__((amdgpu_waves_per_eu(target_waves<T, THREADS, NVEC, RAD, DO_V>())))
 void stream_kernel(const RowArgs A)
@@ -357,7 +361,9 @@ void stream_kernel(const RowArgs A)
     // verifier row's partition sum are reduced over the wave together (wave_sum3) once the verifier row has been summed.
     // (These instances are bound by their vector instructions: workload 5 1951 -> 1905 us.  The fp32 instances, which
     // wait for memory, measured 1 % slower with it and keep one reduction per sum.)
-    constexpr bool MATRIX = sizeof(T) == 2 && !RAD; // the centre row through the matrix cores (see bf16_scaled)
+    // bf16 rows go through the matrix cores (see bf16_scaled; with a radius tensor the verifier row only) where a lane holds enough of
+    // a row for it to pay: with one or two vectors a row is a chain of latencies (871 x 1162 verified 10.2 us without, 10.7 with).
+    constexpr bool MATRIX_T = sizeof(T) == 2 && NVEC >= 4, MATRIX = MATRIX_T && !RAD;
     constexpr bool BATCH3 = DO_Q && DO_V && !RAD && !WIDE && sizeof(T) == 2;
     constexpr int NQ = WIDE ? 8 : 5;                // interval sums a wave hands over
     // A row with a token above 1/2 and a radius tensor: finish_row wants that token's raw radius.  It is picked up in the
@@ -407,7 +413,7 @@ void stream_kernel(const RowArgs A)
         // (in scalar registers; the fp32 instances of eight and sixteen waves spill with it)
         if constexpr (sizeof(T) == 2 || THREADS == 256) { rm.kappa = uniform_f(rm.kappa); rm.rmax = uniform_f(rm.rmax); rm.am1_max = uniform_f(rm.am1_max); }
     }
-    const bool partial = V != NVEC * CHUNK;                        // uniform: the row does not fill the tile
+    const bool partial = !WHOLE && V != NVEC * CHUNK;              // uniform: the row does not fill the tile
     const int last_vec = (V + EPV - 1) / EPV - 1;
     const int nrows = (int)A.N;
     const int step = (int)gridDim.x;
@@ -471,7 +477,7 @@ void stream_kernel(const RowArgs A)
     // (the lane's share of the sum about the reference nref; quads: the tokens widened by the matrix cores)
     auto verifier_lane_sum = [&](u32x4 (&tb)[NVEC], float nref, bool quads) {
         float zacc[4] = {0.f, 0.f, 0.f, 0.f};
-        if constexpr (sizeof(T) == 2) {
+        if constexpr (MATRIX_T) {
             if (quads) {
                 const Bf16Scale bs = bf16_scale(opaque_tid());
                 float z[2][EPV];
@@ -502,13 +508,13 @@ void stream_kernel(const RowArgs A)
     auto verifier_redo = [&](u32x4 (&tb)[NVEC], float& ntw, double& Zw, bool& quads) {
         auto in_range = [&]() { return Zw >= 0x1p-40 && Zw <= 0x1p100; };   // (false for NaN)
         if constexpr (sizeof(T) == 2) {
-            if (quads && !in_range()) {                            // uniform over the wave
+            if (__builtin_expect(quads && !in_range(), false)) {                            // uniform over the wave
                 quads = false;
                 verifier_mask(tb, E::kNegInfWord);
                 Zw = wave_sum(verifier_lane_sum(tb, ntw, false));
             }
         }
-        if (!in_range()) {                                         // uniform over the wave
+        if (__builtin_expect(!in_range(), false)) {                // uniform over the wave
             float mt = -INFINITY;
 #pragma unroll
             for (int j = 0; j < NVEC; ++j) {
@@ -741,8 +747,7 @@ void stream_kernel(const RowArgs A)
         // 1.012 - 0.99 in the failing case), which multiplies the 1e-8 that a dominant token's vector loses by 45.
         double sacc[2] = {0.0, 0.0};
         // bf16 rows: the maximum from the packed words, the tokens widened by the matrix cores (`quads`: the slots of e[] are
-        // transposed, see bf16_scaled; uniform over the wave).  Not where the slots meet a radius tensor's, nor for a handful of
-        // tokens (their pass wants them in order).
+        // transposed, see bf16_scaled; uniform over the wave).  Not where the slots meet a radius tensor's.
         bool quads = false;
         if constexpr (MATRIX) {
             if (partial) {
@@ -751,9 +756,8 @@ void stream_kernel(const RowArgs A)
                 for (int j = 0; j < NVEC; ++j) mask_with(buf[j], (j * THREADS + ot) * EPV, kNoTokenWord);
             }
             mcw = wave_top(top_words(buf), quads);
-            if (NVEC == 1 && V <= kTinyVocab) quads = false;
         }
-        if (MATRIX && quads) {
+        if (MATRIX && __builtin_expect(quads, true)) {
             nw = Elt<T>::ref_of(mcw);
             const Bf16Scale bs = bf16_scale(opaque_tid());
             bf16_scaled(buf[0], bs, &e[0]);
@@ -859,7 +863,7 @@ void stream_kernel(const RowArgs A)
             __builtin_amdgcn_sched_barrier(0);
         }
         float ntw = -INFINITY;                                     // the reference this wave's Z_w is taken about
-        bool tquads = MATRIX ? quads : sizeof(T) == 2;             // the verifier row goes through the matrix cores
+        bool tquads = MATRIX ? quads : MATRIX_T;             // the verifier row goes through the matrix cores
         bool lane_sums = false;                                    // uniform: q5[1], q5[3] are still the lanes' own sums
         if constexpr (DO_Q) {
             // x_i = e_i fw / S: hand fuse_row the partition sum expressed in this wave's units
@@ -891,7 +895,7 @@ void stream_kernel(const RowArgs A)
             // lane 0 moves them to the common shift afterwards.
             bool near = false;
             Shift sh = {0.f, 0.f, 0.f};
-            if (flat) {
+            if (__builtin_expect(flat, false)) {
                 if constexpr (RAD) {
                     const float up = sm_ref[1] - nw;               // e0 is 2^up times larger in this wave's units
                     near = fabsf(up) <= 64.f;                      // uniform over the wave; false for inf and nan
@@ -916,7 +920,7 @@ void stream_kernel(const RowArgs A)
             const int base = slot_base(MATRIX && quads, MATRIX ? opaque_tid() : tid, EPV), step4 = slot_step(MATRIX && quads, EPV);
             bool tiny = false;
             if constexpr (NVEC == 1) tiny = V <= kTinyVocab;       // uniform
-            if (tiny) {
+            if (__builtin_expect(tiny, false)) {
                 if constexpr (NVEC == 1) {
                     if constexpr (RAD) {
                         __builtin_amdgcn_sched_barrier(0);
@@ -955,9 +959,9 @@ void stream_kernel(const RowArgs A)
                 fuse_sums_wide<THREADS, NVEC, EPV>(e, fr, sh, V, base, step4, q5);
 #pragma unroll
                 for (int i = 0; i < 5; ++i) q5[i] = wave_sum(q5[i]);
-            } else if (capless) {
+            } else if (__builtin_expect(capless, true)) {
                 if (partial)    fuse_sums<THREADS, NVEC, EPV, true, true, true>(e, fr, wp, sh, V, base, step4, q5);
-                else if (split) fuse_sums<THREADS, NVEC, EPV, true, true, false>(e, fr, wp, sh, V, base, step4, q5);
+                else if (__builtin_expect(split, false)) fuse_sums<THREADS, NVEC, EPV, true, true, false>(e, fr, wp, sh, V, base, step4, q5);
                 else            fuse_sums<THREADS, NVEC, EPV, true, false, false>(e, fr, wp, sh, V, base, step4, q5);
                 if constexpr (BATCH3) {
                     // reduced below, together with the verifier row's sum; until then the quads' sums wait in LDS
@@ -1008,7 +1012,7 @@ void stream_kernel(const RowArgs A)
                 double ku = fw;
                 const double f2 = fw * fw;
                 q5[0] *= fw; q5[1] *= fw; q5[2] *= f2; q5[3] *= f2; q5[4] *= f2;
-                if (flat && !near && !tiny) {
+                if (__builtin_expect(flat && !near && !tiny, false)) {
                     // Rare: this wave's sums are about 0.  Form the common shift the long way round, in row units
                     // (scalar radius) or in wave 0's (tensor radius), and move the sums to it:  with c = 0 - K and
                     // n tokens,  sum (d - K) = s1 + n c,  sum (d - K)^2 = s2 + 2 c s1 + n c^2,  likewise the cross
@@ -1117,7 +1121,7 @@ void stream_kernel(const RowArgs A)
             // lane that finishes the row decides in fp64 whether it counts (about one row in a few thousand)
             const int verdict = accept_quick(cx, tx, ua, n, ntq, Sf, Zq);
             if (tid == 0) sm_close[done] = (uint8_t)(verdict < 0);
-            if (verdict > 0) {
+            if (__builtin_expect(verdict > 0, true)) {
                 if (tid == 0) sm_draw[done] = -1;
             } else {
                 // p_i = e_i pfac, q_i = 2^(t_i log2e - ntw) qfac, res_i = max(0, q_i - p_i) rounded to fp32: every
@@ -1229,7 +1233,7 @@ void stream_kernel(const RowArgs A)
                 }
                 const double R = carry;
                 const float ur = sm_ur[done];
-                if (R > 0.0) {
+                if (__builtin_expect(R > 0.0, true)) {
                     const double thr = (double)ur * R;
                     int istar = -1;
                     double before = 0.0;
@@ -1244,7 +1248,7 @@ void stream_kernel(const RowArgs A)
                         }
                         prev_end = lane_value(run[p], 63);
                     }
-                    if (istar < 0) {                               // unreachable for u < 1; keeps the draw valid
+                    if (__builtin_expect(istar < 0, false)) {                               // unreachable for u < 1; keeps the draw valid
 #pragma unroll
                         for (int p = 0; p < PER; ++p) {
                             const unsigned long long live = __ballot(p * 64 + dlane < NT && tot[p] > 0.0);
@@ -1465,12 +1469,14 @@ hipError_t launch_stream_kernel(const RowArgs& a, StreamLaunch& L)
     b.finish = p.can_finish ? 1 : 0;
     b.unit = p.unit;
     b.win_count = p.windows_counted ? a.win_words : nullptr;
+    auto kernel = &stream_kernel<T, THREADS, NVEC, DO_Q, DO_V, RAD, WIDE, false>;
+    if constexpr (!WIDE) {
+        if (b.V == NVEC * THREADS * Elt<T>::kPerVec) kernel = &stream_kernel<T, THREADS, NVEC, DO_Q, DO_V, RAD, WIDE, true>;
+    }
     if (L.ev_start && L.ev_stop)
-        hipExtLaunchKernelGGL((stream_kernel<T, THREADS, NVEC, DO_Q, DO_V, RAD, WIDE>), dim3(p.grid), dim3(THREADS),
-                              0, L.stream, L.ev_start, L.ev_stop, 0, b);
+        hipExtLaunchKernelGGL(kernel, dim3(p.grid), dim3(THREADS), 0, L.stream, L.ev_start, L.ev_stop, 0, b);
     else
-        hipLaunchKernelGGL((stream_kernel<T, THREADS, NVEC, DO_Q, DO_V, RAD, WIDE>), dim3(p.grid), dim3(THREADS), 0,
-                           L.stream, b);
+        hipLaunchKernelGGL(kernel, dim3(p.grid), dim3(THREADS), 0, L.stream, b);
     return hipGetLastError();
 }
 
