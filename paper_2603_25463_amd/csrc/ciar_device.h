@@ -166,7 +166,7 @@ template <> struct Elt<bf16_t> {
 // x * kBf16Scale gives, bit for bit.
 // Slots: the tokens of a quad's four lanes come back transposed: slot 4 g + r of lane l holds token 4 g + (l & 3) of lane
 // (l & ~3) + r's vector.  Sums over a row do not care; whoever wants a slot's token index asks slot_base and slot_step.
-// An infinity would make its three neighbours 0 * inf: rows that may hold one are widened on the vector ALUs (ordinary_top; sums
+// An infinity would make its three neighbours 0 * inf: rows that may hold one are widened on the vector ALUs (wave_top; sums
 // that come out as no number).
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -234,7 +234,7 @@ __device__ __forceinline__ void quad_transpose(float& v0, float& v1, float& v2, 
 // The largest logit of a wave's bf16 words without unpacking them: as fp16 numbers bf16 patterns have the same order, and gfx950
 // takes the maximum of three packed pairs in one issue (a quarter of an issue per token; unpacked: a half, and the
 // unpacking).  Patterns that are infinities or no numbers in fp16 -- bf16 magnitudes from 2^121 on, masked tokens at -inf or the
-// type's lowest value among them -- come through as such (ordinary_top is false): then the wave's tokens are unpacked.
+// type's lowest value among them -- come through as such (`ordinary` is false in wave_top): then the wave's tokens are unpacked.
 constexpr uint32_t kNoTokenWord = 0xfbfffbffu;                     // below every ordinary logit: padding
 __device__ __forceinline__ uint32_t pk_max3(uint32_t a, uint32_t b, uint32_t c)
 {
