@@ -75,6 +75,9 @@ __device__ __forceinline__ double recip(double x)
     return fma(r, fma(-x, r, 1.0), r);
 }
 
+// Most binary orders that a wave's units lie below its row's when the row's sum is taken to them: with logits of 1e9 the sum itself
+// is up to 2^100 (2^1000 S overflowed, and recip of that is no number); the wave's tokens weigh nothing from 2^200 on.
+constexpr float kFarUnits = 900.f;
 // 2^k as a double for an integer-valued float difference k <= 0 (clamped: below 2^-1000 it is 0 anyway)
 __device__ __forceinline__ double pow2_of(float k) { return ldexp(1.0, (int)fmaxf(k, -1000.f)); }
 
@@ -88,9 +91,20 @@ __device__ __forceinline__ float exp2_scaled(float z, float n)         // z = kB
     return __builtin_amdgcn_exp2f(fmaf(z, kBf16ToLog2e, -n));
 }
 
+// Logits of large magnitude.  From 2^24 on a float reference n is a multiple of 2, 4, ..., 128 (up to 2^31), so that the largest
+// token's exponential is anything from 2^-83 to 2^83 instead of 1/2 to 1.  Sums, reciprocals and token widths hold that, and a
+// row masked throughout with -1e9, or a token forced with 1e9, comes out right (any logit up to a magnitude of 1.48e9; beyond, those
+// whose exponential the reference's rounding leaves in range).  Powers of 1 / S do not hold it, and ask ref_is_near.
+// Further up that exponential can overflow, and a wave of masked tokens (-1e30, say) would outweigh the others': where
+// `top`, the largest token's exponent about n, says so, n is raised by more than its own rounding.  (n = -inf, nothing but tokens at
+// -inf: top is no number, and n stays.)
+__device__ __forceinline__ float ref_above(float n, float top) { return top > 100.f ? fmaf(fabsf(n), 0x1p-22f, n) : n; }
+__device__ __forceinline__ bool ref_is_near(float n) { return !(fabsf(n) >= 0x1p24f); }
+
 template <typename T> struct Elt;
 template <> struct Elt<float> {
     static constexpr int kPerVec = 4;
+    static constexpr double kLog2e = (double)kLog2eHi + (double)kLog2eLo;          // as the exponentials have it
     __device__ static __forceinline__ float exp2_ref(float x, float n) { return ciar::exp2_ref(x, n); }
     __device__ static __forceinline__ float ref_of(float m) { return ciar::ref_of(m); }
     static constexpr uint32_t kNegInfWord = 0xff800000u;
@@ -118,13 +132,13 @@ template <> struct Elt<float> {
 struct bf16_t { uint16_t bits; };
 template <> struct Elt<bf16_t> {
     static constexpr int kPerVec = 8;
-    // ref_of, and where a reference that large is no longer good to an integer (masked tokens at -1e37, say) a little above it: no
-    // exponential of its tokens overflows, as with the two-part log2(e) of fp32 logits.
+    static constexpr double kLog2e = (double)kBf16Scale * (double)kBf16ToLog2e;    // as the exponentials have it
     __device__ static __forceinline__ float ref_of(float m)
     {
         const float n = ciar::ref_of(m);
-        return fabsf(n) < 0x1p24f || n == -INFINITY ? n : fmaf(fabsf(n), 0x1p-22f, n);
+        return ref_above(n, exp2_arg(m, n));
     }
+    __device__ static __forceinline__ float exp2_arg(float x, float n) { return fmaf(x * kBf16Scale, kBf16ToLog2e, -n); }
     // (the same number, bit for bit, as from the matrix cores' product: see bf16_scaled)
     __device__ static __forceinline__ float exp2_ref(float x, float n) { return exp2_scaled(x * kBf16Scale, n); }
     static constexpr uint32_t kNegInfWord = 0xff80ff80u;
@@ -251,6 +265,11 @@ __device__ __forceinline__ uint32_t top_words(const u32x4 (&v)[N])
     for (int j = 0; j < N; ++j) m = pk_max3(pk_max3(m, v[j].x, v[j].y), v[j].z, v[j].w);
     return m;
 }
+
+// ln of 2^(x log2(e) - n) in fp64, to stand next to sums of such numbers: with the log2(e) they are taken with, whose error a logit
+// of 1e8 multiplies to 1e-5.
+template <typename T>
+__device__ __forceinline__ double ln_exp2(float x, double n) { return fma((double)x, Elt<T>::kLog2e, -n) * kLn2; }
 
 template <typename T>
 __device__ __forceinline__ float load_logit(const T* row, int i)
@@ -701,10 +720,11 @@ __device__ __forceinline__ RowScore finish_score(const double* s, double S, floa
 // The accept test of a drafted token in the log domain, fp64 (Algorithm 1, "Cloud verification"):
 //   ln p_x = cx - n ln2 - ln S,  ln q_x = tx - nt ln2 - ln Z;  accepted iff ln u < min(0, ln q_x - ln p_x).
 // Returns whether the token is rejected.
+template <typename T>
 __device__ __forceinline__ bool reject_exact(float cx, float tx, float u, float n, float nt, double S, double Z)
 {
-    const double lp = ((double)cx - (double)n * kLn2) - log(S);
-    const double lq = ((double)tx - (double)nt * kLn2) - log(Z);
+    const double lp = ln_exp2<T>(cx, (double)n) - log(S);
+    const double lq = ln_exp2<T>(tx, (double)nt) - log(Z);
     const double lnu = log((double)u);                             // log(0) = -inf: always accepted
     return !(lnu < fmin(0.0, lq - lp));
 }
@@ -818,7 +838,7 @@ __device__ __forceinline__ bool finish_row(const RowArgs& A, int64_t row, const 
     }
     bool rej = false;
     if (do_v) {
-        rej = reject_exact(cx, tx, u, n, st.nt, S, st.Z);
+        rej = reject_exact<T>(cx, tx, u, n, st.nt, S, st.Z);
         if (A.accept) A.accept[row] = (uint8_t)(!rej);
         if (A.row_id && !rej) A.row_id[row] = -1;
     }

@@ -81,7 +81,7 @@ __global__ __launch_bounds__(256) void ensemble_kernel(const RowArgs A, const in
         // A handful of tokens: e as the streaming kernel summed it into S, so that 1 - x stays accurate as x -> 1.
         // A flat row: the fp64 exponential (every x is tiny; the fp32 one would leave 6e-8 of each width behind,
         // uncorrelated from token to token, where the widths themselves agree to 1e-6).
-        const double ed = V <= 64 ? (double)Elt<T>::exp2_ref(cval, sm_n[h]) : exp((double)cval - (double)sm_n[h] * kLn2);
+        const double ed = V <= 64 ? (double)Elt<T>::exp2_ref(cval, sm_n[h]) : exp(ln_exp2<T>(cval, (double)sm_n[h]));
         const double x = ed / sm_S[h], omx = fmax(0.0, sm_S[h] - ed) / sm_S[h];
         double a = A.a, b = A.b;
         if (rad) {
@@ -357,8 +357,8 @@ __device__ __forceinline__ FuseRow uniform_fr(FuseRow r)
     r.cu = uniform_f(r.cu); r.nih = uniform_f(r.nih); r.nil = uniform_f(r.nil); r.b = uniform_f(r.b); r.omb = uniform_f(r.omb);
     return r;
 }
-// 2^k as a double for an integer-valued float k of either sign (clamped to what a double holds)
-__device__ __forceinline__ double pow2_any(float k) { return ldexp(1.0, (int)fminf(fmaxf(k, -1000.f), 1000.f)); }
+// 2^k as a double for an integer-valued float k of either sign (clamped to what leaves a sum finite)
+__device__ __forceinline__ double pow2_any(float k) { return ldexp(1.0, (int)fminf(fmaxf(k, -1000.f), kFarUnits)); }
 
 // Ensemble in one sweep, for up to kFusedHeads heads with a scalar radius whose rows fit a 512-lane workgroup
 // (32 elements of a row per lane): every head's row of a position is read from memory once.  A workgroup takes one
@@ -619,7 +619,7 @@ void ensemble_fused_kernel(const RowArgs A, const int64_t head_stride)
                 const float is = -fr[h].nih, is2 = is * is;
                 pd[h][0] = uniform_f(A.wpoly[0] * is); pd[h][1] = uniform_f(A.wpoly[1] * is2);
                 pd[h][2] = uniform_f(A.wpoly[2] * (is2 * is)); pd[h][3] = uniform_f(A.wpoly[3] * (is2 * is2));
-                poly = poly && (double)emw[h] <= (double)A.wpoly_x * Sw_units[h];
+                poly = poly && ref_is_near(n[h]) && (double)emw[h] <= (double)A.wpoly_x * Sw_units[h];
             }
             auto sweep = [&](auto nolow_c, auto split_c, auto poly_c) {
                 constexpr bool NOLOW = decltype(nolow_c)::value, SPLIT = decltype(split_c)::value;
@@ -960,7 +960,7 @@ void ensemble_sweep_kernel(const RowArgs A, const int H, const int64_t head_stri
             if (tid == 0) { pk_S[done][h] = S; pk_n[done][h] = n; pk_mc[done][h] = mc; }
             const double emax = (double)Elt<T>::exp2_ref(mc, n == -INFINITY ? 0.f : n);
             all_flat = all_flat && emax * (double)V <= 2.0 * S;
-            const double Su = nw == -INFINITY ? 1.0 : ldexp(S, (int)fminf(n - nw, 1000.f));   // S in this wave's units
+            const double Su = nw == -INFINITY ? 1.0 : ldexp(S, (int)fminf(n - nw, kFarUnits));   // S in this wave's units
             const double inv = uniform_d(recip(Su));
             // ---- 2: the head's widths ------------------------------------------------------------------------------
             const FuseRow fr = uniform_fr(fuse_row_inv(inv, ra, rb));
@@ -999,7 +999,7 @@ void ensemble_sweep_kernel(const RowArgs A, const int H, const int64_t head_stri
                 // (the host's bound on the largest probability, as in the streaming kernel)
                 const bool capless = !A.normalize || emax <= A.capless_xmax * S;          // uniform over the workgroup
                 const float is = -fr.nih, is2 = is * is;
-                const bool poly = capless && A.wpoly_x >= 0.f && (double)Elt<T>::exp2_ref(mw, nref) <= (double)A.wpoly_x * Su;
+                const bool poly = capless && A.wpoly_x >= 0.f && ref_is_near(n) && (double)Elt<T>::exp2_ref(mw, nref) <= (double)A.wpoly_x * Su;
                 if (poly) {                                        // uniform over the wave: see RowArgs::wpoly
                     const float d0 = uniform_f(A.wpoly[0] * is), d1 = uniform_f(A.wpoly[1] * is2);
                     const float d2 = uniform_f(A.wpoly[2] * (is2 * is)), d3 = uniform_f(A.wpoly[3] * (is2 * is2));
@@ -1114,7 +1114,7 @@ void ensemble_sweep_kernel(const RowArgs A, const int H, const int64_t head_stri
             for (int h = 0; h < H; ++h) {
                 const int64_t off = (int64_t)h * head_stride + r * A.stride;
                 const double S = pk_S[at][h];
-                const double ed = exp((double)load_logit(static_cast<const T*>(A.draft) + off, i) - (double)pk_n[at][h] * kLn2);
+                const double ed = exp(ln_exp2<T>(load_logit(static_cast<const T*>(A.draft) + off, i), (double)pk_n[at][h]));
                 const double inv = recip(S), x = ed * inv, omx = fmax(0.0, S - ed) * inv;
                 double a = A.a, b = A.b;
                 if constexpr (RAD) {

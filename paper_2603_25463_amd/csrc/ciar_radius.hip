@@ -301,7 +301,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
         }
         if (tid == 0) { pk[done].S = S; pk[done].n = n; pk[done].mc = mc; }
         const double fw = nw == -INFINITY ? 0.0 : pow2_of(nw - n);                         // this wave's e_i are 1 / fw too large
-        const double Su = nw == -INFINITY ? 1.0 : ldexp(S, (int)fminf(n - nw, 1000.f));   // S in this wave's units
+        const double Su = nw == -INFINITY ? 1.0 : ldexp(S, (int)fminf(n - nw, kFarUnits));   // S in this wave's units
         const bool top = (double)Elt<T>::exp2_ref(mc, n == -INFINITY ? 0.f : n) > 0.5 * S;         // uniform over the workgroup
         FuseRow fr;
         {
@@ -689,7 +689,7 @@ void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ vote
         }
         if (tid == 0) { pk[done].S = S; pk[done].n = n; pk[done].mc = mc; }
         const double fw = nw == -INFINITY ? 0.0 : pow2_of(nw - n);                         // this wave's e_i are 1 / fw too large
-        const double Su = nw == -INFINITY ? 1.0 : ldexp(S, (int)fminf(n - nw, 1000.f));   // S in this wave's units
+        const double Su = nw == -INFINITY ? 1.0 : ldexp(S, (int)fminf(n - nw, kFarUnits));   // S in this wave's units
         const bool top = (double)Elt<T>::exp2_ref(mc, n == -INFINITY ? 0.f : n) > 0.5 * S;         // uniform over the workgroup
         FuseRow fr;
         {

@@ -618,11 +618,11 @@ void stream_kernel(const RowArgs A)
                 const RowStats& st = sm_rows[i];
                 if constexpr (KEEP_E) {
                     // the row loop has decided in fp32 and drawn; rows it found too close to call are decided here
-                    if (sm_close[i] && !reject_exact(sm_fx[i][0], sm_fx[i][2], sm_fx[i][3], st.n, st.nt, st.S, st.Z))
+                    if (sm_close[i] && !reject_exact<T>(sm_fx[i][0], sm_fx[i][2], sm_fx[i][3], st.n, st.nt, st.S, st.Z))
                         sm_draw[i] = -1;                           // accepted after all: the draw does not count
                 } else {
                     // the accept test (Algorithm 1, "Cloud verification"); a rejected row's draw is resample_kernel's
-                    sm_draw[i] = reject_exact(sm_fx[i][0], sm_fx[i][2], sm_fx[i][3], st.n, st.nt, st.S, st.Z)
+                    sm_draw[i] = reject_exact<T>(sm_fx[i][0], sm_fx[i][2], sm_fx[i][3], st.n, st.nt, st.S, st.Z)
                                      ? kDrawPending : -1;
                 }
             }
@@ -868,7 +868,7 @@ void stream_kernel(const RowArgs A)
         if constexpr (DO_Q) {
             // x_i = e_i fw / S: hand fuse_row the partition sum expressed in this wave's units
             // (fw is a power of two: the division is a change of exponent)
-            const double Su = nw == -INFINITY ? 1.0 : ldexp(S, (int)fminf(n - nw, 1000.f));   // S / fw
+            const double Su = nw == -INFINITY ? 1.0 : ldexp(S, (int)fminf(n - nw, kFarUnits));   // S / fw
             // (the call's a, b and polynomial bound through opaque copies in scalar registers: what is derived from
             // them -- a - 1, 1 - b, the bound as a double -- is then formed here, an instruction each, instead of ahead
             // of the row loop, where it is kept in vector registers, or spilled, for all of it)
@@ -911,7 +911,7 @@ void stream_kernel(const RowArgs A)
                 const float is = -fr.nih, is2 = is * is;
                 wp.d0 = A.wpoly[0] * is; wp.d1 = A.wpoly[1] * is2; wp.d2 = A.wpoly[2] * (is2 * is);
                 wp.d3 = A.wpoly[3] * (is2 * is2);
-                wp.ethr = wpx < 0.f ? -1.f : (float)((double)wpx * Su);
+                wp.ethr = wpx < 0.f || !ref_is_near(n) ? -1.f : (float)((double)wpx * Su);
                 // uniform over the wave: scalar registers (an FMA reads one of them per issue, so d2 stays a vector)
                 auto uniform = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
                 wp.d0 = uniform(wp.d0); wp.d1 = uniform(wp.d1); wp.d3 = uniform(wp.d3); wp.ethr = uniform(wp.ethr);

@@ -1666,6 +1666,83 @@ def test_bf16_rows_with_masked_and_extreme_tokens(ciar, oracle, V, stride, tenso
     _run_case(ciar, oracle, c[:, :V] if stride == V else c, t, ids, ua, ur, P, vocab=V, tag=f"masks V={V}", radius=raw)
 
 
+def _large_logit_rows(V, stride, N, dtype, seed):
+    """Centre and verifier rows without an ordinary token (masked throughout with -1e8 to -1.3e9, alone or on both sides, one
+    token a step above the others, part of them at -inf), rows with a token forced by 1e9, and ordinary rows whose waves are
+    partly masked with -1e9, -1e12, -1e30.  Returns them with the drafted ids."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    c = 2.0 * torch.randn(N, stride, device="cuda", generator=g)
+    t = c + 0.7 * torch.randn(N, stride, device="cuda", generator=g)
+    ids = torch.randint(0, V, (N,), device="cuda", generator=g).to(torch.int32)
+    step = 2.0 ** (-7 if dtype == torch.bfloat16 else -22)
+    some = torch.arange(stride, device="cuda") < V // 2
+    for i in range(N):
+        k, x, at = i % 9, (-1e8, -3e8, -1e9, -1.3e9)[i // 9 % 4], int(ids[i])
+        if k in (0, 2, 3, 4):
+            c[i] = x
+        if k in (1, 2, 3):
+            t[i] = x
+        if k == 3:
+            c[i, at] = t[i, at] = x * (1.0 - step)
+        if k == 4:
+            c[i, : V // 3] = -math.inf
+            ids[i] = V - 1
+        if k in (5, 7):
+            c[i, at] = 1e9
+        if k in (6, 7):
+            t[i, at] = 1e9
+        if k == 8:
+            c[i, some] = t[i, some] = (-1e9, -1e12, -1e30, -3e36)[i // 9 % 4]
+            ids[i] = V - 1
+    c, t = c.to(dtype), t.to(dtype)
+    if stride > V:
+        c[:, V:] = float("nan")
+        t[:, V:] = float("nan")
+    return c, t, ids
+
+
+LARGE_LOGITS = [  # V, stride, N, dtype: every kind of tile, more rows than compute units and fewer
+    (50, 56, 72, torch.bfloat16), (1000, 1000, 300, torch.bfloat16), (4097, 4104, 300, torch.bfloat16), (16384, 16384, 72, torch.bfloat16),
+    (16384, 16384, 300, torch.bfloat16), (40000, 40000, 270, torch.bfloat16),
+]
+
+
+@pytest.mark.parametrize("V,stride,N,dtype", LARGE_LOGITS)
+@pytest.mark.parametrize("tensor_radius", [False, True])
+def test_rows_of_large_logits(ciar, oracle, V, stride, N, dtype, tensor_radius):
+    """Any finite logit is a logit: -1e9 is the usual constant of a masked position."""
+    c, t, ids = _large_logit_rows(V, stride, N, dtype, seed=V + N)
+    g = torch.Generator(device="cuda").manual_seed(V)
+    ua = 0.02 + 0.9 * torch.rand(N, device="cuda", generator=g)
+    ur = torch.randint(0, 1 << 24, (N,), device="cuda", generator=g).float() / (1 << 24)
+    raw = _raw_radius(N, stride, V, dtype, seed=V) if tensor_radius else None
+    kw = dict(radius_scale=1.0) if tensor_radius else dict(confidence=0.9)
+    P = ciar.Params(window=4, tau=1e-3, **kw)
+    _run_case(ciar, oracle, c[:, :V] if stride == V else c, t, ids, ua, ur, P, vocab=V, tag=f"large V={V}", radius=raw)
+    # several heads, and the intervals of every token
+    heads = torch.stack([c, torch.roll(c, 1, 0), c]).contiguous()
+    raws = None if raw is None else torch.stack([raw, raw, torch.roll(raw, 1, 0)]).contiguous()
+    hh, rh = heads.cpu(), None if raws is None else raws.cpu()
+    OP = _oparams(oracle, P)
+    for how in ("ENSEMBLE", "VOTING"):
+        say(f"[large {how}] V={V} N={N} {dtype} {kw}")
+        gm = ciar.quantify_multihead(heads, ids, P, getattr(ciar, how), vocab=V, radius_heads=raws)
+        torch.cuda.synchronize()
+        om = oracle.quantify_multihead(hh, ids.cpu().numpy(), OP, getattr(oracle, how), vocab=V, radius_heads=rh)
+        if how == "ENSEMBLE":
+            parity.check_floats(gm, om)
+        else:
+            for h in range(3):
+                parity.check_floats({k: gm[k][h] for k in parity.FLOAT_KEYS}, {k: om[k][h] for k in parity.FLOAT_KEYS})
+    if not tensor_radius:
+        got = ciar.dense_intervals(c[:9], P, vocab=V)
+        torch.cuda.synchronize()
+        want = oracle.dense_intervals(c[:9].cpu(), OP, vocab=V)
+        for a, b in zip(got, want):
+            a = a.cpu().numpy().astype(np.float64)[:, :V]
+            assert np.all(np.abs(a - b[:, :V]) <= parity.ATOL + parity.RTOL * np.abs(b[:, :V]))
+
+
 @pytest.mark.parametrize("V,dtype", [(1000, torch.float32), (4096, torch.bfloat16), (16384, torch.float32), (20001, torch.bfloat16)])
 @pytest.mark.parametrize("kw", [dict(), dict(radius_scale=0.7), dict(normalize=False)])
 def test_radius_rows_whose_caps_are_not_what_they_look_like(ciar, oracle, V, dtype, kw):
