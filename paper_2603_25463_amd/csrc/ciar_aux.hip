@@ -34,7 +34,7 @@ __global__ __launch_bounds__(256) void dense_kernel(const RowArgs A, float* __re
     if (lane == 0) smem[wave] = (double)m;
     __syncthreads();
     m = fmaxf(fmaxf((float)smem[0], (float)smem[1]), fmaxf((float)smem[2], (float)smem[3]));
-    const float n = Elt<T>::ref_of(m);
+    const float n = ref_of(m);
 
     double acc = 0.0;
     for (int i = tid; i < V; i += 256) acc += (double)Elt<T>::exp2_ref(load_logit(c, i), n);

@@ -40,7 +40,18 @@ __device__ __forceinline__ float exp2_ref(float x, float n)
 
 // Integer reference for a set of logits whose maximum is m: the next integer above m * log2(e), so
 // every 2^(x log2e - n) is <= 1 (up to rounding).  -inf (nothing but masked tokens) maps to -inf.
-__device__ __forceinline__ float ref_of(float m) { return ceilf(m * 1.44269504f); }
+// Logits of large magnitude: from 2^24 on n is a multiple of 2, 4, ..., 128 (up to 2^31), so that the largest token's exponential is
+// anything from 2^-92 to 2^92 instead of 1/2 to 1.  Sums, reciprocals and token widths hold that, and a row masked throughout with
+// -1e9, or a token forced with 1e9, comes out right (any logit up to a magnitude of 1.48e9; beyond, those whose exponential the
+// rounding of n leaves in range).  Powers of 1 / S do not hold it, and ask ref_is_near.  Further up that exponential can overflow,
+// and a wave of masked tokens (-1e10, say) would outweigh the others': where m log2(e) lies that far above the rounded n, n is
+// raised by more than its own rounding (by a finite number: n may be -inf, and stays that).
+__device__ __forceinline__ float ref_of(float m)
+{
+    const float n = ceilf(m * 1.44269504f);
+    return fmaf(m, 1.44269504f, -n) > 100.f ? fmaf(fminf(fabsf(n), 0x1p127f), 0x1p-22f, n) : n;
+}
+__device__ __forceinline__ bool ref_is_near(float n) { return !(fabsf(n) >= 0x1p24f); }
 
 // Maximum of three logits.  (None is a signalling NaN: plain v_max3_f32, without the quieting of each operand that fmaxf
 // adds for values the compiler knows nothing about.)
@@ -91,22 +102,11 @@ __device__ __forceinline__ float exp2_scaled(float z, float n)         // z = kB
     return __builtin_amdgcn_exp2f(fmaf(z, kBf16ToLog2e, -n));
 }
 
-// Logits of large magnitude.  From 2^24 on a float reference n is a multiple of 2, 4, ..., 128 (up to 2^31), so that the largest
-// token's exponential is anything from 2^-83 to 2^83 instead of 1/2 to 1.  Sums, reciprocals and token widths hold that, and a
-// row masked throughout with -1e9, or a token forced with 1e9, comes out right (any logit up to a magnitude of 1.48e9; beyond, those
-// whose exponential the reference's rounding leaves in range).  Powers of 1 / S do not hold it, and ask ref_is_near.
-// Further up that exponential can overflow, and a wave of masked tokens (-1e30, say) would outweigh the others': where
-// `top`, the largest token's exponent about n, says so, n is raised by more than its own rounding.  (n = -inf, nothing but tokens at
-// -inf: top is no number, and n stays.)
-__device__ __forceinline__ float ref_above(float n, float top) { return top > 100.f ? fmaf(fabsf(n), 0x1p-22f, n) : n; }
-__device__ __forceinline__ bool ref_is_near(float n) { return !(fabsf(n) >= 0x1p24f); }
-
 template <typename T> struct Elt;
 template <> struct Elt<float> {
     static constexpr int kPerVec = 4;
     static constexpr double kLog2e = (double)kLog2eHi + (double)kLog2eLo;          // as the exponentials have it
     __device__ static __forceinline__ float exp2_ref(float x, float n) { return ciar::exp2_ref(x, n); }
-    __device__ static __forceinline__ float ref_of(float m) { return ciar::ref_of(m); }
     static constexpr uint32_t kNegInfWord = 0xff800000u;
     __device__ static __forceinline__ void unpack(const u32x4& r, float* o)
     {
@@ -133,12 +133,6 @@ struct bf16_t { uint16_t bits; };
 template <> struct Elt<bf16_t> {
     static constexpr int kPerVec = 8;
     static constexpr double kLog2e = (double)kBf16Scale * (double)kBf16ToLog2e;    // as the exponentials have it
-    __device__ static __forceinline__ float ref_of(float m)
-    {
-        const float n = ciar::ref_of(m);
-        return ref_above(n, exp2_arg(m, n));
-    }
-    __device__ static __forceinline__ float exp2_arg(float x, float n) { return fmaf(x * kBf16Scale, kBf16ToLog2e, -n); }
     // (the same number, bit for bit, as from the matrix cores' product: see bf16_scaled)
     __device__ static __forceinline__ float exp2_ref(float x, float n) { return exp2_scaled(x * kBf16Scale, n); }
     static constexpr uint32_t kNegInfWord = 0xff80ff80u;

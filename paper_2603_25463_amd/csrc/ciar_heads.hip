@@ -455,7 +455,7 @@ void ensemble_fused_kernel(const RowArgs A, const int64_t head_stride)
 #pragma unroll
             for (int i = 1; i < EPT; ++i) ml = fmaxf(ml, e[i]);
             const float mw = wave_max(ml);
-            const float nw = Elt<T>::ref_of(mw);
+            const float nw = ref_of(mw);
             const float nref = nw == -INFINITY ? 0.f : nw;
             double sacc = 0.0;                                     // (one accumulator: registers are scarcer here than issue slots)
 #pragma unroll
@@ -928,7 +928,7 @@ void ensemble_sweep_kernel(const RowArgs A, const int H, const int64_t head_stri
                 fetch(RAD ? 0 : p, A.draft, next_row, next_h, has_next, tid);
                 unpack_row(cbuf, e, true, tid);
             }
-            const float mw = wave_max(max_of(e)), nw = Elt<T>::ref_of(mw), nref = nw == -INFINITY ? 0.f : nw;
+            const float mw = wave_max(max_of(e)), nw = ref_of(mw), nref = nw == -INFINITY ? 0.f : nw;
             double sacc[2] = {0.0, 0.0};
 #pragma unroll
             for (int i = 0; i < kSweepTokens; ++i) {
@@ -951,7 +951,7 @@ void ensemble_sweep_kernel(const RowArgs A, const int H, const int64_t head_stri
             // the waves' results combined, across the first lanes of every wave
             const int src = lane < NW ? lane : 0;
             // (the row's reference is the largest of the waves': the reference of the largest logit)
-            const float m_l = sm_ref[p][src], n_l = Elt<T>::ref_of(m_l), mc = row16_max(m_l), n = Elt<T>::ref_of(mc);
+            const float m_l = sm_ref[p][src], n_l = ref_of(m_l), mc = row16_max(m_l), n = ref_of(mc);
             const double S = row16_sum(lane < NW && n_l != -INFINITY ? sm_S[p][src] * pow2_of(n_l - n) : 0.0);
             // (the radius constants through an empty asm, formed anew for every row, and what is the same in every lane of
             // the wave moved to scalar registers: nothing of it is held in vector registers, or spilled, through the loop)

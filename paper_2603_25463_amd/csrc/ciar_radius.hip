@@ -257,7 +257,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
                 E::unpack(buf[j], &e[j * EPV]);
             }
         }
-        const float mw = wave_max(max_of(e)), nw = Elt<T>::ref_of(mw), nref = nw == -INFINITY ? 0.f : nw;
+        const float mw = wave_max(max_of(e)), nw = ref_of(mw), nref = nw == -INFINITY ? 0.f : nw;
         if constexpr (ARGMAX) {
             int at = INT_MAX;
 #pragma unroll
@@ -291,7 +291,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
         lds_barrier();
         if (wave == 0 && done > 0) park(done - 1, p ^ 1);
         const int src = lane < NW ? lane : 0;
-        const float m_l = sm_ref[p][src], n_l = Elt<T>::ref_of(m_l), mc = row16_max(m_l), n = Elt<T>::ref_of(mc);
+        const float m_l = sm_ref[p][src], n_l = ref_of(m_l), mc = row16_max(m_l), n = ref_of(mc);
         const double S = row16_sum(lane < NW && n_l != -INFINITY ? sm_S[p][src] * pow2_of(n_l - n) : 0.0);
         if constexpr (ARGMAX) {
             if (wave == 0) {                                       // the lowest index of the waves that hold the maximum
@@ -607,7 +607,7 @@ void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ vote
                 mw = wave_top(top_words(buf), quads);
             }
             if (MATRIX && __builtin_expect(quads, true)) {
-                nw = E::ref_of(mw);
+                nw = ref_of(mw);
                 if constexpr (ARGMAX) {
                     int at = INT_MAX;
 #pragma unroll
@@ -643,7 +643,7 @@ void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ vote
                     E::unpack(buf[j], &e[j * EPV]);
                 }
                 mw = wave_max(max_of(e));
-                nw = E::ref_of(mw);
+                nw = ref_of(mw);
                 const float nref = nw == -INFINITY ? 0.f : nw;
                 if constexpr (ARGMAX) {
                     int at = INT_MAX;
@@ -679,7 +679,7 @@ void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ vote
         lds_barrier();
         if (wave == 0 && done > 0) park(done - 1, p ^ 1);
         const int src = lane < NW ? lane : 0;
-        const float m_l = sm_ref[p][src], n_l = Elt<T>::ref_of(m_l), mc = row16_max(m_l), n = Elt<T>::ref_of(mc);
+        const float m_l = sm_ref[p][src], n_l = ref_of(m_l), mc = row16_max(m_l), n = ref_of(mc);
         const double S = row16_sum(lane < NW && n_l != -INFINITY ? sm_S[p][src] * pow2_of(n_l - n) : 0.0);
         if constexpr (ARGMAX) {
             if (wave == 0) {                                       // the lowest index of the waves that hold the maximum

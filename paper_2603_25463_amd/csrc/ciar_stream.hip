@@ -523,7 +523,7 @@ void stream_kernel(const RowArgs A)
 #pragma unroll
                 for (int k = 0; k < EPV; ++k) mt = fmaxf(mt, tv[k]);
             }
-            ntw = Elt<T>::ref_of(wave_max(mt));
+            ntw = ref_of(wave_max(mt));
             Zw = wave_sum(verifier_lane_sum(tb, ntw == -INFINITY ? 0.f : ntw, false));   // an all-masked wave: every term is 2^-inf = 0
         }
     };
@@ -758,7 +758,7 @@ void stream_kernel(const RowArgs A)
             mcw = wave_top(top_words(buf), quads);
         }
         if (MATRIX && __builtin_expect(quads, true)) {
-            nw = Elt<T>::ref_of(mcw);
+            nw = ref_of(mcw);
             const Bf16Scale bs = bf16_scale(opaque_tid());
             bf16_scaled(buf[0], bs, &e[0]);
 #pragma unroll
@@ -780,7 +780,7 @@ void stream_kernel(const RowArgs A)
 #pragma unroll
             for (int j = 0; j < NVEC; ++j) E::unpack(buf[j], &e[j * EPV]);
             mcw = wave_max(max_of(e));
-            nw = Elt<T>::ref_of(mcw);
+            nw = ref_of(mcw);
             const float nref = nw == -INFINITY ? 0.f : nw;
 #pragma unroll
             for (int j = 0; j < NVEC; ++j) {
@@ -819,7 +819,7 @@ void stream_kernel(const RowArgs A)
                 // (... except in the fused bf16 instances of 1024 lanes with a scalar radius: 32768 x 65536 1875 us so, 1894 from the
                 // references)
                 const float mc_l = sm_ref[src * 2], n_l = sm_ref[src * 2 + 1];
-                mc = row16_max(mc_l); n = BATCH3 && THREADS == 1024 ? Elt<T>::ref_of(mc) : row16_max(n_l);
+                mc = row16_max(mc_l); n = BATCH3 && THREADS == 1024 ? ref_of(mc) : row16_max(n_l);
                 S = row16_sum(ln < NW && n_l != -INFINITY ? sm_S[src] * pow2_of(n_l - n) : 0.0);
             } else {
                 mc = sm_ref[0]; n = sm_ref[1];

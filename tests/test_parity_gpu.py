@@ -1669,7 +1669,7 @@ def test_bf16_rows_with_masked_and_extreme_tokens(ciar, oracle, V, stride, tenso
 def _large_logit_rows(V, stride, N, dtype, seed):
     """Centre and verifier rows without an ordinary token (masked throughout with -1e8 to -1.3e9, alone or on both sides, one
     token a step above the others, part of them at -inf), rows with a token forced by 1e9, and ordinary rows whose waves are
-    partly masked with -1e9, -1e12, -1e30.  Returns them with the drafted ids."""
+    partly masked with -1e9 to the type's lowest value.  Returns them with the drafted ids."""
     g = torch.Generator(device="cuda").manual_seed(seed)
     c = 2.0 * torch.randn(N, stride, device="cuda", generator=g)
     t = c + 0.7 * torch.randn(N, stride, device="cuda", generator=g)
@@ -1692,7 +1692,7 @@ def _large_logit_rows(V, stride, N, dtype, seed):
         if k in (6, 7):
             t[i, at] = 1e9
         if k == 8:
-            c[i, some] = t[i, some] = (-1e9, -1e12, -1e30, -3e36)[i // 9 % 4]
+            c[i, some] = t[i, some] = (-1e9, -1e10, -1e12, -1e30, -3e36, torch.finfo(dtype).min)[i // 9 % 6]
             ids[i] = V - 1
     c, t = c.to(dtype), t.to(dtype)
     if stride > V:
@@ -1704,6 +1704,8 @@ def _large_logit_rows(V, stride, N, dtype, seed):
 LARGE_LOGITS = [  # V, stride, N, dtype: every kind of tile, more rows than compute units and fewer
     (50, 56, 72, torch.bfloat16), (1000, 1000, 300, torch.bfloat16), (4097, 4104, 300, torch.bfloat16), (16384, 16384, 72, torch.bfloat16),
     (16384, 16384, 300, torch.bfloat16), (40000, 40000, 270, torch.bfloat16),
+    (50, 52, 72, torch.float32), (1000, 1000, 300, torch.float32), (3000, 3000, 72, torch.float32), (12345, 12348, 300, torch.float32),
+    (16384, 16384, 72, torch.float32), (20001, 20004, 270, torch.float32),
 ]
 
 
