@@ -329,6 +329,11 @@ constexpr bool draws_in_stream()
 // sm_draw / row_id of a rejected row whose draw is still to be made (by resample_kernel)
 constexpr int kDrawPending = -2;
 
+// A condition with what it is expected to be, in the instances where `hint` is true.  (A macro: said inside a function, the expectation
+// is lost before the function is inlined.)
+#define CIAR_USUAL(hint, c) ((hint) ? __builtin_expect(!!(c), 1) : !!(c))
+#define CIAR_RARE(hint, c) ((hint) ? __builtin_expect(!!(c), 0) : !!(c))
+
 // WHOLE: every row fills the tile.  Such calls have instances of their own, without the code for rows that do not (vectors past the
 // end clamped, tokens masked): a call of a few rows waits for its instructions to arrive, and longer for those behind a jump (8 x
 // 16384 fp32 13.8 -> 13.0 us, 256 rows 16.1 -> 15.5, 2048 rows 51.5 -> 50.4).  The others tell at run time: with masks that are
@@ -413,6 +418,18 @@ void stream_kernel(const RowArgs A)
         // (in scalar registers; the fp32 instances of eight and sixteen waves spill with it)
         if constexpr (sizeof(T) == 2 || THREADS == 256) { rm.kappa = uniform_f(rm.kappa); rm.rmax = uniform_f(rm.rmax); rm.am1_max = uniform_f(rm.am1_max); }
     }
+    // What the branches expect decides what lies next to each other, and what the register allocator favours.  Not expected:
+    // anything, where ragged rows are one vector to a lane (or two, bf16): 2048 x 1023 fp32 fused 16.6 us with, 16.3 without, 2048 x
+    // 2500 bf16 23.3 and 22.4; the inactive caps in fp32 calls with a verifier row: eight vectors to a lane spill 12 to 76 B with it (2048
+    // x 5000 28.7 and 28.5; quantify-only 2048 x 2500 wants it, 12.0 and 12.7); the draws' usual course in fp32 on ragged rows of 1024 lanes
+    // (36 B; 2048 x 20001 95.6 and 94.7).
+    constexpr bool FP32_V = sizeof(T) == 4 && DO_V && !RAD;
+    constexpr bool HINTS = RAD || WHOLE || (sizeof(T) == 2 ? NVEC >= 4 : NVEC > 1 || !DO_V);
+    constexpr bool HINT_CAPS = HINTS && !FP32_V, HINT_DRAW = HINTS && !(FP32_V && THREADS == 1024 && !WHOLE);
+    // bf16: what is formed from the thread's index -- masks, slots' addresses -- is formed anew for every row, from an opaque copy of
+    // it, where it would otherwise be held, or spilled, through the row loop.  (Not in calls with one row of few vectors: there is
+    // room to hold it, 2048 x 1162 verified 14.9 us so, 15.1 otherwise.)
+    constexpr bool FORM_ANEW = sizeof(T) == 2 && (MATRIX_T || RAD || (DO_Q && DO_V));
     const bool partial = !WHOLE && V != NVEC * CHUNK;              // uniform: the row does not fill the tile
     const int last_vec = (V + EPV - 1) / EPV - 1;
     const int nrows = (int)A.N;
@@ -469,7 +486,7 @@ void stream_kernel(const RowArgs A)
     // maximum.
     auto verifier_mask = [&](u32x4 (&tb)[NVEC], uint32_t fill) {
         if (partial) {
-            const int ot = sizeof(T) == 2 ? opaque_tid() : tid;
+            const int ot = FORM_ANEW ? opaque_tid() : tid;
 #pragma unroll
             for (int j = 0; j < NVEC; ++j) mask_with(tb[j], (j * THREADS + ot) * EPV, fill);
         }
@@ -508,13 +525,13 @@ void stream_kernel(const RowArgs A)
     auto verifier_redo = [&](u32x4 (&tb)[NVEC], float& ntw, double& Zw, bool& quads) {
         auto in_range = [&]() { return Zw >= 0x1p-40 && Zw <= 0x1p100; };   // (false for NaN)
         if constexpr (sizeof(T) == 2) {
-            if (__builtin_expect(quads && !in_range(), false)) {                            // uniform over the wave
+            if (CIAR_RARE(HINTS, quads && !in_range())) {                            // uniform over the wave
                 quads = false;
                 verifier_mask(tb, E::kNegInfWord);
                 Zw = wave_sum(verifier_lane_sum(tb, ntw, false));
             }
         }
-        if (__builtin_expect(!in_range(), false)) {                // uniform over the wave
+        if (CIAR_RARE(HINTS, !in_range())) {                // uniform over the wave
             float mt = -INFINITY;
 #pragma unroll
             for (int j = 0; j < NVEC; ++j) {
@@ -757,7 +774,7 @@ void stream_kernel(const RowArgs A)
             }
             mcw = wave_top(top_words(buf), quads);
         }
-        if (MATRIX && __builtin_expect(quads, true)) {
+        if (MATRIX && CIAR_USUAL(HINTS, quads)) {
             nw = ref_of(mcw);
             const Bf16Scale bs = bf16_scale(opaque_tid());
             bf16_scaled(buf[0], bs, &e[0]);
@@ -773,7 +790,7 @@ void stream_kernel(const RowArgs A)
             }
         } else {
             if (partial) {
-                const int ot = sizeof(T) == 2 ? opaque_tid() : tid;
+                const int ot = FORM_ANEW ? opaque_tid() : tid;
 #pragma unroll
                 for (int j = 0; j < NVEC; ++j) E::mask_tail(buf[j], (j * THREADS + ot) * EPV, V);
             }
@@ -807,8 +824,7 @@ void stream_kernel(const RowArgs A)
         // l < NW takes wave l; the other lanes of the DPP row repeat wave 0, which changes no maximum, and add
         // nothing); with four a short loop is as quick (measured).
         constexpr bool LANES = NW >= 8;
-        // (bf16: from an opaque copy of the lane index, so that the slots' addresses are not held, or spilled, through the row loop)
-        const int ln = sizeof(T) == 2 ? opaque_tid() & 63 : lane;
+        const int ln = FORM_ANEW ? opaque_tid() & 63 : lane;
         const int src = ln < NW ? ln : 0;
         // (by_lanes: across the first lanes of the wave, which must all be active; else in a loop)
         auto combine_S = [&](auto by_lanes, float& mc, float& n, double& S) {
@@ -895,7 +911,7 @@ void stream_kernel(const RowArgs A)
             // lane 0 moves them to the common shift afterwards.
             bool near = false;
             Shift sh = {0.f, 0.f, 0.f};
-            if (__builtin_expect(flat, false)) {
+            if (CIAR_RARE(HINTS, flat)) {
                 if constexpr (RAD) {
                     const float up = sm_ref[1] - nw;               // e0 is 2^up times larger in this wave's units
                     near = fabsf(up) <= 64.f;                      // uniform over the wave; false for inf and nan
@@ -920,7 +936,7 @@ void stream_kernel(const RowArgs A)
             const int base = slot_base(MATRIX && quads, MATRIX ? opaque_tid() : tid, EPV), step4 = slot_step(MATRIX && quads, EPV);
             bool tiny = false;
             if constexpr (NVEC == 1) tiny = V <= kTinyVocab;       // uniform
-            if (__builtin_expect(tiny, false)) {
+            if (CIAR_RARE(HINTS, tiny)) {
                 if constexpr (NVEC == 1) {
                     if constexpr (RAD) {
                         __builtin_amdgcn_sched_barrier(0);
@@ -959,9 +975,9 @@ void stream_kernel(const RowArgs A)
                 fuse_sums_wide<THREADS, NVEC, EPV>(e, fr, sh, V, base, step4, q5);
 #pragma unroll
                 for (int i = 0; i < 5; ++i) q5[i] = wave_sum(q5[i]);
-            } else if (__builtin_expect(capless, true)) {
+            } else if (CIAR_USUAL(HINT_CAPS, capless)) {
                 if (partial)    fuse_sums<THREADS, NVEC, EPV, true, true, true>(e, fr, wp, sh, V, base, step4, q5);
-                else if (__builtin_expect(split, false)) fuse_sums<THREADS, NVEC, EPV, true, true, false>(e, fr, wp, sh, V, base, step4, q5);
+                else if (CIAR_RARE(HINTS, split)) fuse_sums<THREADS, NVEC, EPV, true, true, false>(e, fr, wp, sh, V, base, step4, q5);
                 else            fuse_sums<THREADS, NVEC, EPV, true, false, false>(e, fr, wp, sh, V, base, step4, q5);
                 if constexpr (BATCH3) {
                     // reduced below, together with the verifier row's sum; until then the quads' sums wait in LDS
@@ -1012,7 +1028,7 @@ void stream_kernel(const RowArgs A)
                 double ku = fw;
                 const double f2 = fw * fw;
                 q5[0] *= fw; q5[1] *= fw; q5[2] *= f2; q5[3] *= f2; q5[4] *= f2;
-                if (__builtin_expect(flat && !near && !tiny, false)) {
+                if (CIAR_RARE(HINTS, flat && !near && !tiny)) {
                     // Rare: this wave's sums are about 0.  Form the common shift the long way round, in row units
                     // (scalar radius) or in wave 0's (tensor radius), and move the sums to it:  with c = 0 - K and
                     // n tokens,  sum (d - K) = s1 + n c,  sum (d - K)^2 = s2 + 2 c s1 + n c^2,  likewise the cross
@@ -1121,7 +1137,7 @@ void stream_kernel(const RowArgs A)
             // lane that finishes the row decides in fp64 whether it counts (about one row in a few thousand)
             const int verdict = accept_quick(cx, tx, ua, n, ntq, Sf, Zq);
             if (tid == 0) sm_close[done] = (uint8_t)(verdict < 0);
-            if (__builtin_expect(verdict > 0, true)) {
+            if (CIAR_USUAL(HINTS, verdict > 0)) {
                 if (tid == 0) sm_draw[done] = -1;
             } else {
                 // p_i = e_i pfac, q_i = 2^(t_i log2e - ntw) qfac, res_i = max(0, q_i - p_i) rounded to fp32: every
@@ -1233,7 +1249,7 @@ void stream_kernel(const RowArgs A)
                 }
                 const double R = carry;
                 const float ur = sm_ur[done];
-                if (__builtin_expect(R > 0.0, true)) {
+                if (CIAR_USUAL(HINT_DRAW, R > 0.0)) {
                     const double thr = (double)ur * R;
                     int istar = -1;
                     double before = 0.0;
@@ -1248,7 +1264,7 @@ void stream_kernel(const RowArgs A)
                         }
                         prev_end = lane_value(run[p], 63);
                     }
-                    if (__builtin_expect(istar < 0, false)) {                               // unreachable for u < 1; keeps the draw valid
+                    if (CIAR_RARE(HINT_DRAW, istar < 0)) {                               // unreachable for u < 1; keeps the draw valid
 #pragma unroll
                         for (int p = 0; p < PER; ++p) {
                             const unsigned long long live = __ballot(p * 64 + dlane < NT && tot[p] > 0.0);
@@ -1470,7 +1486,7 @@ hipError_t launch_stream_kernel(const RowArgs& a, StreamLaunch& L)
     b.unit = p.unit;
     b.win_count = p.windows_counted ? a.win_words : nullptr;
     auto kernel = &stream_kernel<T, THREADS, NVEC, DO_Q, DO_V, RAD, WIDE, false>;
-    if constexpr (!WIDE) {
+    if constexpr (!WIDE && (DO_V || !RAD)) {                       // (quantify-only calls with a radius tensor: V <= 64 comes here)
         if (b.V == NVEC * THREADS * Elt<T>::kPerVec) kernel = &stream_kernel<T, THREADS, NVEC, DO_Q, DO_V, RAD, WIDE, true>;
     }
     if (L.ev_start && L.ev_stop)
