@@ -389,6 +389,18 @@ __device__ __forceinline__ float row16_sum_f(float v)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 15));
 }
 
+// the sum of a float over the wave, handed to every lane
+__device__ __forceinline__ float wave_sum_f(float v)
+{
+    v += __int_as_float(dpp_or<kRowShr1, 0xf>(0, __float_as_int(v)));
+    v += __int_as_float(dpp_or<kRowShr2, 0xf>(0, __float_as_int(v)));
+    v += __int_as_float(dpp_or<kRowShr4, 0xf>(0, __float_as_int(v)));
+    v += __int_as_float(dpp_or<kRowShr8, 0xf>(0, __float_as_int(v)));
+    v += __int_as_float(dpp_or<kRowBcast15, 0xa>(0, __float_as_int(v)));
+    v += __int_as_float(dpp_or<kRowBcast31, 0xc>(0, __float_as_int(v)));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ float dpp_max(float v)
 {

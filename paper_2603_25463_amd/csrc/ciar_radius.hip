@@ -35,6 +35,9 @@ constexpr int kRadVecs = 8, kRadVecsWide16 = 4;
 // for the sweep in calls with a small clamp: 762 x 16384 fp32, radius_max 2, 209 us against 24.5.)
 constexpr double kCrowded = 1e-5;
 constexpr double kCapGuard = 1e-5;     // how far from its cap a sum of bounds taken in fp32 (good to ~1e-6) has to be to settle it
+// The estimate of sum p - p^l from which a wave expects inactive caps (they are from 0.01 on).  On rows of radii around 0.018 the estimates of
+// 64 tokens scatter by 0.0025: at 0.015 one wave in ten expects the worse, at 0.0125 one in a hundred.
+constexpr float kExpectInactive = 0.0125f;
 template <int THREADS> constexpr int radius_rows() { return THREADS >= 512 ? 128 : THREADS / 4; }   // most rows of a workgroup
 
 template <bool WIDE> struct RadiusRow { double S, q[WIDE ? 7 : 5]; float n, mc, raw_top, big; };   // see RowStats, finish_row
@@ -715,10 +718,17 @@ void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ vote
         bool found = false;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         // Where the caps are inactive -- they are on almost every row -- Omega and Sigma want the sums of the widths alone (see
-        // kSumsWidthOnly).  Whether they are is known when the row is summed, so a wave that expects it (no token above 1/2, radii
-        // that are not all small: half of its lanes' first tokens have a - 1 > 1/8) takes those two in fp64 and sum p^l in fp32,
-        // which tells (kCapGuard), and marks the row by a sum that is no number; a row that was expected wrong is taken again
-        // (radius_row_full).  21 instead of 27 issues per token.
+        // kSumsWidthOnly).  Whether they are is known when the row is summed, so a wave that expects it takes those two in
+        // fp64 and sum p^l in fp32, which tells (kCapGuard), and marks the row by a sum that is no number; a row that was
+        // expected wrong is taken again (radius_row_full).  21 instead of 27 issues per token.
+        // The expectation: the caps are inactive where sum p^u - p and sum p - p^l, whose tokens with small p have p (1 - b) as their
+        // common lower bound, are above a hundredth.  The wave estimates that sum from its lanes' first tokens, none of which counts
+        // for more than a quarter of what it takes: a likely token says nothing of the others (kExpectInactive).
+        // (Weighed by p, for a row that is taken again costs as much once more: where the likely tokens have small radii and the others
+        // large ones 2048 x 12345 fp32 took 88 us when the radii alone were looked at, and takes 46.5; radius_kernel 44.2.  Only rows
+        // that hide their mass from the tokens looked at still cost that.  Rows with radii of 0.018 throughout: radius_kernel 43.3, by
+        // the radii alone, above 1/8, 45.6, so 41.0.  Active caps on every row, radii of 0.0025: 42.9 and 46.3, bf16 39.7 and 43.2.)
+        // A wave without weight in the row (its tokens masked, say) takes the widths' sums and marks nothing.
         // Token widths of a row whose largest probability is at most 1/8 need 1/S as one float (1 - x to 1e-8).
         const bool split = (double)Elt<T>::exp2_ref(mc, n == -INFINITY ? 0.f : n) > 0.125 * S;
         auto am1_of = [&](float v) {
@@ -739,10 +749,18 @@ void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ vote
             }
             widen = __builtin_amdgcn_ballot_w64(any_huge(huge)) == 0;
         }
-        bool lean = false;                                         // uniform over the wave
+        bool lean = false, weightless = false;                     // uniform over the wave
         if (!top && (!MATRIX || widen)) {
-            const float raw = sizeof(T) == 4 ? bits_f(sm_next[tid].x) : bits_f(sm_next[tid].x << 16);
-            lean = !A.normalize || __popcll(__builtin_amdgcn_ballot_w64(am1_of(SCALED ? raw * kBf16Scale : raw) > 0.125f)) >= 32;
+            lean = !A.normalize;
+            if (A.normalize) {
+                // (the raw radius of the lane's first slot; bf16, transposed: token l & 3 of the quad's first lane)
+                const float raw = sizeof(T) == 4 ? bits_f(sm_next[tid].x)
+                                                 : bits_f((uint32_t)reinterpret_cast<const uint16_t*>(sm_next)[(tid & ~3) * EPV + (tid & 3)] << 16);
+                const float am1 = am1_of(SCALED ? raw * kBf16Scale : raw), Suf = uniform((float)Su), Vf = (float)V;
+                weightless = etop * Vf < 0x1p-30f * Suf;
+                const float enough = kExpectInactive * 64.0f * Suf, share = e[0] * Vf * (am1 * __builtin_amdgcn_rcpf(1.0f + am1));
+                lean = weightless || wave_sum_f(fminf(share, 0.25f * enough)) > enough;
+            }
         }
         float sum_pl = 0.f;
         constexpr int GROUP = sizeof(T) == 2 ? 2 : 4;              // vectors taken at a time
@@ -752,7 +770,7 @@ void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ vote
         auto pass = [&](auto kind) {
             constexpr int KIND = decltype(kind)::value;
             FuseRow f = fr;
-            asm volatile("" : "+v"(f.nih), "+v"(f.nil));
+            if (KIND > 0) asm volatile("" : "+v"(f.nih), "+v"(f.nil));
 #pragma unroll
             for (int g = 0; g < NVEC; g += GROUP) {
                 u32x4 rb[GROUP];
@@ -835,7 +853,8 @@ void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ vote
                 // (the fifth sum's slots hold anything; the constant through an empty asm, or it is held through the row loop)
                 int nan_hi = 0x7ff80000;
                 asm volatile("" : "+v"(nan_hi));
-                if ((lane & 7) == 0) sm_red[wave][2 * 8 + (lane >> 3)] = __hiloint2double(nan_hi, nan_hi);
+                if ((lane & 7) == 0) sm_red[wave][2 * 8 + (lane >> 3)] = weightless ? 0.0 : __hiloint2double(nan_hi, nan_hi);
+                if (weightless) put(0.0, 4, lane);
             } else {
                 put(q[0] * fw, 0, lane); put(q[1] * fw, 1, lane);
                 put(q[2] * f2, 2, lane); put(q[3] * f2, 3, lane); put(q[4] * f2, 4, lane);
@@ -1002,7 +1021,7 @@ hipError_t launch_radius_tile(const RowArgs& a, int heads, uint8_t* votes, hipSt
     // 12.4); fp32 rows without drafted ids spill with it (2048 x 4096 22.8 and 25.3);
     // with a clamp that small no wave would expect inactive caps (2048 x 16384 bf16 44.3 and 46.6).
     if constexpr (!WIDE) {
-        if (a.N > compute_units() && !(argmax && sizeof(T) == 4) && (a.am1_max > 0.125f || !a.normalize)) {
+        if (a.N > compute_units() && !(argmax && sizeof(T) == 4) && (a.am1_max > kExpectInactive || !a.normalize)) {
             if constexpr (sizeof(T) == 2) {
                 if (argmax) return a.kappa == 1.0 ? launch_radius_cfg<T, THREADS, NVEC, true, true, false, true>(a, heads, votes, stream, ev_start, ev_stop)
                                                   : launch_radius_cfg<T, THREADS, NVEC, false, true, false, true>(a, heads, votes, stream, ev_start, ev_stop);

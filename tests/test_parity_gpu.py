@@ -1745,31 +1745,58 @@ def test_rows_of_large_logits(ciar, oracle, V, stride, N, dtype, tensor_radius):
             assert np.all(np.abs(a - b[:, :V]) <= parity.ATOL + parity.RTOL * np.abs(b[:, :V]))
 
 
-@pytest.mark.parametrize("V,dtype", [(1000, torch.float32), (4096, torch.bfloat16), (16384, torch.float32), (20001, torch.bfloat16)])
-@pytest.mark.parametrize("kw", [dict(), dict(radius_scale=0.7), dict(normalize=False)])
-def test_radius_rows_whose_caps_are_not_what_they_look_like(ciar, oracle, V, dtype, kw):
-    """The quantifier's waves expect inactive caps from the row's largest probability and the radii of a few of its tokens:
-    rows that look so and have an active cap (small radii on the likely tokens, large ones elsewhere), rows that look the
-    other way round, rows whose waves disagree, infinite raw radii; more rows than compute units and fewer."""
-    stride = -(-V // 8) * 8
-    g = torch.Generator(device="cuda").manual_seed(V)
-    N = 600
+def _cap_rows(V, stride, N, dtype, seed):
+    """Rows for the quantifier's expectation of inactive caps, which it forms from the first tokens of a wave's lanes: centre rows, raw
+    radii, drafted ids.  By row: the tokens looked at weigh little together but more than their share, so that the
+    expectation is wrong; likely tokens with small radii and a tail with large ones; small radii throughout; tokens ruled out here and there;
+    small radii in one half; infinite raw radii; large ones; one half ruled out, its radii large, the others' small."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
     c = 0.5 * torch.randn(N, stride, device="cuda", generator=g)
     raw = torch.randn(N, stride, device="cuda", generator=g)
-    at = torch.randint(0, V, (N, 3), device="cuda", generator=g)
-    kind = torch.arange(N, device="cuda") % 7
+    i = torch.arange(stride, device="cuda")
+    at = torch.randint(V // 2, V, (N, 3), device="cuda", generator=g)
+    kind = torch.arange(N, device="cuda") % 8
+    some = torch.rand(N, stride, device="cuda", generator=g) < 0.1
+    seen = (i % 4 == 0) if dtype == torch.float32 else (i % 32 < 4)
+    few = kind == 0
+    c[few] = torch.where(seen, math.log(0.007 / 0.993 * 3.0 / int(seen[:V].sum())), -40.0)
+    raw[few] = torch.where(seen, 3.0, -9.0)
+    likely = kind < 2
     for k in range(3):                                                     # three likely tokens of about 1/3 each
-        c.scatter_(1, at[:, k:k + 1], torch.where(kind < 4, 9.0 + math.log(V / 1000.0) + 0.01 * k, 0.5)[:, None].expand(N, 1))
-    tiny = torch.full((N, 1), -9.0, device="cuda")
-    for k in range(3):
-        raw.scatter_(1, at[:, k:k + 1], torch.where((kind < 2)[:, None], tiny, raw.gather(1, at[:, k:k + 1])))
-    raw[kind == 2] -= 9.0                                                  # small radii throughout
-    raw[kind == 4] = torch.where(torch.arange(stride, device="cuda") < V // 2, raw[kind == 4], raw[kind == 4] - 9.0)
-    raw[kind == 5] = torch.where(torch.rand(raw[kind == 5].shape, device="cuda", generator=g) < 0.1, -math.inf, raw[kind == 5])
-    raw[kind == 6] = torch.where(torch.rand(raw[kind == 6].shape, device="cuda", generator=g) < 0.1, 60.0, raw[kind == 6])
-    c, raw = c.to(dtype), raw.to(dtype)
-    ids = at[:, 0].to(torch.int32)
-    P = ciar.Params(**{"radius_scale": 1.0, "tau": 0.01, **kw})
+        top = torch.where(few, 0.01 * k, 13.0 + math.log(V / 1000.0) + 0.01 * k)[:, None]
+        c.scatter_(1, at[:, k:k + 1], torch.where(likely[:, None], top, c.gather(1, at[:, k:k + 1])))
+        raw.scatter_(1, at[:, k:k + 1], torch.where(likely[:, None], -9.0, raw.gather(1, at[:, k:k + 1])))
+    raw[kind == 2] -= 9.0
+    dead = some.scatter(1, at, False)
+    c[kind == 3] = torch.where(dead[kind == 3], -math.inf, c[kind == 3])
+    raw[kind == 4] = torch.where(i < V // 2, raw[kind == 4], raw[kind == 4] - 9.0)
+    raw[kind == 5] = torch.where(some[kind == 5], -math.inf, raw[kind == 5])
+    raw[kind == 6] = torch.where(some[kind == 6], 60.0, raw[kind == 6])
+    c[kind == 7] = torch.where(i < V // 2, -math.inf, c[kind == 7])
+    raw[kind == 7] = torch.where(i < V // 2, raw[kind == 7], raw[kind == 7] - 9.0)
+    if stride > V:
+        c[:, V:] = float("nan")
+        raw[:, V:] = math.inf
+    return c.to(dtype), raw.to(dtype), at[:, 0].to(torch.int32)
+
+
+CAP_SHAPES = [  # V, dtype, radius_max (radii that are not wide for the vocabulary), rows: every number of lanes of radius_lean_kernel
+    (4000, torch.float32, 8.0, 2100), (8000, torch.float32, 9.0, 1100), (16384, torch.float32, 10.0, 600), (20001, torch.float32, 10.0, 300),
+    (4001, torch.bfloat16, 8.0, 6200), (8000, torch.bfloat16, 9.0, 2100), (12345, torch.bfloat16, 10.0, 600), (20001, torch.bfloat16, 10.0, 300),
+    (40000, torch.bfloat16, 10.0, 270),
+]
+
+
+@pytest.mark.parametrize("V,dtype,rmax,N", CAP_SHAPES)
+@pytest.mark.parametrize("kw", [dict(), dict(radius_scale=0.7), dict(normalize=False)])
+def test_radius_rows_whose_caps_are_not_what_they_look_like(ciar, oracle, V, dtype, rmax, N, kw):
+    """Rows that look as if their caps were inactive and have an active one (taken again in full), rows that look the other way
+    round, rows whose waves disagree, infinite raw radii; rows one after another and few rows."""
+    if kw and N > 1000:
+        N = 256 * (N // 256) + 8 if dtype == torch.float32 else N // 3      # (the other instances of the token arithmetic: fewer rows do)
+    stride = -(-V // 8) * 8
+    c, raw, ids = _cap_rows(V, stride, N, dtype, seed=V)
+    P = ciar.Params(**{"radius_scale": 1.0, "tau": 0.01, "radius_max": rmax, **kw})
     OP = _oparams(oracle, P)
     for rows in (N, 40):
         say(f"[caps] V={V} {dtype} rows={rows} {kw}")
@@ -1779,3 +1806,24 @@ def test_radius_rows_whose_caps_are_not_what_they_look_like(ciar, oracle, V, dty
             torch.cuda.synchronize()
             parity.check_floats(q, o, keys=parity.FLOAT_KEYS if use is not None else ("omega", "sigma", "score"))
             parity.check_flags(q["flags"], o, float(np.float32(P.tau)))
+
+
+@pytest.mark.parametrize("V,dtype,N", [(16384, torch.float32, 300), (12345, torch.bfloat16, 300), (20001, torch.bfloat16, 100)])
+def test_radius_vote_of_rows_taken_again(ciar, oracle, V, dtype, N):
+    """Three heads whose rows are partly taken again: the vote counts the flags that these rows got in the end."""
+    stride = -(-V // 8) * 8
+    made = [_cap_rows(V, stride, N, dtype, seed=V + h) for h in range(3)]
+    c, raw, ids = torch.stack([m[0] for m in made]), torch.stack([m[1] for m in made]), made[0][2]
+    o = oracle.quantify_multihead(c.cpu(), ids.cpu().numpy(), _OP(oracle, kappa=1.0), oracle.VOTING, vocab=V, radius_heads=raw.cpu())
+    tau = float(np.float32(np.median(o["score"])))
+    P = ciar.Params(radius_scale=1.0, tau=tau)
+    o = oracle.quantify_multihead(c.cpu(), ids.cpu().numpy(), _oparams(oracle, P), oracle.VOTING, vocab=V, radius_heads=raw.cpu())
+    say(f"[caps, vote] V={V} {dtype} N={N}")
+    v = ciar.quantify_multihead(c, ids, P, ciar.VOTING, vocab=V, radius_heads=raw)
+    torch.cuda.synchronize()
+    for h in range(3):
+        oh = {k: o[k][h] for k in parity.FLOAT_KEYS}
+        oh["flags"] = o["head_flags"][h]
+        parity.check_floats({k: v[k][h] for k in parity.FLOAT_KEYS}, oh)
+        parity.check_flags(v["head_flags"][h], oh, tau)
+    assert torch.equal(v["flags"], (2 * v["head_flags"].sum(0, dtype=torch.int32) > 3).to(torch.uint8))
