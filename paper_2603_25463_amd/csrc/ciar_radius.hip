@@ -742,7 +742,8 @@ void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ vote
 #pragma unroll
             for (int j = 0; j < NVEC; ++j) {
                 if (j < nch) {
-                    const u32x4 r = sm_next[j * THREADS + tid];
+                    u32x4 r = sm_next[j * THREADS + tid];
+                    if ((j + 1) * CHUNK > V) E::zero_tail(r, (j * THREADS + tid) * EPV, V);   // uniform
                     huge = pk_max3(j == 0 ? pk_max3(r.x, r.x, r.y) : pk_max3(huge, r.x, r.y), r.z, r.w);
                 }
                 if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
