@@ -1017,12 +1017,23 @@ template <typename T, int THREADS, int NVEC, bool WIDE>
 hipError_t launch_radius_tile(const RowArgs& a, int heads, uint8_t* votes, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     const bool argmax = a.ids == nullptr && (a.p_lo || a.p_mid || a.p_hi);
-    // The widths' sums alone where rows follow one another.  With a row per compute unit at most, a call waits for one row's
-    // instructions to arrive, of which there are more then (8 x 16384 fp32 with small radii 11.3 us without, 12.2 with; bf16 11.6 and
-    // 12.4); fp32 rows without drafted ids spill with it (2048 x 4096 22.8 and 25.3);
-    // with a clamp that small no wave would expect inactive caps (2048 x 16384 bf16 44.3 and 46.6).
+    // radius_lean_kernel where rows follow one another: a call that has a place for every row waits for one row's instructions to
+    // arrive, of which there are more then.  How many rows it takes to pay, by the lanes of a row (us, radius_kernel / radius_lean_kernel):
+    // fp32, 64 lanes not at all (2048 tokens, 4500 rows 24.2 / 24.3; 1024 tokens, 9600 rows 25.7 / 26.1), from 128 lanes on more than
+    // places (8000 tokens, 800 rows 20.2 / 19.8, 1600 rows 26.7 / 26.2; 16384 tokens, 400 rows 18.5 / 18.7, 520 rows 22.6 / 22.0);
+    // bf16, 64 lanes full tiles and one and a half rows to a place (4096 tokens, 4500 rows 33.6 / 34.0, 6600 rows 41.8 / 40.8; 2500 tokens, 16384 rows
+    // 61.7 / 62.1), 128 lanes more than places (8000 tokens, 1600 rows 26.4 / 26.5, 2200 rows 32.2 / 31.6), 256 lanes more than half
+    // (16384 tokens, 400 rows 16.9 / 17.4, 520 rows 21.1 / 19.9), from 512 on more than compute units (32768 tokens, 270 rows 25.8 / 24.0).
+    // Not with fp32 rows without drafted ids, which spill with it (2048 x 4096 22.8 and 25.3), nor with a clamp so small that no wave would
+    // expect inactive caps (2048 x 16384 bf16 44.3 and 46.6).
     if constexpr (!WIDE) {
-        if (a.N > compute_units() && !(argmax && sizeof(T) == 4) && (a.am1_max > kExpectInactive || !a.normalize)) {
+        constexpr bool B16 = sizeof(T) == 2;
+        const int64_t units = compute_units(), places = (1024 / THREADS) * units;
+        const bool follow = THREADS == 64  ? B16 && 2 * a.N > 3 * places && 4 * (int64_t)a.V > 3 * (int64_t)(NVEC * THREADS * Elt<T>::kPerVec)
+                          : !B16 || THREADS == 128 ? a.N > places
+                          : THREADS == 256 ? 2 * a.N > places
+                                           : a.N > units;
+        if (follow && !(argmax && sizeof(T) == 4) && (a.am1_max > kExpectInactive || !a.normalize)) {
             if constexpr (sizeof(T) == 2) {
                 if (argmax) return a.kappa == 1.0 ? launch_radius_cfg<T, THREADS, NVEC, true, true, false, true>(a, heads, votes, stream, ev_start, ev_stop)
                                                   : launch_radius_cfg<T, THREADS, NVEC, false, true, false, true>(a, heads, votes, stream, ev_start, ev_stop);
