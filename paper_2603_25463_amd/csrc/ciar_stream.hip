@@ -1142,7 +1142,10 @@ void stream_kernel(const RowArgs A)
             } else {
                 // p_i = e_i pfac, q_i = 2^(t_i log2e - ntw) qfac, res_i = max(0, q_i - p_i) rounded to fp32: every
                 // partial sum below is a sum of those floats, so that the totals of the pieces and the running sum
-                // inside the piece that holds u R are sums of the same numbers
+                // inside the piece that holds u R are sums of the same numbers.  (Not of the same roundings: a lane adds its
+                // tokens in fp32 before the lanes are added in fp64, and with transposed slots the totals' lanes hold other tokens of their
+                // quad than the running sum's.  The two differ by about 1e-7 of a lane's mass; a u R that falls into the difference
+                // at a piece's end draws that piece's last token with mass, see lastpos.)
                 // (the lane index goes through an empty asm, so that nothing of this branch is computed ahead of the
                 // row loop and kept in registers, or spilled, for all of it)
                 int dt = tid;
