@@ -131,6 +131,99 @@ __device__ void radius_row_full(const RowArgs& A, int64_t row, double (*red)[64]
     st.mode = kSumsFull;
 }
 
+// ---- what radius_kernel and radius_lean_kernel have in common ------------------------------------------------------------
+
+// The lane's index, asked for anew wherever it is used, through an empty asm: no LDS address formed from it is held in registers, or
+// spilled, through the row loop -- and a reload would wait for the row in flight.
+__device__ __forceinline__ int my_tid()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+template <typename T>
+__device__ __forceinline__ gbytes radius_row_base(const RowArgs& A, int H, const void* rows, uint32_t pos, int h)
+{
+    const int64_t off = H > 1 ? (int64_t)h * A.head_stride + (int64_t)pos * A.stride : row_offset(A, pos);
+    const uint64_t b = (uint64_t)(static_cast<const T*>(rows) + off);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    return (gbytes)(((uint64_t)hi << 32) | lo);
+}
+
+// Vector j of a row goes in flight (lane l of a wave lands 16 l bytes behind the address the wave names); lanes past the end of
+// the row fetch its last vector.
+template <int THREADS>
+__device__ __forceinline__ void fetch_vector(gbytes base, u32x4* slots, int j, int wave, int tid, uint32_t last_off)
+{
+    using lds_ptr = __attribute__((address_space(3))) void*;
+    using glb_ptr = const __attribute__((address_space(1))) void*;
+    __builtin_amdgcn_global_load_lds((glb_ptr)(base + min((uint32_t)(j * THREADS + tid) * 16u, last_off)),
+                                     (lds_ptr)(slots + j * THREADS + wave * 64), 16, 0, kNonTemporal);
+}
+
+// The sum over eight lanes, in each of them: lane ^ 1, lane ^ 2, the other quad.
+__device__ __forceinline__ double sum_of_eight(double v)
+{
+    v = dpp_add<0xB1, 0xf>(v);
+    v = dpp_add<0x4E, 0xf>(v);
+    return dpp_add<0x141, 0xf>(v);
+}
+
+// One wave: a row's sums over the workgroup's waves.
+template <int NW, int NQ>
+__device__ __forceinline__ void park_sums(const double (&tot)[NW][NQ], double* q, int lane)
+{
+    const int grp = lane >> 3, part = lane & 7;
+    double v = 0.0;
+    if (grp < NQ) {
+        if (part < NW) v = tot[part][grp];
+        if (NW > 8) v += tot[part + (NW > 8 ? 8 : 0)][grp];
+    }
+    v = sum_of_eight(v);
+    if (grp < NQ && part == 0) q[grp] = v;
+}
+
+// Wave priority by progress: whoever of the workgroups of a compute unit is behind is served first.
+__device__ __forceinline__ void priority_by_progress(int done, int count)
+{
+    if (done < (count + 3) >> 2) __builtin_amdgcn_s_setprio(3);
+    else if (done < (count + 1) >> 1) __builtin_amdgcn_s_setprio(2);
+    else if (done < (3 * count + 3) >> 2) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+}
+
+// A lane finishes a row, see finish_row, with its arg-max token (ARGMAX) or the drafted one.  The flag is left for the vote, which
+// counts the flags as written.
+template <typename T, bool ARGMAX, typename Again>
+__device__ __forceinline__ bool finish_radius_row(const RowArgs& A, int64_t r, int argmax, const RowStats& st, float raw_top,
+                                                  uint8_t* flag, Again again)
+{
+    const int64_t off = row_offset(A, r);
+    int xid = ARGMAX ? argmax : A.ids ? A.ids[ids_index(A, r)] : 0;
+    xid = xid < 0 ? 0 : (xid >= A.V ? A.V - 1 : xid);
+    const float cx = load_logit(static_cast<const T*>(A.draft) + off, xid);
+    const float rawx = load_logit(static_cast<const T*>(A.radius) + off, xid);
+    if (finish_row<T, true>(A, r, st, cx, 0.f, rawx, 0.f, true, false, raw_top, flag, again)) return true;
+    A.stats[r] = st;
+    return false;
+}
+
+// The strict majority of the workgroup's positions' flags.
+__device__ __forceinline__ void vote_of_positions(const uint8_t* flags, int H, int mine, uint32_t step, uint8_t* __restrict__ votes)
+{
+    __syncthreads();
+    const int t = my_tid();
+    if (t < mine) {
+        int yes = 0;
+        for (int i = 0; i < H; ++i) yes += flags[t * H + i];
+        votes[blockIdx.x + (int64_t)t * step] = (uint8_t)(2 * yes > H);
+    }
+}
+
+// ---- the kernels -----------------------------------------------------------------------------------------------------------
+
 // A.N rows: H > 1: [H, P], H heads of P = A.head_rows positions, the H rows of a position one after another in one workgroup,
 // which can then vote; H = 1: P = A.N rows dealt singly, of one head or of several (see row_offset).
 // ARGMAX = no drafted ids: every row reports its arg-max token.  votes: [P] flags by strict majority, or null.
@@ -159,56 +252,26 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
     __shared__ int pk_id[ARGMAX ? ROWS : 1];
     __shared__ uint8_t pk_fp64[ROWS], pk_flag[ROWS];
 
-    // (the lane's index is asked for anew wherever it is used, through an empty asm: no LDS address formed from it is held in
-    // registers, or spilled, through the loop -- and a reload would wait for the row in flight)
-    auto my_tid = []() {
-        int t = threadIdx.x;
-        asm volatile("" : "+v"(t));
-        return t;
-    };
-    auto uniform = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int V = A.V;
     const int nch = (V + CHUNK - 1) / CHUNK;                       // vectors of a lane that hold tokens at all
     const int last_vec = (V + EPV - 1) / EPV - 1;
     const uint32_t P = (uint32_t)(H > 1 ? A.head_rows : A.N), step = gridDim.x;
-    const float kappa = uniform((float)A.kappa), rmax = uniform((float)A.rmax), am1_max = A.am1_max;
+    const float kappa = uniform_f((float)A.kappa), rmax = uniform_f((float)A.rmax), am1_max = A.am1_max;
     // this workgroup's rows: H of each of its positions blockIdx.x, blockIdx.x + step, ...
     const uint32_t mine = blockIdx.x < P ? (P - blockIdx.x + step - 1u) / step : 0u;
     const int count = (int)mine * H;                               // <= ROWS: the launcher sizes the grid accordingly
     if (count == 0) return;
 
-    using lds_ptr = __attribute__((address_space(3))) void*;
-    using glb_ptr = const __attribute__((address_space(1))) void*;
-    auto offset_of = [&](uint32_t pos, int h) {
-        return H > 1 ? (int64_t)h * A.head_stride + (int64_t)pos * A.stride : row_offset(A, pos);
-    };
-    auto row_base = [&](const void* rows, uint32_t pos, int h) {
-        const uint64_t b = (uint64_t)(static_cast<const T*>(rows) + offset_of(pos, h));
-        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
-        const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
-        return (gbytes)(((uint64_t)hi << 32) | lo);
-    };
-    // vector j of a row goes in flight (lane l of a wave lands 16 l bytes behind the address the wave names); lanes past the end
-    // of the row fetch its last vector
+    auto row_base = [&](const void* rows, uint32_t pos, int h) { return radius_row_base<T>(A, H, rows, pos, h); };
     const uint32_t last_off = (uint32_t)last_vec * 16u;
     auto fetch = [&](gbytes base, int j, int tid) {
-        if (j < nch)                                               // uniform
-            __builtin_amdgcn_global_load_lds((glb_ptr)(base + min((uint32_t)(j * THREADS + tid) * 16u, last_off)),
-                                             (lds_ptr)(sm_next + j * THREADS + wave * 64), 16, 0, kNonTemporal);
+        if (j < nch) fetch_vector<THREADS>(base, sm_next, j, wave, tid, last_off);   // uniform
     };
     // wave 0: a row's sums over the waves, parked
     auto park = [&](int at, int p) {
-        const int lane = my_tid() & 63, grp = lane >> 3, part = lane & 7;
-        double v = 0.0;
-        if (grp < NQ) {
-            if (part < NW) v = sm_tot[p][part][grp];
-            if (NW > 8) v += sm_tot[p][part + (NW > 8 ? 8 : 0)][grp];
-        }
-        v = dpp_add<0xB1, 0xf>(v);                                 // lane ^ 1, lane ^ 2, the other quad of the eight
-        v = dpp_add<0x4E, 0xf>(v);
-        v = dpp_add<0x141, 0xf>(v);
-        if (grp < NQ && part == 0) pk[at].q[grp] = v;
+        const int lane = my_tid() & 63;
+        park_sums(sm_tot[p], pk[at].q, lane);
         if constexpr (WIDE) {
             const float big = row16_max(lane < NW ? sm_big[p][lane < NW ? lane : 0] : 0.f);
             if (lane == 0) pk[at].big = big;
@@ -216,17 +279,10 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
     };
     // the sums of a wave reduced together: every lane's value -> groups of eight lanes (three DPP steps) -> LDS
     auto put = [&](double v, int which, int lane) {
-        v = dpp_add<0xB1, 0xf>(v);
-        v = dpp_add<0x4E, 0xf>(v);
-        v = dpp_add<0x141, 0xf>(v);
+        v = sum_of_eight(v);
         if ((lane & 7) == 0) sm_red[wave][which * 8 + (lane >> 3)] = v;
     };
-    auto get = [&](int lane) {                                     // lanes 8 q ... 8 q + 7: quantity q over the wave
-        double v = sm_red[wave][lane < 8 * (NQ + 1) ? lane : 0];
-        v = dpp_add<0xB1, 0xf>(v);
-        v = dpp_add<0x4E, 0xf>(v);
-        return dpp_add<0x141, 0xf>(v);
-    };
+    auto get = [&](int lane) { return sum_of_eight(sm_red[wave][lane < 8 * (NQ + 1) ? lane : 0]); };   // lanes 8 q ...: quantity q
 
     uint32_t pos = blockIdx.x;
     int h = 0;
@@ -310,7 +366,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
         {
             const double inv = recip(Su);
             const float nih = (float)-inv;
-            fr = {0.f, uniform(nih), uniform((float)(-inv - (double)nih)), 0.f, 0.f};
+            fr = {0.f, uniform_f(nih), uniform_f((float)(-inv - (double)nih)), 0.f, 0.f};
         }
         // ---- 2: the radius row; its slots take the next centre row as they are read ---------------------------------------
         uint32_t npos = pos;
@@ -325,7 +381,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
         // A row with a token above 1/2: its raw radius is parked for finish_row by the lane that has it, in the wave with the row's
         // largest token.  (No other token has its e: two of them would be all of S.)
         const bool search = top && mw == mc;                       // uniform over the wave
-        const float etop = uniform(Elt<T>::exp2_ref(mw, nref));
+        const float etop = uniform_f(Elt<T>::exp2_ref(mw, nref));
         float raw_top = 0.f;
         bool found = false;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -405,13 +461,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
         }
         if (!has_next) break;
         pos = npos; h = nh;
-        // wave priority by progress: whoever of the workgroups of a compute unit is behind is served first
-        if constexpr (THREADS < 1024) {
-            if (done + 1 < (count + 3) >> 2) __builtin_amdgcn_s_setprio(3);
-            else if (done + 1 < (count + 1) >> 1) __builtin_amdgcn_s_setprio(2);
-            else if (done + 1 < (3 * count + 3) >> 2) __builtin_amdgcn_s_setprio(1);
-            else __builtin_amdgcn_s_setprio(0);
-        }
+        if constexpr (THREADS < 1024) priority_by_progress(done + 1, count);
     }
     {
         const int lane = my_tid() & 63;
@@ -438,16 +488,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
     };
     auto row_of = [&](int at) { return (int64_t)(at % H) * P + blockIdx.x + (int64_t)(at / H) * step; };
     auto finish = [&](int at, const RowStats& st, auto again) {
-        const int64_t r = row_of(at);
-        const int64_t off = row_offset(A, r);
-        int xid = ARGMAX ? pk_id[ARGMAX ? at : 0] : A.ids ? A.ids[ids_index(A, r)] : 0;
-        xid = xid < 0 ? 0 : (xid >= V ? V - 1 : xid);
-        const float cx = load_logit(static_cast<const T*>(A.draft) + off, xid);
-        const float rawx = load_logit(static_cast<const T*>(A.radius) + off, xid);
-        // (the vote counts the flags as written)
-        if (finish_row<T, true>(A, r, st, cx, 0.f, rawx, 0.f, true, false, pk[at].raw_top, &pk_flag[at], again)) return true;
-        A.stats[r] = st;
-        return false;
+        return finish_radius_row<T, ARGMAX>(A, row_of(at), pk_id[ARGMAX ? at : 0], st, pk[at].raw_top, &pk_flag[at], again);
     };
     {
         const int t = my_tid();
@@ -472,15 +513,7 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
         radius_row_fp64<T, THREADS>(A, row_of(at), sm_red, st);
         if (my_tid() == 0) finish(at, st, NeverAgain{});
     }
-    if (votes) {
-        __syncthreads();
-        const int t = my_tid();
-        if (t < (int)mine) {
-            int yes = 0;
-            for (int i = 0; i < H; ++i) yes += pk_flag[t * H + i];
-            votes[blockIdx.x + (int64_t)t * step] = (uint8_t)(2 * yes > H);
-        }
-    }
+    if (votes) vote_of_positions(pk_flag, H, (int)mine, step, votes);
 }
 
 // The same for calls whose rows follow one another (see launch_radius_tile): where a row's caps are expected to be inactive a wave
@@ -509,70 +542,33 @@ void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ vote
     __shared__ int pk_id[ARGMAX ? ROWS : 1];
     __shared__ uint8_t pk_fp64[ROWS], pk_flag[ROWS];
 
-    // (the lane's index is asked for anew wherever it is used, through an empty asm: no LDS address formed from it is held in
-    // registers, or spilled, through the loop -- and a reload would wait for the row in flight)
-    auto my_tid = []() {
-        int t = threadIdx.x;
-        asm volatile("" : "+v"(t));
-        return t;
-    };
-    auto uniform = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int V = A.V;
     const int nch = (V + CHUNK - 1) / CHUNK;                       // vectors of a lane that hold tokens at all
     const int last_vec = (V + EPV - 1) / EPV - 1;
     const uint32_t P = (uint32_t)(H > 1 ? A.head_rows : A.N), step = gridDim.x;
-    const float kappa = uniform((float)A.kappa), rmax = uniform((float)A.rmax), am1_max = A.am1_max;
+    const float kappa = uniform_f((float)A.kappa), rmax = uniform_f((float)A.rmax), am1_max = A.am1_max;
     // this workgroup's rows: H of each of its positions blockIdx.x, blockIdx.x + step, ...
     const uint32_t mine = blockIdx.x < P ? (P - blockIdx.x + step - 1u) / step : 0u;
     const int count = (int)mine * H;                               // <= ROWS: the launcher sizes the grid accordingly
     if (count == 0) return;
 
-    using lds_ptr = __attribute__((address_space(3))) void*;
-    using glb_ptr = const __attribute__((address_space(1))) void*;
-    auto offset_of = [&](uint32_t pos, int h) {
-        return H > 1 ? (int64_t)h * A.head_stride + (int64_t)pos * A.stride : row_offset(A, pos);
-    };
-    auto row_base = [&](const void* rows, uint32_t pos, int h) {
-        const uint64_t b = (uint64_t)(static_cast<const T*>(rows) + offset_of(pos, h));
-        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
-        const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
-        return (gbytes)(((uint64_t)hi << 32) | lo);
-    };
-    // vector j of a row goes in flight (lane l of a wave lands 16 l bytes behind the address the wave names); lanes past the end
-    // of the row fetch its last vector
+    auto row_base = [&](const void* rows, uint32_t pos, int h) { return radius_row_base<T>(A, H, rows, pos, h); };
     const uint32_t last_off = (uint32_t)last_vec * 16u;
     auto fetch = [&](gbytes base, int j, int tid) {
-        if (j < nch)                                               // uniform
-            __builtin_amdgcn_global_load_lds((glb_ptr)(base + min((uint32_t)(j * THREADS + tid) * 16u, last_off)),
-                                             (lds_ptr)(sm_next + j * THREADS + wave * 64), 16, 0, kNonTemporal);
+        if (j < nch) fetch_vector<THREADS>(base, sm_next, j, wave, tid, last_off);   // uniform
     };
     // wave 0: a row's sums over the waves, parked
     auto park = [&](int at, int p) {
-        const int lane = my_tid() & 63, grp = lane >> 3, part = lane & 7;
-        double v = 0.0;
-        if (grp < NQ) {
-            if (part < NW) v = sm_tot[p][part][grp];
-            if (NW > 8) v += sm_tot[p][part + (NW > 8 ? 8 : 0)][grp];
-        }
-        v = dpp_add<0xB1, 0xf>(v);                                 // lane ^ 1, lane ^ 2, the other quad of the eight
-        v = dpp_add<0x4E, 0xf>(v);
-        v = dpp_add<0x141, 0xf>(v);
-        if (grp < NQ && part == 0) pk[at].q[grp] = v;
+        const int lane = my_tid() & 63;
+        park_sums(sm_tot[p], pk[at].q, lane);
     };
     // the sums of a wave reduced together: every lane's value -> groups of eight lanes (three DPP steps) -> LDS
     auto put = [&](double v, int which, int lane) {
-        v = dpp_add<0xB1, 0xf>(v);
-        v = dpp_add<0x4E, 0xf>(v);
-        v = dpp_add<0x141, 0xf>(v);
+        v = sum_of_eight(v);
         if ((lane & 7) == 0) sm_red[wave][which * 8 + (lane >> 3)] = v;
     };
-    auto get = [&](int lane) {                                     // lanes 8 q ... 8 q + 7: quantity q over the wave
-        double v = sm_red[wave][lane < 8 * (NQ + 1) ? lane : 0];
-        v = dpp_add<0xB1, 0xf>(v);
-        v = dpp_add<0x4E, 0xf>(v);
-        return dpp_add<0x141, 0xf>(v);
-    };
+    auto get = [&](int lane) { return sum_of_eight(sm_red[wave][lane < 8 * (NQ + 1) ? lane : 0]); };   // lanes 8 q ...: quantity q
 
     uint32_t pos = blockIdx.x;
     int h = 0;
@@ -698,7 +694,7 @@ void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ vote
         {
             const double inv = recip(Su);
             const float nih = (float)-inv;
-            fr = {0.f, uniform(nih), uniform((float)(-inv - (double)nih)), 0.f, 0.f};
+            fr = {0.f, uniform_f(nih), uniform_f((float)(-inv - (double)nih)), 0.f, 0.f};
         }
         // ---- 2: the radius row; its slots take the next centre row as they are read ---------------------------------------
         uint32_t npos = pos;
@@ -713,7 +709,7 @@ void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ vote
         // A row with a token above 1/2: its raw radius is parked for finish_row by the lane that has it, in the wave with the row's
         // largest token.  (No other token has its e: two of them would be all of S.)
         const bool search = top && mw == mc;                       // uniform over the wave
-        const float etop = uniform(Elt<T>::exp2_ref(mw, nw == -INFINITY ? 0.f : nw));
+        const float etop = uniform_f(Elt<T>::exp2_ref(mw, nw == -INFINITY ? 0.f : nw));
         float raw_top = 0.f;
         bool found = false;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -757,7 +753,7 @@ void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ vote
                 // (the raw radius of the lane's first slot; bf16, transposed: token l & 3 of the quad's first lane)
                 const float raw = sizeof(T) == 4 ? bits_f(sm_next[tid].x)
                                                  : bits_f((uint32_t)reinterpret_cast<const uint16_t*>(sm_next)[(tid & ~3) * EPV + (tid & 3)] << 16);
-                const float am1 = am1_of(SCALED ? raw * kBf16Scale : raw), Suf = uniform((float)Su), Vf = (float)V;
+                const float am1 = am1_of(SCALED ? raw * kBf16Scale : raw), Suf = uniform_f((float)Su), Vf = (float)V;
                 weightless = etop * Vf < 0x1p-30f * Suf;
                 const float enough = kExpectInactive * 64.0f * Suf, share = e[0] * Vf * (am1 * __builtin_amdgcn_rcpf(1.0f + am1));
                 lean = weightless || wave_sum_f(fminf(share, 0.25f * enough)) > enough;
@@ -863,13 +859,7 @@ void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ vote
         }
         if (!has_next) break;
         pos = npos; h = nh;
-        // wave priority by progress: whoever of the workgroups of a compute unit is behind is served first
-        if constexpr (THREADS < 1024) {
-            if (done + 1 < (count + 3) >> 2) __builtin_amdgcn_s_setprio(3);
-            else if (done + 1 < (count + 1) >> 1) __builtin_amdgcn_s_setprio(2);
-            else if (done + 1 < (3 * count + 3) >> 2) __builtin_amdgcn_s_setprio(1);
-            else __builtin_amdgcn_s_setprio(0);
-        }
+        if constexpr (THREADS < 1024) priority_by_progress(done + 1, count);
     }
     {
         const int lane = my_tid() & 63;
@@ -897,16 +887,7 @@ void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ vote
     };
     auto row_of = [&](int at) { return (int64_t)(at % H) * P + blockIdx.x + (int64_t)(at / H) * step; };
     auto finish = [&](int at, const RowStats& st, auto again) {
-        const int64_t r = row_of(at);
-        const int64_t off = row_offset(A, r);
-        int xid = ARGMAX ? pk_id[ARGMAX ? at : 0] : A.ids ? A.ids[ids_index(A, r)] : 0;
-        xid = xid < 0 ? 0 : (xid >= V ? V - 1 : xid);
-        const float cx = load_logit(static_cast<const T*>(A.draft) + off, xid);
-        const float rawx = load_logit(static_cast<const T*>(A.radius) + off, xid);
-        // (the vote counts the flags as written)
-        if (finish_row<T, true>(A, r, st, cx, 0.f, rawx, 0.f, true, false, pk[at].raw_top, &pk_flag[at], again)) return true;
-        A.stats[r] = st;
-        return false;
+        return finish_radius_row<T, ARGMAX>(A, row_of(at), pk_id[ARGMAX ? at : 0], st, pk[at].raw_top, &pk_flag[at], again);
     };
     constexpr uint8_t kFull = 1, kExact = 2;                       // what a row is taken again with: all sums in fp32, in fp64
     auto crowded = [&](const RowStats& st) {
@@ -951,15 +932,7 @@ void radius_lean_kernel(const RowArgs A, const int H, uint8_t* __restrict__ vote
         radius_row_fp64<T, THREADS>(A, row_of(at), sm_red, st);
         if (my_tid() == 0) finish(at, st, NeverAgain{});
     }
-    if (votes) {
-        __syncthreads();
-        const int t = my_tid();
-        if (t < (int)mine) {
-            int yes = 0;
-            for (int i = 0; i < H; ++i) yes += pk_flag[t * H + i];
-            votes[blockIdx.x + (int64_t)t * step] = (uint8_t)(2 * yes > H);
-        }
-    }
+    if (votes) vote_of_positions(pk_flag, H, (int)mine, step, votes);
 }
 
 template <typename T, int THREADS, int NVEC, bool UNIT, bool ARGMAX, bool WIDE, bool LEAN>
