@@ -996,7 +996,8 @@ hipError_t launch_radius_tile(const RowArgs& a, int heads, uint8_t* votes, hipSt
     // places (8000 tokens, 800 rows 20.2 / 19.8, 1600 rows 26.7 / 26.2; 16384 tokens, 400 rows 18.5 / 18.7, 520 rows 22.6 / 22.0);
     // bf16, 64 lanes full tiles and one and a half rows to a place (4096 tokens, 4500 rows 33.6 / 34.0, 6600 rows 41.8 / 40.8; 2500 tokens, 16384 rows
     // 61.7 / 62.1), 128 lanes more than places (8000 tokens, 1600 rows 26.4 / 26.5, 2200 rows 32.2 / 31.6), 256 lanes more than half
-    // (16384 tokens, 400 rows 16.9 / 17.4, 520 rows 21.1 / 19.9), from 512 on more than compute units (32768 tokens, 270 rows 25.8 / 24.0).
+    // (16384 tokens, 400 rows 16.9 / 17.4, 520 rows 21.1 / 19.9), without drafted ids, and from 512 on, more than compute units (16384 tokens, 300
+    // rows without ids 17.9 / 17.2; 32768 tokens, 270 rows 25.8 / 24.0).
     // Not with fp32 rows without drafted ids, which spill with it (2048 x 4096 22.8 and 25.3), nor with a clamp so small that no wave would
     // expect inactive caps (2048 x 16384 bf16 44.3 and 46.6).
     if constexpr (!WIDE) {
@@ -1004,7 +1005,7 @@ hipError_t launch_radius_tile(const RowArgs& a, int heads, uint8_t* votes, hipSt
         const int64_t units = compute_units(), places = (1024 / THREADS) * units;
         const bool follow = THREADS == 64  ? B16 && 2 * a.N > 3 * places && 4 * (int64_t)a.V > 3 * (int64_t)(NVEC * THREADS * Elt<T>::kPerVec)
                           : !B16 || THREADS == 128 ? a.N > places
-                          : THREADS == 256 ? 2 * a.N > places
+                          : THREADS == 256 && !argmax ? 2 * a.N > places
                                            : a.N > units;
         if (follow && !(argmax && sizeof(T) == 4) && (a.am1_max > kExpectInactive || !a.normalize)) {
             if constexpr (sizeof(T) == 2) {
