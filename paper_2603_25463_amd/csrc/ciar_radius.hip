@@ -239,7 +239,10 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
     constexpr int CHUNK = THREADS * EPV;                           // tokens of one vector of every lane
     extern __shared__ u32x4 sm_next[];                             // [NVEC][THREADS]: the row in flight
     // exchange slots of a row: written before its barrier, read behind it; rows alternate between two sets
-    __shared__ float sm_ref[2][NW];
+    // per wave: largest logit; bf16: and the reference n_w.  (Formed again from the largest logits by every wave, 2048 x 4096 bf16 19.5 us, 8
+    // rows 8.7, so 18.8 and 8.4; fp32 rows lose up to 2 % so.)
+    constexpr bool REFS = sizeof(T) == 2;
+    __shared__ float sm_ref[2][NW][REFS ? 2 : 1];
     constexpr int NQ = WIDE ? 7 : 5;                               // sums of a row
     __shared__ double sm_S[2][NW], sm_tot[2][NW][NQ];
     __shared__ double sm_red[NW][64];                              // per wave: [the sums of the row before, S_w][eight groups of lanes]
@@ -345,12 +348,16 @@ void radius_kernel(const RowArgs A, const int H, uint8_t* __restrict__ votes)
                 if (grp < NQ) { if (done > 0) sm_tot[p ^ 1][wave][grp] = v; }
                 else if (grp == NQ) sm_S[p][wave] = v;
             }
-            if (lane == 0) sm_ref[p][wave] = mw;
+            if (lane == 0) {
+                sm_ref[p][wave][0] = mw;
+                if constexpr (REFS) sm_ref[p][wave][1] = nw;
+            }
         }
         lds_barrier();
         if (wave == 0 && done > 0) park(done - 1, p ^ 1);
         const int src = lane < NW ? lane : 0;
-        const float m_l = sm_ref[p][src], n_l = ref_of(m_l), mc = row16_max(m_l), n = ref_of(mc);
+        const float m_l = sm_ref[p][src][0], mc = row16_max(m_l);
+        const float n_l = REFS ? sm_ref[p][src][REFS ? 1 : 0] : ref_of(m_l), n = REFS ? row16_max(n_l) : ref_of(mc);
         const double S = row16_sum(lane < NW && n_l != -INFINITY ? sm_S[p][src] * pow2_of(n_l - n) : 0.0);
         if constexpr (ARGMAX) {
             if (wave == 0) {                                       // the lowest index of the waves that hold the maximum
