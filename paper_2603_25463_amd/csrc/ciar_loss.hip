@@ -16,8 +16,7 @@ namespace {
 // probability, and for logits of magnitude ~30 it shows as ~1e-6 absolute in a cross-entropy and in an L1 distance.
 //
 // The exponentials of c + r and c - r are formed as products, e^(c - cs) e^(r - rs) and e^(c - cs) e^-(r - rs), not from
-// the sums of the exponents: where the radius is the same for every token of a row (scalar mode, or a row clamped at
-// r_max) r - rs is one number, and adding it to exponents of one binade rounds them all the same way -- by up to half
+// the sums of the exponents: where the radius is the same for every token of a row (a row clamped at r_max) r - rs is one number, and adding it to exponents of one binade rounds them all the same way -- by up to half
 // an ulp of that binade, another amount in the next one.  That tilts the distribution between the binades by up to
 // ~3e-7 of the mass they hold, upwards for c + r and downwards for c - r, and showed as 1.7e-7 absolute in an L1
 // distance of 6e-3 (a seeded random case).  As products the three distributions of such a row agree to the rounding
@@ -72,12 +71,14 @@ constexpr uint32_t kRuledOutBits = 0xf1800000u;                    // (its upper
 // The radius parameters as the row arithmetic takes them: floats, formed by the host, so that they arrive in scalar
 // registers with the kernel arguments.  (Converted from RowArgs' doubles inside a kernel they are loop invariants that
 // the optimiser holds in vector registers, or spills, through the whole row loop.)
-struct DroRadius { float kappa, rmax, scalar; };                   // scalar = min(kappa, rmax), the radius without a tensor
+struct DroRadius { float kappa, rmax; };
 
-// RAD = 1 / 0: with / without a radius tensor, -1: to be asked.  (Told apart where the three rows do not fit the registers, eight
-// vectors of bf16: one kernel for both spilled 1808 bytes per lane, 1250 x 40000 8992 us with a radius tensor, 1746 without;
-// two spill 616 and 484, 809 and 367 us.)
-template <typename T, int NVEC, int THREADS, int RAD = -1>
+// RAD: with a radius tensor.  Without one the radius is the same for every token, c + r and c - r have the softmax of c, and the
+// terms of the three distributions are one number each: the partition sum, the weighted sums and the distance of c alone are
+// formed, and dro_finish_row writes them three times.  Half the instructions and half the registers (62 of 128 before), so
+// that two workgroups of 1024 lanes fit a compute unit where their rows fit its LDS (bf16): 15653 x 11630 bf16 593 -> 379 us, 2048 x
+// 16384 71 -> 51 (fp32 88 -> 65), 4 x 21156 29 -> 16 (which spilled).
+template <typename T, int NVEC, int THREADS, bool RAD>
 __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadius R, double* fin,
                                                 u32x4 (&cw)[NVEC], u32x4 (&tw)[NVEC], u32x4 (&rw)[NVEC], double* sm_d,
                                                 const int tid)
@@ -86,34 +87,28 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     constexpr int EPV = E::kPerVec, NW = THREADS / 64;
     const int lane = tid & 63, wave = tid >> 6;
     const int V = A.V;
-    const bool rad = RAD < 0 ? A.radius != nullptr : RAD == 1;     // uniform
     auto uniform = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
-    const float kap = R.kappa, rmax = R.rmax, r0 = R.scalar;
+    const float kap = R.kappa, rmax = R.rmax;
     if (V < NVEC * THREADS * EPV) {                                // uniform: the row does not fill the tile
 #pragma unroll
         for (int j = 0; j < NVEC; ++j) {
             const int base = (j * THREADS + tid) * EPV;
             E::mask_tail(cw[j], base, V);
             E::mask_tail(tw[j], base, V);
-            if (rad) E::zero_tail(rw[j], base, V);
+            if constexpr (RAD) E::zero_tail(rw[j], base, V);
         }
     }
     // The radii are formed once (Softplus costs about as much as the rest of a pass) and kept as floats where
     // the registers allow: up to 32 tokens per lane.  Beyond that they are recomputed in every pass.
-    constexpr bool CACHE_R = NVEC * EPV <= 32;
+    constexpr bool CACHE_R = RAD && NVEC * EPV <= 32;
     float rc[CACHE_R ? NVEC * EPV : 1];
     if constexpr (CACHE_R) {
-        if (rad) {                                                 // (one branch for the row, not one per token)
 #pragma unroll
-            for (int j = 0; j < NVEC; ++j) {
-                float rv[EPV];
-                E::unpack(rw[j], rv);
+        for (int j = 0; j < NVEC; ++j) {
+            float rv[EPV];
+            E::unpack(rw[j], rv);
 #pragma unroll
-                for (int k = 0; k < EPV; ++k) rc[j * EPV + k] = radius_abs(rv[k], kap, rmax);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < NVEC * EPV; ++i) rc[i] = r0;
+            for (int k = 0; k < EPV; ++k) rc[j * EPV + k] = radius_abs(rv[k], kap, rmax);
         }
     }
     // element k of vector j: centre logit, radius, cloud logit
@@ -124,9 +119,11 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
         c = cv[k]; t = tv[k];
         if constexpr (CACHE_R) {
             r = rc[j * EPV + k];
+        } else if constexpr (RAD) {
+            E::unpack(rw[j], rv);
+            r = radius_abs(rv[k], kap, rmax);
         } else {
-            r = r0;
-            if (rad) { E::unpack(rw[j], rv); r = radius_abs(rv[k], kap, rmax); }
+            r = 0.f;
         }
     };
     // The three passes recompute the radius and the sums c +- r from the rows as loaded.  Passing the row
@@ -136,7 +133,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
 #pragma unroll
         for (int j = 0; j < NVEC; ++j) {
             asm volatile("" : "+v"(cw[j]), "+v"(tw[j]));
-            if (!CACHE_R && rad) asm volatile("" : "+v"(rw[j]));
+            if constexpr (!CACHE_R && RAD) asm volatile("" : "+v"(rw[j]));
         }
     };
     // pass 1: the maxima of c and of the cloud logits, and a reference radius r* for the sums of c + r and c - r: the
@@ -170,7 +167,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
             element(j, k + 1, c2, r2, t2);
             mc = fmaxf(fmaxf(mc, c), c2); mt = fmaxf(fmaxf(mt, t), t2);
             c_least = fminf(fminf(c_least, c), c2);
-            key = key_max(key, key_of(c, r), key_of(c2, r2));
+            if constexpr (RAD) key = key_max(key, key_of(c, r), key_of(c2, r2));
         }
     }
     // Does any lane of this wave hold a centre logit of -inf (a token the device rules out, or the masked tail)?  Its
@@ -197,13 +194,14 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
                 float c, r, t, c2, r2, t2;
                 element(j, k, c, r, t);
                 element(j, k + 1, c2, r2, t2);
-                key = key_max(key, key_of(c, r), key_of(c2, r2));
+                if constexpr (RAD) key = key_max(key, key_of(c, r), key_of(c2, r2));
             }
         }
     }
     // LDS for the reductions over the workgroup (see pass 2 for the scheme: quad sums by DPP, then transposed through
     // LDS so that one short reduction serves all quantities at once)
-    __shared__ __attribute__((aligned(16))) double sm_w[NW][8][16];   // per wave: [quantity][quad]
+    constexpr int NS = RAD ? 8 : 4;                                // quantities summed (without a radius tensor: 0, 3, 4 and 7 of pass 2)
+    __shared__ __attribute__((aligned(16))) double sm_w[NW][NS][16];  // per wave: [quantity][quad]
     __shared__ __attribute__((aligned(16))) double sm_x[8][NW];       // [quantity][wave]
     float rref;
     {
@@ -212,7 +210,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
         // over the waves.  (Four wave-wide DPP maxima, twice, cost ~240 instructions.)
         float m4[4] = {mc, mt, key, 0.f};
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < (RAD ? 3 : 2); ++i) {
             m4[i] = dpp_max<0xB1, 0xf>(m4[i]);
             m4[i] = dpp_max<0x4E, 0xf>(m4[i]);
         }
@@ -240,7 +238,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
         }
         mc = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 15));
         mt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 31));
-        rref = (float)(__builtin_amdgcn_readlane(__float_as_int(v), 47) & 0xFFF) * (1.0f / 128.0f);
+        rref = !RAD ? 0.f : (float)(__builtin_amdgcn_readlane(__float_as_int(v), 47) & 0xFFF) * (1.0f / 128.0f);
         // (sm_m is written again in the next row's pass 1, with the barriers of passes 2 and 3 in between)
     }
     // a row without a live token: any finite reference will do (every exponential is 0)
@@ -262,9 +260,10 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     // with it -- as much as a whole cross-entropy of such a row may be off.  The four weighted sums of exponents are
     // taken per lane in fp32 (the dominant token has exponent 0 and adds nothing to them; what a lane's rounding
     // leaves is ~1e-7 of that lane's share of a cross-entropy), and in fp64 across lanes and waves.
-    constexpr bool CACHE_E = NVEC * EPV <= 16;
+    // (without a radius tensor there are two exponentials: at most 32)
+    constexpr bool CACHE_E = NVEC * EPV <= (RAD ? 16 : 32);
     constexpr int NE = CACHE_E ? NVEC * EPV : 1;
-    float em[NE], eu[NE], el[NE], ec[NE];
+    float em[NE], eu[RAD ? NE : 1], el[RAD ? NE : 1], ec[NE];
     fresh();
     double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};     // S_mid, S_up, S_lo, Z, sum et d_mid, d_up, d_lo, d_t
     float s32[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -299,20 +298,29 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
             element(j, k, c, r, t);
             // (each difference is exact for tokens near the reference and rounded relative to itself elsewhere:
             // c + r is never rounded to fp32)
-            const float x0 = log2e_times(c - mc), xa = log2e_times(r - rref);
+            const float x0 = log2e_times(c - mc);
             const float xt = log2e_times(fmaxf(t - mt, -1e30f));
-            // (the exponentials of c + r and c - r are products: see radius_factors)
             const float e0 = __builtin_amdgcn_exp2f(x0), et = __builtin_amdgcn_exp2f(xt);
-            const float e1 = e0 * __builtin_amdgcn_exp2f(xa), e2 = e0 * __builtin_amdgcn_exp2f(-xa);
+            acc[0] += (double)e0; acc[3] += (double)et;
             if constexpr (CACHE_E) {
-                em[j * EPV + k] = e0; eu[j * EPV + k] = e1; el[j * EPV + k] = e2; ec[j * EPV + k] = et;
-                acc[0] += (double)e0; acc[1] += (double)e1; acc[2] += (double)e2; acc[3] += (double)et;
-                s32[4] = fmaf(et, x0, s32[4]); s32[5] = fmaf(et, xa, s32[5]);
+                em[j * EPV + k] = e0; ec[j * EPV + k] = et;
+                s32[4] = fmaf(et, x0, s32[4]);
                 s32[7] = fmaf(et, xt - x0, s32[7]);
             } else {
-                acc[0] += (double)e0; acc[1] += (double)e1; acc[2] += (double)e2; acc[3] += (double)et;
-                acc[4] = fma((double)et, (double)x0, acc[4]); acc[5] = fma((double)et, (double)xa, acc[5]);
+                acc[4] = fma((double)et, (double)x0, acc[4]);
                 acc[7] = fma((double)et, (double)(xt - x0), acc[7]);
+            }
+            if constexpr (RAD) {
+                // (the exponentials of c + r and c - r are products: see radius_factors)
+                const float xa = log2e_times(r - rref);
+                const float e1 = e0 * __builtin_amdgcn_exp2f(xa), e2 = e0 * __builtin_amdgcn_exp2f(-xa);
+                acc[1] += (double)e1; acc[2] += (double)e2;
+                if constexpr (CACHE_E) {
+                    eu[j * EPV + k] = e1; el[j * EPV + k] = e2;
+                    s32[5] = fmaf(et, xa, s32[5]);
+                } else {
+                    acc[5] = fma((double)et, (double)xa, acc[5]);
+                }
             }
             if (k & 1) __builtin_amdgcn_sched_barrier(0);          // two tokens at a time: bounded working set
         }
@@ -329,10 +337,13 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
         for (int i = 4; i < 7; ++i) { s32[i] = -INFINITY; acc[i] = -INFINITY; }
         s32[7] = INFINITY; acc[7] = INFINITY;                      // KL is infinite with the cross-entropies
     }
+    auto wanted = [](int i) { return RAD || i == 0 || i == 3 || i == 4 || i == 7; };
+    auto slot_of = [](int i) { return RAD ? i : (i >= 3) + (i >= 4) + (i >= 7); };
     if constexpr (CACHE_E) {
         // (the weighted sums of a quad in fp32 as well: one instruction per DPP step of a float, five of a double)
 #pragma unroll
         for (int i = 4; i < 8; ++i) {
+            if (!wanted(i)) continue;
             float v = s32[i];
             v += __int_as_float(dpp_or<0xB1, 0xf>(0, __float_as_int(v)));
             v += __int_as_float(dpp_or<0x4E, 0xf>(0, __float_as_int(v)));
@@ -345,7 +356,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     // quantity; lane l then takes two of the 16 quad sums of quantity l / 8 (one 16-byte read) and three butterfly
     // steps over its group of eight lanes finish the wave's sums of all quantities at once.  Across the waves the same
     // two last steps run on the wave sums.
-    const int grp = lane >> 3, part = lane & 7;
+    const int grp = (lane >> 3) & (NS - 1), part = lane & 7;
     auto group8_total = [](double a) {
         a = dpp_add<0xB1, 0xf>(a);                                 // lane ^ 1  (quad_perm 1,0,3,2)
         a = dpp_add<0x4E, 0xf>(a);                                 // lane ^ 2  (quad_perm 2,3,0,1)
@@ -354,12 +365,15 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     };
 #pragma unroll
     for (int i = 0; i < (CACHE_E ? 4 : 8); ++i) {
+        if (!wanted(i)) continue;
         acc[i] = dpp_add<0xB1, 0xf>(acc[i]);
         acc[i] = dpp_add<0x4E, 0xf>(acc[i]);
     }
     if ((lane & 3) == 0) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) sm_w[wave][i][lane >> 2] = acc[i];
+        for (int i = 0; i < 8; ++i) {
+            if (wanted(i)) sm_w[wave][slot_of(i)][lane >> 2] = acc[i];
+        }
     }
     double wave_total;
     {
@@ -383,8 +397,9 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i)
-            tot[i] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(a), 8 * i),
-                                      __builtin_amdgcn_readlane(__double2loint(a), 8 * i));
+            tot[i] = !wanted(i) ? 0.0
+                                : __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(a), 8 * slot_of(i)),
+                                                   __builtin_amdgcn_readlane(__double2loint(a), 8 * slot_of(i)));
     }
     // (sm_x is written again only after the next barriers: pass 3's exchange uses sm_d)
 
@@ -396,29 +411,32 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     // distance is small that was the whole absolute tolerance (a seeded random case: distance 4.0e-4, off by 1.06e-7).
     // (A product e * (1/S) rounded on its own would leave that much per factor and per term.)
     // The division by S is left to dro_finish_row.
-    float rho[3], rlo[3];
+    constexpr int NL = RAD ? 3 : 1;                                // distances
+    float rho[NL], rlo[NL];
     {
         // 1 / Z: hardware reciprocal and one Newton step in fp64 (~1e-14), no fp64 division
         const double z = tot[3], r0 = (double)__builtin_amdgcn_rcpf((float)z);
         const double rz = fma(r0, fma(-z, r0, 1.0), r0);
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
+        for (int i = 0; i < NL; ++i) {
             const double rr = tot[i] * rz;
             rho[i] = (float)rr;
             rlo[i] = (float)(rr - (double)rho[i]);
         }
     }
-    double l1[3] = {0.0, 0.0, 0.0};
+    double l1[NL] = {};
     if constexpr (CACHE_E) {
-        float a32[3] = {0.f, 0.f, 0.f};                            // (per lane in fp32: sums of non-negative terms)
+        float a32[NL] = {};                                        // (per lane in fp32: sums of non-negative terms)
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
             a32[0] += fabsf(fmaf(-ec[i], rlo[0], fmaf(-ec[i], rho[0], em[i])));
-            a32[1] += fabsf(fmaf(-ec[i], rlo[1], fmaf(-ec[i], rho[1], eu[i])));
-            a32[2] += fabsf(fmaf(-ec[i], rlo[2], fmaf(-ec[i], rho[2], el[i])));
+            if constexpr (RAD) {
+                a32[1] += fabsf(fmaf(-ec[i], rlo[1], fmaf(-ec[i], rho[1], eu[i])));
+                a32[2] += fabsf(fmaf(-ec[i], rlo[2], fmaf(-ec[i], rho[2], el[i])));
+            }
         }
 #pragma unroll
-        for (int i = 0; i < 3; ++i) l1[i] = (double)a32[i];
+        for (int i = 0; i < NL; ++i) l1[i] = (double)a32[i];
     } else {
         fresh();
 #pragma unroll
@@ -428,10 +446,12 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
                 float c, r, t;
                 element(j, k, c, r, t);
                 const float et = exp_rel(t, mt), e0 = exp_rel(c, mc);
-                const RadiusFactors f = radius_factors(r, rref);
                 l1[0] += (double)fabsf(fmaf(-et, rlo[0], fmaf(-et, rho[0], e0)));
-                l1[1] += (double)fabsf(fmaf(-et, rlo[1], fmaf(-et, rho[1], e0 * f.up)));
-                l1[2] += (double)fabsf(fmaf(-et, rlo[2], fmaf(-et, rho[2], e0 * f.lo)));
+                if constexpr (RAD) {
+                    const RadiusFactors f = radius_factors(r, rref);
+                    l1[1] += (double)fabsf(fmaf(-et, rlo[1], fmaf(-et, rho[1], e0 * f.up)));
+                    l1[2] += (double)fabsf(fmaf(-et, rlo[2], fmaf(-et, rho[2], e0 * f.lo)));
+                }
                 if (k & 1) __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -441,7 +461,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     {
         float* slot = reinterpret_cast<float*>(sm_d);              // [3][NW] floats
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
+        for (int i = 0; i < NL; ++i) {
             float v = (float)l1[i];
             v += __int_as_float(dpp_or<kRowShr1, 0xf>(0, __float_as_int(v)));
             v += __int_as_float(dpp_or<kRowShr2, 0xf>(0, __float_as_int(v)));
@@ -457,13 +477,14 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
         double L[3];
         const float* slot = reinterpret_cast<const float*>(sm_d);
 #pragma unroll
-        for (int i = 0; i < 3; ++i) L[i] = (double)row16_sum_f(lane < NW ? slot[i * NW + lane] : 0.f);
+        for (int i = 0; i < NL; ++i) L[i] = (double)row16_sum_f(lane < NW ? slot[i * NW + lane] : 0.f);
         // the row's totals, for dro_finish_row: S_mid, S_up, S_lo, Z, the four p_cloud-weighted sums of exponents (times Z),
         // the three L1 distances (times S_mid, S_up, S_lo)
         if (lane == 0) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) fin[i] = tot[i];
-            fin[8] = L[0]; fin[9] = L[1]; fin[10] = L[2];
+            fin[8] = L[0];
+            if constexpr (RAD) { fin[9] = L[1]; fin[10] = L[2]; }
         }
     }
 }
@@ -472,26 +493,29 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
 // Kept out of the row loop of dro_row_stream_kernel: the constants of the fp64 logarithm would otherwise be hoisted to
 // the top of that loop and live in registers (or in scratch memory) through all of it.
 constexpr int kDroTotals = 11;
+template <bool RAD>
 __device__ __forceinline__ void dro_finish_row(const RowArgs& A, float* __restrict__ terms, const int64_t row,
                                                const double* fin)
 {
     const double Z = fin[3], ln2_Z = kLn2 / Z;                     // (the weighted sums are over base-2 exponents)
     const double ce_mid = log(fin[0]) - fin[4] * ln2_Z;
-    const double ce_up = log(fin[1]) - fin[5] * ln2_Z;
-    const double ce_lo = log(fin[2]) - fin[6] * ln2_Z;
+    const double ce_up = RAD ? log(fin[1]) - fin[5] * ln2_Z : ce_mid;
+    const double ce_lo = RAD ? log(fin[2]) - fin[6] * ln2_Z : ce_mid;
     // KL = CE(p_cloud, p_mid) - H(p_cloud) = ln S - ln Z + sum_i p_cloud_i (dt_i - d_i): the last sum is taken over the
     // differences token by token (fin[7]), so that a cloud row close to the centre row -- a small KL, the difference of two
     // cross-entropy-sized numbers -- keeps its accuracy (a seeded random case missed the absolute bound by a quarter
     // with the two sums taken separately)
     const double kl = (log(fin[0]) - log(Z)) + fin[7] * ln2_Z;
     const int64_t N = A.N;
-    terms[0 * N + row] = (float)(fin[8] / fin[0]); terms[1 * N + row] = (float)(fin[9] / fin[1]);
-    terms[2 * N + row] = (float)(fin[10] / fin[2]);
+    const double l1 = fin[8] / fin[0];
+    terms[0 * N + row] = (float)l1;
+    terms[1 * N + row] = (float)(RAD ? fin[9] / fin[1] : l1);
+    terms[2 * N + row] = (float)(RAD ? fin[10] / fin[2] : l1);
     terms[3 * N + row] = (float)ce_mid; terms[4 * N + row] = (float)ce_up; terms[5 * N + row] = (float)ce_lo;
     terms[6 * N + row] = (float)kl;
 }
 
-template <typename T, int NVEC, int RAD = -1>
+template <typename T, int NVEC, bool RAD>
 __global__ __launch_bounds__(1024) void dro_row_kernel(const RowArgs A, const DroRadius R, float* __restrict__ terms)
 {
     constexpr int THREADS = 1024, NW = 16;
@@ -499,26 +523,28 @@ __global__ __launch_bounds__(1024) void dro_row_kernel(const RowArgs A, const Dr
     const int tid = threadIdx.x;
     const int64_t row = blockIdx.x;
     const int last_vec = (A.V + Elt<T>::kPerVec - 1) / Elt<T>::kPerVec - 1;
-    const bool rad = RAD < 0 ? A.radius != nullptr : RAD == 1;     // uniform
     const gbytes cb = (gbytes)(static_cast<const T*>(A.draft) + row * A.stride);
     const gbytes tb = (gbytes)(static_cast<const T*>(A.target) + row * A.stride);
-    const gbytes rb = (gbytes)(static_cast<const T*>(rad ? A.radius : A.draft) + row * A.stride);
+    const gbytes rb = (gbytes)(static_cast<const T*>(RAD ? A.radius : A.draft) + row * A.stride);
     u32x4 cw[NVEC], tw[NVEC], rw[NVEC];
 #pragma unroll
     for (int j = 0; j < NVEC; ++j) {
         const uint32_t off = (uint32_t)min(j * THREADS + tid, last_vec) * 16u;
         cw[j] = __builtin_nontemporal_load((gvec)(cb + off));     // every row is used once: stream past the caches
         tw[j] = __builtin_nontemporal_load((gvec)(tb + off));
-        if (rad) rw[j] = __builtin_nontemporal_load((gvec)(rb + off));
+        if constexpr (RAD) rw[j] = __builtin_nontemporal_load((gvec)(rb + off));
     }
     __shared__ double sm_fin[kDroTotals];
     dro_row_compute<T, NVEC, THREADS, RAD>(A, R, sm_fin, cw, tw, rw, sm_d, tid);
-    if (tid == 0) dro_finish_row(A, terms, row, sm_fin);           // (the lane that has written the totals)
+    if (tid == 0) dro_finish_row<RAD>(A, terms, row, sm_fin);           // (the lane that has written the totals)
 }
 
 // Most rows that a workgroup of dro_row_stream_kernel takes: what fits in its share of a compute unit's LDS next to the rows
 // in flight.
-template <int THREADS> constexpr int dro_rows() { return THREADS >= 512 ? 64 : THREADS / 8; }
+template <int THREADS, bool RAD> constexpr int dro_rows()
+{
+    return RAD ? (THREADS >= 512 ? 64 : THREADS / 8) : (THREADS >= 256 ? THREADS / 32 : 8);
+}
 
 // The same with the next row on its way while a row is worked on.  1024 / THREADS workgroups per compute unit walk
 // over rows blockIdx.x, blockIdx.x + gridDim.x, ...; the three rows of a position and the working set leave no
@@ -528,18 +554,17 @@ template <int THREADS> constexpr int dro_rows() { return THREADS >= 512 ? 64 : T
 // row into the NVEC registers that the current radius row has left.  Every lane reads back only the slots that its own
 // wave's loads have written, so the hand-over needs the wave's own vmcnt(0) and no barrier.
 // Dynamic LDS: 2 x NVEC x 16 x THREADS bytes (NVEC <= 4).
-template <typename T, int NVEC, int THREADS>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) void dro_row_stream_kernel(const RowArgs A, const DroRadius R,
+template <typename T, int NVEC, int THREADS, bool RAD>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(RAD || NVEC * Elt<T>::kPerVec > 16 ? 4 : 8))) void dro_row_stream_kernel(const RowArgs A, const DroRadius R,
                                                               float* __restrict__ terms)
 {
-    constexpr int NW = THREADS / 64, ROWS = dro_rows<THREADS>();
+    constexpr int NW = THREADS / 64, ROWS = dro_rows<THREADS, RAD>();
     extern __shared__ u32x4 sm_rows[];                             // [2][NVEC][THREADS]: next centre row, next cloud row
     __shared__ double sm_d[NW * 7];
     __shared__ double sm_fin[ROWS][kDroTotals];           // the totals of this workgroup's rows
     const int tid = threadIdx.x;
     const int wave_s = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int last_vec = (A.V + Elt<T>::kPerVec - 1) / Elt<T>::kPerVec - 1;
-    const bool rad = A.radius != nullptr;                          // uniform
     using lds_ptr = __attribute__((address_space(3))) void*;
     using glb_ptr = const __attribute__((address_space(1))) void*;
 
@@ -572,7 +597,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) vo
     int done = 0;                                                  // rows of this workgroup finished so far (<= ROWS)
     if (row < n_rows) {
         request_rows(row, tid);
-        if (rad) request_radius(row, rnext, tid);
+        if constexpr (RAD) request_radius(row, rnext, tid);
     }
     for (; row < n_rows; row += gridDim.x) {
         // this wave's loads have landed (its slots of the two rows in LDS, and the radius registers)
@@ -593,16 +618,16 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(4))) vo
         const uint32_t next = row + gridDim.x;
         if (next < n_rows) {
             request_rows(next, t);
-            if (rad) request_radius(next, rnext, t);
+            if constexpr (RAD) request_radius(next, rnext, t);
         }
-        dro_row_compute<T, NVEC, THREADS>(A, R, sm_fin[done], cw, tw, rw, sm_d, t);
+        dro_row_compute<T, NVEC, THREADS, RAD>(A, R, sm_fin[done], cw, tw, rw, sm_d, t);
         // (no barrier here: what wave 0 still reads of sm_d is written again only in the next row's pass 3, two
         // barriers on)
         ++done;
     }
     // one lane per row turns the totals into the row's terms
     __syncthreads();
-    if (tid < done) dro_finish_row(A, terms, (int64_t)blockIdx.x + (int64_t)tid * gridDim.x, sm_fin[tid]);
+    if (tid < done) dro_finish_row<RAD>(A, terms, (int64_t)blockIdx.x + (int64_t)tid * gridDim.x, sm_fin[tid]);
 }
 
 // The same terms for a handful of tokens (V <= kTinyVocab): one thread per row, fp64 throughout.  With so few
@@ -712,7 +737,7 @@ __global__ __launch_bounds__(T) void dro_batch_kernel(const float* __restrict__ 
 }  // namespace
 
 namespace {
-template <typename T, int NVEC, int THREADS>
+template <typename T, int NVEC, int THREADS, bool RAD>
 hipError_t launch_dro_stream_cfg(const RowArgs& a, float* terms, hipStream_t stream)
 {
     constexpr unsigned lds = 2u * NVEC * THREADS * 16u;
@@ -724,16 +749,21 @@ hipError_t launch_dro_stream_cfg(const RowArgs& a, float* terms, hipStream_t str
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
         std::lock_guard<std::mutex> lock(guard);
         if (!raised[dev]) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dro_row_stream_kernel<T, NVEC, THREADS>),
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dro_row_stream_kernel<T, NVEC, THREADS, RAD>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
             raised[dev] = true;
         }
     }
-    const int64_t g = whole_rounds(a.N, dro_rows<THREADS>(), (int64_t)(1024 / THREADS) * compute_units());
+    // Workgroups of a compute unit: sixteen waves with a radius tensor (128 registers).  Without one a wave of 16 tokens per lane gets
+    // by with 64 registers, and there are as many workgroups as the unit's LDS has room for, thirty-two waves at most.
+    constexpr int kLds = 160 * 1024, kUsed = (int)lds + THREADS / 64 * 648 + 88 * dro_rows<THREADS, RAD>();
+    constexpr int kFit = kLds / ((kUsed + 1279) / 1280 * 1280), kMost = 2048 / THREADS;
+    constexpr int per_cu = RAD || NVEC * Elt<T>::kPerVec > 16 ? 1024 / THREADS : kFit < kMost ? kFit : kMost;
+    const int64_t g = whole_rounds(a.N, dro_rows<THREADS, RAD>(), (int64_t)per_cu * compute_units());
     const dim3 grid((unsigned)g), block(THREADS);
-    const DroRadius R = {(float)a.kappa, (float)a.rmax, (float)fmin(a.kappa, a.rmax)};
-    hipLaunchKernelGGL((dro_row_stream_kernel<T, NVEC, THREADS>), grid, block, lds, stream, a, R, terms);
+    const DroRadius R = {(float)a.kappa, (float)a.rmax};
+    hipLaunchKernelGGL((dro_row_stream_kernel<T, NVEC, THREADS, RAD>), grid, block, lds, stream, a, R, terms);
     return hipGetLastError();
 }
 // 16 tokens per lane -- the most whose exponentials pass 3 finds in registers -- and as many lanes as the row then takes:
@@ -742,16 +772,34 @@ hipError_t launch_dro_stream_cfg(const RowArgs& a, float* terms, hipStream_t str
 // tensor, with 1024 lanes to every row -> with these: V = 1024 726 -> 183 us (bf16: 2667 -> 340), 4096 204 -> 148 (bf16:
 // 861 -> 271), 8192 168 -> 154 (bf16: 298 -> 243); 257 to 1000 rows, where the calls wait for latency, 18 to 26 us -> 17 to 20.
 // bf16 rows of 16385 to 32768 tokens take 32 tokens per lane.
-template <typename T>
+template <typename T, bool RAD>
 hipError_t launch_dro_stream(int vecs, const RowArgs& a, float* terms, hipStream_t stream)
 {
     constexpr int NV = 16 / Elt<T>::kPerVec;
-    if (vecs <= 64 * NV) return launch_dro_stream_cfg<T, NV, 64>(a, terms, stream);
-    if (vecs <= 128 * NV) return launch_dro_stream_cfg<T, NV, 128>(a, terms, stream);
-    if (vecs <= 256 * NV) return launch_dro_stream_cfg<T, NV, 256>(a, terms, stream);
-    if (vecs <= 512 * NV) return launch_dro_stream_cfg<T, NV, 512>(a, terms, stream);
-    if (vecs <= 1024 * NV) return launch_dro_stream_cfg<T, NV, 1024>(a, terms, stream);
-    return launch_dro_stream_cfg<T, 4, 1024>(a, terms, stream);
+    if (vecs <= 64 * NV) return launch_dro_stream_cfg<T, NV, 64, RAD>(a, terms, stream);
+    if (vecs <= 128 * NV) return launch_dro_stream_cfg<T, NV, 128, RAD>(a, terms, stream);
+    if (vecs <= 256 * NV) return launch_dro_stream_cfg<T, NV, 256, RAD>(a, terms, stream);
+    if (vecs <= 512 * NV) return launch_dro_stream_cfg<T, NV, 512, RAD>(a, terms, stream);
+    if (vecs <= 1024 * NV) return launch_dro_stream_cfg<T, NV, 1024, RAD>(a, terms, stream);
+    return launch_dro_stream_cfg<T, 4, 1024, RAD>(a, terms, stream);
+}
+template <typename T, bool RAD>
+hipError_t launch_dro_rows(int vecs, const RowArgs& a, float* terms, hipStream_t stream)
+{
+    if (vecs <= 4096 && a.N > (int64_t)compute_units()) return launch_dro_stream<T, RAD>(vecs, a, terms, stream);
+    const dim3 grid((unsigned)a.N), block(1024);
+    const DroRadius R = {(float)a.kappa, (float)a.rmax};
+    if (vecs <= 1024) hipLaunchKernelGGL((dro_row_kernel<T, 1, RAD>), grid, block, 0, stream, a, R, terms);
+    else if (vecs <= 2048) hipLaunchKernelGGL((dro_row_kernel<T, 2, RAD>), grid, block, 0, stream, a, R, terms);
+    else if (vecs <= 4096) hipLaunchKernelGGL((dro_row_kernel<T, 4, RAD>), grid, block, 0, stream, a, R, terms);
+    else if (vecs <= 8192) hipLaunchKernelGGL((dro_row_kernel<T, 8, RAD>), grid, block, 0, stream, a, R, terms);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+template <typename T>
+hipError_t launch_dro_typed(int vecs, const RowArgs& a, float* terms, hipStream_t stream)
+{
+    return a.radius ? launch_dro_rows<T, true>(vecs, a, terms, stream) : launch_dro_rows<T, false>(vecs, a, terms, stream);
 }
 }  // namespace
 
@@ -761,30 +809,15 @@ hipError_t launch_dro(int dtype, const RowArgs& args, float* terms, double lambd
     if (args.N <= 0) return hipSuccess;
     const int epv = dtype == 0 ? 4 : 8;
     const int vecs = (args.V + epv - 1) / epv;
-    const dim3 grid((unsigned)args.N), block(1024);
-    const DroRadius R = {(float)args.kappa, (float)args.rmax, (float)fmin(args.kappa, args.rmax)};
-#define CIAR_DRO_LAUNCH(NV)                                                                             \
-    do {                                                                                                \
-        if (dtype == 0) hipLaunchKernelGGL((dro_row_kernel<float, NV>), grid, block, 0, stream, args, R, terms);   \
-        else hipLaunchKernelGGL((dro_row_kernel<bf16_t, NV>), grid, block, 0, stream, args, R, terms);           \
-    } while (0)
     if (args.V <= kTinyVocab) {
         const dim3 tgrid((unsigned)((args.N + 255) / 256)), tblock(256);
         if (dtype == 0) hipLaunchKernelGGL(dro_row_tiny_kernel<float>, tgrid, tblock, 0, stream, args, terms);
         else hipLaunchKernelGGL(dro_row_tiny_kernel<bf16_t>, tgrid, tblock, 0, stream, args, terms);
-    } else if (vecs <= 4096 && args.N > (int64_t)compute_units()) {
-        // more rows than compute units: persistent workgroups that fetch the next row through LDS
-        const hipError_t e = dtype == 0 ? launch_dro_stream<float>(vecs, args, terms, stream)
-                                        : launch_dro_stream<bf16_t>(vecs, args, terms, stream);
+    } else {
+        const hipError_t e = dtype == 0 ? launch_dro_typed<float>(vecs, args, terms, stream)
+                                        : launch_dro_typed<bf16_t>(vecs, args, terms, stream);
         if (e != hipSuccess) return e;
-    } else if (vecs <= 1024) CIAR_DRO_LAUNCH(1);
-    else if (vecs <= 2048) CIAR_DRO_LAUNCH(2);
-    else if (vecs <= 4096) CIAR_DRO_LAUNCH(4);
-    else if (vecs <= 8192 && dtype == 0) hipLaunchKernelGGL((dro_row_kernel<float, 8>), grid, block, 0, stream, args, R, terms);
-    else if (vecs <= 8192 && args.radius) hipLaunchKernelGGL((dro_row_kernel<bf16_t, 8, 1>), grid, block, 0, stream, args, R, terms);
-    else if (vecs <= 8192) hipLaunchKernelGGL((dro_row_kernel<bf16_t, 8, 0>), grid, block, 0, stream, args, R, terms);
-    else return hipErrorInvalidValue;
-#undef CIAR_DRO_LAUNCH
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || (!weights && !losses)) return e;
     if (args.N > 8192)
