@@ -695,11 +695,25 @@ __global__ __launch_bounds__(T) void dro_batch_kernel(const float* __restrict__ 
     const float* ce_lo = terms + 5 * N;
     float mxf = -INFINITY;
     double c = 0.0, u = 0.0, l = 0.0;
-    for (int64_t n = tid; n < N; n += T) {
-        mxf = fmaxf(mxf, (float)(alpha * (double)ce_lo[n]));
-        c += lambda_v * terms[n] + lambda_p * terms[3 * N + n] + lambda_beta * terms[6 * N + n];
-        u += lambda_v * terms[N + n] + lambda_p * terms[4 * N + n];
-        l += lambda_v * terms[2 * N + n] + lambda_p * terms[5 * N + n];
+    // (four rows' terms requested at a time: one compute unit waits for its trips to memory, 8000 rows 15.5 -> 13.3
+    // us, 20000 26 -> 22, 60000 70 -> 57)
+    constexpr int U = 4;
+    for (int64_t n0 = tid; n0 < N; n0 += U * T) {
+        float v[U][7];
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int64_t n = n0 + i * T < N ? n0 + i * T : n0;
+#pragma unroll
+            for (int k = 0; k < 7; ++k) v[i][k] = terms[k * N + n];
+        }
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            if (n0 + i * T >= N) break;
+            mxf = fmaxf(mxf, (float)(alpha * (double)v[i][5]));
+            c += lambda_v * v[i][0] + lambda_p * v[i][3] + lambda_beta * v[i][6];
+            u += lambda_v * v[i][1] + lambda_p * v[i][4];
+            l += lambda_v * v[i][2] + lambda_p * v[i][5];
+        }
     }
     mxf = wave_max(mxf);
     if (lane == 0) sm[wave] = (double)mxf;
@@ -708,12 +722,19 @@ __global__ __launch_bounds__(T) void dro_batch_kernel(const float* __restrict__ 
     for (int w = 1; w < NW; ++w) mx = fmax(mx, sm[w]);
     __syncthreads();
     double den = 0.0, num = 0.0;
-    for (int64_t n = tid; n < N; n += T) {
-        const double ce = (double)ce_lo[n];
-        const double e = exp(alpha * ce - mx);
-        den += e;
-        num = fma(e, ce, num);
-        if (weights) weights[n] = (float)e;                        // scaled below
+    for (int64_t n0 = tid; n0 < N; n0 += U * T) {
+        float v[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) v[i] = ce_lo[n0 + i * T < N ? n0 + i * T : n0];
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            if (n0 + i * T >= N) break;
+            const double ce = (double)v[i];
+            const double e = exp(alpha * ce - mx);
+            den += e;
+            num = fma(e, ce, num);
+            if (weights) weights[n0 + i * T] = (float)e;           // scaled below
+        }
     }
     c = wave_sum(c); u = wave_sum(u); l = wave_sum(l); den = wave_sum(den); num = wave_sum(num);
     if (lane == 0) { sm[wave * 5] = c; sm[wave * 5 + 1] = u; sm[wave * 5 + 2] = l; sm[wave * 5 + 3] = den; sm[wave * 5 + 4] = num; }
@@ -724,7 +745,14 @@ __global__ __launch_bounds__(T) void dro_batch_kernel(const float* __restrict__ 
     if (weights) {
         // float(e) / den in fp64 rounds e twice (once to float above): 6e-8 relative, far inside the weights' tolerance
         const double inv = 1.0 / tot[3];
-        for (int64_t n = tid; n < N; n += T) weights[n] = (float)((double)weights[n] * inv);
+        for (int64_t n0 = tid; n0 < N; n0 += U * T) {
+            float v[U];
+#pragma unroll
+            for (int i = 0; i < U; ++i) v[i] = weights[n0 + i * T < N ? n0 + i * T : n0];
+#pragma unroll
+            for (int i = 0; i < U; ++i)
+                if (n0 + i * T < N) weights[n0 + i * T] = (float)((double)v[i] * inv);
+        }
     }
     if (tid == 0 && losses) {
         const double Nd = (double)N, dro = tot[4] / tot[3];
