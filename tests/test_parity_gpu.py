@@ -1827,3 +1827,26 @@ def test_radius_vote_of_rows_taken_again(ciar, oracle, V, dtype, N):
         parity.check_floats({k: v[k][h] for k in parity.FLOAT_KEYS}, oh)
         parity.check_flags(v["head_flags"][h], oh, tau)
     assert torch.equal(v["flags"], (2 * v["head_flags"].sum(0, dtype=torch.int32) > 3).to(torch.uint8))
+
+
+# bf16 rows of more than 8192 tokens with a verifier row: both ends of the tiles of 128, 256 and 512 lanes with twelve and sixteen
+# vectors each, rows that fill a tile and rows that do not, one row to a workgroup and several.
+BOTH_ROWS = [
+    (8193, 8200, 1100), (12288, 12288, 300), (12289, 12296, 300), (16383, 16384, 1100), (16384, 16384, 1100), (16385, 16392, 200),
+    (24576, 24576, 560), (24577, 24584, 100), (32768, 32768, 520), (32769, 32776, 300), (49152, 49152, 60), (49153, 49160, 270),
+    (65536, 65536, 30),
+]
+
+
+@pytest.mark.parametrize("V,stride,N", BOTH_ROWS)
+def test_large_bf16_rows_with_a_verifier_row(ciar, oracle, V, stride, N):
+    c, t, ids, ua, ur = _random_case(V, stride, N, 5, torch.bfloat16, seed=8100 + V, sigma=0.8)
+    low = torch.finfo(torch.bfloat16).min
+    for r in range(0, N, 7):                                               # rows that may not go through the matrix cores, in part
+        lo = (r * 613) % V
+        (c if r % 2 else t)[r, lo:min(lo + 700, V)] = (float("-inf"), low, -1e30)[r % 3]
+    c[3, :V] = 0.25                                                        # a flat row
+    ids = torch.where(c[torch.arange(N, device="cuda"), ids.long()].float() < -1e20, c[:, :V].float().argmax(1).to(torch.int32), ids)
+    for kw in (dict(confidence=0.9, window=5), dict(radius_scale=0.02, window=1), dict(radius_scale=0.7, normalize=False, window=300)):
+        P = ciar.Params(tau=0.01, **kw)
+        _run_case(ciar, oracle, c, t, ids, ua, ur, P, vocab=V, tag=f"both rows V={V} N={N} {kw}")
