@@ -70,6 +70,9 @@ struct StreamLaunch {
 
 // Calls on bf16 rows of more than 8192 tokens with a verifier row, without a radius tensor and without complements (wide_radius).
 hipError_t launch_both_rows(Mode mode, const RowArgs& a, StreamLaunch& s);
+// Calls with a verifier row, without a radius tensor and without complements, on short rows where there are enough of them.
+bool short_rows_fit(int dtype, int vecs, int64_t rows);
+hipError_t launch_short_rows(int dtype, Mode mode, const RowArgs& a, StreamLaunch& s);
 
 namespace {
 
@@ -80,6 +83,11 @@ namespace {
 // unit rather than by fetching ahead into a second set of registers: measured on this chip, three or
 // four resident workgroups beat two with a register prefetch of the next row at every vocabulary size.
 // (Tensor-radius mode: the raw radius row sits in registers next to the centre row during the interval pass.)
+// Short rows with a verifier row, many of them: a wave to a row, or two, of at most eight vectors per lane.  With 256 lanes to
+// every row a row of 1024 tokens left a lane four of them, and the 415 instructions that a wave spends per row were nearly all of
+// its work; here one wave has them all, no wave waits for another, and its rows come through LDS as below (16384 x 1024 fused bf16
+// 90 -> 33 us, fp32 65 -> 35; the rule and more figures: short_rows_fit).
+//
 // Large bf16 rows with a verifier row: twelve or sixteen vectors per lane at two waves per SIMD, the rows arriving through LDS.
 // Bound by vector instructions: 16.9 of them per position and token are the tokens' own arithmetic, what a wave does per row besides
 // (reductions, exchange, accept test) is spread over 128 tokens of a lane instead of 64, and with 256 registers the exponentials
@@ -94,12 +102,18 @@ namespace {
 // instructions busy 80 % of the time; a fused pass over rows that stay in the caches takes 186 us without its draws, 229 with.
 // (Same tiles, fp32: 2048 x 16384 50 / 55; those calls wait for memory.  Voting with radius tensors, radius_lean_kernel with
 // sixteen vectors: 106 / 121.)
-template <int NVEC, bool DO_V, bool RAD, bool WIDE>
-constexpr bool next_by_lds() { return DO_V && !RAD && !WIDE && (NVEC == 16 || NVEC == 12); }
+template <typename T, int THREADS, int NVEC, bool DO_V, bool RAD, bool WIDE>
+constexpr bool next_by_lds()
+{
+    return DO_V && !RAD && !WIDE && (NVEC == 16 || NVEC == 12 || THREADS <= 128);
+}
 template <typename T, int THREADS, int NVEC, bool RAD, bool DO_V = false>
 constexpr int target_waves()
 {
-    if (next_by_lds<NVEC, DO_V, RAD, false>()) return 2;
+    if (next_by_lds<T, THREADS, NVEC, DO_V, RAD, false>()) {
+        constexpr int regs = NVEC * Elt<T>::kPerVec + NVEC * 4 + 56;   // the centre row's exponentials, the verifier row, working registers
+        return regs <= 128 ? 4 : regs <= 168 ? 3 : 2;
+    }
     constexpr int ept = NVEC * Elt<T>::kPerVec;                    // one row as floats
     constexpr int fit = 512 / (ept + (RAD ? NVEC * 4 + 8 : 0) + 40);
     constexpr int lo = (THREADS + 255) / 256;                      // waves per SIMD one workgroup needs
@@ -347,23 +361,23 @@ __device__ __forceinline__ void fuse_sums_rad(const float (&e)[NVEC * Elt<T>::kP
 // up to 8 vectors per lane) ...
 // ... during the interval pass, so that the verifier row can be requested ahead of it (scalar radius: with a radius
 // tensor that place is taken by the raw radius row);
-template <typename T, int NVEC, bool DO_V, bool RAD, bool WIDE>
+template <typename T, int THREADS, int NVEC, bool DO_V, bool RAD, bool WIDE>
 constexpr bool second_row_early()
 {
-    return DO_V && !RAD && !WIDE && !next_by_lds<NVEC, DO_V, RAD, WIDE>() && (NVEC * Elt<T>::kPerVec + NVEC * 4 + 56) * 4 <= 512;
+    return DO_V && !RAD && !WIDE && !next_by_lds<T, THREADS, NVEC, DO_V, RAD, WIDE>() && (NVEC * Elt<T>::kPerVec + NVEC * 4 + 56) * 4 <= 512;
 }
 // ... behind it, so that a launch with a verifier row makes the residual draws of its rejected rows inside the
 // streaming kernel (scalar or tensor radius: by then the verifier row has taken the raw radius row's place).
-template <typename T, int NVEC, bool DO_V, bool RAD, bool WIDE>
+template <typename T, int THREADS, int NVEC, bool DO_V, bool RAD, bool WIDE>
 constexpr bool draws_in_stream()
 {
-    return next_by_lds<NVEC, DO_V, RAD, WIDE>() || (DO_V && !WIDE && (NVEC * Elt<T>::kPerVec + NVEC * 4 + 56) * 4 <= 512);
+    return next_by_lds<T, THREADS, NVEC, DO_V, RAD, WIDE>() || (DO_V && !WIDE && (NVEC * Elt<T>::kPerVec + NVEC * 4 + 56) * 4 <= 512);
 }
 // Most rows a workgroup has room for: kMaxRowsPerWg, or what the rows in flight leave of a compute unit's LDS.
-template <int THREADS, int NVEC, bool DO_V, bool RAD, bool WIDE>
+template <typename T, int THREADS, int NVEC, bool DO_V, bool RAD, bool WIDE>
 constexpr int rows_per_wg()
 {
-    return !next_by_lds<NVEC, DO_V, RAD, WIDE>() || THREADS >= 512 ? kMaxRowsPerWg : THREADS == 256 ? 64 : 40;
+    return !next_by_lds<T, THREADS, NVEC, DO_V, RAD, WIDE>() || THREADS >= 512 ? kMaxRowsPerWg : THREADS == 256 ? 64 : THREADS == 128 && NVEC > 8 ? 40 : 16;
 }
 
 // sm_draw / row_id of a rejected row whose draw is still to be made (by resample_kernel)
@@ -391,7 +405,7 @@ void stream_kernel(const RowArgs A)
     // The verifier row is requested before the interval pass where a second row fits in the registers at
     // four waves per SIMD next to the centre row's floats (fp32 tiles of up to 8 vectors per lane; measured
     // 51 -> 48.6 us on the benchmark); elsewhere it would spill, and it is requested after the pass.
-    constexpr bool EARLY_T = second_row_early<T, NVEC, DO_V, RAD, WIDE>();
+    constexpr bool EARLY_T = second_row_early<T, THREADS, NVEC, DO_V, RAD, WIDE>();
     // Quantify-only launches have no verifier row; under the same condition the next centre row is requested
     // before the interval pass instead.
     constexpr bool EARLY_NEXT = !DO_V && !RAD && !WIDE && (EPT + NVEC * 4 + 56) * 4 <= 512;
@@ -401,9 +415,9 @@ void stream_kernel(const RowArgs A)
     // draws them behind this kernel (measured with the draw here and the centre row fetched again: the branch
     // alone, never taken, cost the bf16 row loop 11 % -- registers and scheduling -- and workload 3 ran 318 against
     // 285 us per step).
-    constexpr bool KEEP_E = draws_in_stream<T, NVEC, DO_V, RAD, WIDE>();
-    constexpr bool LDS_NEXT = next_by_lds<NVEC, DO_V, RAD, WIDE>();
-    constexpr int ROWS = rows_per_wg<THREADS, NVEC, DO_V, RAD, WIDE>();
+    constexpr bool KEEP_E = draws_in_stream<T, THREADS, NVEC, DO_V, RAD, WIDE>();
+    constexpr bool LDS_NEXT = next_by_lds<T, THREADS, NVEC, DO_V, RAD, WIDE>();
+    constexpr int ROWS = rows_per_wg<T, THREADS, NVEC, DO_V, RAD, WIDE>();
     // Fused launches on bf16 rows with a scalar radius: the two interval sums of a row whose caps are inactive and the
     // verifier row's partition sum are reduced over the wave together (wave_sum3) once the verifier row has been summed.
     // (These instances are bound by their vector instructions: workload 5 1951 -> 1905 us.  The fp32 instances, which
@@ -431,8 +445,8 @@ void stream_kernel(const RowArgs A)
     __shared__ float  sm_nt2[LDS_NEXT ? 2 : 1][NW]; // per wave: nt_w
     __shared__ double sm_Z2[LDS_NEXT ? 2 : 1][NW];  // per wave: Z_w
     __shared__ double sm_q52[LDS_NEXT ? 2 : 1][NW * NQ];   // per wave: the interval sums, already in row units
-    __shared__ double sm_sum[LDS_NEXT ? NW : 1][64];       // LDS_NEXT, per wave: [interval sums of the row before, S_w, Z_w][eight groups of lanes]
-    __shared__ double sm_red[BATCH3 ? NW : 1][48];  // per wave: the slots of wave_sum3
+    __shared__ double sm_sum[LDS_NEXT ? NW : 1][LDS_NEXT ? 64 : 1];       // LDS_NEXT, per wave: [interval sums of the row before, S_w, Z_w][eight groups of lanes]
+    __shared__ double sm_red[BATCH3 ? NW : 1][BATCH3 ? 48 : 1];  // per wave: the slots of wave_sum3
     __shared__ double sm_k[3];                      // the shift the sums are taken about (row units), from wave 0
     __shared__ float  sm_e0;                        // e of the row's first token, in the units of wave 0
     // Finishing inside this kernel: the statistics of the rows this workgroup has streamed since its last
@@ -446,7 +460,7 @@ void stream_kernel(const RowArgs A)
     __shared__ int      sm_draw[DO_V ? ROWS : 1];   // -1: the drafted token was accepted; else the row's draw
     __shared__ uint8_t  sm_close[DO_V ? ROWS : 1];  // the fp32 accept test could not decide the row
     __shared__ double   sm_tab[DO_V ? NT : 1];      // residual mass of each piece of a rejected row
-    __shared__ __attribute__((aligned(16))) double sm_quad[KEEP_E && NVEC >= 8 ? NW : 1][8][16];   // a draw's quad sums
+    __shared__ __attribute__((aligned(16))) double sm_quad[KEEP_E && (NVEC >= 8 || LDS_NEXT) ? NW : 1][KEEP_E && (NVEC >= 8 || LDS_NEXT) ? 8 : 1][16];   // a draw's quad sums
     __shared__ float    sm_auxf[DO_V ? NW : 1];
     extern __shared__ u32x4 sm_next[];              // LDS_NEXT: [NVEC][THREADS], the centre row in flight
     __shared__ int      sm_auxi[DO_V ? NW : 1];
@@ -455,7 +469,7 @@ void stream_kernel(const RowArgs A)
     // (uniform over the wave; bf16 instances keep it in a scalar register, so that nothing indexed by it -- the waves'
     // exchange slots in LDS -- is held in vector registers across the row loop: they have none to spare.  The fp32
     // instances measured 1 % slower that way.)
-    const int wave = sizeof(T) == 2 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
+    const int wave = THREADS == 64 ? 0 : sizeof(T) == 2 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
     const int V = A.V;
     RadiusMode rm = {false, 0.f, 0.f, 0.f};
     if constexpr (RAD) {
@@ -1376,9 +1390,14 @@ void stream_kernel(const RowArgs A)
                     // in between (with two waves per SIMD nobody else fills the gaps of a chain per vector); then four vectors at a
                     // time through LDS, lane l adding those of lanes 4 (l % 16) ... + 3 of vector l / 16 and a reduction over 16
                     // lanes finishing all four.
+                    auto sum_of = [](const float (&r)[EPV]) {
+                        const float a = (r[0] + r[1]) + (r[2] + r[3]);
+                        return EPV == 4 ? a : a + ((r[4 % EPV] + r[5 % EPV]) + (r[6 % EPV] + r[7 % EPV]));
+                    };
                     float* const slots = reinterpret_cast<float*>(&sm_quad[dwave][0][0]);   // [4][64]
-                    double part[NVEC / 4];
-                    float sums[4];
+                    constexpr int GROUPS = (NVEC + 3) / 4;
+                    double part[GROUPS];
+                    float sums[4] = {0.f, 0.f, 0.f, 0.f};
                     auto four = [&](int g) {
                         // (LDS operations of a wave complete in order)
 #pragma unroll
@@ -1398,8 +1417,8 @@ void stream_kernel(const RowArgs A)
                             for (int k = 0; k < EPV; ++k) {
                                 r[k] = fmaxf(fmaf(exp2_scaled(tz[j & 1][k], ntref), qfac, -(e[j * EPV + k] * pfac)), 0.f);
                             }
-                            sums[j & 3] = ((r[0] + r[1]) + (r[2] + r[3])) + ((r[4 % EPV] + r[5 % EPV]) + (r[6 % EPV] + r[7 % EPV]));
-                            if ((j & 3) == 3) four(j / 4);
+                            sums[j & 3] = sum_of(r);
+                            if ((j & 3) == 3 || j == NVEC - 1) four(j / 4);
                             __builtin_amdgcn_sched_barrier(0);
                         }
                     } else {
@@ -1407,22 +1426,23 @@ void stream_kernel(const RowArgs A)
                         for (int j = 0; j < NVEC; ++j) {
                             float r[EPV];
                             residuals(j, r);
-                            sums[j & 3] = ((r[0] + r[1]) + (r[2] + r[3])) + ((r[4 % EPV] + r[5 % EPV]) + (r[6 % EPV] + r[7 % EPV]));
-                            if ((j & 3) == 3) four(j / 4);
+                            sums[j & 3] = sum_of(r);
+                            if ((j & 3) == 3 || j == NVEC - 1) four(j / 4);
                             __builtin_amdgcn_sched_barrier(0);
                         }
                     }
 #pragma unroll
-                    for (int g = 0; g < NVEC / 4; ++g) part[g] = dpp_add<kRowShr1, 0xf>(part[g]);
+                    for (int g = 0; g < GROUPS; ++g) part[g] = dpp_add<kRowShr1, 0xf>(part[g]);
 #pragma unroll
-                    for (int g = 0; g < NVEC / 4; ++g) part[g] = dpp_add<kRowShr2, 0xf>(part[g]);
+                    for (int g = 0; g < GROUPS; ++g) part[g] = dpp_add<kRowShr2, 0xf>(part[g]);
 #pragma unroll
-                    for (int g = 0; g < NVEC / 4; ++g) part[g] = dpp_add<kRowShr4, 0xf>(part[g]);
+                    for (int g = 0; g < GROUPS; ++g) part[g] = dpp_add<kRowShr4, 0xf>(part[g]);
 #pragma unroll
-                    for (int g = 0; g < NVEC / 4; ++g) part[g] = dpp_add<kRowShr8, 0xf>(part[g]);
+                    for (int g = 0; g < GROUPS; ++g) part[g] = dpp_add<kRowShr8, 0xf>(part[g]);
                     if ((dlane & 15) == 15) {
 #pragma unroll
-                        for (int g = 0; g < NVEC / 4; ++g) sm_tab[(4 * g + (dlane >> 4)) * NW + dwave] = part[g];
+                        for (int g = 0; g < GROUPS; ++g)
+                            if (4 * g + (dlane >> 4) < NVEC) sm_tab[(4 * g + (dlane >> 4)) * NW + dwave] = part[g];
                     }
                 } else {
                     constexpr int GROUP = NVEC >= 8 ? 8 : NVEC;
@@ -1501,36 +1521,47 @@ void stream_kernel(const RowArgs A)
                     }
                     const int wstar = istar % NW, jstar = istar / NW;
                     if (dwave == wstar) {
-                        float r[EPV];
-#pragma unroll
-                        for (int k = 0; k < EPV; ++k) r[k] = 0.f;
-#pragma unroll
-                        for (int j = 0; j < NVEC; ++j) {
-                            if (j == jstar) residuals(j, r);       // uniform; the register arrays keep constant indices
-                        }
-                        if constexpr (MATRIX) {
-                            if (quads && tquads) {
-#pragma unroll
-                                for (int g = 0; g < EPV; g += 4) quad_transpose(r[g], r[g + 1], r[g + 2], r[g + 3], dt);
-                            }
-                        }
-                        float s = 0.f;
-#pragma unroll
-                        for (int k = 0; k < EPV; ++k) s += r[k];
-                        const double incl = wave_scan((double)s);
-                        double cum = before + (incl - (double)s);
+                        int cand = INT_MAX, lastpos = -1;
                         // smallest token of the piece whose inclusive running sum exceeds u R; tokens without
                         // residual mass cannot be drawn; lastpos covers a crossing lost to rounding at its end
-                        int cand = INT_MAX, lastpos = -1;
-                        const int base = (jstar * THREADS + dt) * EPV;
+                        auto scan_piece = [&](int j, float (&r)[EPV]) {
+                            if constexpr (MATRIX) {
+                                if (quads && tquads) {
 #pragma unroll
-                        for (int k = 0; k < EPV; ++k) {
-                            cum += (double)r[k];
-                            if (r[k] > 0.f) {
-                                lastpos = base + k;
-                                if (cum > thr && cand == INT_MAX) cand = base + k;
+                                    for (int g = 0; g < EPV; g += 4) quad_transpose(r[g], r[g + 1], r[g + 2], r[g + 3], dt);
+                                }
+                            }
+                            float s = 0.f;
+#pragma unroll
+                            for (int k = 0; k < EPV; ++k) s += r[k];
+                            const double incl = wave_scan((double)s);
+                            double cum = before + (incl - (double)s);
+                            const int base = (j * THREADS + dt) * EPV;
+#pragma unroll
+                            for (int k = 0; k < EPV; ++k) {
+                                cum += (double)r[k];
+                                if (r[k] > 0.f) {
+                                    lastpos = base + k;
+                                    if (cum > thr && cand == INT_MAX) cand = base + k;
+                                }
+                            }
+                        };
+                        // (j == jstar is uniform; the register arrays keep constant indices.  The scan once behind the choice of the vector:
+                        // sixteen copies of it are half a draw's instructions to fetch; of one or two the calls of few rows lose 5 % so.)
+                        float chosen[EPV];
+#pragma unroll
+                        for (int j = 0; j < NVEC; ++j) {
+                            if (j == jstar) {
+                                if constexpr (LDS_NEXT) {
+                                    residuals(j, chosen);
+                                } else {
+                                    float r[EPV];
+                                    residuals(j, r);
+                                    scan_piece(j, r);
+                                }
                             }
                         }
+                        if constexpr (LDS_NEXT) scan_piece(jstar, chosen);
                         cand = wave_min_i(cand);
                         lastpos = wave_max_i(lastpos);
                         if (dlane == 0) {
@@ -1699,10 +1730,11 @@ hipError_t launch_stream_kernel(const RowArgs& a, StreamLaunch& L)
     // budget the kernel was compiled for fixes how many fit: target_waves() waves per SIMD, and a
     // workgroup puts THREADS / 256 waves on each of the four SIMDs of a compute unit (a 128-lane one: one
     // wave on two of them).
-    constexpr int per_cu = target_waves<T, THREADS, NVEC, RAD, DO_V>() * 256 / THREADS;
+    // (fp32, one wave to a row and eight vectors: what the LDS has room for)
+    constexpr int per_cu = THREADS == 64 && NVEC == 8 && sizeof(T) == 4 ? 12 : target_waves<T, THREADS, NVEC, RAD, DO_V>() * 256 / THREADS;
     const int64_t resident = (int64_t)per_cu * compute_units();
     const int64_t N = a.N;
-    constexpr int ROWS = rows_per_wg<THREADS, NVEC, DO_V, RAD, WIDE>();   // (at most so many rows per workgroup)
+    constexpr int ROWS = rows_per_wg<T, THREADS, NVEC, DO_V, RAD, WIDE>();   // (at most so many rows per workgroup)
     const int64_t grid1 = whole_rounds(N, ROWS, resident), max1 = (N + grid1 - 1) / grid1;
     StreamPlan& p = L.plan;
     p.unit = 1;
@@ -1722,7 +1754,7 @@ hipError_t launch_stream_kernel(const RowArgs& a, StreamLaunch& L)
         }
     }
     p.can_finish = DO_V || L.finish_rows;
-    p.draws_inline = draws_in_stream<T, NVEC, DO_V, RAD, WIDE>();
+    p.draws_inline = draws_in_stream<T, THREADS, NVEC, DO_V, RAD, WIDE>();
     // Windows that span workgroups: where this kernel knows every row's draw it can still write the window outputs,
     // from the lane that finishes a window's last row (one 64-bit word per window in the workspace, see window_arrive).
     p.windows_counted = p.draws_inline && a.win_words && (a.accept_len || a.resampled_id) && !p.windows_inline && a.window >= 2 &&
@@ -1737,8 +1769,8 @@ hipError_t launch_stream_kernel(const RowArgs& a, StreamLaunch& L)
     if constexpr (!WIDE && (DO_V || !RAD) && NVEC != 12) {                       // (quantify-only calls with a radius tensor: V <= 64 comes here)
         if (b.V == NVEC * THREADS * Elt<T>::kPerVec) kernel = &stream_kernel<T, THREADS, NVEC, DO_Q, DO_V, RAD, WIDE, true>;
     }
-    constexpr unsigned lds = next_by_lds<NVEC, DO_V, RAD, WIDE>() ? THREADS * NVEC * 16u : 0u;
-    if constexpr (lds > 0) {
+    constexpr unsigned lds = next_by_lds<T, THREADS, NVEC, DO_V, RAD, WIDE>() ? THREADS * NVEC * 16u : 0u;
+    if constexpr (lds > 32 * 1024 - 1) {
         // with the static arrays above the default limit: raised once per device and instance
         static std::mutex guard;
         static bool raised[2][64] = {};
