@@ -70,8 +70,8 @@ struct StreamLaunch {
 
 // Calls on bf16 rows of more than 8192 tokens with a verifier row, without a radius tensor and without complements (wide_radius).
 hipError_t launch_both_rows(Mode mode, const RowArgs& a, StreamLaunch& s);
-// Calls with a verifier row, without a radius tensor and without complements, on short rows where there are enough of them.
-bool short_rows_fit(int dtype, int vecs, int64_t rows);
+// Calls without a radius tensor and without complements, whose rows the kernel finishes, on short rows where there are enough of them.
+bool short_rows_fit(Mode mode, int dtype, int vecs, int64_t rows);
 hipError_t launch_short_rows(int dtype, Mode mode, const RowArgs& a, StreamLaunch& s);
 
 namespace {
@@ -83,10 +83,10 @@ namespace {
 // unit rather than by fetching ahead into a second set of registers: measured on this chip, three or
 // four resident workgroups beat two with a register prefetch of the next row at every vocabulary size.
 // (Tensor-radius mode: the raw radius row sits in registers next to the centre row during the interval pass.)
-// Short rows with a verifier row, many of them: a wave to a row, or two, of at most eight vectors per lane.  With 256 lanes to
+// Short rows, many of them: a wave to a row, or two, of at most eight vectors per lane.  With 256 lanes to
 // every row a row of 1024 tokens left a lane four of them, and the 415 instructions that a wave spends per row were nearly all of
 // its work; here one wave has them all, no wave waits for another, and its rows come through LDS as below (16384 x 1024 fused bf16
-// 90 -> 33 us, fp32 65 -> 35; the rule and more figures: short_rows_fit).
+// 90 -> 33 us, fp32 65 -> 35, quantified 50 -> 20 and 42 -> 21; the rule and more figures: short_rows_fit).
 //
 // Large bf16 rows with a verifier row: twelve or sixteen vectors per lane at two waves per SIMD, the rows arriving through LDS.
 // Bound by vector instructions: 16.9 of them per position and token are the tokens' own arithmetic, what a wave does per row besides
@@ -105,13 +105,13 @@ namespace {
 template <typename T, int THREADS, int NVEC, bool DO_V, bool RAD, bool WIDE>
 constexpr bool next_by_lds()
 {
-    return DO_V && !RAD && !WIDE && (NVEC == 16 || NVEC == 12 || THREADS <= 128);
+    return !RAD && !WIDE && (THREADS <= 64 || (DO_V && (NVEC == 16 || NVEC == 12)) || (THREADS == 128 && NVEC == 8));
 }
 template <typename T, int THREADS, int NVEC, bool RAD, bool DO_V = false>
 constexpr int target_waves()
 {
     if (next_by_lds<T, THREADS, NVEC, DO_V, RAD, false>()) {
-        constexpr int regs = NVEC * Elt<T>::kPerVec + NVEC * 4 + 56;   // the centre row's exponentials, the verifier row, working registers
+        constexpr int regs = NVEC * Elt<T>::kPerVec + (DO_V ? NVEC * 4 : 0) + 56;   // the centre row's exponentials, the verifier row, working registers
         return regs <= 128 ? 4 : regs <= 168 ? 3 : 2;
     }
     constexpr int ept = NVEC * Elt<T>::kPerVec;                    // one row as floats
@@ -371,7 +371,7 @@ constexpr bool second_row_early()
 template <typename T, int THREADS, int NVEC, bool DO_V, bool RAD, bool WIDE>
 constexpr bool draws_in_stream()
 {
-    return next_by_lds<T, THREADS, NVEC, DO_V, RAD, WIDE>() || (DO_V && !WIDE && (NVEC * Elt<T>::kPerVec + NVEC * 4 + 56) * 4 <= 512);
+    return (DO_V && next_by_lds<T, THREADS, NVEC, DO_V, RAD, WIDE>()) || (DO_V && !WIDE && (NVEC * Elt<T>::kPerVec + NVEC * 4 + 56) * 4 <= 512);
 }
 // Most rows a workgroup has room for: kMaxRowsPerWg, or what the rows in flight leave of a compute unit's LDS.
 template <typename T, int THREADS, int NVEC, bool DO_V, bool RAD, bool WIDE>
@@ -402,13 +402,14 @@ void stream_kernel(const RowArgs A)
     constexpr int EPT = NVEC * EPV;
     constexpr int NW = THREADS / 64;
     constexpr int CHUNK = THREADS * EPV;            // tokens covered by one load instruction of the workgroup
+    constexpr bool LDS_NEXT = next_by_lds<T, THREADS, NVEC, DO_V, RAD, WIDE>();
     // The verifier row is requested before the interval pass where a second row fits in the registers at
     // four waves per SIMD next to the centre row's floats (fp32 tiles of up to 8 vectors per lane; measured
     // 51 -> 48.6 us on the benchmark); elsewhere it would spill, and it is requested after the pass.
     constexpr bool EARLY_T = second_row_early<T, THREADS, NVEC, DO_V, RAD, WIDE>();
     // Quantify-only launches have no verifier row; under the same condition the next centre row is requested
     // before the interval pass instead.
-    constexpr bool EARLY_NEXT = !DO_V && !RAD && !WIDE && (EPT + NVEC * 4 + 56) * 4 <= 512;
+    constexpr bool EARLY_NEXT = !DO_V && !RAD && !WIDE && !LDS_NEXT && (EPT + NVEC * 4 + 56) * 4 <= 512;
     // A rejected row's draw needs both rows.  Where two rows fit, the centre row's exponentials simply stay in their
     // registers next to the verifier row and the draw is made here (KEEP_E).  Elsewhere (bf16 tiles of eight vectors, the 16-vector
     // fp32 tile, wide radii) the two do not fit: such rows are only marked, and resample_kernel
@@ -416,7 +417,6 @@ void stream_kernel(const RowArgs A)
     // alone, never taken, cost the bf16 row loop 11 % -- registers and scheduling -- and workload 3 ran 318 against
     // 285 us per step).
     constexpr bool KEEP_E = draws_in_stream<T, THREADS, NVEC, DO_V, RAD, WIDE>();
-    constexpr bool LDS_NEXT = next_by_lds<T, THREADS, NVEC, DO_V, RAD, WIDE>();
     constexpr int ROWS = rows_per_wg<T, THREADS, NVEC, DO_V, RAD, WIDE>();
     // Fused launches on bf16 rows with a scalar radius: the two interval sums of a row whose caps are inactive and the
     // verifier row's partition sum are reduced over the wave together (wave_sum3) once the verifier row has been summed.
@@ -880,7 +880,8 @@ void stream_kernel(const RowArgs A)
         if constexpr (LDS_NEXT) {
             // the centre row has landed; its slots take the verifier row, which arrives during B
             take_row(buf);
-            fetch_row(A.target, row);
+            if constexpr (DO_V) fetch_row(A.target, row);
+            else if (has_next) fetch_row(A.draft, next);
             __builtin_amdgcn_sched_barrier(0);
         }
         // ---- B: centre row: per-wave max, e_i = 2^(c_i log2e - n_w), S_w -------------------------------
@@ -950,22 +951,26 @@ void stream_kernel(const RowArgs A)
         double Zw = 0.0;
         if constexpr (LDS_NEXT) {
             // ---- T (these instances): the verifier row; its slots take the next centre row, which arrives during the rest
-            take_row(buf);
-            if (has_next) fetch_row(A.draft, next);
-            __builtin_amdgcn_sched_barrier(0);
-            verifier_mask(buf, quads ? kNoTokenWord : E::kNegInfWord);
-            ntw = nw == -INFINITY ? 0.f : nw;
+            if constexpr (DO_V) {
+                take_row(buf);
+                if (has_next) fetch_row(A.draft, next);
+                __builtin_amdgcn_sched_barrier(0);
+                verifier_mask(buf, quads ? kNoTokenWord : E::kNegInfWord);
+                ntw = nw == -INFINITY ? 0.f : nw;
+            }
             const int ol = opaque_tid() & 63;
             put_sum(sacc[0] + sacc[1], 5, ol);
-            put_sum(verifier_lane_sum(buf, ntw, quads), 6, ol);
+            if constexpr (DO_V) put_sum(verifier_lane_sum(buf, ntw, quads), 6, ol);
             const double v = get_sums(ol);
             if (DO_Q && (ol & 7) == 0 && ol < 40) sm_q52[LDS_NEXT ? (done & 1) ^ 1 : 0][wave * NQ + (ol >> 3)] = v;   // (the row before's)
             auto of_group = [&](int g) {
                 return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 8 * g), __builtin_amdgcn_readlane(__double2loint(v), 8 * g));
             };
             Sw = of_group(5);
-            Zw = of_group(6);
-            verifier_redo(buf, ntw, Zw, tquads);
+            if constexpr (DO_V) {
+                Zw = of_group(6);
+                verifier_redo(buf, ntw, Zw, tquads);
+            }
         } else {
             Sw = wave_sum(sacc[0] + sacc[1]);
         }
@@ -980,7 +985,7 @@ void stream_kernel(const RowArgs A)
             sm_ref[wave * 2] = mcw; sm_ref[wave * 2 + 1] = nw;
             sm_S[wave] = Sw;
             if (DO_Q && wave == 0) sm_e0 = e[0];
-            if constexpr (LDS_NEXT) { sm_nt[wave] = ntw; sm_Z[wave] = Zw; }
+            if constexpr (LDS_NEXT && DO_V) { sm_nt[wave] = ntw; sm_Z[wave] = Zw; }
         }
         row_barrier();
         // Combining the waves' results.  With eight waves or more every wave does it across its first lanes (lane
@@ -1259,7 +1264,7 @@ void stream_kernel(const RowArgs A)
         }
         // The next centre row goes in flight before the barrier and thread 0's bookkeeping -- except where this
         // kernel makes the draws: there both rows stay in the registers until the accept test has been decided (below).
-        if constexpr (!EARLY_NEXT && !KEEP_E) {
+        if constexpr (!EARLY_NEXT && !KEEP_E && !LDS_NEXT) {
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (DO_V) {
                 if (has_next) load_row(buf, A.draft, next);
@@ -1620,9 +1625,9 @@ void stream_kernel(const RowArgs A)
         if constexpr (LDS_NEXT) {
             // (the interval sums follow behind the next row's barrier)
             if (wave == 0) {
-                float nt;
-                double Z;
-                combine_Z(std::integral_constant<bool, LANES>{}, nt, Z);
+                float nt = -INFINITY;
+                double Z = 0.0;
+                if constexpr (DO_V) combine_Z(std::integral_constant<bool, LANES>{}, nt, Z);
                 if (lane == 0) {
                     RowStats& st = sm_rows[done];
                     st.S = S; st.Z = Z; st.n = n; st.nt = nt; st.mc = mc;
