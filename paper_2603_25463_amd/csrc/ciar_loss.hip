@@ -103,6 +103,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     constexpr bool CACHE_R = RAD && NVEC * EPV <= 32;
     float rc[CACHE_R ? NVEC * EPV : 1];
     if constexpr (CACHE_R) {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < NVEC; ++j) {
             float rv[EPV];
@@ -110,6 +111,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
 #pragma unroll
             for (int k = 0; k < EPV; ++k) rc[j * EPV + k] = radius_abs(rv[k], kap, rmax);
         }
+        __builtin_amdgcn_sched_barrier(0);
     }
     // element k of vector j: centre logit, radius, cloud logit
     auto element = [&](int j, int k, float& c, float& r, float& t) {
@@ -702,6 +704,7 @@ __global__ __launch_bounds__(T) void dro_batch_kernel(const float* __restrict__ 
         float v[U][7];
 #pragma unroll
         for (int i = 0; i < U; ++i) {
+            if (i * T >= N) break;                                 // uniform: a call of few rows requests them once
             const int64_t n = n0 + i * T < N ? n0 + i * T : n0;
 #pragma unroll
             for (int k = 0; k < 7; ++k) v[i][k] = terms[k * N + n];
@@ -725,7 +728,8 @@ __global__ __launch_bounds__(T) void dro_batch_kernel(const float* __restrict__ 
     for (int64_t n0 = tid; n0 < N; n0 += U * T) {
         float v[U];
 #pragma unroll
-        for (int i = 0; i < U; ++i) v[i] = ce_lo[n0 + i * T < N ? n0 + i * T : n0];
+        for (int i = 0; i < U; ++i)
+            if (i * T < N) v[i] = ce_lo[n0 + i * T < N ? n0 + i * T : n0];
 #pragma unroll
         for (int i = 0; i < U; ++i) {
             if (n0 + i * T >= N) break;
@@ -748,7 +752,8 @@ __global__ __launch_bounds__(T) void dro_batch_kernel(const float* __restrict__ 
         for (int64_t n0 = tid; n0 < N; n0 += U * T) {
             float v[U];
 #pragma unroll
-            for (int i = 0; i < U; ++i) v[i] = weights[n0 + i * T < N ? n0 + i * T : n0];
+            for (int i = 0; i < U; ++i)
+                if (i * T < N) v[i] = weights[n0 + i * T < N ? n0 + i * T : n0];
 #pragma unroll
             for (int i = 0; i < U; ++i)
                 if (n0 + i * T < N) weights[n0 + i * T] = (float)((double)v[i] * inv);
