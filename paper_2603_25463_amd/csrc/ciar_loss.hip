@@ -78,6 +78,11 @@ struct DroRadius { float kappa, rmax; };
 // formed, and dro_finish_row writes them three times.  Half the instructions and half the registers (62 of 128 before), so
 // that two workgroups of 1024 lanes fit a compute unit where their rows fit its LDS (bf16): 15653 x 11630 bf16 593 -> 379 us, 2048 x
 // 16384 71 -> 51 (fp32 88 -> 65), 4 x 21156 29 -> 16 (which spilled).
+//
+// (bf16: the instances with a radius tensor ask for it all the same.  It is there; but with what depends on it in blocks of its own
+// the compiler leaves more of the rows' requests ahead of the arithmetic: 2048 x 16384 87 us so, 89 otherwise; fp32 107 and 105.)
+template <typename T, bool RAD>
+__device__ __forceinline__ bool dro_rad(const RowArgs& A) { return RAD && (sizeof(T) == 4 || A.radius != nullptr); }
 template <typename T, int NVEC, int THREADS, bool RAD>
 __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadius R, double* fin,
                                                 u32x4 (&cw)[NVEC], u32x4 (&tw)[NVEC], u32x4 (&rw)[NVEC], double* sm_d,
@@ -89,13 +94,14 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     const int V = A.V;
     auto uniform = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
     const float kap = R.kappa, rmax = R.rmax;
+    const bool rad = dro_rad<T, RAD>(A);
     if (V < NVEC * THREADS * EPV) {                                // uniform: the row does not fill the tile
 #pragma unroll
         for (int j = 0; j < NVEC; ++j) {
             const int base = (j * THREADS + tid) * EPV;
             E::mask_tail(cw[j], base, V);
             E::mask_tail(tw[j], base, V);
-            if constexpr (RAD) E::zero_tail(rw[j], base, V);
+            if (rad) E::zero_tail(rw[j], base, V);
         }
     }
     // The radii are formed once (Softplus costs about as much as the rest of a pass) and kept as floats where
@@ -103,15 +109,18 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     constexpr bool CACHE_R = RAD && NVEC * EPV <= 32;
     float rc[CACHE_R ? NVEC * EPV : 1];
     if constexpr (CACHE_R) {
-        __builtin_amdgcn_sched_barrier(0);
+        if (rad) {
 #pragma unroll
-        for (int j = 0; j < NVEC; ++j) {
-            float rv[EPV];
-            E::unpack(rw[j], rv);
+            for (int j = 0; j < NVEC; ++j) {
+                float rv[EPV];
+                E::unpack(rw[j], rv);
 #pragma unroll
-            for (int k = 0; k < EPV; ++k) rc[j * EPV + k] = radius_abs(rv[k], kap, rmax);
+                for (int k = 0; k < EPV; ++k) rc[j * EPV + k] = radius_abs(rv[k], kap, rmax);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NVEC * EPV; ++i) rc[i] = 0.f;
         }
-        __builtin_amdgcn_sched_barrier(0);
     }
     // element k of vector j: centre logit, radius, cloud logit
     auto element = [&](int j, int k, float& c, float& r, float& t) {
@@ -300,29 +309,25 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
             element(j, k, c, r, t);
             // (each difference is exact for tokens near the reference and rounded relative to itself elsewhere:
             // c + r is never rounded to fp32)
-            const float x0 = log2e_times(c - mc);
+            const float x0 = log2e_times(c - mc), xa = RAD ? log2e_times(r - rref) : 0.f;
             const float xt = log2e_times(fmaxf(t - mt, -1e30f));
+            // (the exponentials of c + r and c - r are products: see radius_factors)
             const float e0 = __builtin_amdgcn_exp2f(x0), et = __builtin_amdgcn_exp2f(xt);
-            acc[0] += (double)e0; acc[3] += (double)et;
+            float e1 = 0.f, e2 = 0.f;
+            if constexpr (RAD) { e1 = e0 * __builtin_amdgcn_exp2f(xa); e2 = e0 * __builtin_amdgcn_exp2f(-xa); }
+            acc[0] += (double)e0;
+            if constexpr (RAD) { acc[1] += (double)e1; acc[2] += (double)e2; }
+            acc[3] += (double)et;
             if constexpr (CACHE_E) {
                 em[j * EPV + k] = e0; ec[j * EPV + k] = et;
+                if constexpr (RAD) { eu[j * EPV + k] = e1; el[j * EPV + k] = e2; }
                 s32[4] = fmaf(et, x0, s32[4]);
+                if constexpr (RAD) s32[5] = fmaf(et, xa, s32[5]);
                 s32[7] = fmaf(et, xt - x0, s32[7]);
             } else {
                 acc[4] = fma((double)et, (double)x0, acc[4]);
+                if constexpr (RAD) acc[5] = fma((double)et, (double)xa, acc[5]);
                 acc[7] = fma((double)et, (double)(xt - x0), acc[7]);
-            }
-            if constexpr (RAD) {
-                // (the exponentials of c + r and c - r are products: see radius_factors)
-                const float xa = log2e_times(r - rref);
-                const float e1 = e0 * __builtin_amdgcn_exp2f(xa), e2 = e0 * __builtin_amdgcn_exp2f(-xa);
-                acc[1] += (double)e1; acc[2] += (double)e2;
-                if constexpr (CACHE_E) {
-                    eu[j * EPV + k] = e1; el[j * EPV + k] = e2;
-                    s32[5] = fmaf(et, xa, s32[5]);
-                } else {
-                    acc[5] = fma((double)et, (double)xa, acc[5]);
-                }
             }
             if (k & 1) __builtin_amdgcn_sched_barrier(0);          // two tokens at a time: bounded working set
         }
@@ -528,13 +533,14 @@ __global__ __launch_bounds__(1024) void dro_row_kernel(const RowArgs A, const Dr
     const gbytes cb = (gbytes)(static_cast<const T*>(A.draft) + row * A.stride);
     const gbytes tb = (gbytes)(static_cast<const T*>(A.target) + row * A.stride);
     const gbytes rb = (gbytes)(static_cast<const T*>(RAD ? A.radius : A.draft) + row * A.stride);
+    const bool rad = dro_rad<T, RAD>(A);
     u32x4 cw[NVEC], tw[NVEC], rw[NVEC];
 #pragma unroll
     for (int j = 0; j < NVEC; ++j) {
         const uint32_t off = (uint32_t)min(j * THREADS + tid, last_vec) * 16u;
         cw[j] = __builtin_nontemporal_load((gvec)(cb + off));     // every row is used once: stream past the caches
         tw[j] = __builtin_nontemporal_load((gvec)(tb + off));
-        if constexpr (RAD) rw[j] = __builtin_nontemporal_load((gvec)(rb + off));
+        if (rad) rw[j] = __builtin_nontemporal_load((gvec)(rb + off));
     }
     __shared__ double sm_fin[kDroTotals];
     dro_row_compute<T, NVEC, THREADS, RAD>(A, R, sm_fin, cw, tw, rw, sm_d, tid);
@@ -567,6 +573,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(RAD || 
     const int tid = threadIdx.x;
     const int wave_s = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int last_vec = (A.V + Elt<T>::kPerVec - 1) / Elt<T>::kPerVec - 1;
+    const bool rad = dro_rad<T, RAD>(A);
     using lds_ptr = __attribute__((address_space(3))) void*;
     using glb_ptr = const __attribute__((address_space(1))) void*;
 
@@ -599,7 +606,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(RAD || 
     int done = 0;                                                  // rows of this workgroup finished so far (<= ROWS)
     if (row < n_rows) {
         request_rows(row, tid);
-        if constexpr (RAD) request_radius(row, rnext, tid);
+        if (rad) request_radius(row, rnext, tid);
     }
     for (; row < n_rows; row += gridDim.x) {
         // this wave's loads have landed (its slots of the two rows in LDS, and the radius registers)
@@ -620,7 +627,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(RAD || 
         const uint32_t next = row + gridDim.x;
         if (next < n_rows) {
             request_rows(next, t);
-            if constexpr (RAD) request_radius(next, rnext, t);
+            if (rad) request_radius(next, rnext, t);
         }
         dro_row_compute<T, NVEC, THREADS, RAD>(A, R, sm_fin[done], cw, tw, rw, sm_d, t);
         // (no barrier here: what wave 0 still reads of sm_d is written again only in the next row's pass 3, two
