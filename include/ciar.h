@@ -211,9 +211,10 @@ int ciar_quantify_verify_static(const void* draft_logits, const void* radius, co
  *                    residual draws of the rejected rows, from the registers that still hold both rows, and
  *                    writes the window outputs; the call is then this one launch.  (Calls whose flat rows need the
  *                    fp64 pass launch that behind it, see the radius notes above.)
- * ciar_finish_rows   what remains, if anything: for bfloat16 logits and very wide radii the residual
- *                    draws of the rejected rows (their rows are read again), and the window outputs where neither
- *                    kernel could write them (windows longer than 255 rows that span workgroups).
+ * ciar_finish_rows   what remains, if anything: for float32 rows above 16384 tokens, large bfloat16 rows with a
+ *                    radius tensor and very wide radii the residual draws of the rejected rows (their rows are read
+ *                    again), and the window outputs where neither kernel could write them (windows of more than 16
+ *                    to 32 rows that span workgroups).
  */
 int ciar_stream_rows(const void* draft_logits, const void* radius, const void* target_logits,
                      const int32_t* draft_ids,

@@ -1878,3 +1878,20 @@ def test_short_rows_many_of_them(ciar, oracle, V, stride, N, dtype):
         _run_case(ciar, oracle, c, t, ids, ua, ur, P, vocab=V, tag=f"short rows V={V} N={N} {kw}")
         if N > 8000:
             break
+
+
+# Windows that meet in a word of the workspace, and those that are left to a launch of their own: lengths on both sides of the rule,
+# with one row to a workgroup and with several.
+@pytest.mark.parametrize("K", [16, 17, 31, 32, 33])
+@pytest.mark.parametrize("N,V,dtype", [(333, 1000, torch.float32), (5003, 1000, torch.float32), (333, 8200, torch.bfloat16), (4500, 8200, torch.bfloat16)])
+def test_long_windows_however_they_are_put_together(ciar, oracle, K, N, V, dtype):
+    c, t, ids, ua, ur = _random_case(V, V, N, K, dtype, seed=8500 + K, sigma=0.15)
+    P = ciar.Params(confidence=0.9, window=K, tau=0.01)
+    g = ciar.quantify_verify(c, t, ids, ua, ur, P)
+    torch.cuda.synchronize()
+    acc, row_id = g["accept"].cpu().numpy(), g["row_id"].cpu().numpy()
+    for w in range(-(-N // K)):                                            # the windows from the rows' own outputs
+        a = acc[w * K:(w + 1) * K]
+        n = int(a.argmin()) if (a == 0).any() else len(a)
+        assert int(g["accept_len"][w]) == n, w
+        assert int(g["resampled_id"][w]) == (int(row_id[w * K + n]) if n < len(a) else -1), w
