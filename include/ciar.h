@@ -206,13 +206,13 @@ int ciar_quantify_verify_static(const void* draft_logits, const void* radius, co
  * no verify output is a quantify-only call, no quantify output a verify-only call (radius must be NULL).
  *
  * ciar_stream_rows   the streaming kernel: reads every logit row once from HBM and writes every per-row output:
- *                    the quantifier's (p_lo ... flags) and, with a verifier row, the accept bits.  For float32
- *                    logits (V <= 32768) under a scalar or tensor radius that is not very wide it also makes the
+ *                    the quantifier's (p_lo ... flags) and, with a verifier row, the accept bits.  Under a scalar
+ *                    or tensor radius that is not very wide (bfloat16 rows above 8192 tokens: scalar) it also makes the
  *                    residual draws of the rejected rows, from the registers that still hold both rows, and
  *                    writes the window outputs; the call is then this one launch.  (Calls whose flat rows need the
  *                    fp64 pass launch that behind it, see the radius notes above.)
- * ciar_finish_rows   what remains, if anything: for float32 rows above 16384 tokens, large bfloat16 rows with a
- *                    radius tensor and very wide radii the residual draws of the rejected rows (their rows are read
+ * ciar_finish_rows   what remains, if anything: for bfloat16 rows above 8192 tokens with a radius tensor and
+ *                    for very wide radii the residual draws of the rejected rows (their rows are read
  *                    again), and the window outputs where neither kernel could write them (windows of more than 16
  *                    to 32 rows that span workgroups).
  */

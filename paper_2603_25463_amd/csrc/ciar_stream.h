@@ -1,5 +1,5 @@
-// gfx950 streaming kernel of the CIAR quantify + verify pass (this file: the kernel and its launch; ciar_stream.hip and ciar_rows.hip:
-// its instances and which call takes which), with an overview of the pass.
+// gfx950 streaming kernel of the CIAR quantify + verify pass (this file: the kernel and its launch; ciar_stream.hip, ciar_rows.hip and
+// ciar_short.hip: its instances and which call takes which), with an overview of the pass.
 //
 //   stream_kernel   reads every logit row exactly once from HBM.  A workgroup of 256 lanes (512 or 1024 for large
 //                   vocabularies or few rows) owns one row at a time and walks over rows blockIdx.x, blockIdx.x +
@@ -15,7 +15,7 @@
 //                   token, the exact accept test, the window outputs.  A call whose rows fit this scheme is this
 //                   one launch.
 //   resample_kernel (ciar_finish.hip) draws for the rejected rows of launches whose tiles cannot keep both rows in
-//                   registers (fp32 rows above 16384 tokens, wide radii, large bf16 rows with a radius tensor), re-reading the two.
+//                   registers (wide radii, bf16 rows above 8192 tokens with a radius tensor), re-reading the two rows.
 //
 // The centre row has to be resident between its statistics pass and its interval pass: the InterFuse
 // bounds need the partition sum S of the complete row before the first bound can be formed (App.
