@@ -16,8 +16,8 @@ namespace {
 // probability, and for logits of magnitude ~30 it shows as ~1e-6 absolute in a cross-entropy and in an L1 distance.
 //
 // The exponentials of c + r and c - r are formed as products, e^(c - cs) e^(r - rs) and e^(c - cs) e^-(r - rs), not from
-// the sums of the exponents: where the radius is the same for every token of a row (a row clamped at r_max) r - rs is one number, and adding it to exponents of one binade rounds them all the same way -- by up to half
-// an ulp of that binade, another amount in the next one.  That tilts the distribution between the binades by up to
+// the sums of the exponents: where the radius is the same for every token of a row (a row clamped at r_max) r - rs is one
+// number, and adding it to exponents of one binade rounds them all the same way -- by up to half an ulp of that binade, another amount in the next one.  That tilts the distribution between the binades by up to
 // ~3e-7 of the mass they hold, upwards for c + r and downwards for c - r, and showed as 1.7e-7 absolute in an L1
 // distance of 6e-3 (a seeded random case).  As products the three distributions of such a row agree to the rounding
 // of single tokens.  |r - rs| <= r_max <= 16: the factors stay within 2^+-24.
@@ -77,7 +77,7 @@ struct DroRadius { float kappa, rmax; };
 // terms of the three distributions are one number each: the partition sum, the weighted sums and the distance of c alone are
 // formed, and dro_finish_row writes them three times.  Half the instructions and half the registers (62 of 128 before), so
 // that two workgroups of 1024 lanes fit a compute unit where their rows fit its LDS (bf16): 15653 x 11630 bf16 593 -> 379 us, 2048 x
-// 16384 71 -> 51 (fp32 88 -> 65), 4 x 21156 29 -> 16 (which spilled).
+// 16384 71 -> 51 (fp32 88 -> 65), 4 x 21156 29 -> 17 (which spilled).
 //
 // (bf16: the instances with a radius tensor ask for it all the same.  It is there; but with what depends on it in blocks of its own
 // the compiler leaves more of the rows' requests ahead of the arithmetic: 2048 x 16384 87 us so, 89 otherwise; fp32 107 and 105.)
@@ -273,6 +273,8 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     // leaves is ~1e-7 of that lane's share of a cross-entropy), and in fp64 across lanes and waves.
     // (without a radius tensor there are two exponentials: at most 32)
     constexpr bool CACHE_E = NVEC * EPV <= (RAD ? 16 : 32);
+    // (more than 16 tokens: a lane's weighted sums and distances in fp64)
+    constexpr bool SUMS32 = NVEC * EPV <= 16;
     constexpr int NE = CACHE_E ? NVEC * EPV : 1;
     float em[NE], eu[RAD ? NE : 1], el[RAD ? NE : 1], ec[NE];
     fresh();
@@ -321,6 +323,8 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
             if constexpr (CACHE_E) {
                 em[j * EPV + k] = e0; ec[j * EPV + k] = et;
                 if constexpr (RAD) { eu[j * EPV + k] = e1; el[j * EPV + k] = e2; }
+            }
+            if constexpr (SUMS32) {
                 s32[4] = fmaf(et, x0, s32[4]);
                 if constexpr (RAD) s32[5] = fmaf(et, xa, s32[5]);
                 s32[7] = fmaf(et, xt - x0, s32[7]);
@@ -346,7 +350,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     }
     auto wanted = [](int i) { return RAD || i == 0 || i == 3 || i == 4 || i == 7; };
     auto slot_of = [](int i) { return RAD ? i : (i >= 3) + (i >= 4) + (i >= 7); };
-    if constexpr (CACHE_E) {
+    if constexpr (SUMS32) {
         // (the weighted sums of a quad in fp32 as well: one instruction per DPP step of a float, five of a double)
 #pragma unroll
         for (int i = 4; i < 8; ++i) {
@@ -371,7 +375,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
         return a;
     };
 #pragma unroll
-    for (int i = 0; i < (CACHE_E ? 4 : 8); ++i) {
+    for (int i = 0; i < (SUMS32 ? 4 : 8); ++i) {
         if (!wanted(i)) continue;
         acc[i] = dpp_add<0xB1, 0xf>(acc[i]);
         acc[i] = dpp_add<0x4E, 0xf>(acc[i]);
@@ -433,13 +437,14 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     }
     double l1[NL] = {};
     if constexpr (CACHE_E) {
-        float a32[NL] = {};                                        // (per lane in fp32: sums of non-negative terms)
+        using Sum = std::conditional_t<SUMS32, float, double>;
+        Sum a32[NL] = {};                                          // (up to 16 terms per lane in fp32: sums of non-negative terms)
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
-            a32[0] += fabsf(fmaf(-ec[i], rlo[0], fmaf(-ec[i], rho[0], em[i])));
+            a32[0] += (Sum)fabsf(fmaf(-ec[i], rlo[0], fmaf(-ec[i], rho[0], em[i])));
             if constexpr (RAD) {
-                a32[1] += fabsf(fmaf(-ec[i], rlo[1], fmaf(-ec[i], rho[1], eu[i])));
-                a32[2] += fabsf(fmaf(-ec[i], rlo[2], fmaf(-ec[i], rho[2], el[i])));
+                a32[1] += (Sum)fabsf(fmaf(-ec[i], rlo[1], fmaf(-ec[i], rho[1], eu[i])));
+                a32[2] += (Sum)fabsf(fmaf(-ec[i], rlo[2], fmaf(-ec[i], rho[2], el[i])));
             }
         }
 #pragma unroll
