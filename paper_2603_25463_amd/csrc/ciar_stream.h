@@ -618,6 +618,16 @@ void stream_kernel(const RowArgs A)
     // (the lane's share of the sum about the reference nref; quads: the tokens widened by the matrix cores)
     auto verifier_lane_sum = [&](u32x4 (&tb)[NVEC], float nref, bool quads) {
         float zacc[4] = {0.f, 0.f, 0.f, 0.f};
+        // (LDS_NEXT, where a lane holds more of a row: a vector's tokens in fp32, the vectors in fp64)
+        double zsum = 0.0;
+        auto add_vector = [&](float (&t)[EPV]) {
+#pragma unroll
+            for (int w = EPV / 2; w > 0; w /= 2) {
+#pragma unroll
+                for (int k = 0; k < w; ++k) t[k] += t[k + w];
+            }
+            zsum += (double)t[0];
+        };
         if constexpr (MATRIX_T) {
             if (quads) {
                 const Bf16Scale bs = bf16_scale(opaque_tid());
@@ -626,22 +636,37 @@ void stream_kernel(const RowArgs A)
 #pragma unroll
                 for (int j = 0; j < NVEC; ++j) {
                     if (j + 1 < NVEC) bf16_scaled(tb[j + 1], bs, z[(j + 1) & 1]);   // (the matrix cores one vector ahead)
+                    if constexpr (LDS_NEXT) {
+                        float t[EPV];
 #pragma unroll
-                    for (int k = 0; k < EPV; ++k) zacc[k & 3] += exp2_scaled(z[j & 1][k], nref);
+                        for (int k = 0; k < EPV; ++k) t[k] = exp2_scaled(z[j & 1][k], nref);
+                        add_vector(t);
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < EPV; ++k) zacc[k & 3] += exp2_scaled(z[j & 1][k], nref);
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                return (double)((zacc[0] + zacc[1]) + (zacc[2] + zacc[3]));
+                if constexpr (LDS_NEXT) return zsum;
+                else return (double)((zacc[0] + zacc[1]) + (zacc[2] + zacc[3]));
             }
         }
 #pragma unroll
         for (int j = 0; j < NVEC; ++j) {
             float tv[EPV];
             E::unpack(tb[j], tv);
+            if constexpr (LDS_NEXT) {
 #pragma unroll
-            for (int k = 0; k < EPV; ++k) zacc[k & 3] += E::exp2_ref(tv[k], nref);
+                for (int k = 0; k < EPV; ++k) tv[k] = E::exp2_ref(tv[k], nref);
+                add_vector(tv);
+            } else {
+#pragma unroll
+                for (int k = 0; k < EPV; ++k) zacc[k & 3] += E::exp2_ref(tv[k], nref);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
-        return (double)((zacc[0] + zacc[1]) + (zacc[2] + zacc[3]));
+        if constexpr (LDS_NEXT) return zsum;
+        else return (double)((zacc[0] + zacc[1]) + (zacc[2] + zacc[3]));
     };
     // (the sum about the guess was out of range: about the wave's own maximum -- after a second look without the matrix cores
     // where a masked token can have got into the way)
