@@ -84,6 +84,9 @@ struct RowArgs {
 
 enum class Mode { Quantify, Verify, Fused };
 
+// Workgroups of so many bytes of LDS that a compute unit has room for: 160 KiB, dealt out in pieces of 1280 bytes.
+constexpr int lds_fit(int bytes) { return 160 * 1024 / ((bytes + 1279) / 1280 * 1280); }
+
 // Calls whose radius can push every width of a row close to 1 run kernel instances that also accumulate the
 // complements of the widths: there the widths crowd against 1, and fp32 widths no longer resolve their own
 // spread.  A row's complement sums are used when every 1 - width_i is below 1/2 (the complement is then the

@@ -782,6 +782,19 @@ __global__ __launch_bounds__(T) void dro_batch_kernel(const float* __restrict__ 
 }  // namespace
 
 namespace {
+// Workgroups of dro_row_stream_kernel on a compute unit: sixteen waves with a radius tensor (128 registers).  Without one a wave of
+// 16 tokens per lane gets by with 64 registers, and there are as many workgroups as the unit's LDS has room for, thirty-two
+// waves at most.  (Held against the built kernels by tests/test_resources.py.)
+template <typename T, int NVEC, int THREADS, bool RAD>
+constexpr int dro_workgroups_per_unit()
+{
+    if (RAD || NVEC * Elt<T>::kPerVec > 16) return 1024 / THREADS;
+    constexpr int NW = THREADS / 64;
+    constexpr int waves = NW * ((RAD ? 8 : 4) * 128 + 64 + 16 + 56);                // sm_w, sm_x, sm_m, sm_d
+    constexpr int fit = lds_fit(2 * NVEC * THREADS * 16 + waves + dro_rows<THREADS, RAD>() * kDroTotals * 8), most = 2048 / THREADS;
+    return fit < most ? fit : most;
+}
+
 template <typename T, int NVEC, int THREADS, bool RAD>
 hipError_t launch_dro_stream_cfg(const RowArgs& a, float* terms, hipStream_t stream)
 {
@@ -800,12 +813,7 @@ hipError_t launch_dro_stream_cfg(const RowArgs& a, float* terms, hipStream_t str
             raised[dev] = true;
         }
     }
-    // Workgroups of a compute unit: sixteen waves with a radius tensor (128 registers).  Without one a wave of 16 tokens per lane gets
-    // by with 64 registers, and there are as many workgroups as the unit's LDS has room for, thirty-two waves at most.
-    constexpr int kLds = 160 * 1024, kUsed = (int)lds + THREADS / 64 * 648 + 88 * dro_rows<THREADS, RAD>();
-    constexpr int kFit = kLds / ((kUsed + 1279) / 1280 * 1280), kMost = 2048 / THREADS;
-    constexpr int per_cu = RAD || NVEC * Elt<T>::kPerVec > 16 ? 1024 / THREADS : kFit < kMost ? kFit : kMost;
-    const int64_t g = whole_rounds(a.N, dro_rows<THREADS, RAD>(), (int64_t)per_cu * compute_units());
+    const int64_t g = whole_rounds(a.N, dro_rows<THREADS, RAD>(), (int64_t)dro_workgroups_per_unit<T, NVEC, THREADS, RAD>() * compute_units());
     const dim3 grid((unsigned)g), block(THREADS);
     const DroRadius R = {(float)a.kappa, (float)a.rmax};
     hipLaunchKernelGGL((dro_row_stream_kernel<T, NVEC, THREADS, RAD>), grid, block, lds, stream, a, R, terms);

@@ -36,13 +36,14 @@ hipError_t launch_short_rows_typed(Mode mode, int vecs, const RowArgs& a, Stream
 //   fp32, up to 256: 2048 x 600 16.9 / 16.4 and 14.5 / 12.1, 1024 x 600 13.3 / 14.2 and 11.9 / 11.6, 16384 x 1024 65 / 35 and 52 / 29;
 //   up to 512: 4096 x 2048 25.5 / 23.7 and 21.5 / 18.8, 2048 x 2048 17.6 / 18.1 and 15.0 / 14.2, 16384 x 2048 75 / 55 and 61 / 49;
 //   beyond that 128 lanes lose (4096 x 4096 31.2 / 37.2 and 27.8 / 28.9: the rows of twelve workgroups fill the LDS).
-// Quantify-only: the same lines, and above 256 vectors bf16 rows from 32 per compute unit on (4096 x 4096 18.1 / 19.3, 16384 x 4096 59 / 51,
-// 16384 x 8192 84 / 71; up to 256: 4096 x 1024 15.7 / 10.5, 2048 x 2048 10.5 / 10.2, 16384 x 2048 48 / 28; fp32 4096 x 2048 15.3 / 13.5).
+// Quantify-only: the same lines, but above 512 vectors from 32 rows per compute unit on (up to 256 vectors: 4096 x 1024 15.7 / 10.5, 2048 x 2048
+// 10.5 / 10.2, 16384 x 2048 48 / 28; up to 512: 2048 x 4096 11.8 / 11.2, 4096 x 3000 20.2 / 17.4, 8192 x 4096 31.1 / 24.7, 16384 x 4096 59 / 40;
+// 16384 x 8192 84 / 71; fp32 4096 x 2048 15.3 / 13.5).
 bool short_rows_fit(Mode mode, int dtype, int vecs, int64_t rows)
 {
     if (vecs > (dtype == 0 ? 512 : 1024)) return false;
     const int64_t units = compute_units();
-    if (mode == Mode::Quantify && dtype != 0 && vecs > 256) return rows > 32 * units;
+    if (mode == Mode::Quantify && dtype != 0 && vecs > 512) return rows > 32 * units;
     if (dtype != 0) return vecs <= 128 ? rows > 2 * units : vecs <= 256 ? rows > 3 * units : vecs <= 512 ? rows > 6 * units : rows > 10 * units;
     return vecs <= 256 ? rows > 6 * units : rows > 12 * units;
 }

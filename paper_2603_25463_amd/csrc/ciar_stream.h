@@ -379,6 +379,26 @@ constexpr int rows_per_wg()
 {
     return !next_by_lds<T, THREADS, NVEC, DO_V, RAD, WIDE>() || THREADS >= 512 ? kMaxRowsPerWg : THREADS == 256 ? 64 : THREADS == 128 && NVEC > 8 ? 40 : 16;
 }
+// Workgroups of an instance on a compute unit.  The register budget the kernel was compiled for fixes how many fit: target_waves()
+// waves per SIMD, and a workgroup puts THREADS / 256 waves on each of the four SIMDs (a 128-lane one: one wave on two of them).
+// Where rows come through LDS, no more than its LDS has room for, and as many waves on every SIMD: 12 of 64 lanes and eight vectors.
+// (Quantified, on a grid for the 16 that the registers allow / for 14, which fit / for 12: 16384 x 4096 bf16 49.9 / 43.9 / 40.1 us,
+// 9000 x 4096 32.2 / 28.6 / 26.8, 60000 x 4096 150 / 141 / 142; fp32 4096 x 2048 - / 14.5 / 13.2.)  The arrays in LDS are counted as the
+// kernel declares them; tests/test_resources.py holds the result against the built kernels.
+template <typename T, int THREADS, int NVEC, bool DO_Q, bool DO_V, bool RAD, bool WIDE>
+constexpr int workgroups_per_unit()
+{
+    constexpr int by_waves = target_waves<T, THREADS, NVEC, RAD, DO_V>() * 256 / THREADS;
+    if (!next_by_lds<T, THREADS, NVEC, DO_V, RAD, WIDE>()) return by_waves;
+    constexpr int NW = THREADS / 64, rows = rows_per_wg<T, THREADS, NVEC, DO_V, RAD, WIDE>();
+    constexpr int in_flight = THREADS * NVEC * 16;                                                   // sm_next
+    constexpr int waves = NW * (16 + 16 + 512 + (DO_Q ? 80 : 0) + (DO_V ? 8 + 16 : 0)) + 24;         // sm_ref2 ... sm_sum, sm_k
+    constexpr int parked = rows * ((int)sizeof(RowStats) + 16 + (DO_V ? 4 + 4 + 1 : 0));             // sm_rows ... sm_close
+    constexpr int draws = DO_V ? NW * (NVEC * 8 + 1024 + 4 + 4) : 0;                                 // sm_tab, sm_quad, sm_auxf, sm_auxi
+    constexpr int even = THREADS < 256 ? 256 / THREADS : 1;
+    constexpr int by_lds = lds_fit(in_flight + waves + parked + draws) / even * even;
+    return by_lds < by_waves ? by_lds : by_waves;
+}
 
 // sm_draw / row_id of a rejected row whose draw is still to be made (by resample_kernel)
 constexpr int kDrawPending = -2;
@@ -1756,13 +1776,8 @@ void stream_kernel(const RowArgs A)
 template <typename T, int THREADS, int NVEC, bool DO_Q, bool DO_V, bool RAD, bool WIDE = false>
 hipError_t launch_stream_kernel(const RowArgs& a, StreamLaunch& L)
 {
-    // One wave of resident workgroups, each walking over its pieces of rows with stride gridDim.x.  The register
-    // budget the kernel was compiled for fixes how many fit: target_waves() waves per SIMD, and a
-    // workgroup puts THREADS / 256 waves on each of the four SIMDs of a compute unit (a 128-lane one: one
-    // wave on two of them).
-    // (fp32, one wave to a row and eight vectors: what the LDS has room for)
-    constexpr int per_cu = THREADS == 64 && NVEC == 8 && sizeof(T) == 4 ? 12 : target_waves<T, THREADS, NVEC, RAD, DO_V>() * 256 / THREADS;
-    const int64_t resident = (int64_t)per_cu * compute_units();
+    // One wave of resident workgroups, each walking over its pieces of rows with stride gridDim.x.
+    const int64_t resident = (int64_t)workgroups_per_unit<T, THREADS, NVEC, DO_Q, DO_V, RAD, WIDE>() * compute_units();
     const int64_t N = a.N;
     constexpr int ROWS = rows_per_wg<T, THREADS, NVEC, DO_V, RAD, WIDE>();   // (at most so many rows per workgroup)
     const int64_t grid1 = whole_rounds(N, ROWS, resident), max1 = (N + grid1 - 1) / grid1;
