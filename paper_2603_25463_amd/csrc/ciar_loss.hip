@@ -696,7 +696,7 @@ __global__ __launch_bounds__(256) void dro_row_tiny_kernel(const RowArgs A, floa
 // terms.  One workgroup of 256 lanes; losses = { centre, upper, lower, DRO, total }.  One fp64 exponential per row:
 // the unnormalised weight is parked in `weights` (when the caller wants them) and scaled by the normaliser in a last
 // pass by the lane that wrote it.
-template <int T>
+template <int T, int U>
 __global__ __launch_bounds__(T) void dro_batch_kernel(const float* __restrict__ terms, int64_t N, double lambda_v,
                                                         double lambda_p, double lambda_beta, double alpha,
                                                         float* __restrict__ weights, float* __restrict__ losses)
@@ -709,14 +709,14 @@ __global__ __launch_bounds__(T) void dro_batch_kernel(const float* __restrict__ 
     const float* ce_lo = terms + 5 * N;
     float mxf = -INFINITY;
     double c = 0.0, u = 0.0, l = 0.0;
-    // (four rows' terms requested at a time: one compute unit waits for its trips to memory, 8000 rows 15.5 -> 13.3
-    // us, 20000 26 -> 22, 60000 70 -> 57)
-    constexpr int U = 4;
+    // (U = four rows' terms requested at a time: one compute unit waits for its trips to memory, 8000 rows 15.5 -> 13.3
+    // us, 20000 26 -> 22, 60000 70 -> 57.  With no more rows than lanes U = 1: the loops of four are twice the instructions to
+    // fetch, the kernel on 7 rows 2.96 / 2.72 us at its fastest.)
     for (int64_t n0 = tid; n0 < N; n0 += U * T) {
         float v[U][7];
 #pragma unroll
         for (int i = 0; i < U; ++i) {
-            if (i * T >= N) break;                                 // uniform: a call of few rows requests them once
+            if (i > 0 && i * T >= N) break;                        // uniform: a call of few rows requests them once
             const int64_t n = n0 + i * T < N ? n0 + i * T : n0;
 #pragma unroll
             for (int k = 0; k < 7; ++k) v[i][k] = terms[k * N + n];
@@ -741,7 +741,7 @@ __global__ __launch_bounds__(T) void dro_batch_kernel(const float* __restrict__ 
         float v[U];
 #pragma unroll
         for (int i = 0; i < U; ++i)
-            if (i * T < N) v[i] = ce_lo[n0 + i * T < N ? n0 + i * T : n0];
+            if (i == 0 || i * T < N) v[i] = ce_lo[n0 + i * T < N ? n0 + i * T : n0];
 #pragma unroll
         for (int i = 0; i < U; ++i) {
             if (n0 + i * T >= N) break;
@@ -765,7 +765,7 @@ __global__ __launch_bounds__(T) void dro_batch_kernel(const float* __restrict__ 
             float v[U];
 #pragma unroll
             for (int i = 0; i < U; ++i)
-                if (i * T < N) v[i] = weights[n0 + i * T < N ? n0 + i * T : n0];
+                if (i == 0 || i * T < N) v[i] = weights[n0 + i * T < N ? n0 + i * T : n0];
 #pragma unroll
             for (int i = 0; i < U; ++i)
                 if (n0 + i * T < N) weights[n0 + i * T] = (float)((double)v[i] * inv);
@@ -874,10 +874,13 @@ hipError_t launch_dro(int dtype, const RowArgs& args, float* terms, double lambd
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || (!weights && !losses)) return e;
     if (args.N > 8192)
-        hipLaunchKernelGGL(dro_batch_kernel<1024>, dim3(1), dim3(1024), 0, stream, terms, args.N, lambda_v, lambda_p,
+        hipLaunchKernelGGL((dro_batch_kernel<1024, 4>), dim3(1), dim3(1024), 0, stream, terms, args.N, lambda_v, lambda_p,
+                           lambda_beta, alpha, weights, losses);
+    else if (args.N > 512)
+        hipLaunchKernelGGL((dro_batch_kernel<512, 4>), dim3(1), dim3(512), 0, stream, terms, args.N, lambda_v, lambda_p,
                            lambda_beta, alpha, weights, losses);
     else
-        hipLaunchKernelGGL(dro_batch_kernel<512>, dim3(1), dim3(512), 0, stream, terms, args.N, lambda_v, lambda_p,
+        hipLaunchKernelGGL((dro_batch_kernel<512, 1>), dim3(1), dim3(512), 0, stream, terms, args.N, lambda_v, lambda_p,
                            lambda_beta, alpha, weights, losses);
     return hipGetLastError();
 }

@@ -872,6 +872,12 @@ def test_interdro_loss_many_rows(ciar, oracle, V, stride, N, dtype, tensor_radiu
     _check_dro(g, o, N)
 
 
+# The batch stage with as many rows as it has lanes, one less and one more.
+@pytest.mark.parametrize("N", [511, 512, 513, 1025, 8192, 8193])
+def test_interdro_loss_batch_stage(ciar, oracle, N):
+    test_interdro_loss_many_rows(ciar, oracle, 70, 72, N, torch.float32, True)
+
+
 # The persistent row kernel at both ends of each workgroup size (one to sixteen waves to a row), and with more rows than the
 # workgroups of each have room for.
 DRO_TILE_EDGES = [
