@@ -71,7 +71,7 @@ constexpr uint32_t kRuledOutBits = 0xf1800000u;                    // (its upper
 // The radius parameters as the row arithmetic takes them: floats, formed by the host, so that they arrive in scalar
 // registers with the kernel arguments.  (Converted from RowArgs' doubles inside a kernel they are loop invariants that
 // the optimiser holds in vector registers, or spills, through the whole row loop.)
-struct DroRadius { float kappa, rmax; };
+struct DroRadius { float kappa, rmax, scalar; };                   // scalar = min(kappa, rmax)
 
 // RAD: with a radius tensor.  Without one the radius is the same for every token, c + r and c - r have the softmax of c, and the
 // terms of the three distributions are one number each: the partition sum, the weighted sums and the distance of c alone are
@@ -79,10 +79,12 @@ struct DroRadius { float kappa, rmax; };
 // that two workgroups of 1024 lanes fit a compute unit where their rows fit its LDS (bf16): 15653 x 11630 bf16 593 -> 379 us, 2048 x
 // 16384 71 -> 51 (fp32 88 -> 65), 4 x 21156 29 -> 17 (which spilled).
 //
-// (bf16: the instances with a radius tensor ask for it all the same.  It is there; but with what depends on it in blocks of its own
-// the compiler leaves more of the rows' requests ahead of the arithmetic: 2048 x 16384 87 us so, 89 otherwise; fp32 107 and 105.)
-template <typename T, bool RAD>
-__device__ __forceinline__ bool dro_rad(const RowArgs& A) { return RAD && (sizeof(T) == 4 || A.radius != nullptr); }
+// (bf16 rows of up to 32 tokens per lane: the instances with a radius tensor ask for it all the same, as one for both kinds of calls would, with
+// DroRadius::scalar for a call without one.  It is there; but with what depends on it in blocks of its own the compiler leaves more of
+// the rows' requests ahead of the arithmetic: 2048 x 16384 87.5 us so, 88.4 otherwise, 300 x 16384 27.9 and 28.1; 7 x 40000, 64 tokens, the
+// other way round 99.4 and 94.1; fp32 107 and 105.)
+template <typename T, bool RAD, int NVEC>
+__device__ __forceinline__ bool dro_rad(const RowArgs& A) { return RAD && (sizeof(T) == 4 || NVEC == 8 || A.radius != nullptr); }
 template <typename T, int NVEC, int THREADS, bool RAD>
 __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadius R, double* fin,
                                                 u32x4 (&cw)[NVEC], u32x4 (&tw)[NVEC], u32x4 (&rw)[NVEC], double* sm_d,
@@ -94,7 +96,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     const int V = A.V;
     auto uniform = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
     const float kap = R.kappa, rmax = R.rmax;
-    const bool rad = dro_rad<T, RAD>(A);
+    const bool rad = dro_rad<T, RAD, NVEC>(A);
     if (V < NVEC * THREADS * EPV) {                                // uniform: the row does not fill the tile
 #pragma unroll
         for (int j = 0; j < NVEC; ++j) {
@@ -119,7 +121,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < NVEC * EPV; ++i) rc[i] = 0.f;
+            for (int i = 0; i < NVEC * EPV; ++i) rc[i] = R.scalar;
         }
     }
     // element k of vector j: centre logit, radius, cloud logit
@@ -131,8 +133,8 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
         if constexpr (CACHE_R) {
             r = rc[j * EPV + k];
         } else if constexpr (RAD) {
-            E::unpack(rw[j], rv);
-            r = radius_abs(rv[k], kap, rmax);
+            r = R.scalar;
+            if (rad) { E::unpack(rw[j], rv); r = radius_abs(rv[k], kap, rmax); }
         } else {
             r = 0.f;
         }
@@ -144,7 +146,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
 #pragma unroll
         for (int j = 0; j < NVEC; ++j) {
             asm volatile("" : "+v"(cw[j]), "+v"(tw[j]));
-            if constexpr (!CACHE_R && RAD) asm volatile("" : "+v"(rw[j]));
+            if (!CACHE_R && rad) asm volatile("" : "+v"(rw[j]));
         }
     };
     // pass 1: the maxima of c and of the cloud logits, and a reference radius r* for the sums of c + r and c - r: the
@@ -221,7 +223,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
         // over the waves.  (Four wave-wide DPP maxima, twice, cost ~240 instructions.)
         float m4[4] = {mc, mt, key, 0.f};
 #pragma unroll
-        for (int i = 0; i < (RAD ? 3 : 2); ++i) {
+        for (int i = 0; i < (RAD ? 4 : 2); ++i) {                  // (all four, the last a zero: 4000 x 8000 104.7 us with three, 103.8)
             m4[i] = dpp_max<0xB1, 0xf>(m4[i]);
             m4[i] = dpp_max<0x4E, 0xf>(m4[i]);
         }
@@ -537,8 +539,8 @@ __global__ __launch_bounds__(1024) void dro_row_kernel(const RowArgs A, const Dr
     const int last_vec = (A.V + Elt<T>::kPerVec - 1) / Elt<T>::kPerVec - 1;
     const gbytes cb = (gbytes)(static_cast<const T*>(A.draft) + row * A.stride);
     const gbytes tb = (gbytes)(static_cast<const T*>(A.target) + row * A.stride);
-    const gbytes rb = (gbytes)(static_cast<const T*>(RAD ? A.radius : A.draft) + row * A.stride);
-    const bool rad = dro_rad<T, RAD>(A);
+    const bool rad = dro_rad<T, RAD, NVEC>(A);
+    const gbytes rb = (gbytes)(static_cast<const T*>(rad ? A.radius : A.draft) + row * A.stride);
     u32x4 cw[NVEC], tw[NVEC], rw[NVEC];
 #pragma unroll
     for (int j = 0; j < NVEC; ++j) {
@@ -578,7 +580,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(RAD || 
     const int tid = threadIdx.x;
     const int wave_s = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int last_vec = (A.V + Elt<T>::kPerVec - 1) / Elt<T>::kPerVec - 1;
-    const bool rad = dro_rad<T, RAD>(A);
+    const bool rad = dro_rad<T, RAD, NVEC>(A);
     using lds_ptr = __attribute__((address_space(3))) void*;
     using glb_ptr = const __attribute__((address_space(1))) void*;
 
@@ -815,7 +817,7 @@ hipError_t launch_dro_stream_cfg(const RowArgs& a, float* terms, hipStream_t str
     }
     const int64_t g = whole_rounds(a.N, dro_rows<THREADS, RAD>(), (int64_t)dro_workgroups_per_unit<T, NVEC, THREADS, RAD>() * compute_units());
     const dim3 grid((unsigned)g), block(THREADS);
-    const DroRadius R = {(float)a.kappa, (float)a.rmax};
+    const DroRadius R = {(float)a.kappa, (float)a.rmax, (float)fmin(a.kappa, a.rmax)};
     hipLaunchKernelGGL((dro_row_stream_kernel<T, NVEC, THREADS, RAD>), grid, block, lds, stream, a, R, terms);
     return hipGetLastError();
 }
@@ -841,7 +843,7 @@ hipError_t launch_dro_rows(int vecs, const RowArgs& a, float* terms, hipStream_t
 {
     if (vecs <= 4096 && a.N > (int64_t)compute_units()) return launch_dro_stream<T, RAD>(vecs, a, terms, stream);
     const dim3 grid((unsigned)a.N), block(1024);
-    const DroRadius R = {(float)a.kappa, (float)a.rmax};
+    const DroRadius R = {(float)a.kappa, (float)a.rmax, (float)fmin(a.kappa, a.rmax)};
     if (vecs <= 1024) hipLaunchKernelGGL((dro_row_kernel<T, 1, RAD>), grid, block, 0, stream, a, R, terms);
     else if (vecs <= 2048) hipLaunchKernelGGL((dro_row_kernel<T, 2, RAD>), grid, block, 0, stream, a, R, terms);
     else if (vecs <= 4096) hipLaunchKernelGGL((dro_row_kernel<T, 4, RAD>), grid, block, 0, stream, a, R, terms);
