@@ -75,9 +75,9 @@ struct DroRadius { float kappa, rmax, scalar; };                   // scalar = m
 
 // RAD: with a radius tensor.  Without one the radius is the same for every token, c + r and c - r have the softmax of c, and the
 // terms of the three distributions are one number each: the partition sum, the weighted sums and the distance of c alone are
-// formed, and dro_finish_row writes them three times.  Half the instructions and half the registers (62 of 128 before), so
-// that two workgroups of 1024 lanes fit a compute unit where their rows fit its LDS (bf16): 15653 x 11630 bf16 593 -> 379 us, 2048 x
-// 16384 71 -> 51 (fp32 88 -> 65), 4 x 21156 29 -> 17 (which spilled).
+// formed, and dro_finish_row writes them three times.  Half the instructions and half the registers (62 of 128 before, bf16 57), so
+// that two workgroups of 1024 lanes fit a compute unit where their rows fit its LDS (bf16): 15653 x 11630 bf16 593 -> 359 us, 2048 x
+// 16384 71 -> 46 (fp32 88 -> 65), 4 x 21156 29 -> 17 (which spilled).
 //
 // (bf16 rows of up to 32 tokens per lane: the instances with a radius tensor ask for it all the same, as one for both kinds of calls would, with
 // DroRadius::scalar for a call without one.  It is there; but with what depends on it in blocks of its own the compiler leaves more of
@@ -85,7 +85,7 @@ struct DroRadius { float kappa, rmax, scalar; };                   // scalar = m
 // other way round 99.4 and 94.1; fp32 107 and 105.)
 template <typename T, bool RAD, int NVEC>
 __device__ __forceinline__ bool dro_rad(const RowArgs& A) { return RAD && (sizeof(T) == 4 || NVEC == 8 || A.radius != nullptr); }
-template <typename T, int NVEC, int THREADS, bool RAD>
+template <typename T, int NVEC, int THREADS, bool RAD, bool STREAM>
 __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadius R, double* fin,
                                                 u32x4 (&cw)[NVEC], u32x4 (&tw)[NVEC], u32x4 (&rw)[NVEC], double* sm_d,
                                                 const int tid)
@@ -292,6 +292,10 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     // is looked for beforehand, by the waves that hold such a logit.
     bool ce_infinite = false;
     if (!wave_c_finite) {
+        // (dro_row_stream_kernel, bf16: what this branch converts must not be shared with the pass behind it.  The tokens widened and taken
+        // from their references ahead of the branch were 64 registers and 28 B of scratch, read back in the middle of the pass, behind a
+        // vmcnt(0) that waits for the next row as well: 2048 x 16384 50.9 -> 45.7 us, 15653 x 11630 378 -> 359.  fp32 spills so.)
+        if constexpr (STREAM && !RAD && EPV == 8) fresh();
 #pragma unroll
         for (int j = 0; j < NVEC; ++j) {
 #pragma unroll
@@ -550,7 +554,7 @@ __global__ __launch_bounds__(1024) void dro_row_kernel(const RowArgs A, const Dr
         if (rad) rw[j] = __builtin_nontemporal_load((gvec)(rb + off));
     }
     __shared__ double sm_fin[kDroTotals];
-    dro_row_compute<T, NVEC, THREADS, RAD>(A, R, sm_fin, cw, tw, rw, sm_d, tid);
+    dro_row_compute<T, NVEC, THREADS, RAD, false>(A, R, sm_fin, cw, tw, rw, sm_d, tid);
     if (tid == 0) dro_finish_row<RAD>(A, terms, row, sm_fin);           // (the lane that has written the totals)
 }
 
@@ -636,7 +640,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(RAD || 
             request_rows(next, t);
             if (rad) request_radius(next, rnext, t);
         }
-        dro_row_compute<T, NVEC, THREADS, RAD>(A, R, sm_fin[done], cw, tw, rw, sm_d, t);
+        dro_row_compute<T, NVEC, THREADS, RAD, true>(A, R, sm_fin[done], cw, tw, rw, sm_d, t);
         // (no barrier here: what wave 0 still reads of sm_d is written again only in the next row's pass 3, two
         // barriers on)
         ++done;

@@ -78,3 +78,9 @@ def test_the_grids_count_on_no_more_workgroups_than_a_compute_unit_has_room_for(
     r = subprocess.run(["/opt/rocm/bin/hipcc", "--offload-arch=gfx950", "--cuda-host-only", "-fsyntax-only", "-std=c++17", "-w",
                         "-I", CSRC, str(source)], capture_output=True, text=True)
     assert r.returncode == 0, "\n".join(l for l in r.stderr.splitlines() if "error" in l)
+
+
+def test_rows_that_come_through_lds_are_not_waited_for_by_a_scratch_reload(kernels):
+    """A reload of a spilled register waits for every load in flight, the next row's among them."""
+    persistent = {n: k["scratch"] for n, k in kernels.items() if n.startswith("dro_row_stream_kernel") and n.endswith("false>")}
+    assert len(persistent) >= 10 and not any(persistent.values()), persistent
