@@ -213,8 +213,8 @@ int ciar_quantify_verify_static(const void* draft_logits, const void* radius, co
  *                    fp64 pass launch that behind it, see the radius notes above.)
  * ciar_finish_rows   what remains, if anything: for bfloat16 rows above 8192 tokens with a radius tensor and
  *                    for very wide radii the residual draws of the rejected rows (their rows are read
- *                    again), and the window outputs where neither kernel could write them (windows of more than 16
- *                    to 32 rows that span workgroups).
+ *                    again), and the window outputs where neither kernel could write them (windows that span
+ *                    workgroups and hold more than 16 to 32 of the call's rows).
  */
 int ciar_stream_rows(const void* draft_logits, const void* radius, const void* target_logits,
                      const int32_t* draft_ids,

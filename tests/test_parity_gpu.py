@@ -1901,3 +1901,22 @@ def test_long_windows_however_they_are_put_together(ciar, oracle, K, N, V, dtype
         n = int(a.argmin()) if (a == 0).any() else len(a)
         assert int(g["accept_len"][w]) == n, w
         assert int(g["resampled_id"][w]) == (int(row_id[w * K + n]) if n < len(a) else -1), w
+
+
+# A window longer than the call has rows: only those meet in its word, and stage 1 alone writes its outputs (up to 16 of them).
+@pytest.mark.parametrize("N,K", [(1, 31), (5, 300), (16, 17), (17, 40), (20, 255)])
+def test_windows_longer_than_the_call(ciar, oracle, N, K):
+    c, t, ids, ua, ur = _random_case(5000, 5000, N, K, torch.float32, seed=8700 + N, sigma=0.3)
+    P = ciar.Params(confidence=0.9, window=K, tau=0.01)
+    ws = torch.empty(ciar.binding.workspace_bytes(N, P.to_c(c)), dtype=torch.uint8, device="cuda")
+    out = {k: torch.full((1,), -7, dtype=torch.int32, device="cuda") for k in ("accept_len", "resampled_id")}
+    g = ciar.stream_rows(c, t, ids, ua, ur, P, ws, out=out)
+    torch.cuda.synchronize()
+    first = (int(g["accept_len"][0]), int(g["resampled_id"][0]))
+    ciar.finish_rows(c, t, ids, ua, ur, P, ws, out=g)
+    torch.cuda.synchronize()
+    acc, row_id = g["accept"].cpu().numpy(), g["row_id"].cpu().numpy()
+    n = int(acc.argmin()) if (acc == 0).any() else N
+    want = (n, int(row_id[n]) if n < N else -1)
+    assert (int(g["accept_len"][0]), int(g["resampled_id"][0])) == want
+    assert first == (want if N <= 16 else (-7, -7))
