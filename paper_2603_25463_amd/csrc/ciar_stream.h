@@ -1587,14 +1587,17 @@ void stream_kernel(const RowArgs A)
                             const double incl = wave_scan((double)s);
                             double cum = before + (incl - (double)s);
                             const int base = (j * THREADS + dt) * EPV;
+                            int above = INT_MAX, last = -1;        // (local: selections, not branches)
 #pragma unroll
                             for (int k = 0; k < EPV; ++k) {
                                 cum += (double)r[k];
                                 if (r[k] > 0.f) {
-                                    lastpos = base + k;
-                                    if (cum > thr && cand == INT_MAX) cand = base + k;
+                                    last = base + k;
+                                    if (cum > thr && above == INT_MAX) above = base + k;
                                 }
                             }
+                            cand = above;
+                            lastpos = last;
                         };
                         // (j == jstar is uniform; the register arrays keep constant indices.  The scan once behind the choice of the vector:
                         // sixteen copies of it are half a draw's instructions to fetch; of one or two the calls of few rows lose 5 % so.)
@@ -1777,7 +1780,7 @@ template <typename T, int THREADS, int NVEC, bool DO_Q, bool DO_V, bool RAD, boo
 hipError_t launch_stream_kernel(const RowArgs& a, StreamLaunch& L)
 {
     // One wave of resident workgroups, each walking over its pieces of rows with stride gridDim.x.
-    const int64_t resident = (int64_t)workgroups_per_unit<T, THREADS, NVEC, DO_Q, DO_V, RAD, WIDE>() * compute_units();
+    const int64_t resident = (int64_t)workgroups_per_unit<T, THREADS, NVEC, DO_Q, DO_V, RAD, WIDE>() * L.units;
     const int64_t N = a.N;
     constexpr int ROWS = rows_per_wg<T, THREADS, NVEC, DO_V, RAD, WIDE>();   // (at most so many rows per workgroup)
     const int64_t grid1 = whole_rounds(N, ROWS, resident), max1 = (N + grid1 - 1) / grid1;
