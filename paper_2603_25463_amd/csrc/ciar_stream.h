@@ -64,6 +64,7 @@ struct StreamLaunch {
     bool launch;
     bool finish_rows;      // the caller wants the kernel to finish its rows (launches with a verifier row always do)
     hipStream_t stream;
+    int units;             // compute units of the device
     StreamPlan plan;       // out
     hipEvent_t ev_start, ev_stop;   // both or neither: recorded by the dispatch at the kernel's start and end
 };

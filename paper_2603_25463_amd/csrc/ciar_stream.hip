@@ -51,7 +51,7 @@ hipError_t launch_stream_typed(Mode mode, const RowArgs& a, StreamLaunch& s)
         if constexpr (sizeof(T) == 2) {
             return launch_stream_cfg<T, 512, 8>(mode, a, s);
         } else {
-            if (mode != Mode::Quantify || a.N < 12 * (int64_t)compute_units()) return launch_stream_cfg<T, 512, 8>(mode, a, s);
+            if (mode != Mode::Quantify || a.N < 12 * (int64_t)s.units) return launch_stream_cfg<T, 512, 8>(mode, a, s);
             return wide_radius(a) ? launch_stream_kernel<T, 256, 16, true, false, false, true>(a, s)
                                   : launch_stream_kernel<T, 256, 16, true, false, false>(a, s);
         }
@@ -66,7 +66,7 @@ int max_vocab(int dtype) { return dtype == 0 ? 1024 * 8 * 4 : 1024 * 8 * 8; }
 
 StreamPlan plan_stream(Mode mode, int dtype, const RowArgs& args, bool finish_rows)
 {
-    StreamLaunch L{false, finish_rows, nullptr, {0u, 0, false, 1, false, false, false}, nullptr, nullptr};
+    StreamLaunch L{false, finish_rows, nullptr, compute_units(), {0u, 0, false, 1, false, false, false}, nullptr, nullptr};
     if (args.N > 0) {
         if (dtype == 0) (void)launch_stream_typed<float>(mode, args, L);
         else (void)launch_stream_typed<bf16_t>(mode, args, L);
@@ -78,7 +78,7 @@ hipError_t launch_stream(Mode mode, int dtype, const RowArgs& args, bool finish_
                          hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     if (args.N <= 0) return hipSuccess;
-    StreamLaunch L{true, finish_rows, stream, {0u, 0, false, 1, false, false, false}, ev_start, ev_stop};
+    StreamLaunch L{true, finish_rows, stream, compute_units(), {0u, 0, false, 1, false, false, false}, ev_start, ev_stop};
     return dtype == 0 ? launch_stream_typed<float>(mode, args, L)
                       : launch_stream_typed<bf16_t>(mode, args, L);
 }
