@@ -29,23 +29,32 @@ hipError_t launch_short_rows_typed(Mode mode, int vecs, const RowArgs& a, Stream
 
 // How many rows it takes to pay, by the row's vectors (a call of few rows waits for one row's chain of instructions, and more
 // lanes make it shorter; us, 256 lanes to a row / these, fused and verify-only):
-//   bf16, up to 128 vectors: 1000 x 300 16.8 / 15.4 and 12.1 / 11.2, 40000 x 100 212 / 71 and 134 / 47, 520 x 600 13.3 / 12.6 and 11.6 / 11.2, 64 x 600 12.0 / 12.5 and 10.9 / 11.2, 16384 x 1024 90 / 33 and 62 / 24;
-//   up to 256: 1024 x 2048 14.4 / 13.3 and 12.0 / 11.1, 520 x 1100 13.1 / 13.5 and 11.3 / 11.0, 16384 x 2048 78 / 45 and 59 / 32;
-//   up to 512: 2048 x 3000 23.3 / 21.2 and 17.1 / 16.2, 1024 x 3000 17.1 / 16.9 and 13.0 / 13.2, 16384 x 4096 97 / 70 and 72 / 53;
-//   up to 1024: 4096 x 6000 49.6 / 42.2 and 36.9 / 31.7, 2048 x 6000 29.4 / 29.8 and 22.6 / 22.8, 16384 x 8192 139 / 120 and 103 / 93;
-//   fp32, up to 256: 2048 x 600 16.9 / 16.4 and 14.5 / 12.1, 1024 x 600 13.3 / 14.2 and 11.9 / 11.6, 16384 x 1024 65 / 35 and 52 / 29;
-//   up to 512: 4096 x 2048 25.5 / 23.7 and 21.5 / 18.8, 2048 x 2048 17.6 / 18.1 and 15.0 / 14.2, 16384 x 2048 75 / 55 and 61 / 49;
+//   bf16, up to 128 vectors: 1000 x 300 16.8 / 15.4 and 12.1 / 11.2, 40000 x 100 212 / 71 and 134 / 47, 530 x 1000 12.8 / 11.7, 64 x 600 12.0 / 12.5 and 10.9 / 11.2, 16384 x 1024 90 / 33 and 62 / 24;
+//   up to 256: 1000 x 1672 14.1 / 13.4, 1150 x 1672 14.9 / 15.6, 1330 x 1500 15.9 / 15.4, 1282 x 1672 12.3 / 11.7 verified, 520 x 1100 13.1 / 13.5 and 11.3 / 11.0, 16384 x 2048 78 / 45 and 59 / 32;
+//   up to 512: 1700 x 4096 18.0 / 18.5, 1900 x 4096 19.7 / 18.7, 2300 x 4096 21.3 / 22.2, 2900 x 4096 24.7 / 24.1, verified 1700 x 3500 15.5 / 15.7,
+//     1900 16.7 / 16.3, 2300 17.8 / 18.5, 2900 20.6 / 19.7, 16384 x 4096 97 / 70 and 72 / 53;
+//   up to 1024: 2600 x 6000 34.2 / 34.7, 2900 x 5000 37.7 / 35.1, 2900 x 8192 33.2 / 34.0, 3400 x 8192 36.0 / 36.8, 3900 x 8192 40.0 / 38.0, 2600 x 8192 24.0 / 23.0 verified, 16384 x 8192 139 / 120 and 103 / 93;
+//   fp32, up to 256: 1700 x 800 15.0 / 15.4, 1900 x 800 16.3 / 15.5, 2300 x 800 16.9 / 17.3, 2600 x 600 18.4 / 17.5, rows of 1024 tokens 2060 15.9 / 14.9 and 2300 16.3 / 15.2, 1600 x 1024 12.6 / 10.9 verified, 16384 x 1024 65 / 35 and 52 / 29;
+//   up to 512: 3100 x 1300 23.6 / 22.3, 3500 x 2048 22.6 / 23.2, 3900 x 2048 24.2 / 24.1 to 23.9 / 22.7, 3100 x 2048 18.6 / 17.0 verified, 16384 x 2048 75 / 55 and 61 / 49;
 //   beyond that 128 lanes lose (4096 x 4096 31.2 / 37.2 and 27.8 / 28.9: the rows of twelve workgroups fill the LDS).
-// Quantify-only: the same lines, but above 512 vectors from 32 rows per compute unit on (up to 256 vectors: 4096 x 1024 15.7 / 10.5, 2048 x 2048
-// 10.5 / 10.2, 16384 x 2048 48 / 28; up to 512: 2048 x 4096 11.8 / 11.2, 4096 x 3000 20.2 / 17.4, 8192 x 4096 31.1 / 24.7, 16384 x 4096 59 / 40;
-// 16384 x 8192 84 / 71; fp32 4096 x 2048 15.3 / 13.5).
-bool short_rows_fit(Mode mode, int dtype, int vecs, int64_t rows)
+// (The gaps: four rows per compute unit are one to a SIMD, eight two.  The first rows beyond add a wave to a few SIMDs, and the call waits
+// for those, where the four waves of the other tiles share them out.)
+// Quantify-only: up to 512 vectors 700 x 1000 9.5 / 9.7, 2100 x 600 10.5 / 9.5, 1100 x 1672 9.6 / 9.8, 2060 x 1672 10.7 / 10.4, 2300 x 4096 12.1 / 13.1, 2900 x 2600 16.3 / 15.0, 16384 x 4096 59 / 40;
+// above that from 32 rows per compute unit on (8500 x 8192 46.4 / 43.0); fp32 1600 x 800 9.5 / 9.8, 2300 x 800 10.0 / 9.7, 3200 x 2048 13.0 / 12.1.
+bool short_rows_fit(Mode mode, int dtype, const RowArgs& a, int units)
 {
+    const int vecs = dtype == 0 ? (a.V + 3) / 4 : (a.V + 7) / 8;
     if (vecs > (dtype == 0 ? 512 : 1024)) return false;
-    const int64_t units = compute_units();
-    if (mode == Mode::Quantify && dtype != 0 && vecs > 512) return rows > 32 * units;
-    if (dtype != 0) return vecs <= 128 ? rows > 2 * units : vecs <= 256 ? rows > 3 * units : vecs <= 512 ? rows > 6 * units : rows > 10 * units;
-    return vecs <= 256 ? rows > 6 * units : rows > 12 * units;
+    const double n = (double)a.N / units;
+    const bool fused = mode == Mode::Fused, quantify = mode == Mode::Quantify;
+    if (dtype != 0) {
+        if (vecs <= 128) return n > (quantify ? 6 : 2);
+        if (vecs <= 256) return quantify ? n > 6 : n > 3 && (!fused || n <= 4 || n > 5.25);
+        if (vecs <= 512) return (n > 7 && n <= 8) || n > 11;
+        return n > (quantify ? 32 : !fused ? 10 : vecs <= 768 ? 11 : 14);
+    }
+    if (vecs <= 256) return quantify ? n > 8 : n > (fused ? 7 : 6) && (!fused || n <= 8 || n > 9.5 || a.V == 1024);
+    return n > (fused && vecs > 384 ? 15 : 12);
 }
 
 hipError_t launch_short_rows(int dtype, Mode mode, const RowArgs& a, StreamLaunch& s)

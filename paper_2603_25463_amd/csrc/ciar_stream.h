@@ -72,7 +72,7 @@ struct StreamLaunch {
 // Calls on bf16 rows of more than 8192 tokens with a verifier row, without a radius tensor and without complements (wide_radius).
 hipError_t launch_both_rows(Mode mode, const RowArgs& a, StreamLaunch& s);
 // Calls without a radius tensor and without complements, whose rows the kernel finishes, on short rows where there are enough of them.
-bool short_rows_fit(Mode mode, int dtype, int vecs, int64_t rows);
+bool short_rows_fit(Mode mode, int dtype, const RowArgs& a, int units);
 hipError_t launch_short_rows(int dtype, Mode mode, const RowArgs& a, StreamLaunch& s);
 
 namespace {

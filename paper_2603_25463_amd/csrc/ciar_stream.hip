@@ -37,7 +37,7 @@ hipError_t launch_stream_typed(Mode mode, const RowArgs& a, StreamLaunch& s)
     if (mode == Mode::Verify || (!a.radius && !wide_radius(a) && (mode == Mode::Fused || s.finish_rows))) {
         if (sizeof(T) == 2 && vecs > 1024 && mode != Mode::Quantify) return launch_both_rows(mode, a, s);
         constexpr int kDtype = sizeof(T) == 4 ? 0 : 1;
-        if (a.V > kTinyVocab && short_rows_fit(mode, kDtype, vecs, a.N)) return launch_short_rows(kDtype, mode, a, s);
+        if (a.V > kTinyVocab && short_rows_fit(mode, kDtype, a, s.units)) return launch_short_rows(kDtype, mode, a, s);
     }
     if (vecs <= 256 * 1)  return launch_stream_cfg<T, 256, 1>(mode, a, s);
     if (vecs <= 256 * 2)  return launch_stream_cfg<T, 256, 2>(mode, a, s);

@@ -1861,12 +1861,12 @@ def test_large_bf16_rows_with_a_verifier_row(ciar, oracle, V, stride, N):
 # Short rows, enough of them for a wave or two to a row: both ends of the tiles of one wave (two, four and eight
 # vectors per lane) and of two (bf16), rows that fill a tile and rows that do not; more rows than a workgroup has room for.
 SHORT_ROWS = [
-    (65, 68, 2000, torch.float32), (511, 512, 1700, torch.float32), (512, 512, 1700, torch.float32), (513, 516, 1700, torch.float32),
-    (1024, 1024, 1700, torch.float32), (1025, 1028, 3200, torch.float32), (2047, 2048, 3200, torch.float32),
-    (2048, 2048, 3200, torch.float32), (600, 600, 70000, torch.float32), (66, 72, 700, torch.bfloat16), (1024, 1024, 700, torch.bfloat16),
-    (1025, 1032, 900, torch.bfloat16), (2048, 2048, 900, torch.bfloat16), (2049, 2056, 1700, torch.bfloat16),
-    (4096, 4096, 1700, torch.bfloat16), (4097, 4104, 2700, torch.bfloat16), (8191, 8192, 2700, torch.bfloat16),
-    (8192, 8192, 2700, torch.bfloat16), (520, 520, 70000, torch.bfloat16), (4095, 4096, 8300, torch.bfloat16),
+    (65, 68, 2500, torch.float32), (511, 512, 2500, torch.float32), (512, 512, 2500, torch.float32), (513, 516, 2500, torch.float32),
+    (1024, 1024, 2100, torch.float32), (1025, 1028, 3200, torch.float32), (2047, 2048, 3900, torch.float32),
+    (2048, 2048, 3900, torch.float32), (600, 600, 70000, torch.float32), (66, 72, 1700, torch.bfloat16), (1024, 1024, 1700, torch.bfloat16),
+    (1025, 1032, 1700, torch.bfloat16), (2048, 2048, 1700, torch.bfloat16), (2049, 2056, 2900, torch.bfloat16),
+    (4096, 4096, 2900, torch.bfloat16), (4097, 4104, 2900, torch.bfloat16), (8191, 8192, 3700, torch.bfloat16),
+    (8192, 8192, 3700, torch.bfloat16), (520, 520, 70000, torch.bfloat16), (4095, 4096, 8300, torch.bfloat16),
     (4096, 4096, 8300, torch.bfloat16), (4104, 4104, 8300, torch.bfloat16), (8192, 8192, 8300, torch.bfloat16),
 ]
 
