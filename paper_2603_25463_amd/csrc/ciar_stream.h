@@ -1046,10 +1046,8 @@ void stream_kernel(const RowArgs A)
                 // (n is the largest of the waves' references.  It is ref_of(mc) as well, but formed from mc it comes later and in a
                 // vector register: one 1024-token row verified 5.45 -> 5.63 us, 36621 of them 109 -> 116, 65104 bf16 rows
                 // quantified and verified with a radius tensor 529 -> 620)
-                // (... except in the fused bf16 instances of 1024 lanes with a scalar radius: 32768 x 65536 1875 us so, 1894 from the
-                // references)
                 const float mc_l = sm_ref[src * 2], n_l = sm_ref[src * 2 + 1];
-                mc = row16_max(mc_l); n = BATCH3 && THREADS == 1024 ? ref_of(mc) : row16_max(n_l);
+                mc = row16_max(mc_l); n = row16_max(n_l);
                 S = row16_sum(ln < NW && n_l != -INFINITY ? sm_S[src] * pow2_of(n_l - n) : 0.0);
             } else {
                 mc = sm_ref[0]; n = sm_ref[1];
@@ -1218,11 +1216,6 @@ void stream_kernel(const RowArgs A)
             }
             if constexpr (BATCH3) {
                 // ---- T (these instances): verifier row statistics, per wave ----------------------------------------
-                if constexpr (!EARLY_T) {
-                    // no registers to spare next to the interval pass: the verifier row is fetched only now
-                    __builtin_amdgcn_sched_barrier(0);
-                    load_row(buf, A.target, row);
-                }
                 verifier_mask(buf, quads ? kNoTokenWord : E::kNegInfWord);
                 ntw = nw == -INFINITY ? 0.f : nw;
                 Zw = verifier_lane_sum(buf, ntw, quads);
@@ -1496,37 +1489,33 @@ void stream_kernel(const RowArgs A)
                             if (4 * g + (dlane >> 4) < NVEC) sm_tab[(4 * g + (dlane >> 4)) * NW + dwave] = part[g];
                     }
                 } else {
-                    constexpr int GROUP = NVEC >= 8 ? 8 : NVEC;
 #pragma unroll
-                    for (int j0 = 0; j0 < NVEC; j0 += GROUP) {
+                    for (int j = 0; j < NVEC; ++j) {
+                        float sj = 0.f;
+                        if (j * CHUNK < V) {                       // uniform: the vector holds tokens
+                            float r[EPV];
+                            residuals(j, r);
 #pragma unroll
-                        for (int j = j0; j < j0 + GROUP; ++j) {
-                            float sj = 0.f;
-                            if (j * CHUNK < V) {                       // uniform: the vector holds tokens
-                                float r[EPV];
-                                residuals(j, r);
-#pragma unroll
-                                for (int k = 0; k < EPV; ++k) sj += r[k];
-                            }
-                            if constexpr (NVEC >= 8) {
-                                double q = (double)sj;
-                                q = dpp_add<0xB1, 0xf>(q);             // lane ^ 1  (quad_perm 1,0,3,2)
-                                q = dpp_add<0x4E, 0xf>(q);             // lane ^ 2  (quad_perm 2,3,0,1)
-                                if ((dlane & 3) == 0) sm_quad[dwave][j - j0][dlane >> 2] = q;
-                            } else {
-                                const double ws = wave_sum((double)sj);
-                                if (dlane == 0) sm_tab[j * NW + dwave] = ws;
-                            }
+                            for (int k = 0; k < EPV; ++k) sj += r[k];
                         }
-                        if constexpr (NVEC >= 8) {
-                            // (the wave reads what its own lanes have written: LDS operations of a wave complete in order)
-                            const double* pr = &sm_quad[dwave][dlane >> 3][2 * (dlane & 7)];
-                            double t2 = pr[0] + pr[1];
-                            t2 = dpp_add<0xB1, 0xf>(t2);
-                            t2 = dpp_add<0x4E, 0xf>(t2);
-                            t2 = dpp_add<0x141, 0xf>(t2);              // the other quad of the eight (row_half_mirror)
-                            if ((dlane & 7) == 0) sm_tab[(j0 + (dlane >> 3)) * NW + dwave] = t2;
+                        if constexpr (NVEC == 8) {
+                            double q = (double)sj;
+                            q = dpp_add<0xB1, 0xf>(q);             // lane ^ 1  (quad_perm 1,0,3,2)
+                            q = dpp_add<0x4E, 0xf>(q);             // lane ^ 2  (quad_perm 2,3,0,1)
+                            if ((dlane & 3) == 0) sm_quad[dwave][j][dlane >> 2] = q;
+                        } else {
+                            const double ws = wave_sum((double)sj);
+                            if (dlane == 0) sm_tab[j * NW + dwave] = ws;
                         }
+                    }
+                    if constexpr (NVEC == 8) {
+                        // (the wave reads what its own lanes have written: LDS operations of a wave complete in order)
+                        const double* pr = &sm_quad[dwave][dlane >> 3][2 * (dlane & 7)];
+                        double t2 = pr[0] + pr[1];
+                        t2 = dpp_add<0xB1, 0xf>(t2);
+                        t2 = dpp_add<0x4E, 0xf>(t2);
+                        t2 = dpp_add<0x141, 0xf>(t2);              // the other quad of the eight (row_half_mirror)
+                        if ((dlane & 7) == 0) sm_tab[(dlane >> 3) * NW + dwave] = t2;
                     }
                 }
                 row_barrier();
