@@ -439,14 +439,9 @@ void stream_kernel(const RowArgs A)
     // 285 us per step).
     constexpr bool KEEP_E = draws_in_stream<T, THREADS, NVEC, DO_V, RAD, WIDE>();
     constexpr int ROWS = rows_per_wg<T, THREADS, NVEC, DO_V, RAD, WIDE>();
-    // Fused launches on bf16 rows with a scalar radius: the two interval sums of a row whose caps are inactive and the
-    // verifier row's partition sum are reduced over the wave together (wave_sum3) once the verifier row has been summed.
-    // (These instances are bound by their vector instructions: workload 5 1951 -> 1905 us.  The fp32 instances, which
-    // wait for memory, measured 1 % slower with it and keep one reduction per sum.)
     // bf16 rows go through the matrix cores (see bf16_scaled; with a radius tensor the verifier row only) where a lane holds enough of
     // a row for it to pay: with one or two vectors a row is a chain of latencies (871 x 1162 verified 10.2 us without, 10.7 with).
     constexpr bool MATRIX_T = sizeof(T) == 2 && NVEC >= 4, MATRIX = MATRIX_T && !RAD;
-    constexpr bool BATCH3 = DO_Q && DO_V && !RAD && !WIDE && sizeof(T) == 2 && !LDS_NEXT;
     constexpr int NQ = WIDE ? 8 : 5;                // interval sums a wave hands over
     // A row with a token above 1/2 and a radius tensor: finish_row wants that token's raw radius.  It is picked up in the
     // interval pass -- except in the instances of 1024 lanes with bf16 rows, which spill: there only the token's index is
@@ -467,7 +462,6 @@ void stream_kernel(const RowArgs A)
     __shared__ double sm_Z2[LDS_NEXT ? 2 : 1][NW];  // per wave: Z_w
     __shared__ double sm_q52[LDS_NEXT ? 2 : 1][NW * NQ];   // per wave: the interval sums, already in row units
     __shared__ double sm_sum[LDS_NEXT ? NW : 1][LDS_NEXT ? 64 : 1];       // LDS_NEXT, per wave: [interval sums of the row before, S_w, Z_w][eight groups of lanes]
-    __shared__ double sm_red[BATCH3 ? NW : 1][BATCH3 ? 48 : 1];  // per wave: the slots of wave_sum3
     __shared__ double sm_k[3];                      // the shift the sums are taken about (row units), from wave 0
     __shared__ float  sm_e0;                        // e of the row's first token, in the units of wave 0
     // Finishing inside this kernel: the statistics of the rows this workgroup has streamed since its last
@@ -483,7 +477,7 @@ void stream_kernel(const RowArgs A)
     __shared__ double   sm_tab[DO_V ? NT : 1];      // residual mass of each piece of a rejected row
     __shared__ __attribute__((aligned(16))) double sm_quad[KEEP_E && (NVEC >= 8 || LDS_NEXT) ? NW : 1][KEEP_E && (NVEC >= 8 || LDS_NEXT) ? 8 : 1][16];   // a draw's quad sums
     __shared__ float    sm_auxf[DO_V ? NW : 1];
-    extern __shared__ u32x4 sm_next[];              // LDS_NEXT: [NVEC][THREADS], the centre row in flight
+    extern __shared__ u32x4 sm_next[];              // LDS_NEXT: [NVEC][THREADS], the row in flight, centre and verifier row in turn
     __shared__ int      sm_auxi[DO_V ? NW : 1];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1090,7 +1084,6 @@ void stream_kernel(const RowArgs A)
             load_row(buf, A.target, row);
             __builtin_amdgcn_sched_barrier(0);
         }
-        bool lane_sums = false;                                    // uniform: q5[1], q5[3] are still the lanes' own sums
         if constexpr (DO_Q) {
             // x_i = e_i fw / S: hand fuse_row the partition sum expressed in this wave's units
             // (fw is a power of two: the division is a change of exponent)
@@ -1189,15 +1182,7 @@ void stream_kernel(const RowArgs A)
                 if (partial)    fuse_sums<THREADS, NVEC, EPV, true, true, true>(e, fr, wp, sh, V, base, step4, q5);
                 else if (CIAR_RARE(HINTS, split)) fuse_sums<THREADS, NVEC, EPV, true, true, false>(e, fr, wp, sh, V, base, step4, q5);
                 else            fuse_sums<THREADS, NVEC, EPV, true, false, false>(e, fr, wp, sh, V, base, step4, q5);
-                if constexpr (BATCH3) {
-                    // reduced below, together with the verifier row's sum; until then the quads' sums wait in LDS
-                    // (slot addresses from an opaque copy of the lane index: hoisted out of the row loop they are spilled)
-                    lane_sums = true;
-                    int ol = tid;
-                    asm volatile("" : "+v"(ol));
-                    wave_sum3_put(q5[1], sm_red[ol >> 6], 0, ol & 63);
-                    wave_sum3_put(q5[3], sm_red[ol >> 6], 1, ol & 63);
-                } else if constexpr (!LDS_NEXT) {
+                if constexpr (!LDS_NEXT) {
                     q5[1] = wave_sum(q5[1]);
                     q5[3] = wave_sum(q5[3]);
                 }
@@ -1213,22 +1198,6 @@ void stream_kernel(const RowArgs A)
                 q5[5] = wave_sum(q5[5]);
                 q5[6] = wave_sum(q5[6]);
                 q5[7] = (double)wave_max((float)q5[7]);
-            }
-            if constexpr (BATCH3) {
-                // ---- T (these instances): verifier row statistics, per wave ----------------------------------------
-                verifier_mask(buf, quads ? kNoTokenWord : E::kNegInfWord);
-                ntw = nw == -INFINITY ? 0.f : nw;
-                Zw = verifier_lane_sum(buf, ntw, quads);
-                if (lane_sums) {
-                    int ol = tid;
-                    asm volatile("" : "+v"(ol));
-                    wave_sum3_put(Zw, sm_red[ol >> 6], 2, ol & 63);
-                    wave_sum3_get(sm_red[ol >> 6], ol & 63, q5[1], q5[3], Zw);
-                } else {
-                    Zw = wave_sum(Zw);
-                }
-                verifier_redo(buf, ntw, Zw, tquads);
-                if (lane == 0) { sm_nt[wave] = ntw; sm_Z[wave] = Zw; }
             }
             if constexpr (LDS_NEXT) {
                 if (CIAR_RARE(HINTS, flat && !near)) {             // (uniform over the wave) the wave's sums, as from its lane 0
@@ -1292,7 +1261,7 @@ void stream_kernel(const RowArgs A)
         }
 
         // ---- T: verifier row statistics, per wave -----------------------------------------------------------
-        if constexpr (DO_V && !BATCH3 && !LDS_NEXT) {
+        if constexpr (DO_V && !LDS_NEXT) {
             if constexpr (!EARLY_T) {
                 // no registers to spare next to the interval pass: the verifier row is fetched only now
                 __builtin_amdgcn_sched_barrier(0);
