@@ -894,16 +894,18 @@ DRO_TILE_EDGES = [
 def test_interdro_loss_tile_edges(ciar, oracle, V, stride, N, dtype, tensor_radius):
     test_interdro_loss_many_rows(ciar, oracle, V, stride, N, dtype, tensor_radius)
     if N < 5000:
-        test_interdro_tokens_the_device_rules_out(ciar, oracle, stride, N, dtype)      # (its rows are not padded)
+        test_interdro_tokens_the_device_rules_out(ciar, oracle, stride, N, dtype, tensor_radius)      # (its rows are not padded)
 
 
 @pytest.mark.parametrize("V,N,dtype", [(1000, 40, torch.float32), (4100, 300, torch.float32), (16384, 270, torch.float32),
-                                       (16384, 300, torch.bfloat16), (40000, 7, torch.bfloat16)])
-def test_interdro_tokens_the_device_rules_out(ciar, oracle, V, N, dtype):
+                                       (16384, 300, torch.bfloat16), (20000, 300, torch.bfloat16), (20000, 7, torch.bfloat16),
+                                       (40000, 7, torch.bfloat16)])
+@pytest.mark.parametrize("tensor_radius", [True, False])
+def test_interdro_tokens_the_device_rules_out(ciar, oracle, V, N, dtype, tensor_radius):
     """Centre logits of -inf.  Where the cloud rules the same tokens out the terms stay finite and match; a row in which
     the cloud keeps such a token has infinite cross-entropies and KL (its L1 distances stay finite)."""
     c, t, *_ = _random_case(V, V, N, 4, dtype, seed=6900 + V)
-    raw = _raw_radius(N, V, V, dtype, seed=6950 + V)
+    raw = _raw_radius(N, V, V, dtype, seed=6950 + V) if tensor_radius else None
     gen = torch.Generator(device="cpu").manual_seed(6990 + V)
     dead = torch.randint(0, V, (N, 9), generator=gen).cuda()
     rows = torch.arange(N, device="cuda")[:, None]
@@ -913,12 +915,12 @@ def test_interdro_tokens_the_device_rules_out(ciar, oracle, V, N, dtype):
     t[:, V - 3:] = float("-inf")
     infinite = torch.arange(N) % 5 == 2
     t[infinite.cuda(), dead[infinite.cuda(), 0]] = 0.5               # the cloud keeps one of them
-    say(f"[interdro ruled out] V={V} N={N} {dtype}")
+    say(f"[interdro ruled out] V={V} N={N} {dtype} radius={'tensor' if tensor_radius else 'scalar'}")
     lam = (1.0, 1.0, 1.0, 1.0)
     P = ciar.Params(radius_scale=1.0)
     g = ciar.interdro_loss(c, raw, t, P, *lam, vocab=V)
     torch.cuda.synchronize()
-    o = oracle.interdro_loss(c.cpu(), raw.cpu(), t.cpu(), _OP(oracle, kappa=1.0), *lam, vocab=V)
+    o = oracle.interdro_loss(c.cpu(), raw.cpu() if tensor_radius else None, t.cpu(), _OP(oracle, kappa=1.0), *lam, vocab=V)
     terms = g["terms"].cpu().numpy().astype(np.float64)
     inf = infinite.numpy()
     for i, k in enumerate(("l1_mid", "l1_up", "l1_lo", "ce_mid", "ce_up", "ce_lo", "kl")):
@@ -1886,10 +1888,54 @@ def test_short_rows_many_of_them(ciar, oracle, V, stride, N, dtype):
             break
 
 
+# The same tiles quantify-only without drafted ids (the most probable token is reported) and under a vote, whose heads' rows follow
+# one another.
+@pytest.mark.parametrize("V,stride,N,dtype", [(511, 512, 2500, torch.float32), (1025, 1028, 3200, torch.float32), (2048, 2048, 3900, torch.float32),
+                                              (1000, 1000, 1700, torch.bfloat16), (2048, 2048, 1700, torch.bfloat16), (4095, 4096, 2900, torch.bfloat16),
+                                              (8192, 8192, 8300, torch.bfloat16)])
+def test_short_rows_without_ids_and_in_a_vote(ciar, oracle, V, stride, N, dtype):
+    c, _, ids, *_ = _random_case(V, stride, N, 5, dtype, seed=8400 + V)
+    P = ciar.Params(confidence=0.9, tau=0.01)
+    OP = _oparams(oracle, P)
+    say(f"[short rows, no ids, vote] V={V} N={N} {dtype}")
+    q = ciar.quantify(c, None, P, vocab=V)
+    torch.cuda.synchronize()
+    o = oracle.quantify(c.cpu(), None, OP, vocab=V)
+    parity.check_floats(q, o)
+    parity.check_flags(q["flags"], o, float(np.float32(P.tau)))
+    n = N // 3 + 2                                                         # positions; three heads' rows are a few more than N
+    heads = torch.stack([c[:n], c[n - 7:2 * n - 7], c[N - n:]])
+    v = ciar.quantify_multihead(heads, ids[:n], P, ciar.VOTING, vocab=V)
+    torch.cuda.synchronize()
+    o = oracle.quantify_multihead(heads.cpu(), ids[:n].cpu().numpy(), OP, oracle.VOTING, vocab=V)
+    for h in range(3):
+        oh = {k: o[k][h] for k in parity.FLOAT_KEYS}
+        oh["flags"] = o["head_flags"][h]
+        parity.check_floats({k: v[k][h] for k in parity.FLOAT_KEYS}, oh)
+        parity.check_flags(v["head_flags"][h], oh, float(np.float32(P.tau)))
+    assert torch.equal(v["flags"], (2 * v["head_flags"].sum(0, dtype=torch.int32) > 3).to(torch.uint8))
+
+
+# Flat rows in which one wave of a tile whose rows come through LDS has no token, or none but those far below the rest: its
+# interval sums are moved to the common shift.  A wave's tokens are blocks of 512, dealt out in turn.
+@pytest.mark.parametrize("V,N,waves", [(4097, 2900, 2), (8191, 3700, 2), (12288, 300, 2), (16383, 300, 2), (24570, 300, 4), (32003, 300, 4), (40000, 60, 8), (65536, 40, 8)])
+@pytest.mark.parametrize("kw", [dict(confidence=0.9), dict(radius_scale=0.02), dict(radius_scale=0.7, normalize=False)])
+def test_flat_rows_without_a_waves_tokens(ciar, oracle, V, N, waves, kw):
+    c, t, ids, ua, ur = _random_case(V, -(-V // 8) * 8, N, 5, torch.bfloat16, seed=8600 + V)
+    block = torch.arange(V, device="cuda") // 512 % waves
+    for r in range(0, 24):
+        c[r, :V] = 0.25
+        c[r, :V] += 0.002 * (r % 3) * t[r, :V]                             # exactly flat, or nearly
+        c[r, :V][block == (1, 0)[r % 2]] = (float("-inf"), -200.0, -30.0)[r // 2 % 3]
+    ids = torch.where(c[torch.arange(N, device="cuda"), ids.long()].float() < -20, c[:, :V].float().argmax(1).to(torch.int32), ids)
+    _run_case(ciar, oracle, c, t, ids, ua, ur, ciar.Params(tau=0.01, window=5, **kw), vocab=V, tag=f"flat rows without a wave V={V} {kw}")
+
+
 # Windows that meet in a word of the workspace, and those that are left to a launch of their own: lengths on both sides of the rule,
 # with one row to a workgroup and with several.
 @pytest.mark.parametrize("K", [16, 17, 31, 32, 33])
-@pytest.mark.parametrize("N,V,dtype", [(333, 1000, torch.float32), (5003, 1000, torch.float32), (333, 8200, torch.bfloat16), (4500, 8200, torch.bfloat16)])
+@pytest.mark.parametrize("N,V,dtype", [(333, 1000, torch.float32), (5003, 1000, torch.float32), (20000, 1000, torch.float32), (20000, 1000, torch.bfloat16),
+                                       (333, 8200, torch.bfloat16), (4500, 8200, torch.bfloat16)])
 def test_long_windows_however_they_are_put_together(ciar, oracle, K, N, V, dtype):
     c, t, ids, ua, ur = _random_case(V, V, N, K, dtype, seed=8500 + K, sigma=0.15)
     P = ciar.Params(confidence=0.9, window=K, tau=0.01)
