@@ -1213,7 +1213,11 @@ void stream_kernel(const RowArgs A)
                 double ku = fw;
                 const double f2 = fw * fw;
                 q5[0] *= fw; q5[1] *= fw; q5[2] *= f2; q5[3] *= f2; q5[4] *= f2;
-                if (CIAR_RARE(HINTS, flat && !near && !tiny && (!LDS_NEXT || lane == 0))) {
+                // (the lane asked for only where it has to be: as a further term of the branch's condition, even a constant one, it made
+                // the compiler keep the tiny rows' constants otherwise, and fused bf16 calls of 256 vectors with a radius tensor lost 9 %)
+                bool move = flat && !near && !tiny;
+                if constexpr (LDS_NEXT) move = move && lane == 0;
+                if (CIAR_RARE(HINTS, move)) {
                     // Rare: this wave's sums are about 0.  Form the common shift the long way round, in row units
                     // (scalar radius) or in wave 0's (tensor radius), and move the sums to it:  with c = 0 - K and
                     // n tokens,  sum (d - K) = s1 + n c,  sum (d - K)^2 = s2 + 2 c s1 + n c^2,  likewise the cross
