@@ -108,6 +108,13 @@ constexpr bool next_by_lds()
 {
     return !RAD && !WIDE && (THREADS <= 64 || (DO_V && (NVEC == 16 || NVEC == 12)) || (THREADS == 128 && NVEC == 8));
 }
+// The first vectors of every lane that all rows of an instance fill: large bf16 rows, which take the tile of fewer vectors otherwise
+// (launch_both_rows; launch_stream_kernel refuses others).
+template <typename T, int THREADS, int NVEC, bool DO_V, bool RAD, bool WIDE>
+constexpr int full_vectors()
+{
+    return !next_by_lds<T, THREADS, NVEC, DO_V, RAD, WIDE>() ? 0 : NVEC == 16 ? 12 : NVEC == 12 ? 8 : 0;
+}
 template <typename T, int THREADS, int NVEC, bool RAD, bool DO_V = false>
 constexpr int target_waves()
 {
@@ -140,7 +147,7 @@ struct Shift { float kl, kw, kc; };
 // delta_i = w_i and only the sums of gw are needed.
 // SPLIT = see fuse_parts.
 // MASK = the row does not fill the tile: slots past its end contribute nothing (they hold e = 0, which would
-// otherwise enter as 0 - k).  base, step: see slot_base.
+// otherwise enter as 0 - k).  base, step: see slot_base.  FULL = the first vectors of every lane, which all rows fill.
 //
 // Small probabilities (WIDTH_ONLY instances).  The raw width per unit of e,
 //   G(x) = (1 - x) / ((1 + (a-1) x)(1 - (1-b) x)),   gw = e G(x),
@@ -151,7 +158,7 @@ struct Shift { float kl, kw, kc; };
 // issues instead of ten.  The test costs half an issue per token (a running maximum and one compare per vector).
 struct WidthPoly { float d0, d1, d2, d3, ethr; };   // gw = e (1 + e (d0 + e (d1 + e (d2 + e d3)))) for e <= ethr
 
-template <int THREADS, int NVEC, int EPV, bool WIDTH_ONLY, bool SPLIT, bool MASK>
+template <int THREADS, int NVEC, int EPV, bool WIDTH_ONLY, bool SPLIT, bool MASK, int FULL = 0>
 __device__ __forceinline__ void fuse_sums(const float (&e)[NVEC * EPV], const FuseRow& fr_in, const WidthPoly& wp,
                                           const Shift& sh, int V, int base, int step, double (&q5)[5])
 {
@@ -166,7 +173,7 @@ __device__ __forceinline__ void fuse_sums(const float (&e)[NVEC * EPV], const Fu
     double a0[2] = {0.0, 0.0}, a1[2] = {0.0, 0.0}, a2[2] = {0.0, 0.0}, a3[2] = {0.0, 0.0}, a4[2] = {0.0, 0.0};
 #pragma unroll
     for (int j = 0; j < NVEC; ++j) {
-        if (j * THREADS * EPV >= V) continue;                      // uniform: the chunk holds no token
+        if (j >= FULL && j * THREADS * EPV >= V) continue;         // uniform: the chunk holds no token
         if constexpr (WIDTH_ONLY) {
             // e >= 0: the order of the floats is the order of their bit patterns (integer maxima need no
             // canonicalisation of their operands); a negative bound compares below every e
@@ -179,7 +186,7 @@ __device__ __forceinline__ void fuse_sums(const float (&e)[NVEC * EPV], const Fu
                     const float ek = e[j * EPV + k];
                     const float G = fmaf(fmaf(fmaf(fmaf(wp.d3, ek, wp.d2), ek, wp.d1), ek, wp.d0), ek, 1.0f);
                     float sw = fmaf(ek, G, -sh.kw);
-                    if (MASK && !live_slot(j, k)) sw = 0.f;
+                    if (MASK && j >= FULL && !live_slot(j, k)) sw = 0.f;
                     const double dw = (double)sw;
                     a1[k & 1] += dw;
                     a3[k & 1] = fma(dw, dw, a3[k & 1]);
@@ -192,7 +199,7 @@ __device__ __forceinline__ void fuse_sums(const float (&e)[NVEC * EPV], const Fu
         for (int k = 0; k < EPV; ++k) {
             float g, du, om;
             fuse_parts<SPLIT>(e[j * EPV + k], fr, g, du, om);
-            const bool live = !MASK || live_slot(j, k);
+            const bool live = !MASK || j < FULL || live_slot(j, k);
             float sw = fmaf(g, om, -sh.kw);
             if (!live) sw = 0.f;
             const double dw = (double)sw;
@@ -439,6 +446,7 @@ void stream_kernel(const RowArgs A)
     // 285 us per step).
     constexpr bool KEEP_E = draws_in_stream<T, THREADS, NVEC, DO_V, RAD, WIDE>();
     constexpr int ROWS = rows_per_wg<T, THREADS, NVEC, DO_V, RAD, WIDE>();
+    constexpr int FULL = full_vectors<T, THREADS, NVEC, DO_V, RAD, WIDE>();
     // bf16 rows go through the matrix cores (see bf16_scaled; with a radius tensor the verifier row only) where a lane holds enough of
     // a row for it to pay: with one or two vectors a row is a chain of latencies (871 x 1162 verified 10.2 us without, 10.7 with).
     constexpr bool MATRIX_T = sizeof(T) == 2 && NVEC >= 4, MATRIX = MATRIX_T && !RAD;
@@ -1187,8 +1195,13 @@ void stream_kernel(const RowArgs A)
                     q5[3] = wave_sum(q5[3]);
                 }
             } else {
-                if (partial) fuse_sums<THREADS, NVEC, EPV, false, true, true>(e, fr, wp, sh, V, base, step4, q5);
-                else         fuse_sums<THREADS, NVEC, EPV, false, true, false>(e, fr, wp, sh, V, base, step4, q5);
+                // (Large bf16 rows: only flat ones have a shift, and without one a slot past the row's end adds nothing by itself.  The
+                // masks are more than the registers hold there: ten sums read back from scratch for every vector.  us, tiles of eight
+                // vectors / masks on every ragged row / on flat ones, rows with one token of nearly all the mass: 4099 x 26001 255 / 381 / 185, 4099 x
+                // 13001 144 / 203 / 101, 256 x 13000 26.8 / 34.9 / 23.0, 8 x 26000 30.2 / 39.1 / 23.4.)
+                const bool masked = partial && (!(LDS_NEXT && NVEC >= 12) || flat);
+                if (masked) fuse_sums<THREADS, NVEC, EPV, false, true, true, FULL>(e, fr, wp, sh, V, base, step4, q5);
+                else        fuse_sums<THREADS, NVEC, EPV, false, true, false>(e, fr, wp, sh, V, base, step4, q5);
                 if constexpr (!LDS_NEXT) {
 #pragma unroll
                     for (int i = 0; i < 5; ++i) q5[i] = wave_sum(q5[i]);
@@ -1742,6 +1755,7 @@ void stream_kernel(const RowArgs A)
 template <typename T, int THREADS, int NVEC, bool DO_Q, bool DO_V, bool RAD, bool WIDE = false>
 hipError_t launch_stream_kernel(const RowArgs& a, StreamLaunch& L)
 {
+    if (a.V < full_vectors<T, THREADS, NVEC, DO_V, RAD, WIDE>() * THREADS * Elt<T>::kPerVec) return hipErrorInvalidValue;
     // One wave of resident workgroups, each walking over its pieces of rows with stride gridDim.x.
     const int64_t resident = (int64_t)workgroups_per_unit<T, THREADS, NVEC, DO_Q, DO_V, RAD, WIDE>() * L.units;
     const int64_t N = a.N;

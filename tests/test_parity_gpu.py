@@ -1931,6 +1931,24 @@ def test_flat_rows_without_a_waves_tokens(ciar, oracle, V, N, waves, kw):
     _run_case(ciar, oracle, c, t, ids, ua, ur, ciar.Params(tau=0.01, window=5, **kw), vocab=V, tag=f"flat rows without a wave V={V} {kw}")
 
 
+# Active caps on bf16 rows above 8192 tokens that do not fill their tile: one token of nearly all the mass, a radius of less than 1 %,
+# and both on flat rows, whose sums are taken about a shift and want the slots past the row's end left out.  Vocabularies one to
+# either side of a whole vector, of the tile of fewer vectors and of the tile.
+@pytest.mark.parametrize("V", [8193, 12287, 12289, 16383, 16385, 24577, 26001, 32767, 49153, 65535])
+@pytest.mark.parametrize("kw", [dict(confidence=0.9), dict(radius_scale=0.005)])
+def test_large_bf16_rows_with_active_caps(ciar, oracle, V, kw):
+    N = 37
+    c, t, ids, ua, ur = _random_case(V, -(-V // 8) * 8, N, 5, torch.bfloat16, seed=8700 + V)
+    for r in range(N):
+        if r % 4 == 1:                                                     # flat, or nearly
+            c[r, :V] = 0.25
+            c[r, :V] += 0.002 * (r % 8 // 4) * t[r, :V]
+        if r % 3 == 0:                                                     # a token of much of the mass, in the row's last vector
+            c[r, V - 1 - r % 8] = 12.0 + r / 4
+            ids[r] = V - 1 - r % 8
+    _run_case(ciar, oracle, c, t, ids, ua, ur, ciar.Params(tau=0.01, window=5, **kw), vocab=V, tag=f"active caps V={V} {kw}")
+
+
 # Windows that meet in a word of the workspace, and those that are left to a launch of their own: lengths on both sides of the rule,
 # with one row to a workgroup and with several.
 @pytest.mark.parametrize("K", [16, 17, 31, 32, 33])
