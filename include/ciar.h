@@ -214,7 +214,7 @@ int ciar_quantify_verify_static(const void* draft_logits, const void* radius, co
  * ciar_finish_rows   what remains, if anything: for bfloat16 rows above 8192 tokens with a radius tensor and
  *                    for very wide radii the residual draws of the rejected rows (their rows are read
  *                    again), and the window outputs where neither kernel could write them (windows that span
- *                    workgroups and hold more than 16 to 32 of the call's rows).
+ *                    workgroups, of more than 16 to 32 rows, in calls of more than 10).
  */
 int ciar_stream_rows(const void* draft_logits, const void* radius, const void* target_logits,
                      const int32_t* draft_ids,

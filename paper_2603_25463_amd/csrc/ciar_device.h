@@ -859,7 +859,7 @@ __device__ __forceinline__ bool finish_row(const RowArgs& A, int64_t row, const 
 // A run of `rows` consecutive rows of the window that one workgroup has finished arrives with one call: its rows'
 // first rejected offset in the window and that row's draw (id = -1: all accepted).  The call that completes the
 // window returns true with the window's first rejected offset (-1: none) and its draw.
-constexpr int kMaxCountedRows = 32;                                 // of a window (the word would hold 255)
+constexpr int kMaxCountedWindow = 32;                               // (the word would hold 255 rows)
 __device__ __forceinline__ bool window_arrive(unsigned long long* p, uint32_t tag, int rows, int off, int id, int len,
                                               int& first, int& draw)
 {

@@ -1785,10 +1785,11 @@ hipError_t launch_stream_kernel(const RowArgs& a, StreamLaunch& L)
     // (Its rows arrive one after another: with one row to a workgroup all of a window at once, and long windows take longer so than a
     // launch of window_kernel.  us, counted / window_kernel, verified bf16 rows of 8629 tokens: 123 rows, windows of 16 16.3 / 15.4, of 31
     // 22.0 / 14.6, of 100 71 / 15; 1000 rows, of 16 21.3 / 21.9, of 31 27.3 / 22.3; 9000 rows, nine to a workgroup, of 31 89.4 / 93.4,
-    // of 100 135 / 94.  A call with fewer rows than a window has only those to count.)
-    const int64_t meet = N < a.window ? N : a.window;              // rows that arrive at a window's word
+    // of 100 135 / 94.  A call with fewer rows than a window has only those to count: windows of 31, fused fp32 rows of 16244 tokens
+    // 1 row 12.2 / 13.7, 10 rows 15.9 / 17.2, 16 rows 18.4 / 17.3; bf16 of 7614 tokens 10 rows 13.0 / 13.8, 12 rows 14.0 / 13.8, 16 rows
+    // 15.5 / 13.8; verified fp32 10 rows 12.8 / 12.8.)
     p.windows_counted = p.draws_inline && a.win_words && (a.accept_len || a.resampled_id) && !p.windows_inline && a.window >= 2 &&
-                        meet <= (p.rows_per_wg > 3 ? kMaxCountedRows : 16);
+                        (a.window <= (p.rows_per_wg > 3 ? kMaxCountedWindow : 16) || N <= 10);
 
     if (!L.launch) return hipSuccess;
     RowArgs b = a;
