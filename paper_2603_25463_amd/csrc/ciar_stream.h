@@ -1563,17 +1563,26 @@ void stream_kernel(const RowArgs A)
                             const double incl = wave_scan((double)s);
                             double cum = before + (incl - (double)s);
                             const int base = (j * THREADS + dt) * EPV;
-                            int above = INT_MAX, last = -1;        // (local: selections, not branches)
+                            auto search = [&](int& above, int& last) {
 #pragma unroll
-                            for (int k = 0; k < EPV; ++k) {
-                                cum += (double)r[k];
-                                if (r[k] > 0.f) {
-                                    last = base + k;
-                                    if (cum > thr && above == INT_MAX) above = base + k;
+                                for (int k = 0; k < EPV; ++k) {
+                                    cum += (double)r[k];
+                                    if (r[k] > 0.f) {
+                                        last = base + k;
+                                        if (cum > thr && above == INT_MAX) above = base + k;
+                                    }
                                 }
+                            };
+                            // (local: selections, not branches.  1024 lanes have no registers for them: fp32 4328 x 31744 226.5 us in place,
+                            // 229.4 local, with 8 B of scratch)
+                            if constexpr (THREADS < 1024) {
+                                int above = INT_MAX, last = -1;
+                                search(above, last);
+                                cand = above;
+                                lastpos = last;
+                            } else {
+                                search(cand, lastpos);
                             }
-                            cand = above;
-                            lastpos = last;
                         };
                         // (j == jstar is uniform; the register arrays keep constant indices.  The scan once behind the choice of the vector:
                         // sixteen copies of it are half a draw's instructions to fetch; of one or two the calls of few rows lose 5 % so.)
