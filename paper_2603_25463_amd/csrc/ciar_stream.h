@@ -113,7 +113,7 @@ constexpr bool next_by_lds()
 template <typename T, int THREADS, int NVEC, bool DO_V, bool RAD, bool WIDE>
 constexpr int full_vectors()
 {
-    return !next_by_lds<T, THREADS, NVEC, DO_V, RAD, WIDE>() ? 0 : NVEC == 16 ? 12 : NVEC == 12 ? 8 : 0;
+    return next_by_lds<T, THREADS, NVEC, DO_V, RAD, WIDE>() && NVEC == 16 ? 12 : 0;
 }
 template <typename T, int THREADS, int NVEC, bool RAD, bool DO_V = false>
 constexpr int target_waves()
@@ -1195,11 +1195,11 @@ void stream_kernel(const RowArgs A)
                     q5[3] = wave_sum(q5[3]);
                 }
             } else {
-                // (Large bf16 rows: only flat ones have a shift, and without one a slot past the row's end adds nothing by itself.  The
+                // (Sixteen vectors of bf16: only flat rows have a shift, and without one a slot past the row's end adds nothing by itself.  The
                 // masks are more than the registers hold there: ten sums read back from scratch for every vector.  us, tiles of eight
                 // vectors / masks on every ragged row / on flat ones, rows with one token of nearly all the mass: 4099 x 26001 255 / 381 / 185, 4099 x
                 // 13001 144 / 203 / 101, 256 x 13000 26.8 / 34.9 / 23.0, 8 x 26000 30.2 / 39.1 / 23.4.)
-                const bool masked = partial && (!(LDS_NEXT && NVEC >= 12) || flat);
+                const bool masked = partial && (!(LDS_NEXT && NVEC == 16) || flat);
                 if (masked) fuse_sums<THREADS, NVEC, EPV, false, true, true, FULL>(e, fr, wp, sh, V, base, step4, q5);
                 else        fuse_sums<THREADS, NVEC, EPV, false, true, false>(e, fr, wp, sh, V, base, step4, q5);
                 if constexpr (!LDS_NEXT) {
