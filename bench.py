@@ -474,8 +474,14 @@ def run_workload(args, torch, ciar, wl, dev, workload: int, steps: int, warmup: 
     achieved = bytes_per_launch / (kern_avg_ms * 1e-3) / 1e9
     step_gbs = bytes_per_launch / (ms_per_step * 1e-3) / 1e9
     traffic = None if rads or args.mode != "fused" else measured_traffic(spec.name)
-    cdll_plan = "one launch: stream_kernel makes the accept test, the draws and every output" if elt == 4 and not rads \
-        else "two launches: stream_kernel (accept test, outputs), resample_kernel (draws of the rejected rows)"
+    # (with a radius tensor and the default clamp widths may be large: flat rows are summed once more in fp64)
+    if not rads:
+        cdll_plan = "one launch: stream_kernel makes the accept test, the draws and every output"
+    elif elt == 4 or V <= 8192:
+        cdll_plan = "two launches: stream_kernel (accept test, draws, every output), flatrow_kernel (flat rows, if any)"
+    else:
+        cdll_plan = "three launches: stream_kernel (accept test, outputs), flatrow_kernel (flat rows, if any), " \
+                    "resample_kernel (draws of the rejected rows)"
 
     result = {
         "metric": "token positions/sec (quantify+verify, V=16384 fp32)"

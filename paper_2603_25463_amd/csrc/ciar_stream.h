@@ -93,14 +93,16 @@ namespace {
 // Bound by vector instructions: 16.9 of them per position and token are the tokens' own arithmetic, what a wave does per row besides
 // (reductions, exchange, accept test) is spread over 128 tokens of a lane instead of 64, and with 256 registers the exponentials
 // of the centre row (128) and the packed verifier row (64) are both there when the accept test has been decided, so that the
-// draws of rejected rows are made here and resample_kernel's second read of their rows (57 of 250 us, below) is gone.
+// draws of rejected rows are made here and resample_kernel's second read of their rows (57 of 250 us, below) is gone.  (What does not fit
+// 256 registers with sixteen vectors, 52 to 88 B per lane, lies in blocks away from the usual path, mostly of waves whose rows may not go through
+// the matrix cores; twelve vectors fit.)
 // Two waves hide less of each other's waiting than four, so the rows are requested by global_load_lds into one row of LDS per
 // workgroup that takes them in turn -- the verifier row while the centre row is exponentiated, the next centre row during the
 // rest -- and there is one barrier per row: the verifier row is summed ahead of the exchange, and the interval sums are handed
 // over with the next row's.  (Twelve vectors: rows that would fill less than three quarters of sixteen.)
-// us per call, tiles of eight vectors and resample_kernel / these: fused 16384 x 16384 251 / 233, 32768 x 65536 1800 / 1679,
-// 2048 x 20000 78 / 64, 256 x 16384 24 / 19; verified 4099 x 32003 129 / 103, 520 x 9714 27 / 18, 64 x 40000 31 / 18.  Vector
-// instructions busy 80 % of the time; a fused pass over rows that stay in the caches takes 186 us without its draws, 229 with.
+// us per call, tiles of eight vectors and resample_kernel / these: fused 16384 x 16384 260 / 243, 32768 x 65536 1900 / 1769 (on another card
+// 235 and 1705), 2048 x 20000 78 / 64, 256 x 16384 24 / 19; verified 4099 x 32003 131 / 106, 520 x 9714 27 / 18, 64 x 40000 31 / 18.  Vector
+// instructions busy 85 % of the time; a fused pass over rows that stay in the caches takes 186 us without its draws, 229 with.
 // (Same tiles, fp32: 2048 x 16384 50 / 55; those calls wait for memory.  Voting with radius tensors, radius_lean_kernel with
 // sixteen vectors: 106 / 121.)
 template <typename T, int THREADS, int NVEC, bool DO_V, bool RAD, bool WIDE>
@@ -473,7 +475,7 @@ void stream_kernel(const RowArgs A)
     __shared__ double sm_k[3];                      // the shift the sums are taken about (row units), from wave 0
     __shared__ float  sm_e0;                        // e of the row's first token, in the units of wave 0
     // Finishing inside this kernel: the statistics of the rows this workgroup has streamed since its last
-    // finishing step (at most kMaxRowsPerWg of them) and, fetched ahead, what their finishing needs from memory:
+    // finishing step (at most ROWS of them) and, fetched ahead, what their finishing needs from memory:
     // the reported token's centre logit, raw radius and verifier logit, the row's two uniforms.
     __shared__ RowStats sm_rows[ROWS];
     __shared__ float    sm_fx[ROWS][4];    // cx, rawx, tx, u_accept
@@ -764,9 +766,9 @@ void stream_kernel(const RowArgs A)
             if constexpr (DO_V) sm_ur[tid] = f.ur;
         }
     };
-    // Finishing of the rows L0 ... L0 + cnt - 1 from what is parked in LDS, two lanes per row in different waves so that
-    // the two halves run side by side: lane i < 128 writes row i's statistics and its quantifier outputs (Eq.
-    // uncertainty_score, the threshold of Algorithm 1), lane 128 + i its verification outputs; with unit == window
+    // Finishing of the rows L0 ... L0 + cnt - 1 from what is parked in LDS, two lanes per row, from 128 lanes on in different
+    // waves so that the two halves run side by side: lane i < HALF writes row i's statistics and its quantifier outputs (Eq.
+    // uncertainty_score, the threshold of Algorithm 1), lane HALF + i its verification outputs; with unit == window
     // also the outputs of the windows (Algorithm 1: the verified prefix of a drafted window and the token that
     // replaces its first rejection).
     auto finish_batch = [&](int L0, int cnt) {
