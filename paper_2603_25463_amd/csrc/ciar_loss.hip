@@ -82,7 +82,8 @@ struct DroRadius { float kappa, rmax, scalar; };                   // scalar = m
 // (bf16 rows of up to 32 tokens per lane: the instances with a radius tensor ask for it all the same, as one for both kinds of calls would, with
 // DroRadius::scalar for a call without one.  It is there; but with what depends on it in blocks of its own the compiler leaves more of
 // the rows' requests ahead of the arithmetic: 2048 x 16384 87.5 us so, 88.4 otherwise, 300 x 16384 27.9 and 28.1; 7 x 40000, 64 tokens, the
-// other way round 99.4 and 94.1; fp32 107 and 105.)
+// other way round 99.4 and 94.1; fp32 107 and 105.  32 tokens: the requests alone ask, what is done with the row does not (THERE):
+// 1200 x 22065 248 us where all of it asks, 241 so, 232 where nothing does, but then 500 x 30001 95 and 99.)
 template <typename T, bool RAD, int NVEC>
 __device__ __forceinline__ bool dro_rad(const RowArgs& A) { return RAD && (sizeof(T) == 4 || NVEC == 8 || A.radius != nullptr); }
 template <typename T, int NVEC, int THREADS, bool RAD, bool STREAM>
@@ -97,6 +98,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
     auto uniform = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
     const float kap = R.kappa, rmax = R.rmax;
     const bool rad = dro_rad<T, RAD, NVEC>(A);
+    constexpr bool THERE = RAD && sizeof(T) == 2 && NVEC == 4;     // (see dro_rad)
     if (V < NVEC * THREADS * EPV) {                                // uniform: the row does not fill the tile
 #pragma unroll
         for (int j = 0; j < NVEC; ++j) {
@@ -121,7 +123,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < NVEC * EPV; ++i) rc[i] = R.scalar;
+            for (int i = 0; i < NVEC * EPV; ++i) rc[i] = THERE ? 0.f : R.scalar;
         }
     }
     // element k of vector j: centre logit, radius, cloud logit
@@ -134,7 +136,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
             r = rc[j * EPV + k];
         } else if constexpr (RAD) {
             r = R.scalar;
-            if (rad) { E::unpack(rw[j], rv); r = radius_abs(rv[k], kap, rmax); }
+            if (THERE || rad) { E::unpack(rw[j], rv); r = radius_abs(rv[k], kap, rmax); }
         } else {
             r = 0.f;
         }
@@ -146,7 +148,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
 #pragma unroll
         for (int j = 0; j < NVEC; ++j) {
             asm volatile("" : "+v"(cw[j]), "+v"(tw[j]));
-            if (!CACHE_R && rad) asm volatile("" : "+v"(rw[j]));
+            if (!CACHE_R && (THERE || rad)) asm volatile("" : "+v"(rw[j]));
         }
     };
     // pass 1: the maxima of c and of the cloud logits, and a reference radius r* for the sums of c + r and c - r: the
@@ -223,7 +225,7 @@ __device__ __forceinline__ void dro_row_compute(const RowArgs& A, const DroRadiu
         // over the waves.  (Four wave-wide DPP maxima, twice, cost ~240 instructions.)
         float m4[4] = {mc, mt, key, 0.f};
 #pragma unroll
-        for (int i = 0; i < (RAD ? 4 : 2); ++i) {                  // (all four, the last a zero: 4000 x 8000 104.7 us with three, 103.8)
+        for (int i = 0; i < (THERE ? 3 : RAD ? 4 : 2); ++i) {                  // (all four, the last a zero: 4000 x 8000 104.7 us with three, 103.8)
             m4[i] = dpp_max<0xB1, 0xf>(m4[i]);
             m4[i] = dpp_max<0x4E, 0xf>(m4[i]);
         }
@@ -544,7 +546,7 @@ __global__ __launch_bounds__(1024) void dro_row_kernel(const RowArgs A, const Dr
     const gbytes cb = (gbytes)(static_cast<const T*>(A.draft) + row * A.stride);
     const gbytes tb = (gbytes)(static_cast<const T*>(A.target) + row * A.stride);
     const bool rad = dro_rad<T, RAD, NVEC>(A);
-    const gbytes rb = (gbytes)(static_cast<const T*>(rad ? A.radius : A.draft) + row * A.stride);
+    const gbytes rb = (gbytes)(static_cast<const T*>((RAD && sizeof(T) == 2 && NVEC == 4) || rad ? A.radius : A.draft) + row * A.stride);
     u32x4 cw[NVEC], tw[NVEC], rw[NVEC];
 #pragma unroll
     for (int j = 0; j < NVEC; ++j) {
