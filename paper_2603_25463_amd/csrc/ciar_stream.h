@@ -94,7 +94,7 @@ namespace {
 // (reductions, exchange, accept test) is spread over 128 tokens of a lane instead of 64, and with 256 registers the exponentials
 // of the centre row (128) and the packed verifier row (64) are both there when the accept test has been decided, so that the
 // draws of rejected rows are made here and resample_kernel's second read of their rows (57 of 250 us, below) is gone.  (What does not fit
-// 256 registers with sixteen vectors, 52 to 88 B per lane, lies in blocks away from the usual path, mostly of waves whose rows may not go through
+// 256 registers with sixteen vectors, 48 to 88 B per lane, lies in blocks away from the usual path, mostly of waves whose rows may not go through
 // the matrix cores; twelve vectors fit.)
 // Two waves hide less of each other's waiting than four, so the rows are requested by global_load_lds into one row of LDS per
 // workgroup that takes them in turn -- the verifier row while the centre row is exponentiated, the next centre row during the
